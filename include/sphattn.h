@@ -79,7 +79,7 @@ typedef enum {
  * the fp32 maximum (3.4e38); beyond that a row comes out as zeros or NaN.  Inputs are expected
  * to be finite.
  *
- * 16-bit launches use workgroups of 256 query rows, or of 128 when 256-row tiles would
+ * 16-bit and fp8-Q/K launches use workgroups of 256 query rows, or of 128 when 256-row tiles would
  * leave compute units without work (sphattn_fwd_tile_rows forces either shape).
  */
 int sphattn_fwd(const void* Q, const void* K, const void* V, void* O,
@@ -97,12 +97,12 @@ int sphattn_fwd_z(const void* Q, const void* K, const void* V, void* O, float* Z
                   int B, int H, int N, int d, int dtype, void* stream);
 
 /*
- * sphattn_fwd_z with the workgroup shape of the 16-bit kernels forced, for tests and
+ * sphattn_fwd_z with the workgroup shape of the matrix kernels forced, for tests and
  * measurements of both shapes on one problem (same definition as sphattn_fwd; the two shapes
  * add the same terms in different order):
  *   tile_rows : 0 = the library's choice (then this is sphattn_fwd_z), 128 or 256 query rows
  *               per workgroup; anything else returns SPHATTN_ERR_SHAPE.  Ignored where only
- *               one shape exists (fp32, fp16 and fp8-Q/K storage).
+ *               one shape exists (fp32 storage).
  */
 int sphattn_fwd_tile_rows(const void* Q, const void* K, const void* V, void* O, float* Z,
                           int B, int H, int N, int d, int dtype, int tile_rows, void* stream);

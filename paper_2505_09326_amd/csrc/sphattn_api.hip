@@ -3,6 +3,7 @@
 // never synchronises.
 #include "sphattn_device.hpp"
 #include "sphattn_pipelined.hpp"
+#include "sphattn_keysplit.hpp"
 #include "sphattn_softmax32.hpp"
 #include "sphattn_backward.hpp"
 #include "sphattn_fp8.hpp"
@@ -137,6 +138,7 @@ struct Problem {
     hipStream_t stream;
     int n_splits = 1, keys_per_split = 0;
     int tile_rows = 0;          // query rows per workgroup: 0 = the library's choice, else 128 or 256
+    bool one_key_order = false; // every row's sums in the key order of the 256-row kernel, whatever the workgroup
 };
 
 // Key slices are whole 64-key tiles.  Asking for more slices than there are tiles, or for a
@@ -188,9 +190,24 @@ long long balanced_grid(long long n_items, long long resident)
     return grid < resident ? grid : resident;
 }
 
-// Storage types for which the 128-row kernel exists (fp8 Q/K needs whole score instructions per slot).
-template <QKType QKT>
-constexpr bool has_narrow_kernel() { return QKT == QKType::Bf16 || QKT == QKType::F16; }
+// The 128-row kernel over a launch's items of kSplitRows query rows.
+template <int D, QKType QKT, bool MULT, bool PARTIAL>
+int launch_keysplit(const Problem& p)
+{
+    constexpr int lds_bytes = keysplit_lds_bytes<D, QKT, MULT>();
+    auto kern = fwd_keysplit_kernel<D, QKT, MULT, PARTIAL>;
+    static std::atomic<uint64_t> done{0};
+    static std::atomic<int> period[64];
+    if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
+    const int n_qtiles = (p.Nq + kSplitRows - 1) / kSplitRows;
+    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
+    if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
+    const long long grid = balanced_grid(n_wg, (long long)kXcds * stream_period(kern, lds_bytes, period));
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds_bytes, p.stream,
+                       p.Q, p.K, p.V, p.O, p.mult, p.Z, p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
+                       p.n_splits, p.keys_per_split, 0, (int)n_wg, 0);
+    return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
+}
 
 // The 128-row kernel on the remainder of a launch whose items do not fill their last round
 // (launch_pipelined): items item_begin .. n_items - 1 of the 256-row numbering, one half of an
@@ -199,9 +216,8 @@ constexpr bool has_narrow_kernel() { return QKT == QKType::Bf16 || QKT == QKType
 template <int D, QKType QKT>
 long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_begin, bool backwards, bool resident_only)
 {
-    constexpr int EQ = QKT == QKType::Fp8 ? 1 : 2;
-    constexpr int lds_bytes = kNBuf * kBC * (D * EQ + D * 2);
-    auto kern = fwd_pipelined_kernel<D, 2, QKT, Norm::Spherical, false, false>;
+    constexpr int lds_bytes = keysplit_lds_bytes<D, QKT, false>();
+    auto kern = fwd_keysplit_kernel<D, QKT, false, false>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return 0;
@@ -209,11 +225,9 @@ long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_be
     if (resident_only) return resident;
     const int rest = n_items - item_begin;
     const unsigned grid = 2u * kXcds * (unsigned)((rest + kXcds - 1) / kXcds);
-    const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)D);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds_bytes, p.stream,
-                       p.Q, p.K, p.V, p.O, p.mult, p.Z,
-                       p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, n_items, 1, 0, scale_log2,
-                       item_begin, n_items, backwards ? 2 : 1);
+                       p.Q, p.K, p.V, p.O, p.mult, p.Z, p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, n_items,
+                       1, 0, item_begin, n_items, backwards ? 2 : 1);
     return hipGetLastError() == hipSuccess ? resident : -1;
 }
 
@@ -242,7 +256,7 @@ int launch_pipelined(const Problem& p)
     // 8192 x 64 (640 tiles, 1.25 rounds) 273 against 306 us, 12 x 12345 x 64 387 against 425 us.
     // At d = 128 the 128-row kernel is too much slower per row for this (8 x 41472 x 128: 4.84
     // against 4.66 ms, 4 x 20000 x 128: 649 against 632 us), and the balanced grid stays.
-    constexpr bool HAS_HALVES = D == 64 && NQ == 4 && !PARTIAL && !MULT && NORM == Norm::Spherical && has_narrow_kernel<QKT>();
+    constexpr bool HAS_HALVES = D == 64 && NQ == 4 && !PARTIAL && !MULT && NORM == Norm::Spherical && QKT != QKType::Fp8;
     if constexpr (HAS_HALVES) {
         const long long full = resident > 0 ? n_wg / resident : 0, rem = resident > 0 ? n_wg % resident : 0;
         if (p.tile_rows == 0 && full >= 1 && rem > 0) {
@@ -302,79 +316,69 @@ int launch_softmax32(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// Query rows per workgroup: 256 (64 per wave) is the efficient shape; 128 (32 per wave) reads
-// K/V fragments twice as often per flop (measured 15-25 % slower per row) but doubles the
-// number of workgroups.  It pays when the 128-row workgroups still run all at once (one per CU
-// at d = 128, two at d = 64) and 256-row tiles would leave CUs without any: measured, one head
-// of 32768 x 128: 0.42 against 0.51 ms; 4 heads of 8192 x 64: 65 against 84 us.  With more items
-// than that the 128-row launch takes two rounds and loses (5 heads of 8192 x 128, 160 tiles:
-// 182 against 151 us; 3 x 16384 x 128, 192 tiles: 368 against 290 us): a partly filled single
+// Query rows per workgroup: 256 or 128.  Both feed every fragment to 64 query rows of a wave; a
+// 128-row workgroup has each wave do half of every key tile (sphattn_keysplit.hpp), takes 0.56 us
+// for a 64-key tile of d = 128 against 0.97 of a 256-row one while the chip is not full (0.36 against
+// 0.56 at d = 64), and copies twice the K/V bytes per flop.  It pays when the 128-row workgroups
+// still run all at once (one per CU at d = 128; at d = 64, where two fit a CU, up to one and a half
+// per CU) and 256-row tiles would leave CUs without any: one head of 32768 x 128 378 against 529 us, of 32768 x 64 217 against 324; 4 heads of
+// 8192 x 128 103 against 151, fp16 4 x 1999 x 128 24 against 39.  With more items than
+// that the 128-row launch takes two rounds and loses (5 heads of 8192 x 128, 160 tiles:
+// 152 against 136 us; 3 x 16384 x 128, 192 tiles: 311 against 282 us; d = 64: 6 x 8192, 384
+// workgroups, 88 against 88 us, 7 x 8192 95 against 94, 12 x 5003 fp16 66 against 63): a partly filled single
 // round costs less than its share of idle CUs suggests, because the part is power-bound and
 // idle CUs give their share of the budget to the rest.
 bool narrow_tiles_pay(const Problem& p, int d)
 {
     if (p.tile_rows != 0) return p.tile_rows == 128;
-    const long long heads = (long long)p.B * p.H, cus = cu_count();
-    return heads * ((p.Nq + 255) / 256) < cus && heads * ((p.Nq + 127) / 128) <= cus * (d == 64 ? 2 : 1);
+    const long long heads = (long long)p.B * p.H * p.n_splits, cus = cu_count();
+    return heads * ((p.Nq + 255) / 256) < cus && heads * ((p.Nq + 127) / 128) <= (d == 64 ? cus * 3 / 2 : cus);
 }
 
-template <Norm NORM, bool MULT>
-int dispatch(const Problem& p, int d, int dtype)
+template <int D, QKType QKT, bool MULT, bool PARTIAL>
+int launch_spherical(const Problem& p)
 {
-    if (dtype == SPHATTN_BF16) {
-        if constexpr (NORM == Norm::Spherical && !MULT) {
-            if (narrow_tiles_pay(p, d)) {
-                if (d == 128) return launch_pipelined<128, 2, QKType::Bf16, NORM, MULT>(p);
-                return launch_pipelined<64, 2, QKType::Bf16, NORM, MULT>(p);
-            }
-        }
-        if (d == 128) return launch_pipelined<128, 4, QKType::Bf16, NORM, MULT>(p);
-        return launch_pipelined<64, 4, QKType::Bf16, NORM, MULT>(p);
+    if (narrow_tiles_pay(p, D)) {
+        // bf16 has a second 128-row form, four waves of 32 rows over all keys: the same sums as the
+        // 256-row kernel, and without the key groups' exchange (0.7 us) at the end it is ahead on the
+        // shortest launches: 4 tiles of d = 128 7.0 against 7.9 us, 16 tiles 14.1 against 14.8,
+        // 32 tiles 23.4 against 23.7; d = 64: 4 tiles 5.1 against 5.5, 16 tiles 10.2 against 10.0
+        if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
+            if (p.one_key_order || p.Nk <= (D == 128 ? 1024 : 512)) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+        if (!p.one_key_order) return launch_keysplit<D, QKT, MULT, PARTIAL>(p);
     }
-    if constexpr (NORM == Norm::Softmax && !MULT) {
-        if (dtype == SPHATTN_FP8QK_BF16V) {
-            if (d == 128) return launch_pipelined<128, 4, QKType::Fp8, NORM, MULT>(p);
-            return launch_pipelined<64, 4, QKType::Fp8, NORM, MULT>(p);
-        }
-    }
-    if constexpr (NORM == Norm::Spherical) {
-        if (dtype == SPHATTN_F16) {
-            if (d == 128) return launch_pipelined<128, 4, QKType::F16, NORM, MULT>(p);
-            return launch_pipelined<64, 4, QKType::F16, NORM, MULT>(p);
-        }
-        if (dtype == SPHATTN_FP8QK_BF16V) {
-            if (d == 128) return launch_pipelined<128, 4, QKType::Fp8, NORM, MULT>(p);
-            return launch_pipelined<64, 4, QKType::Fp8, NORM, MULT>(p);
-        }
-        if (dtype == SPHATTN_F32) {
-            if (d == 128) return launch_f32<128, MULT>(p);
-            return launch_f32<64, MULT>(p);
-        }
-    }
-    return SPHATTN_ERR_DTYPE;
+    return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
 }
 
-// Partial accumulators over key slices: always the 256-row workgroup (the slices, not narrower
-// tiles, are what fills the CUs).
-template <bool MULT>
-int dispatch_partial(const Problem& p, int d, int dtype)
+// Spherical attention in any storage type; PARTIAL: accumulators over key slices.
+template <bool MULT, bool PARTIAL = false>
+int dispatch_spherical(const Problem& p, int d, int dtype)
 {
-    constexpr Norm S = Norm::Spherical;
     switch (dtype) {
     case SPHATTN_BF16:
-        return d == 128 ? launch_pipelined<128, 4, QKType::Bf16, S, MULT, true>(p)
-                        : launch_pipelined<64, 4, QKType::Bf16, S, MULT, true>(p);
+        return d == 128 ? launch_spherical<128, QKType::Bf16, MULT, PARTIAL>(p) : launch_spherical<64, QKType::Bf16, MULT, PARTIAL>(p);
     case SPHATTN_F16:
-        return d == 128 ? launch_pipelined<128, 4, QKType::F16, S, MULT, true>(p)
-                        : launch_pipelined<64, 4, QKType::F16, S, MULT, true>(p);
+        return d == 128 ? launch_spherical<128, QKType::F16, MULT, PARTIAL>(p) : launch_spherical<64, QKType::F16, MULT, PARTIAL>(p);
     case SPHATTN_FP8QK_BF16V:
-        return d == 128 ? launch_pipelined<128, 4, QKType::Fp8, S, MULT, true>(p)
-                        : launch_pipelined<64, 4, QKType::Fp8, S, MULT, true>(p);
+        return d == 128 ? launch_spherical<128, QKType::Fp8, MULT, PARTIAL>(p) : launch_spherical<64, QKType::Fp8, MULT, PARTIAL>(p);
     case SPHATTN_F32:
-        return d == 128 ? launch_f32<128, MULT, true>(p) : launch_f32<64, MULT, true>(p);
+        return d == 128 ? launch_f32<128, MULT, PARTIAL>(p) : launch_f32<64, MULT, PARTIAL>(p);
     default:
         return SPHATTN_ERR_DTYPE;
     }
+}
+
+// The other normalizers: bf16, and the SoftMax twin also with fp8 Q/K.
+template <Norm NORM>
+int dispatch_normalizer(const Problem& p, int d, int dtype)
+{
+    if (dtype == SPHATTN_BF16)
+        return d == 128 ? launch_pipelined<128, 4, QKType::Bf16, NORM, false>(p) : launch_pipelined<64, 4, QKType::Bf16, NORM, false>(p);
+    if constexpr (NORM == Norm::Softmax) {
+        if (dtype == SPHATTN_FP8QK_BF16V)
+            return d == 128 ? launch_pipelined<128, 4, QKType::Fp8, NORM, false>(p) : launch_pipelined<64, 4, QKType::Fp8, NORM, false>(p);
+    }
+    return SPHATTN_ERR_DTYPE;
 }
 
 template <int D>
@@ -444,11 +448,12 @@ size_t workspace_bytes(int B, int H, int N, int d, int n_splits)
 // second launch reads is written by the first (every planned slice holds at least one tile),
 // so the workspace needs no clearing.
 int run_splitkv(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
-                int B, int H, int H_kv, int N, int d, int dtype, SplitPlan plan, void* workspace, hipStream_t stream)
+                int B, int H, int H_kv, int N, int d, int dtype, int requested, SplitPlan plan, void* workspace, hipStream_t stream)
 {
     if (plan.n_splits == 1) {                      // nothing to combine: the unsplit launch
-        const Problem whole{Q, K, V, O, mult, Z, B, H, H_kv, N, N, stream};
-        return mult ? dispatch<Norm::Spherical, true>(whole, d, dtype) : dispatch<Norm::Spherical, false>(whole, d, dtype);
+        Problem whole{Q, K, V, O, mult, Z, B, H, H_kv, N, N, stream};
+        whole.one_key_order = requested == 1;      // one slice asked for by name: its keys stay in one piece
+        return mult ? dispatch_spherical<true>(whole, d, dtype) : dispatch_spherical<false>(whole, d, dtype);
     }
     const size_t rows = (size_t)B * H * N;
     float* o_parts = (float*)workspace;
@@ -456,7 +461,7 @@ int run_splitkv(const void* Q, const void* K, const void* V, const float* mult, 
     Problem p{Q, K, V, o_parts, mult, z_parts, B, H, H_kv, N, N, stream};
     p.n_splits = plan.n_splits;
     p.keys_per_split = plan.keys_per_split;
-    const int r1 = mult ? dispatch_partial<true>(p, d, dtype) : dispatch_partial<false>(p, d, dtype);
+    const int r1 = mult ? dispatch_spherical<true, true>(p, d, dtype) : dispatch_spherical<false, true>(p, d, dtype);
     if (r1 != SPHATTN_OK) return r1;
     return d == 128 ? launch_combine<128>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, stream)
                     : launch_combine<64>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, stream);
@@ -582,7 +587,7 @@ int sphattn_fwd_tile_rows(const void* Q, const void* K, const void* V, void* O, 
     if (tile_rows != 0 && tile_rows != 128 && tile_rows != 256) return SPHATTN_ERR_SHAPE;
     Problem p{Q, K, V, O, nullptr, Z, B, H, H, N, N, (hipStream_t)stream};
     p.tile_rows = tile_rows;
-    return dispatch<Norm::Spherical, false>(p, d, dtype);
+    return dispatch_spherical<false>(p, d, dtype);
 }
 
 int sphattn_grn_fwd(const void* Q, const void* K, const void* V, const float* mult, void* O,
@@ -591,8 +596,8 @@ int sphattn_grn_fwd(const void* Q, const void* K, const void* V, const float* mu
     const int rc = check_args(Q, K, V, O, out_bytes_of(B, H, N, d, dtype), mult, nullptr, B, H, H_kv, N, N, d, dtype);
     if (rc != SPHATTN_OK) return rc;
     const Problem p{Q, K, V, O, mult, nullptr, B, H, H_kv, N, N, (hipStream_t)stream};
-    return mult ? dispatch<Norm::Spherical, true>(p, d, dtype)
-                : dispatch<Norm::Spherical, false>(p, d, dtype);
+    return mult ? dispatch_spherical<true>(p, d, dtype)
+                : dispatch_spherical<false>(p, d, dtype);
 }
 
 int sphattn_cross_fwd(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
@@ -601,8 +606,8 @@ int sphattn_cross_fwd(const void* Q, const void* K, const void* V, const float* 
     const int rc = check_args(Q, K, V, O, out_bytes_of(B, H, N_q, d, dtype), mult, Z, B, H, H_kv, N_q, N_k, d, dtype);
     if (rc != SPHATTN_OK) return rc;
     const Problem p{Q, K, V, O, mult, Z, B, H, H_kv, N_q, N_k, (hipStream_t)stream};
-    return mult ? dispatch<Norm::Spherical, true>(p, d, dtype)
-                : dispatch<Norm::Spherical, false>(p, d, dtype);
+    return mult ? dispatch_spherical<true>(p, d, dtype)
+                : dispatch_spherical<false>(p, d, dtype);
 }
 
 int sphattn_normalized_fwd(const void* Q, const void* K, const void* V, void* O,
@@ -616,10 +621,10 @@ int sphattn_normalized_fwd(const void* Q, const void* K, const void* V, void* O,
         return SPHATTN_ERR_DTYPE;
     const Problem p{Q, K, V, O, nullptr, nullptr, B, H, H, N, N, (hipStream_t)stream};
     switch (normalizer) {
-    case SPHATTN_NORM_L2: return dispatch<Norm::Spherical, false>(p, d, dtype);
-    case SPHATTN_NORM_SOFTMAX: return dispatch<Norm::Softmax, false>(p, d, dtype);
-    case SPHATTN_NORM_L1: return dispatch<Norm::L1, false>(p, d, dtype);
-    default: return dispatch<Norm::SqRelu, false>(p, d, dtype);
+    case SPHATTN_NORM_L2: return dispatch_spherical<false>(p, d, dtype);
+    case SPHATTN_NORM_SOFTMAX: return dispatch_normalizer<Norm::Softmax>(p, d, dtype);
+    case SPHATTN_NORM_L1: return dispatch_normalizer<Norm::L1>(p, d, dtype);
+    default: return dispatch_normalizer<Norm::SqRelu>(p, d, dtype);
     }
 }
 
@@ -644,7 +649,7 @@ int sphattn_partial_fwd(const void* Q, const void* K, const void* V, const float
     Problem p{Q, K, V, o_part, mult, z_part, B, H, H_kv, N_q, N_k, (hipStream_t)stream};
     p.n_splits = 1;
     p.keys_per_split = plan_splits(N_k, 1).keys_per_split;
-    return mult ? dispatch_partial<true>(p, d, dtype) : dispatch_partial<false>(p, d, dtype);
+    return mult ? dispatch_spherical<true, true>(p, d, dtype) : dispatch_spherical<false, true>(p, d, dtype);
 }
 
 int sphattn_combine(const float* o_parts, const float* z_parts, int n_parts, void* O, float* Z,
@@ -741,6 +746,7 @@ int sphattn_splitkv_fwd(const void* Q, const void* K, const void* V, const float
     const int rc = check_args(Q, K, V, O, out_bytes_of(B, H, N, d, dtype), mult, Z, B, H, H_kv, N, N, d, dtype);
     if (rc != SPHATTN_OK) return rc;
     if (n_splits < 0) return SPHATTN_ERR_SHAPE;
+    const int requested = n_splits;
     if (n_splits == 0) n_splits = sphattn_splitkv_heuristic(B, H, N, d, dtype);
     const SplitPlan plan = plan_splits(N, n_splits);
     const size_t need = sphattn_splitkv_workspace_bytes(B, H, N, d, plan.n_splits);
@@ -755,7 +761,7 @@ int sphattn_splitkv_fwd(const void* Q, const void* K, const void* V, const float
         (mult && overlaps(workspace, need, mult, (size_t)B * N * 4)) ||
         (Z && overlaps(workspace, need, Z, (size_t)B * H * N * 4)))
         return SPHATTN_ERR_ALIAS;
-    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, plan, workspace, (hipStream_t)stream);
+    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, workspace, (hipStream_t)stream);
 }
 
 int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
@@ -764,6 +770,7 @@ int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, con
     const int rc = check_args(Q, K, V, O, out_bytes_of(B, H, N, d, dtype), mult, Z, B, H, H_kv, N, N, d, dtype);
     if (rc != SPHATTN_OK) return rc;
     if (n_splits < 0) return SPHATTN_ERR_SHAPE;
+    const int requested = n_splits;
     if (n_splits == 0) {                           // the library's choice, if the array holds it
         n_splits = sphattn_splitkv_heuristic(B, H, N, d, dtype);
         if (sphattn_splitkv_workspace_bytes(B, H, N, d, plan_splits(N, n_splits).n_splits) > (size_t)SPHATTN_NOALLOC_SCRATCH_BYTES)
@@ -771,13 +778,13 @@ int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, con
     }
     const SplitPlan plan = plan_splits(N, n_splits);
     // one slice is the unsplit launch and needs no scratch
-    if (plan.n_splits == 1) return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, plan, nullptr, (hipStream_t)stream);
+    if (plan.n_splits == 1) return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, nullptr, (hipStream_t)stream);
     const size_t need = sphattn_splitkv_workspace_bytes(B, H, N, d, plan.n_splits);
     if (need == 0 || need > (size_t)SPHATTN_NOALLOC_SCRATCH_BYTES) return SPHATTN_ERR_SCRATCH;
     void* ws = scratch_address();
     if (ws == nullptr) return SPHATTN_ERR_LAUNCH;
     // the caller's buffers are allocations of their own and cannot overlap the library's array
-    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, plan, ws, (hipStream_t)stream);
+    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, ws, (hipStream_t)stream);
 }
 
 int sphattn_grn_bwd(const void* Q, const void* K, const void* V, const float* mult,

@@ -1,0 +1,91 @@
+"""The 128-row forward kernel whose two wave pairs share out every key tile (sphattn_keysplit.hpp):
+odd and even tile counts, ragged last tiles, tiles past the end, rows past the last query; every
+storage type, multiplicities, row aggregates and partial accumulators, element by element against
+the oracle.  Tolerances are those of test_gpu_parity.py and test_gpu_partial_splitkv.py."""
+import numpy as np
+import pytest
+import torch
+
+import synthetic_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+TOL_O = {"bf16": 2e-2, "fp8qk_bf16v": 6e-2, "f16": 5e-3}
+TOL_PART = {"bf16": 1e-2, "fp8qk_bf16v": 1e-2, "f16": 2e-3}
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2505_09326_amd as p
+    p.load_library()
+    return p
+
+
+def _rel_err(got, ref):
+    return np.abs(got - ref).max() / np.sqrt((ref ** 2).mean())
+
+
+def _bits(*ts):
+    pairs = [si.storage_bits(t) for t in ts]
+    return [p[0] for p in pairs], tuple(p[1] for p in pairs)
+
+
+# bf16 below 1025 (d = 128) and 513 (d = 64) keys runs the other 128-row kernel
+SHAPES = [(n, d, t) for t in ("f16", "fp8qk_bf16v") for d in (64, 128) for n in (1, 31, 64, 65, 129, 257, 383)] + \
+         [(1025, 128, "bf16"), (1279, 128, "bf16"), (513, 64, "bf16"), (700, 64, "bf16")]
+
+
+@pytest.mark.parametrize("N,d,dtype", SHAPES)
+def test_forced_128_rows_against_the_oracle(pkg, oracle, N, d, dtype):
+    print(f"case keysplit N={N} d={d} {dtype}", flush=True)
+    q, k, v = si.make_qkv(1, 2, N, d, dtype, seed=4000 + N + d)
+    Z = torch.empty((1, 2, N), dtype=torch.float32, device=DEV)
+    O, _ = pkg.sphattn_fwd_tile_rows(q.to(DEV), k.to(DEV), v.to(DEV), Z=Z, dtype=dtype, tile_rows=128)
+    torch.cuda.synchronize()
+    bits, kinds = _bits(q, k, v)
+    ref, _, ref_z = oracle.spherical_attention_full(*bits, kinds=kinds)
+    got = O.cpu().double().numpy()
+    assert np.all(np.isfinite(got))
+    assert _rel_err(got, ref) <= TOL_O[dtype]
+    if dtype == "fp8qk_bf16v":
+        # the fp8 matrix instruction sums its 128 products with fewer bits than fp32 (a score may be
+        # off by about 2^-16 of the sum of its products' magnitudes, far more than 1e-4 of itself
+        # where they cancel, and a row of one key does not average that out): the same scores as the
+        # 256-row kernel's, squared and summed in another order, N 2^-24 at most
+        _, Z256 = pkg.sphattn_fwd_tile_rows(q.to(DEV), k.to(DEV), v.to(DEV), Z=torch.empty_like(Z), dtype=dtype, tile_rows=256)
+        np.testing.assert_allclose(Z.cpu().double().numpy(), Z256.cpu().double().numpy(), rtol=(N + 8) * 2.0 ** -24)
+    else:
+        # a single key: z carries the fp32 rounding of one score that may nearly cancel
+        np.testing.assert_allclose(Z.cpu().double().numpy(), ref_z, rtol=2e-4, atol=1e-7 * ref_z.max())
+
+
+@pytest.mark.parametrize("Nq,Nk,d,dtype", [(130, 1, 64, "f16"), (127, 65, 128, "f16"), (200, 191, 128, "bf16"),
+                                           (129, 448, 64, "bf16"), (300, 130, 128, "fp8qk_bf16v"), (1, 320, 64, "fp8qk_bf16v")])
+def test_partial_accumulators_with_multiplicities(pkg, oracle, Nq, Nk, d, dtype):
+    print(f"case keysplit partial Nq={Nq} Nk={Nk} d={d} {dtype}", flush=True)
+    q, _, _ = si.make_qkv(1, 4, Nq, d, dtype, seed=4100 + Nq)
+    _, k, v = si.make_qkv(1, 2, Nk, d, dtype, seed=4200 + Nk)
+    g = torch.Generator(device="cpu").manual_seed(4300 + Nk)
+    mult = torch.poisson(torch.full((1, Nk), 1.5), generator=g).to(torch.float32)
+    mult[:, 0] = 2.0
+    o, z = pkg.sphattn_partial_fwd(q.to(DEV), k.to(DEV), v.to(DEV), mult.to(DEV), dtype=dtype)
+    O = pkg.sphattn_cross_fwd(q.to(DEV), k.to(DEV), v.to(DEV), mult.to(DEV), dtype=dtype)
+    torch.cuda.synchronize()
+    bits, kinds = _bits(q, k, v)
+    ref_o, ref_z = oracle.spherical_accumulate(*bits, mult.numpy(), kinds=kinds)
+    nrm = np.sqrt(ref_z)[..., None]
+    assert _rel_err(o.cpu().double().numpy() / nrm, ref_o / nrm) <= TOL_PART[dtype]
+    np.testing.assert_allclose(z.cpu().double().numpy(), ref_z, rtol=2e-4, atol=1e-7 * ref_z.max())
+    assert _rel_err(O.cpu().double().numpy(), oracle.spherical_tail(ref_o[None], ref_z[None])) <= TOL_O[dtype]
+
+
+def test_several_batches_of_128_row_items_walk_the_keys_both_ways(pkg, oracle):
+    """More items than run at once: the second batch of a persistent workgroup reuses its LDS and
+    streams the (ragged) keys backwards."""
+    B, H, N, d = 1, 40, 1100, 128                # 360 items for 256 workgroups
+    q, k, v = si.make_qkv(B, H, N, d, "f16", seed=4400)
+    O, _ = pkg.sphattn_fwd_tile_rows(q.to(DEV), k.to(DEV), v.to(DEV), dtype="f16", tile_rows=128)
+    torch.cuda.synchronize()
+    bits, kinds = _bits(q, k, v)
+    assert _rel_err(O.cpu().double().numpy(), oracle.spherical_attention(*bits, kinds=kinds)) <= TOL_O["f16"]
