@@ -246,6 +246,23 @@ int sphattn_splitkv_fwd(const void* Q, const void* K, const void* V, const float
 int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
                                 int B, int H, int H_kv, int N, int d, int dtype, int n_splits, void* stream);
 
+/*
+ * sphattn_cross_fwd with the key axis cut into as many slices as the library chooses (one: the
+ * unsplit launch) when the query rows alone do not fill the compute units: a chunk of queries
+ * against long keys, or few heads.
+ *   workspace : device scratch, 16-byte aligned, at least sphattn_cross_splitkv_workspace_bytes(...)
+ *               bytes for the same shape; where that is 0 the workspace is not looked at and may be
+ *               NULL.  Contents undefined afterwards; must not overlap any other argument; calls
+ *               that overlap in time need workspaces of their own.
+ * Other arguments and errors as sphattn_cross_fwd; a bad workspace returns SPHATTN_ERR_WORKSPACE.
+ * sphattn_cross_splitkv_workspace_bytes launches nothing and returns 0 for a shape that
+ * sphattn_cross_fwd would reject; its answer depends on the compute units of the current device.
+ */
+size_t sphattn_cross_splitkv_workspace_bytes(int B, int H, int H_kv, int N_q, int N_k, int d, int dtype);
+int sphattn_cross_splitkv_fwd(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
+                              int B, int H, int H_kv, int N_q, int N_k, int d, int dtype,
+                              void* workspace, size_t workspace_size, void* stream);
+
 /* Bytes of workspace sphattn_splitkv_fwd needs for n_splits >= 1 slices: n_splits * B*H*N * (d+1)
  * fp32 values, rounded up to 256.  Returns 0 for arguments sphattn_splitkv_fwd would reject. */
 size_t sphattn_splitkv_workspace_bytes(int B, int H, int N, int d, int n_splits);

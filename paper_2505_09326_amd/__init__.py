@@ -29,6 +29,7 @@ EXPORTED_SYMBOLS = ("sphattn_fwd", "sphattn_fwd_z", "sphattn_fwd_tile_rows", "sp
                     "sphattn_normalized_fwd", "sphattn_softmax_fwd", "sphattn_cross_fwd", "sphattn_partial_fwd",
                     "sphattn_combine", "sphattn_splitkv_fwd", "sphattn_splitkv_workspace_bytes",
                     "sphattn_splitkv_heuristic", "sphattn_splitkv_fwd_noalloc",
+                    "sphattn_cross_splitkv_workspace_bytes", "sphattn_cross_splitkv_fwd",
                     "sphattn_bwd", "sphattn_grn_bwd",
                     "sphattn_fp8_workspace_bytes", "sphattn_fp8_fwd", "sphattn_fp8_grn_fwd", "sphattn_fp8_softmax_fwd",
                     "sphattn_strerror", "sphattn_version")
@@ -80,6 +81,10 @@ def load_library() -> ctypes.CDLL:
         lib.sphattn_splitkv_workspace_bytes.argtypes = [ip, ip, ip, ip, ip]
         lib.sphattn_splitkv_heuristic.restype = ip
         lib.sphattn_splitkv_heuristic.argtypes = [ip, ip, ip, ip, ip]
+        lib.sphattn_cross_splitkv_workspace_bytes.restype = sz
+        lib.sphattn_cross_splitkv_workspace_bytes.argtypes = [ip] * 7
+        lib.sphattn_cross_splitkv_fwd.restype = ip
+        lib.sphattn_cross_splitkv_fwd.argtypes = [vp] * 6 + [ip] * 7 + [vp, sz, vp]
         lib.sphattn_bwd.restype = ip
         lib.sphattn_bwd.argtypes = [vp] * 10 + [ip, ip, ip, ip, ip, vp]
         lib.sphattn_grn_bwd.restype = ip
@@ -218,16 +223,37 @@ def _raise_on(rc):
         raise SphattnError(rc, sphattn_strerror(rc))
 
 
+def _launch_cross(lib, Q, K, V, mult, O, Z, B, H, H_kv, Nq, Nk, d, code, stream, own_output):
+    """sphattn_cross_fwd on checked arguments.  Where the library would cut the key axis (few query
+    rows against many keys) and this call allocates its output anyway, the slices' workspace comes
+    from torch's allocator too: on the current stream, so its reuse is ordered behind the launch.
+    A caller that brings O or a stream handle of its own gets no allocation and the unsplit launch."""
+    if own_output and stream is None:
+        need = lib.sphattn_cross_splitkv_workspace_bytes(B, H, H_kv, Nq, Nk, d, code)
+        if need:
+            import torch
+            try:
+                ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
+            except torch.OutOfMemoryError:
+                ws = None
+            if ws is not None:
+                _raise_on(lib.sphattn_cross_splitkv_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult),
+                                                        O.data_ptr(), _ptr(Z), B, H, H_kv, Nq, Nk, d, code,
+                                                        ws.data_ptr(), need, _stream_of(Q, None)))
+                return
+    _raise_on(lib.sphattn_cross_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), _ptr(Z),
+                                    B, H, H_kv, Nq, Nk, d, code, _stream_of(Q, stream)))
+
+
 # ---- entry points, same names as the C ABI ----------------------------------------------------
 
 def sphattn_fwd(Q, K, V, O=None, dtype="bf16", stream=None):
     """O = (Q K^T) V with each score row divided by its L2 norm; tensors are [B,H,N,d]."""
-    lib, code = load_library(), _dtype_code(dtype)
+    lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
         O = _alloc_out(Q, dtype)
     B, H, N, d, _, _ = _check_forward(Q, K, V, O, None, None, code, same_h=True)
-    _raise_on(lib.sphattn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
-                              B, H, N, d, code, _stream_of(Q, stream)))
+    _launch_cross(lib, Q, K, V, None, O, None, B, H, H, N, N, d, code, stream, own_output)
     return O
 
 
@@ -244,18 +270,23 @@ def sphattn_softmax_fwd(Q, K, V, O=None, dtype="bf16", stream=None):
 
 def sphattn_fwd_z(Q, K, V, O=None, Z=None, dtype="bf16", stream=None):
     """sphattn_fwd that also returns the row aggregates z_i = sum_j s_ij^2: (O, Z [B,H,N] fp32)."""
-    return sphattn_fwd_tile_rows(Q, K, V, O=O, Z=Z, dtype=dtype, tile_rows=0, stream=stream, _want_z=True)
+    import torch
+    lib, code, own_output = load_library(), _dtype_code(dtype), O is None
+    if O is None:
+        O = _alloc_out(Q, dtype)
+    if Z is None:
+        Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
+    B, H, N, d, _, _ = _check_forward(Q, K, V, O, None, Z, code, same_h=True)
+    _launch_cross(lib, Q, K, V, None, O, Z, B, H, H, N, N, d, code, stream, own_output)
+    return O, Z
 
 
-def sphattn_fwd_tile_rows(Q, K, V, O=None, Z=None, dtype="bf16", tile_rows=0, stream=None, _want_z=False):
+def sphattn_fwd_tile_rows(Q, K, V, O=None, Z=None, dtype="bf16", tile_rows=0, stream=None):
     """sphattn_fwd_z with the workgroup shape forced to 128 or 256 query rows (0: the library's
     choice); returns (O, Z), Z being None unless given."""
-    import torch
     lib, code = load_library(), _dtype_code(dtype)
     if O is None:
         O = _alloc_out(Q, dtype)
-    if Z is None and _want_z:
-        Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
     B, H, N, d, _, _ = _check_forward(Q, K, V, O, None, Z, code, same_h=True)
     _raise_on(lib.sphattn_fwd_tile_rows(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), _ptr(Z),
                                         B, H, N, d, code, int(tile_rows), _stream_of(Q, stream)))
@@ -265,12 +296,11 @@ def sphattn_fwd_tile_rows(Q, K, V, O=None, Z=None, dtype="bf16", tile_rows=0, st
 def sphattn_grn_fwd(Q, K, V, mult=None, O=None, dtype="bf16", stream=None):
     """Gene-regulatory-network variant: keys scaled by per-gene multiplicity mult[B,N] (fp32 or
     None) and K, V of shape [B,H_kv,N,d] shared by groups of H/H_kv query heads."""
-    lib, code = load_library(), _dtype_code(dtype)
+    lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
         O = _alloc_out(Q, dtype)
     B, H, N, d, H_kv, _ = _check_forward(Q, K, V, O, mult, None, code)
-    _raise_on(lib.sphattn_grn_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(),
-                                  B, H, H_kv, N, d, code, _stream_of(Q, stream)))
+    _launch_cross(lib, Q, K, V, mult, O, None, B, H, H_kv, N, N, d, code, stream, own_output)
     return O
 
 
@@ -289,12 +319,11 @@ def sphattn_normalized_fwd(Q, K, V, O=None, dtype="bf16", normalizer="l2", strea
 def sphattn_cross_fwd(Q, K, V, mult=None, O=None, Z=None, dtype="bf16", stream=None):
     """Spherical attention of Q [B,H,N_q,d] over the keys K, V [B,H_kv,N_k,d] (optional
     multiplicities mult [B,N_k], optional row aggregates Z [B,H,N_q]); returns O [B,H,N_q,d]."""
-    lib, code = load_library(), _dtype_code(dtype)
+    lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
         O = _alloc_out(Q, dtype)
     B, H, Nq, d, H_kv, Nk = _check_forward(Q, K, V, O, mult, Z, code, same_n=False)
-    _raise_on(lib.sphattn_cross_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), _ptr(Z),
-                                    B, H, H_kv, Nq, Nk, d, code, _stream_of(Q, stream)))
+    _launch_cross(lib, Q, K, V, mult, O, Z, B, H, H_kv, Nq, Nk, d, code, stream, own_output)
     return O
 
 

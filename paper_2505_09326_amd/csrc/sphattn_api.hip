@@ -141,6 +141,22 @@ struct Problem {
     bool one_key_order = false; // every row's sums in the key order of the 256-row kernel, whatever the workgroup
 };
 
+// Query heads that share a K/V head lie next to each other, so their rows are one block of
+// H / H_kv * Nq rows against that K/V head (Q, O, Z and the partial buffers alike, and the
+// multiplicities belong to the batch entry): the launch sees H_kv heads of so many rows.  Whole
+// tiles then run across the heads of a group: 4 heads of 64 queries are one tile of 256 rows
+// instead of four quarter-filled ones that each stream the same K and V.  Not where one head's
+// buffer range would pass 32 bits.
+Problem packed_group(Problem p, int d)
+{
+    const long long group = p.H / p.H_kv;
+    if (group > 1 && group * p.Nq * d * 4 <= 0x7fffffff) {
+        p.Nq = (int)(group * p.Nq);
+        p.H = p.H_kv;
+    }
+    return p;
+}
+
 // Key slices are whole 64-key tiles.  Asking for more slices than there are tiles, or for a
 // count that does not divide them evenly, yields fewer, equally sized slices (the last may be
 // shorter).
@@ -352,8 +368,9 @@ int launch_spherical(const Problem& p)
 
 // Spherical attention in any storage type; PARTIAL: accumulators over key slices.
 template <bool MULT, bool PARTIAL = false>
-int dispatch_spherical(const Problem& p, int d, int dtype)
+int dispatch_spherical(const Problem& call, int d, int dtype)
 {
+    const Problem p = packed_group(call, d);
     switch (dtype) {
     case SPHATTN_BF16:
         return d == 128 ? launch_spherical<128, QKType::Bf16, MULT, PARTIAL>(p) : launch_spherical<64, QKType::Bf16, MULT, PARTIAL>(p);
@@ -447,24 +464,25 @@ size_t workspace_bytes(int B, int H, int N, int d, int n_splits)
 // into `workspace` (o parts, then z parts), then their sum and the tail.  Every partial the
 // second launch reads is written by the first (every planned slice holds at least one tile),
 // so the workspace needs no clearing.
-int run_splitkv(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
-                int B, int H, int H_kv, int N, int d, int dtype, int requested, SplitPlan plan, void* workspace, hipStream_t stream)
+int run_splitkv(Problem p, int d, int dtype, int requested, SplitPlan plan, void* workspace)
 {
     if (plan.n_splits == 1) {                      // nothing to combine: the unsplit launch
-        Problem whole{Q, K, V, O, mult, Z, B, H, H_kv, N, N, stream};
-        whole.one_key_order = requested == 1;      // one slice asked for by name: its keys stay in one piece
-        return mult ? dispatch_spherical<true>(whole, d, dtype) : dispatch_spherical<false>(whole, d, dtype);
+        p.one_key_order = requested == 1;          // one slice asked for by name: its keys stay in one piece
+        return p.mult ? dispatch_spherical<true>(p, d, dtype) : dispatch_spherical<false>(p, d, dtype);
     }
-    const size_t rows = (size_t)B * H * N;
+    const size_t rows = (size_t)p.B * p.H * p.Nq;
+    void* O = p.O;
+    float* Z = p.Z;
     float* o_parts = (float*)workspace;
     float* z_parts = o_parts + (size_t)plan.n_splits * rows * d;
-    Problem p{Q, K, V, o_parts, mult, z_parts, B, H, H_kv, N, N, stream};
+    p.O = o_parts;
+    p.Z = z_parts;
     p.n_splits = plan.n_splits;
     p.keys_per_split = plan.keys_per_split;
-    const int r1 = mult ? dispatch_spherical<true, true>(p, d, dtype) : dispatch_spherical<false, true>(p, d, dtype);
+    const int r1 = p.mult ? dispatch_spherical<true, true>(p, d, dtype) : dispatch_spherical<false, true>(p, d, dtype);
     if (r1 != SPHATTN_OK) return r1;
-    return d == 128 ? launch_combine<128>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, stream)
-                    : launch_combine<64>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, stream);
+    return d == 128 ? launch_combine<128>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, p.stream)
+                    : launch_combine<64>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, p.stream);
 }
 
 template <int D, bool SOFTMAX, bool MULT>
@@ -536,6 +554,119 @@ int fp8_forward(const void* Q, const void* K, const void* V, const float* mult, 
     if (softmax) return launch_fp8<64, true, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
     return mult ? launch_fp8<64, false, true>(Q, K, VT, kmax, mult, O, B, H, H_kv, N, n_tiles, st)
                 : launch_fp8<64, false, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
+}
+
+// Key slices for `heads` heads of Nq query rows against Nk keys: 1 where cutting is not expected to
+// gain at least 3 %, otherwise the count with the lowest estimated run time.
+int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
+{
+    const long long cus = cu_count();
+    const long long tiles = (Nk + kBC - 1) / kBC;
+    const long long most = (tiles + 7) / 8;        // no slice shorter than 8 tiles
+    if (dtype == SPHATTN_F32) {
+        // the fp32 kernel's workgroups hold 32 query rows: enough slices to give every CU one
+        const long long wg = heads * ((Nq + 31) / 32);
+        if (wg >= cus) return 1;
+        const long long want = (cus + wg - 1) / wg;
+        return plan_splits((int)Nk, (int)(want < most ? want : most)).n_splits;
+    }
+    // 256-row workgroups, `resident` of them at once (two per CU at d = 64).  A launch of wg S
+    // items takes rounds = ceil(wg S / resident) rounds, run equally full (balanced_grid); a round
+    // filled to the fraction f of the chip takes about 0.5 + 0.5 f of a full round's time (the
+    // part is power-bound: idle CUs give their share of the budget to the rest), and an item
+    // spends about 3.5 tile times on its prologue and tail.  In units of one full round over all
+    // keys: main(S) = (0.5 rounds / S + 0.5 wg / resident) (1 + 3.5 / tiles per slice); the combine
+    // step adds its launch (about 3 tile times) and S passes over wg / resident of the rows, 300 / Nk
+    // of a round each.  Unsplit, a launch of at most `resident` 128-row workgroups costs
+    // 0.6 (0.5 + wg / resident) on the same scale.  Measured against these (bf16, one GPU):
+    // 1 x 8192 x 128: S = 8 44 us (4: 57, unsplit 99); 2 x 8192 x 128: S = 4; 1 x 32768 x 128: S = 2;
+    // 8 x 4096 x 128: unsplit; 1 x 40000 x 128 (157 tiles): S = 3 533 us (2: 645, unsplit 629);
+    // 3 x 16384 x 128 (192 tiles): S = 4 291 us (2: 300, unsplit 298); 5 x 16384 x 64: S = 3 251 (unsplit 285).
+    // The same holds above one round: 8 x 20000 x 128 (632 tiles, 2.47 rounds): S = 2 1080 us, unsplit 1174.
+    const long long wg = heads * ((Nq + 255) / 256);
+    const long long resident = cus * (d == 64 ? 2 : 1);
+    const double share = (double)wg / (double)resident;
+    const double edge = 3.5;
+    const long long rounds1 = (wg + resident - 1) / resident;
+    double best = (0.5 * (double)rounds1 + 0.5 * share) * (1.0 + edge / (double)tiles);
+    if (d == 64 && (dtype == SPHATTN_BF16 || dtype == SPHATTN_F16) && wg > resident && wg % resident != 0 &&
+        2 * (wg % resident) <= resident) {
+        // the unsplit launch runs this remainder as 128-row halves (launch_pipelined)
+        const double halves = ((double)(wg / resident) + 0.3 + 0.6 * (double)(wg % resident) / (double)resident) *
+                              (1.0 + edge / (double)tiles);
+        best = halves < best ? halves : best;
+    }
+    if (wg < resident && heads * ((Nq + 127) / 128) <= resident) {
+        const double narrow = 0.6 * (0.5 + share) * (1.0 + edge / (double)tiles);
+        best = narrow < best ? narrow : best;
+    }
+    best *= 0.97;                                  // split only for a gain of at least 3 %
+    int pick = 1;
+    for (long long S = 2; S <= most && S <= 32; ++S) {
+        const SplitPlan plan = plan_splits((int)Nk, (int)S);
+        if (plan.n_splits != S) continue;          // this count does not divide the tiles: same as a smaller one
+        const long long rounds = (wg * S + resident - 1) / resident;
+        const double per = (double)(plan.keys_per_split / kBC);
+        const double cost = (0.5 * (double)rounds / (double)S + 0.5 * share) * (1.0 + edge / per)
+                            + 3.0 / (double)tiles + (double)S * share * 300.0 / (double)Nk;
+        // above one round the workspace is large: more slices only for more than 1 %
+        if (cost < (wg >= resident ? 0.99 : 1.0) * best) {
+            best = cost;
+            pick = (int)S;
+        }
+    }
+    return pick;
+}
+
+// The library's choice of slices for a rectangular problem, in the launch's terms (packed_group).
+// A launch is cut only while all its slices still run at once as 128-row workgroups, one per CU
+// (at d = 64 as well: 1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  In us,
+// from launches of one to many slices: a workgroup spends 6 on its first and last bytes and tau on
+// each 64-key tile, tau growing with the share of the CUs in use (the part is power-bound); the
+// second launch costs 4, and each part is written and read at 4 TB/s together.  Measured with the
+// slices this picks against one: 1 x 8192 x 128 39 against 76 us, 2 x 8192 x 128 59 against 77,
+// 1 x 4096 x 128 23 against 40, 1 x 8192 x 64 24 against 49; not cut: 4 x 1999 x 128 (22.7 against
+// 23.3 would be the best), 8 x 1000 x 128 (18.1 against 13.9).
+SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
+{
+    Problem p{};
+    p.B = B; p.H = H; p.H_kv = H_kv; p.Nq = Nq; p.Nk = Nk;
+    p = packed_group(p, d);
+    const long long heads = (long long)p.B * p.H;
+    if (dtype == SPHATTN_F32) return plan_splits(Nk, choose_splits(heads, p.Nq, Nk, d, dtype));
+    const long long items = heads * ((p.Nq + kSplitRows - 1) / kSplitRows), cus = cu_count();
+    const int tiles = (Nk + kBC - 1) / kBC;
+    const double part_us = (double)heads * (double)p.Nq * (d + 1) * 8.0 / 4e6;
+    SplitPlan best = plan_splits(Nk, 1);
+    double best_us = 0.0;
+    for (long long S = 1; S * items <= cus && S <= tiles; ++S) {
+        const SplitPlan plan = plan_splits(Nk, (int)S);
+        if (plan.n_splits != S) continue;          // the same slices as a smaller count
+        const double f = (double)(S * items) / (double)cus;
+        const double tau = d == 64 ? 0.36 + 0.08 * f : 0.55 + 0.22 * f;
+        double us = 6.0 + tau * (double)(plan.keys_per_split / kBC);
+        if (S > 1) us += 4.0 + (double)S * part_us;
+        if (S == 1) { best_us = 0.9 * us; continue; }   // cut only for a gain of at least 10 %
+        if (us < best_us) { best_us = us; best = plan; }
+    }
+    return best;
+}
+
+// The workspace of a split launch against its size and the other arguments.
+int check_workspace(const Problem& p, int d, int dtype, SplitPlan plan, const void* workspace, size_t size)
+{
+    const size_t need = sphattn_splitkv_workspace_bytes(p.B, p.H, p.Nq, d, plan.n_splits);
+    if (!workspace || need == 0 || size < need || ((uintptr_t)workspace & 15)) return SPHATTN_ERR_WORKSPACE;
+    if (wraps(workspace, need)) return SPHATTN_ERR_WORKSPACE;
+    const size_t nq = (size_t)p.B * p.H * p.Nq * d, nkv = (size_t)p.B * p.H_kv * p.Nk * d;
+    const size_t qk = dtype == SPHATTN_F32 ? 4 : dtype == SPHATTN_FP8QK_BF16V ? 1 : 2;
+    const size_t vo = dtype == SPHATTN_F32 ? 4 : 2;
+    if (overlaps(workspace, need, p.Q, nq * qk) || overlaps(workspace, need, p.K, nkv * qk) ||
+        overlaps(workspace, need, p.V, nkv * vo) || overlaps(workspace, need, p.O, out_bytes_of(p.B, p.H, p.Nq, d, dtype)) ||
+        (p.mult && overlaps(workspace, need, p.mult, (size_t)p.B * p.Nk * 4)) ||
+        (p.Z && overlaps(workspace, need, p.Z, (size_t)p.B * p.H * p.Nq * 4)))
+        return SPHATTN_ERR_ALIAS;
+    return SPHATTN_OK;
 }
 
 // Scratch memory of sphattn_splitkv_fwd_noalloc: one array per GPU, part of the library's code
@@ -681,62 +812,7 @@ size_t sphattn_splitkv_workspace_bytes(int B, int H, int N, int d, int n_splits)
 int sphattn_splitkv_heuristic(int B, int H, int N, int d, int dtype)
 {
     if (B <= 0 || H <= 0 || N <= 0 || (d != 64 && d != 128)) return 1;
-    const long long cus = cu_count();
-    const long long tiles = ((long long)N + kBC - 1) / kBC;
-    const long long most = (tiles + 7) / 8;        // no slice shorter than 8 tiles
-    if (dtype == SPHATTN_F32) {
-        // the fp32 kernel's workgroups hold 32 query rows: enough slices to give every CU one
-        const long long wg = (long long)B * H * (((long long)N + 31) / 32);
-        if (wg >= cus) return 1;
-        const long long want = (cus + wg - 1) / wg;
-        return plan_splits(N, (int)(want < most ? want : most)).n_splits;
-    }
-    // 256-row workgroups, `resident` of them at once (two per CU at d = 64).  A launch of wg S
-    // items takes rounds = ceil(wg S / resident) rounds, run equally full (balanced_grid); a round
-    // filled to the fraction f of the chip takes about 0.5 + 0.5 f of a full round's time (the
-    // part is power-bound: idle CUs give their share of the budget to the rest), and an item
-    // spends about 3.5 tile times on its prologue and tail.  In units of one full round over all
-    // keys: main(S) = (0.5 rounds / S + 0.5 wg / resident) (1 + 3.5 / tiles per slice); the combine
-    // step adds its launch (about 3 tile times) and S passes over wg / resident of the rows, 300 / N
-    // of a round each.  Unsplit, a launch of at most `resident` 128-row workgroups costs
-    // 0.6 (0.5 + wg / resident) on the same scale.  Measured against these (bf16, one GPU):
-    // 1 x 8192 x 128: S = 8 44 us (4: 57, unsplit 99); 2 x 8192 x 128: S = 4; 1 x 32768 x 128: S = 2;
-    // 8 x 4096 x 128: unsplit; 1 x 40000 x 128 (157 tiles): S = 3 533 us (2: 645, unsplit 629);
-    // 3 x 16384 x 128 (192 tiles): S = 4 291 us (2: 300, unsplit 298); 5 x 16384 x 64: S = 3 251 (unsplit 285).
-    // The same holds above one round: 8 x 20000 x 128 (632 tiles, 2.47 rounds): S = 2 1080 us, unsplit 1174.
-    const long long wg = (long long)B * H * (((long long)N + 255) / 256);
-    const long long resident = cus * (d == 64 ? 2 : 1);
-    const double share = (double)wg / (double)resident;
-    const double edge = 3.5;
-    const long long rounds1 = (wg + resident - 1) / resident;
-    double best = (0.5 * (double)rounds1 + 0.5 * share) * (1.0 + edge / (double)tiles);
-    if (d == 64 && (dtype == SPHATTN_BF16 || dtype == SPHATTN_F16) && wg > resident && wg % resident != 0 &&
-        2 * (wg % resident) <= resident) {
-        // the unsplit launch runs this remainder as 128-row halves (launch_pipelined)
-        const double halves = ((double)(wg / resident) + 0.3 + 0.6 * (double)(wg % resident) / (double)resident) *
-                              (1.0 + edge / (double)tiles);
-        best = halves < best ? halves : best;
-    }
-    if (wg < resident && (long long)B * H * (((long long)N + 127) / 128) <= resident) {
-        const double narrow = 0.6 * (0.5 + share) * (1.0 + edge / (double)tiles);
-        best = narrow < best ? narrow : best;
-    }
-    best *= 0.97;                                  // split only for a gain of at least 3 %
-    int pick = 1;
-    for (long long S = 2; S <= most && S <= 32; ++S) {
-        const SplitPlan plan = plan_splits(N, (int)S);
-        if (plan.n_splits != S) continue;          // this count does not divide the tiles: same as a smaller one
-        const long long rounds = (wg * S + resident - 1) / resident;
-        const double per = (double)(plan.keys_per_split / kBC);
-        const double cost = (0.5 * (double)rounds / (double)S + 0.5 * share) * (1.0 + edge / per)
-                            + 3.0 / (double)tiles + (double)S * share * 300.0 / (double)N;
-        // above one round the workspace is large: more slices only for more than 1 %
-        if (cost < (wg >= resident ? 0.99 : 1.0) * best) {
-            best = cost;
-            pick = (int)S;
-        }
-    }
-    return pick;
+    return choose_splits((long long)B * H, N, N, d, dtype);
 }
 
 int sphattn_splitkv_fwd(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
@@ -749,19 +825,31 @@ int sphattn_splitkv_fwd(const void* Q, const void* K, const void* V, const float
     const int requested = n_splits;
     if (n_splits == 0) n_splits = sphattn_splitkv_heuristic(B, H, N, d, dtype);
     const SplitPlan plan = plan_splits(N, n_splits);
-    const size_t need = sphattn_splitkv_workspace_bytes(B, H, N, d, plan.n_splits);
-    if (!workspace || need == 0 || workspace_size < need || ((uintptr_t)workspace & 15)) return SPHATTN_ERR_WORKSPACE;
-    const size_t ob = out_bytes_of(B, H, N, d, dtype);
-    const size_t nq = (size_t)B * H * N * d, nkv = (size_t)B * H_kv * N * d;
-    const size_t qk = dtype == SPHATTN_F32 ? 4 : dtype == SPHATTN_FP8QK_BF16V ? 1 : 2;
-    const size_t vo = dtype == SPHATTN_F32 ? 4 : 2;
-    if (wraps(workspace, need)) return SPHATTN_ERR_WORKSPACE;
-    if (overlaps(workspace, need, Q, nq * qk) || overlaps(workspace, need, K, nkv * qk) ||
-        overlaps(workspace, need, V, nkv * vo) || overlaps(workspace, need, O, ob) ||
-        (mult && overlaps(workspace, need, mult, (size_t)B * N * 4)) ||
-        (Z && overlaps(workspace, need, Z, (size_t)B * H * N * 4)))
-        return SPHATTN_ERR_ALIAS;
-    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, workspace, (hipStream_t)stream);
+    const Problem p{Q, K, V, O, mult, Z, B, H, H_kv, N, N, (hipStream_t)stream};
+    const int wrc = check_workspace(p, d, dtype, plan, workspace, workspace_size);
+    return wrc != SPHATTN_OK ? wrc : run_splitkv(p, d, dtype, requested, plan, workspace);
+}
+
+size_t sphattn_cross_splitkv_workspace_bytes(int B, int H, int H_kv, int N_q, int N_k, int d, int dtype)
+{
+    if (check_shape(B, H, H_kv, N_q, N_k, d, dtype) != SPHATTN_OK) return 0;
+    const SplitPlan plan = plan_cross(B, H, H_kv, N_q, N_k, d, dtype);
+    return plan.n_splits == 1 ? 0 : sphattn_splitkv_workspace_bytes(B, H, N_q, d, plan.n_splits);
+}
+
+int sphattn_cross_splitkv_fwd(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
+                              int B, int H, int H_kv, int N_q, int N_k, int d, int dtype,
+                              void* workspace, size_t workspace_size, void* stream)
+{
+    const int rc = check_args(Q, K, V, O, out_bytes_of(B, H, N_q, d, dtype), mult, Z, B, H, H_kv, N_q, N_k, d, dtype);
+    if (rc != SPHATTN_OK) return rc;
+    const SplitPlan plan = plan_cross(B, H, H_kv, N_q, N_k, d, dtype);
+    const Problem p{Q, K, V, O, mult, Z, B, H, H_kv, N_q, N_k, (hipStream_t)stream};
+    if (plan.n_splits > 1) {
+        const int wrc = check_workspace(p, d, dtype, plan, workspace, workspace_size);
+        if (wrc != SPHATTN_OK) return wrc;
+    }
+    return run_splitkv(p, d, dtype, 0, plan, workspace);
 }
 
 int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, const float* mult, void* O, float* Z,
@@ -778,13 +866,14 @@ int sphattn_splitkv_fwd_noalloc(const void* Q, const void* K, const void* V, con
     }
     const SplitPlan plan = plan_splits(N, n_splits);
     // one slice is the unsplit launch and needs no scratch
-    if (plan.n_splits == 1) return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, nullptr, (hipStream_t)stream);
+    const Problem p{Q, K, V, O, mult, Z, B, H, H_kv, N, N, (hipStream_t)stream};
+    if (plan.n_splits == 1) return run_splitkv(p, d, dtype, requested, plan, nullptr);
     const size_t need = sphattn_splitkv_workspace_bytes(B, H, N, d, plan.n_splits);
     if (need == 0 || need > (size_t)SPHATTN_NOALLOC_SCRATCH_BYTES) return SPHATTN_ERR_SCRATCH;
     void* ws = scratch_address();
     if (ws == nullptr) return SPHATTN_ERR_LAUNCH;
     // the caller's buffers are allocations of their own and cannot overlap the library's array
-    return run_splitkv(Q, K, V, mult, O, Z, B, H, H_kv, N, d, dtype, requested, plan, ws, (hipStream_t)stream);
+    return run_splitkv(p, d, dtype, requested, plan, ws);
 }
 
 int sphattn_grn_bwd(const void* Q, const void* K, const void* V, const float* mult,

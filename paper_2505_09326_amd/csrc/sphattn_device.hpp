@@ -393,9 +393,26 @@ void combine_kernel(const float* __restrict__ o_parts, const float* __restrict__
     if (row >= rows) return;
     float z = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < n_parts; ++p) {
-        z += z_parts[(size_t)p * rows + row];
-        acc += *reinterpret_cast<const f32x4*>(o_parts + ((size_t)p * rows + row) * D + 4 * c4);
+    // eight parts' loads in flight at a time, added in order: with one part at a time a thread waits out
+    // the memory latency n_parts times
+    const float* zp = z_parts + row;
+    const float* op = o_parts + row * D + 4 * c4;
+    int p = 0;
+    for (; p + 8 <= n_parts; p += 8) {
+        float zv[8];
+        f32x4 ov[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            zv[u] = zp[(size_t)(p + u) * rows];
+            ov[u] = *reinterpret_cast<const f32x4*>(op + (size_t)(p + u) * rows * D);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { z += zv[u]; acc += ov[u]; }
+    }
+#pragma unroll 4
+    for (; p < n_parts; ++p) {
+        z += zp[(size_t)p * rows];
+        acc += *reinterpret_cast<const f32x4*>(op + (size_t)p * rows * D);
     }
     const float inv = z > 0.f ? 1.0f / __builtin_sqrtf(z) : 0.f;
     if (Zv != nullptr && c4 == 0) Zv[row] = z;

@@ -331,3 +331,21 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True)
     assert r.returncode != 0
     assert "one GPU" in r.stderr
+
+
+def test_cross_split_argument_errors(lib):
+    P = ctypes.c_void_p
+    need = lib.sphattn_cross_splitkv_workspace_bytes(1, 4, 2, 100, 5000, 64, 1)
+    assert need > 0 and need % 256 == 0
+    assert lib.sphattn_cross_splitkv_workspace_bytes(2, 16, 16, 8192, 8192, 128, 1) == 0      # one slice
+    assert lib.sphattn_cross_splitkv_workspace_bytes(1, 4, 3, 100, 5000, 64, 1) == 0          # no such shape
+    assert lib.sphattn_cross_splitkv_workspace_bytes(1, 4, 2, 100, 5000, 96, 1) == 0
+
+    def call(Q=0x1000000, mult=0, O=0x4000000, Z=0, H_kv=2, d=64, dtype=1, ws=0x40000000, size=need):
+        return lib.sphattn_cross_splitkv_fwd(P(Q), P(0x2000000), P(0x3000000), P(mult), P(O), P(Z), 1, 4, H_kv, 100, 5000,
+                                             d, dtype, P(ws), size, None)
+    assert call(Q=0) == -1 and call(H_kv=3) == -2 and call(d=32) == -3 and call(dtype=7) == -4
+    assert call(O=0x1000000) == -7 and call(Z=0x4000000) == -7
+    assert call(ws=0) == -9 and call(ws=0x40000008) == -9 and call(size=need - 1) == -9
+    assert call(ws=0x2000000) == -7 and call(ws=0x4000000) == -7
+    assert call(mult=0x5000000, ws=0x5000000) == -7 and call(Z=0x5000000, ws=0x5000000) == -7

@@ -89,3 +89,59 @@ def test_several_batches_of_128_row_items_walk_the_keys_both_ways(pkg, oracle):
     torch.cuda.synchronize()
     bits, kinds = _bits(q, k, v)
     assert _rel_err(O.cpu().double().numpy(), oracle.spherical_attention(*bits, kinds=kinds)) <= TOL_O["f16"]
+
+
+# B, H, H_kv, N_q, N_k, d, dtype, multiplicities: shapes that the calls below cut into slices (few query
+# rows against many keys), rows of a group of heads packed into whole and ragged tiles
+CUT = [(1, 4, 2, 33, 3001, 128, "bf16", False), (2, 6, 2, 100, 2500, 64, "f16", True), (1, 1, 1, 1, 5000, 128, "bf16", True),
+       (1, 8, 1, 200, 4096, 64, "fp8qk_bf16v", False), (1, 1, 1, 3000, 3000, 128, "f16", False), (1, 3, 1, 77, 6000, 64, "f32", True)]
+
+
+@pytest.mark.parametrize("B,H,H_kv,Nq,Nk,d,dtype,with_mult", CUT)
+def test_few_query_rows_cut_the_key_axis(pkg, oracle, B, H, H_kv, Nq, Nk, d, dtype, with_mult):
+    """sphattn_cross_fwd with an output of its own (slices and their combination) and into a given
+    output (one launch): both against the oracle; z as well."""
+    print(f"case cut B={B} H={H} H_kv={H_kv} Nq={Nq} Nk={Nk} d={d} {dtype}", flush=True)
+    lib = pkg.load_library()
+    need = lib.sphattn_cross_splitkv_workspace_bytes(B, H, H_kv, Nq, Nk, d, pkg._dtype_code(dtype))
+    assert need >= 2 * B * H * Nq * (d + 1) * 4
+    q, _, _ = si.make_qkv(B, H, Nq, d, dtype, seed=4500 + Nq)
+    _, k, v = si.make_qkv(B, H_kv, Nk, d, dtype, seed=4600 + Nk)
+    mult = None
+    if with_mult:
+        g = torch.Generator(device="cpu").manual_seed(4700 + Nk)
+        mult = torch.poisson(torch.full((B, Nk), 1.5), generator=g).to(torch.float32)
+        mult[:, 0] = 2.0
+    qd, kd, vd, md = (t.to(DEV) if t is not None else None for t in (q, k, v, mult))
+    Z = torch.empty((B, H, Nq), dtype=torch.float32, device=DEV)
+    O = pkg.sphattn_cross_fwd(qd, kd, vd, md, Z=Z, dtype=dtype)
+    given = torch.full_like(O, float("nan"))
+    pkg.sphattn_cross_fwd(qd, kd, vd, md, O=given, dtype=dtype)
+    torch.cuda.synchronize()
+    bits, kinds = _bits(q, k, v)
+    ref_o, ref_z = oracle.spherical_accumulate(*bits, None if mult is None else mult.numpy(), kinds=kinds)
+    ref = oracle.spherical_tail(ref_o[None], ref_z[None])
+    tol = {**TOL_O, "f32": 1e-4}[dtype]
+    assert _rel_err(O.cpu().double().numpy(), ref) <= tol
+    assert _rel_err(given.cpu().double().numpy(), ref) <= tol
+    np.testing.assert_allclose(Z.cpu().double().numpy(), ref_z, rtol=2e-4, atol=1e-7 * ref_z.max())
+
+
+def test_cut_launch_writes_inside_its_workspace_and_repeats(pkg):
+    """The slices' workspace, NaN-filled with guard bytes behind it: every slot read was written,
+    nothing past the stated size is, and two calls give the same bits."""
+    import ctypes
+    lib, P = pkg.load_library(), ctypes.c_void_p
+    B, H, H_kv, Nq, Nk, d = 1, 4, 2, 130, 4000, 128
+    q, k, v = (torch.randn(B, h, n, d, device=DEV).to(torch.bfloat16) for h, n in ((H, Nq), (H_kv, Nk), (H_kv, Nk)))
+    need = lib.sphattn_cross_splitkv_workspace_bytes(B, H, H_kv, Nq, Nk, d, 1)
+    outs = []
+    for _ in range(2):
+        ws = torch.full((need + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
+        O = torch.empty_like(q)
+        rc = lib.sphattn_cross_splitkv_fwd(P(q.data_ptr()), P(k.data_ptr()), P(v.data_ptr()), P(0), P(O.data_ptr()), P(0),
+                                           B, H, H_kv, Nq, Nk, d, 1, P(ws.data_ptr()), need, None)
+        torch.cuda.synchronize()
+        assert rc == 0 and bool((ws[need:] == 0xFF).all()) and bool(torch.isfinite(O.float()).all())
+        outs.append(O)
+    assert torch.equal(outs[0], outs[1])
