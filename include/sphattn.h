@@ -32,7 +32,7 @@ extern "C" {
 
 /* Storage formats.  Arithmetic is MFMA with fp32 accumulation in every case. */
 typedef enum {
-    SPHATTN_F32 = 0,         /* Q,K,V,O fp32, fp32 matrix-core arithmetic */
+    SPHATTN_F32 = 0,         /* Q,K,V,O fp32; fp32 matrix instruction, or bf16 ones on exact three-part values */
     SPHATTN_BF16 = 1,        /* Q,K,V,O bfloat16 */
     SPHATTN_FP8QK_BF16V = 2, /* Q,K OCP E4M3 (finite-only) bytes; V,O bfloat16 */
     SPHATTN_F16 = 3          /* Q,K,V,O IEEE half (the paper's precision); scores must stay below 65504 */

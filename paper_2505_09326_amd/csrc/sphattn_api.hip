@@ -4,6 +4,7 @@
 #include "sphattn_device.hpp"
 #include "sphattn_pipelined.hpp"
 #include "sphattn_keysplit.hpp"
+#include "sphattn_f32.hpp"
 #include "sphattn_softmax32.hpp"
 #include "sphattn_backward.hpp"
 #include "sphattn_fp8.hpp"
@@ -315,6 +316,54 @@ int launch_f32(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
+template <int D, int NQ, bool MULT, bool PARTIAL>
+int launch_f32x3(const Problem& p)
+{
+    constexpr int BR = kF32Waves * 16 * NQ, lds_bytes = f32_lds_bytes<D>();
+    auto kern = fwd_f32x3_kernel<D, NQ, MULT, PARTIAL>;
+    static std::atomic<uint64_t> done{0};
+    if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
+    const int n_qtiles = (p.Nq + BR - 1) / BR;
+    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
+    if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(64 * kF32Waves), lds_bytes, p.stream,
+                       (const float*)p.Q, (const float*)p.K, (const float*)p.V, (float*)p.O, p.mult, p.Z,
+                       p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg, p.n_splits, p.keys_per_split);
+    return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
+}
+
+// fp32 storage has three workgroup shapes: 32 rows on the fp32 matrix instruction with the keys dealt
+// to the four waves (the least latency: the launches that cannot give every CU more than that), and 128
+// or 256 rows on six bf16 products.  Time of one round per 32-key tile, in us, as measured on launches
+// that fill a small and the whole part of the CUs (f): d = 128 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
+// 0.68, 1.1 to 1.3, 1.85 to 2.25.  Rounds times that picks the shape (8 heads of 4096 x 128: 704, 328
+// and 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 364, 551, 897;
+// 4 x 1000 x 128 52, 73, 119).  S slices: S times the items, 1 / S of the tiles.
+struct F32Choice { int rows; double us; };
+F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d)
+{
+    const double cus = (double)cu_count(), tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
+    F32Choice best{32, 1e30};
+    for (const int rows : {32, 128, 256}) {
+        const double items = (double)(heads * ((Nq + rows - 1) / rows) * S);
+        const double f = items < cus ? items / cus : 1.0;
+        const double tau = d == 128 ? (rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
+                                    : (rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
+        const double us = __builtin_ceil(items / cus) * tiles * tau;
+        if (us < best.us) best = F32Choice{rows, us};
+    }
+    return best;
+}
+
+template <int D, bool MULT, bool PARTIAL>
+int launch_f32_any(const Problem& p)
+{
+    const int rows = choose_f32((long long)p.B * p.H, p.Nq, PARTIAL ? p.keys_per_split : p.Nk, p.n_splits, D).rows;
+    if (rows == 128) return launch_f32x3<D, 1, MULT, PARTIAL>(p);
+    if (rows == 256) return launch_f32x3<D, 2, MULT, PARTIAL>(p);
+    return launch_f32<D, MULT, PARTIAL>(p);
+}
+
 template <int D>
 int launch_softmax32(const Problem& p)
 {
@@ -379,7 +428,7 @@ int dispatch_spherical(const Problem& call, int d, int dtype)
     case SPHATTN_FP8QK_BF16V:
         return d == 128 ? launch_spherical<128, QKType::Fp8, MULT, PARTIAL>(p) : launch_spherical<64, QKType::Fp8, MULT, PARTIAL>(p);
     case SPHATTN_F32:
-        return d == 128 ? launch_f32<128, MULT, PARTIAL>(p) : launch_f32<64, MULT, PARTIAL>(p);
+        return d == 128 ? launch_f32_any<128, MULT, PARTIAL>(p) : launch_f32_any<64, MULT, PARTIAL>(p);
     default:
         return SPHATTN_ERR_DTYPE;
     }
@@ -633,18 +682,19 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
     p.B = B; p.H = H; p.H_kv = H_kv; p.Nq = Nq; p.Nk = Nk;
     p = packed_group(p, d);
     const long long heads = (long long)p.B * p.H;
-    if (dtype == SPHATTN_F32) return plan_splits(Nk, choose_splits(heads, p.Nq, Nk, d, dtype));
+    const bool f32 = dtype == SPHATTN_F32;
     const long long items = heads * ((p.Nq + kSplitRows - 1) / kSplitRows), cus = cu_count();
     const int tiles = (Nk + kBC - 1) / kBC;
     const double part_us = (double)heads * (double)p.Nq * (d + 1) * 8.0 / 4e6;
     SplitPlan best = plan_splits(Nk, 1);
     double best_us = 0.0;
-    for (long long S = 1; S * items <= cus && S <= tiles; ++S) {
+    for (long long S = 1; (S * items <= cus || S == 1) && S <= tiles; ++S) {
         const SplitPlan plan = plan_splits(Nk, (int)S);
         if (plan.n_splits != S) continue;          // the same slices as a smaller count
         const double f = (double)(S * items) / (double)cus;
         const double tau = d == 64 ? 0.36 + 0.08 * f : 0.55 + 0.22 * f;
-        double us = 6.0 + tau * (double)(plan.keys_per_split / kBC);
+        double us = 6.0 + (f32 ? choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d).us
+                               : tau * (double)(plan.keys_per_split / kBC));
         if (S > 1) us += 4.0 + (double)S * part_us;
         if (S == 1) { best_us = 0.9 * us; continue; }   // cut only for a gain of at least 10 %
         if (us < best_us) { best_us = us; best = plan; }
