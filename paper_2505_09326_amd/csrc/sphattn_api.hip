@@ -207,16 +207,16 @@ long long balanced_grid(long long n_items, long long resident)
     return grid < resident ? grid : resident;
 }
 
-// The 128-row kernel over a launch's items of kSplitRows query rows.
-template <int D, QKType QKT, bool MULT, bool PARTIAL>
+// The key-split kernel over a launch's items of 32 NQ query rows.
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL>
 int launch_keysplit(const Problem& p)
 {
-    constexpr int lds_bytes = keysplit_lds_bytes<D, QKT, MULT>();
-    auto kern = fwd_keysplit_kernel<D, QKT, MULT, PARTIAL>;
+    constexpr int BR = 32 * NQ, lds_bytes = keysplit_lds_bytes<D, QKT, MULT>();
+    auto kern = fwd_keysplit_kernel<D, NQ, QKT, MULT, PARTIAL>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
-    const int n_qtiles = (p.Nq + kSplitRows - 1) / kSplitRows;
+    const int n_qtiles = (p.Nq + BR - 1) / BR;
     const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
     if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
     const long long grid = balanced_grid(n_wg, (long long)kXcds * stream_period(kern, lds_bytes, period));
@@ -234,7 +234,7 @@ template <int D, QKType QKT>
 long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_begin, bool backwards, bool resident_only)
 {
     constexpr int lds_bytes = keysplit_lds_bytes<D, QKT, false>();
-    auto kern = fwd_keysplit_kernel<D, QKT, false, false>;
+    auto kern = fwd_keysplit_kernel<D, 4, QKT, false, false>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return 0;
@@ -381,38 +381,40 @@ int launch_softmax32(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// Query rows per workgroup: 256 or 128.  Both feed every fragment to 64 query rows of a wave; a
-// 128-row workgroup has each wave do half of every key tile (sphattn_keysplit.hpp), takes 0.56 us
-// for a 64-key tile of d = 128 against 0.97 of a 256-row one while the chip is not full (0.36 against
-// 0.56 at d = 64), and copies twice the K/V bytes per flop.  It pays when the 128-row workgroups
-// still run all at once (one per CU at d = 128; at d = 64, where two fit a CU, up to one and a half
-// per CU) and 256-row tiles would leave CUs without any: one head of 32768 x 128 378 against 529 us, of 32768 x 64 217 against 324; 4 heads of
-// 8192 x 128 103 against 151, fp16 4 x 1999 x 128 24 against 39.  With more items than
-// that the 128-row launch takes two rounds and loses (5 heads of 8192 x 128, 160 tiles:
-// 152 against 136 us; 3 x 16384 x 128, 192 tiles: 311 against 282 us; d = 64: 6 x 8192, 384
-// workgroups, 88 against 88 us, 7 x 8192 95 against 94, 12 x 5003 fp16 66 against 63): a partly filled single
-// round costs less than its share of idle CUs suggests, because the part is power-bound and
-// idle CUs give their share of the budget to the rest.
-bool narrow_tiles_pay(const Problem& p, int d)
+// Query rows per workgroup.  256 (four waves of 64 rows) is the efficient shape of a full chip; 128 and 64
+// (sphattn_keysplit.hpp) have each wave do half of every key tile for 64 or 32 rows.  In us per 64-key
+// tile while the chip is not full: d = 128 0.97, 0.55, 0.42; d = 64 0.56, 0.36, 0.26; what is left at 64 rows
+// is the copy of the tile itself, so there is no shape below it.  The smaller ones copy two and four
+// times the K/V bytes per flop and pay while they still run all at once, one per CU:
+//   64 rows:  4 x 1999 x 128 17.8 us against 23.6 of 128 rows (38 of 256), 1 x 8192 x 128 56 against 76,
+//             2 x 8192 x 64 39 against 50; one and a half per CU no more (12 x 1999 x 64 16.6 against 16.1).
+//             Not for fp8 Q/K at d = 128, whose score instruction needs four query blocks a slot.
+//   128 rows: 4 x 8192 x 128 103 against 151 of 256 rows, 1 x 32768 x 128 378 against 529; at d = 64, where
+//             two fit a CU, up to one and a half per CU (5 x 8192 x 64, 320 workgroups, 84 against 88 us,
+//             7 x 8192, 448, 95 against 94, 12 x 5003 fp16, 480, 66 against 63).
+// With more items than that they take two rounds and lose (5 x 8192 x 128, 160 tiles of 256 rows: 152 against
+// 136 us): a partly filled single round costs less than its share of idle CUs suggests, because the
+// part is power-bound and idle CUs give their share of the budget to the rest.
+int rows_per_workgroup(long long heads, long long Nq, long long n_splits, int d, bool fp8)
 {
-    if (p.tile_rows != 0) return p.tile_rows == 128;
-    const long long heads = (long long)p.B * p.H * p.n_splits, cus = cu_count();
-    return heads * ((p.Nq + 255) / 256) < cus && heads * ((p.Nq + 127) / 128) <= (d == 64 ? cus * 3 / 2 : cus);
+    const long long cus = cu_count(), slices = heads * n_splits;
+    if (slices * ((Nq + 255) / 256) >= cus) return 256;
+    if (!(fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
+    return slices * ((Nq + 127) / 128) <= (d == 64 ? cus * 3 / 2 : cus) ? 128 : 256;
 }
 
 template <int D, QKType QKT, bool MULT, bool PARTIAL>
 int launch_spherical(const Problem& p)
 {
-    if (narrow_tiles_pay(p, D)) {
-        // bf16 has a second 128-row form, four waves of 32 rows over all keys: the same sums as the
-        // 256-row kernel, and without the key groups' exchange (0.7 us) at the end it is ahead on the
-        // shortest launches: 4 tiles of d = 128 7.0 against 7.9 us, 16 tiles 14.1 against 14.8,
-        // 32 tiles 23.4 against 23.7; d = 64: 4 tiles 5.1 against 5.5, 16 tiles 10.2 against 10.0
-        if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
-            if (p.one_key_order || p.Nk <= (D == 128 ? 1024 : 512)) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
-        if (!p.one_key_order) return launch_keysplit<D, QKT, MULT, PARTIAL>(p);
-    }
-    return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+    const int rows = p.tile_rows != 0 ? p.tile_rows
+                                      : rows_per_workgroup((long long)p.B * p.H, p.Nq, p.n_splits, D, QKT == QKType::Fp8);
+    // a row's sums in the 256-row kernel's order, on the narrower form of that kernel (bf16 has one)
+    if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
+        if (p.one_key_order && rows < 256) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+    if (rows == 256 || p.one_key_order) return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+    if constexpr (QKT != QKType::Fp8 || D == 64)
+        if (rows == 64) return launch_keysplit<D, 2, QKT, MULT, PARTIAL>(p);
+    return launch_keysplit<D, 4, QKT, MULT, PARTIAL>(p);
 }
 
 // Spherical attention in any storage type; PARTIAL: accumulators over key slices.
@@ -668,36 +670,41 @@ int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
 }
 
 // The library's choice of slices for a rectangular problem, in the launch's terms (packed_group).
-// A launch is cut only while all its slices still run at once as 128-row workgroups, one per CU
-// (at d = 64 as well: 1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  In us,
-// from launches of one to many slices: a workgroup spends 6 on its first and last bytes and tau on
-// each 64-key tile, tau growing with the share of the CUs in use (the part is power-bound); the
-// second launch costs 4, and each part is written and read at 4 TB/s together.  Measured with the
-// slices this picks against one: 1 x 8192 x 128 39 against 76 us, 2 x 8192 x 128 59 against 77,
-// 1 x 4096 x 128 23 against 40, 1 x 8192 x 64 24 against 49; not cut: 4 x 1999 x 128 (22.7 against
-// 23.3 would be the best), 8 x 1000 x 128 (18.1 against 13.9).
+// A launch is cut only while all its slices still run at once as workgroups of 128 rows or fewer, one
+// per CU (at d = 64 as well: 1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  In us,
+// from launches of one to many slices: a workgroup spends 4 (64 rows) or 6 on its first and last bytes
+// and tau on each 64-key tile, tau growing with the share f of the CUs in use (the part is power-bound); the
+// second launch costs 4, and each part is written and read at 6 TB/s together.  Measured with the
+// slices this picks against one: 1 x 8192 x 128 39 against 56 us, 1 x 8192 x 64 24 against 37; not cut:
+// 4 x 1999 x 128 (22.7 at best against 17.8), 8 x 1000 x 128 (18.1 against 10.9).
 SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
 {
     Problem p{};
     p.B = B; p.H = H; p.H_kv = H_kv; p.Nq = Nq; p.Nk = Nk;
     p = packed_group(p, d);
-    const long long heads = (long long)p.B * p.H;
-    const bool f32 = dtype == SPHATTN_F32;
-    const long long items = heads * ((p.Nq + kSplitRows - 1) / kSplitRows), cus = cu_count();
+    const long long heads = (long long)p.B * p.H, cus = cu_count();
+    const long long items = heads * ((p.Nq + kSplitRows - 1) / kSplitRows);
     const int tiles = (Nk + kBC - 1) / kBC;
-    const double part_us = (double)heads * (double)p.Nq * (d + 1) * 8.0 / 4e6;
+    const double part_us = (double)heads * (double)p.Nq * (d + 1) * 8.0 / 6e6;
     SplitPlan best = plan_splits(Nk, 1);
     double best_us = 0.0;
     for (long long S = 1; (S * items <= cus || S == 1) && S <= tiles; ++S) {
         const SplitPlan plan = plan_splits(Nk, (int)S);
         if (plan.n_splits != S) continue;          // the same slices as a smaller count
-        const double f = (double)(S * items) / (double)cus;
-        const double tau = d == 64 ? 0.36 + 0.08 * f : 0.55 + 0.22 * f;
-        double us = 6.0 + (f32 ? choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d).us
-                               : tau * (double)(plan.keys_per_split / kBC));
+        const double per = (double)(S == 1 ? tiles : plan.keys_per_split / kBC);
+        double us;
+        if (dtype == SPHATTN_F32) {
+            us = 6.0 + choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d).us;
+        } else {
+            const int rows = rows_per_workgroup(heads, p.Nq, S, d, dtype == SPHATTN_FP8QK_BF16V);
+            const double f = (double)(S * heads * ((p.Nq + rows - 1) / rows)) / (double)cus;
+            const double tau = d == 128 ? (rows == 64 ? 0.40 + 0.08 * f : 0.55 + 0.17 * f)
+                                        : (rows == 64 ? 0.25 + 0.03 * f : 0.36 + 0.08 * f);
+            us = (rows == 64 ? 4.0 : 6.0) + tau * per;
+        }
         if (S > 1) us += 4.0 + (double)S * part_us;
-        if (S == 1) { best_us = 0.9 * us; continue; }   // cut only for a gain of at least 10 %
-        if (us < best_us) { best_us = us; best = plan; }
+        if (S == 1) best_us = 0.9 * us;            // cut only for a gain of at least 10 %
+        else if (us < best_us) { best_us = us; best = plan; }
     }
     return best;
 }

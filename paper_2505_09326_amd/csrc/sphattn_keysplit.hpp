@@ -1,13 +1,18 @@
-// Forward kernel for launches that 256-row workgroups cannot spread over the chip: 128 query rows
-// per workgroup, the key axis dealt to two pairs of wavefronts.
+// Forward kernel for launches that 256-row workgroups cannot spread over the chip: 32 NQ query rows
+// per workgroup (128 or 64), the key axis dealt to two pairs of wavefronts.
 //
 // Same slot pipeline, layouts and matrix instructions as fwd_pipelined_kernel (read that first);
-// what differs is who does what.  Wave w owns the 64 query rows of row group w % 2 and, of every
-// 64-key tile, the 32 keys of key group w / 2: one sub-step per wave and tile.  A wave still feeds
-// every K and V^T fragment it reads to NQ = 4 query blocks.  (The other way to 128 rows, four waves
+// what differs is who does what.  Wave w owns the 16 NQ query rows of row group w % 2 and, of every
+// 64-key tile, the 32 keys of key group w / 2: one sub-step per wave and tile.  At NQ = 4 a wave still
+// feeds every K and V^T fragment it reads to four query blocks.  (The other way to 128 rows, four waves
 // of 32 rows over all keys, reads every fragment for two blocks only: twice the LDS reads per
 // matrix instruction, which then bound it.)  The accumulator of Lemma 1 is a plain sum, so the two
 // key groups' partial (o, z) are added once, through LDS, before the tail.
+//
+// What bounds it, measured while the chip is not full (d = 128, bf16, 2.4 GHz): 128 rows 0.55 us per tile
+// = 1310 cycles, 1024 of them matrix instructions; 64 rows 0.42 us = 1000 cycles, 512 of them matrix
+// instructions: there the copy of the tile, 32 KB at 33 bytes per cycle and CU, is the bound.
+// 1 x 32768 x 64 281 us (four waves of 32 rows) to 217; 4 x 1999 x 128 23.4 to 17.8 (64 rows), fp16 38.6 to 18.0.
 //
 // Per tile a workgroup copies 32 KB (d = 128, bf16) for half the matrix work of a 256-row one,
 // about 28 bytes per cycle and CU, near what direct copies reach (30 to 38); K and V therefore
@@ -23,7 +28,7 @@
 
 namespace sphattn {
 
-constexpr int kSplitRows = 128;        // query rows per workgroup
+constexpr int kSplitRows = 128;        // query rows per workgroup at NQ = 4; 64 at NQ = 2
 constexpr int kSplitMultRing = 8;      // multiplicities outlive their K tile: a longer ring
 
 template <int D, QKType QKT, bool MULT>
@@ -33,7 +38,7 @@ constexpr int keysplit_lds_bytes()
 }
 
 // One work item; arguments as fwd_pipelined_item.
-template <int D, QKType QKT, bool MULT, bool PARTIAL>
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL>
 __device__ __forceinline__
 void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
                        const void* __restrict__ Vv, void* __restrict__ Ov,
@@ -44,7 +49,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
 {
     constexpr bool FP8 = QKT == QKType::Fp8;
     constexpr bool HALF = QKT == QKType::F16;
-    constexpr int BC = kBC, NQ = 4, NBUF = kNBuf;
+    constexpr int BC = kBC, NBUF = kNBuf;
     constexpr int EQ = FP8 ? 1 : 2;
     constexpr int KROWB = D * EQ, KTILE = BC * KROWB;
     constexpr int VROWB = D * 2, VTILE = BC * VROWB;
@@ -57,6 +62,8 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     constexpr int QKM = FP8 ? 2 * NQ / SLOTS : NQ; // score matrix instructions per slot
     constexpr int PAIRS = 4 * NQ / SLOTS;          // score register pairs of stage B per slot
     constexpr int VALU_PER_MFMA = (MULT || D == 64) ? 2 : 1;
+    static_assert(NQ == 4 || NQ == 2, "128 or 64 query rows per workgroup");
+    static_assert(!FP8 || (2 * NQ) % SLOTS == 0, "fp8: whole score instructions per slot");
     static_assert(NBUF == 4 && SLOTS % RING == 0 && PD < RING && PD < SLOTS, "ring indices repeat every iteration");
     static_assert(LDK + LDV <= SLOTS, "one copy per slot (the multiplicities ride with the first)");
     static_assert(FP8 || 2 * KK == SLOTS, "16-bit: one K fragment per slot");
@@ -117,9 +124,9 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     // instruction with consecutive lanes in different rows, it arrives at 16 bytes per cycle and CU,
     // and both key groups would fetch it (64 KB = 1.8 us at d = 128); as 1 KB block copies, once, it
     // takes a quarter of that.  It waits in the buffers of V_1 and V_2, in K's block format.
-    constexpr int QTILE = kSplitRows * KROWB, QLDS = VLDS + VTILE;
+    constexpr int QTILE = 32 * NQ * KROWB, QLDS = VLDS + VTILE;
     constexpr int QCOPIES = QTILE / 1024 / kWaves;
-    static_assert(QTILE <= 2 * VTILE && QCOPIES % KBLK == 0, "Q fits the buffers of V_1 and V_2");
+    static_assert(QTILE <= 2 * VTILE && QTILE % (1024 * kWaves) == 0, "Q fits the buffers of V_1 and V_2, in whole copies per wave");
     const int tile_row0 = qt * tile_rows + row_off;
     // (byte offsets of one head fit 32 bits; rows past the last query arrive as zeros)
     const i32x4 qrw = rsrc_words(Qh, (uint32_t)Nq * KROWB);
@@ -424,7 +431,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
 
 // Persistent workgroups over the items, every other batch streaming the keys backwards, and the
 // remainder launch of half tiles: as fwd_pipelined_kernel.
-template <int D, QKType QKT, bool MULT, bool PARTIAL>
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL>
 __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1)
 void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv,
                          const void* __restrict__ Vv, void* __restrict__ Ov,
@@ -432,7 +439,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
                          int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_items,
                          int n_splits, int keys_per_split, int item_begin, int item_end, int halves)
 {
-    constexpr int BR = kSplitRows;
+    constexpr int BR = 32 * NQ;
     if (halves) {
         // Remainder launch: the items item_begin .. item_end - 1 of a launch whose tiles are
         // 2 BR rows (n_qtiles and n_items count those), one half of an item per workgroup.
@@ -444,7 +451,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
         if (item >= item_end) return;
         const int qt = xcd_contiguous_id(item, n_items) % n_qtiles;
         if (qt * 2 * BR + half * BR >= Nq) return;     // the tile's second half lies past the last row
-        fwd_keysplit_item<D, QKT, MULT, PARTIAL>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
+        fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
                                                  n_splits, keys_per_split, item, halves == 2, true, 2 * BR, half * BR);
         return;
     }
@@ -452,7 +459,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
     int batch = 0;
     for (int item = item_begin + blockIdx.x; item < item_end; item += gridDim.x, ++batch) {
         if (batch > 0) __syncthreads();            // every wave is done with the previous item's LDS
-        fwd_keysplit_item<D, QKT, MULT, PARTIAL>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
+        fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
                                                  n_splits, keys_per_split, item, batch % 2 == 1, several_batches, BR, 0);
     }
 }

@@ -1,4 +1,4 @@
-"""The 128-row forward kernel whose two wave pairs share out every key tile (sphattn_keysplit.hpp):
+"""The 128- and 64-row forward kernel whose two wave pairs share out every key tile (sphattn_keysplit.hpp):
 odd and even tile counts, ragged last tiles, tiles past the end, rows past the last query; every
 storage type, multiplicities, row aggregates and partial accumulators, element by element against
 the oracle.  Tolerances are those of test_gpu_parity.py and test_gpu_partial_splitkv.py."""
@@ -31,17 +31,18 @@ def _bits(*ts):
     return [p[0] for p in pairs], tuple(p[1] for p in pairs)
 
 
-# bf16 below 1025 (d = 128) and 513 (d = 64) keys runs the other 128-row kernel
 SHAPES = [(n, d, t) for t in ("f16", "fp8qk_bf16v") for d in (64, 128) for n in (1, 31, 64, 65, 129, 257, 383)] + \
-         [(1025, 128, "bf16"), (1279, 128, "bf16"), (513, 64, "bf16"), (700, 64, "bf16")]
+         [(1025, 128, "bf16"), (449, 128, "bf16"), (513, 64, "bf16"), (100, 64, "bf16")]
 
 
+@pytest.mark.parametrize("tile_rows", [0, 128])
 @pytest.mark.parametrize("N,d,dtype", SHAPES)
-def test_forced_128_rows_against_the_oracle(pkg, oracle, N, d, dtype):
-    print(f"case keysplit N={N} d={d} {dtype}", flush=True)
+def test_both_widths_against_the_oracle(pkg, oracle, N, d, dtype, tile_rows):
+    """tile_rows 0: launches this small take 64 rows per workgroup (fp8 Q/K at d = 128: 128)."""
+    print(f"case keysplit N={N} d={d} {dtype} tile_rows={tile_rows}", flush=True)
     q, k, v = si.make_qkv(1, 2, N, d, dtype, seed=4000 + N + d)
     Z = torch.empty((1, 2, N), dtype=torch.float32, device=DEV)
-    O, _ = pkg.sphattn_fwd_tile_rows(q.to(DEV), k.to(DEV), v.to(DEV), Z=Z, dtype=dtype, tile_rows=128)
+    O, _ = pkg.sphattn_fwd_tile_rows(q.to(DEV), k.to(DEV), v.to(DEV), Z=Z, dtype=dtype, tile_rows=tile_rows)
     torch.cuda.synchronize()
     bits, kinds = _bits(q, k, v)
     ref, _, ref_z = oracle.spherical_attention_full(*bits, kinds=kinds)
