@@ -318,6 +318,25 @@ int sphattn_grn_bwd(const void* Q, const void* K, const void* V, const float* mu
                     int B, int H, int H_kv, int N, int d, int dtype, void* stream);
 
 /*
+ * sphattn_grn_bwd for shapes whose tiles leave compute units without work (few heads, shared K/V
+ * heads): the axis that each of the two kernels streams is cut into slices, whose fp32 partial
+ * gradients go to the workspace and are added, in a fixed order, by a third launch.  Where the library
+ * sees no use in that it is sphattn_grn_bwd itself.
+ *   workspace : device scratch, 16-byte aligned, at least sphattn_bwd_workspace_bytes(...) bytes for the
+ *               same shape; where that is 0 it is not looked at and may be NULL.  Must not overlap
+ *               any other argument; calls that overlap in time need workspaces of their own.
+ * Other arguments and errors as sphattn_grn_bwd; a bad workspace returns SPHATTN_ERR_WORKSPACE.
+ * sphattn_bwd_workspace_bytes launches nothing and returns 0 for arguments sphattn_grn_bwd would
+ * reject; its answer depends on the compute units of the current device.
+ */
+size_t sphattn_bwd_workspace_bytes(int B, int H, int H_kv, int N, int d, int dtype);
+int sphattn_grn_bwd_split(const void* Q, const void* K, const void* V, const float* mult,
+                          const void* O, const void* dO, const float* Z,
+                          void* dQ, void* dK, void* dV, float* delta,
+                          int B, int H, int H_kv, int N, int d, int dtype,
+                          void* workspace, size_t workspace_size, void* stream);
+
+/*
  * Spherical attention with Q, K AND V stored in OCP E4M3 and both contractions on the fp8
  * matrix instructions (paper, Section 1 and Section 3.1: without the row-wise exponential the
  * whole operator can run at the matrix cores' low-precision rate).  Same function as

@@ -31,7 +31,7 @@ EXPORTED_SYMBOLS = ("sphattn_fwd", "sphattn_fwd_z", "sphattn_fwd_tile_rows", "sp
                     "sphattn_combine", "sphattn_splitkv_fwd", "sphattn_splitkv_workspace_bytes",
                     "sphattn_splitkv_heuristic", "sphattn_splitkv_fwd_noalloc",
                     "sphattn_cross_splitkv_workspace_bytes", "sphattn_cross_splitkv_fwd",
-                    "sphattn_bwd", "sphattn_grn_bwd",
+                    "sphattn_bwd", "sphattn_grn_bwd", "sphattn_bwd_workspace_bytes", "sphattn_grn_bwd_split",
                     "sphattn_fp8_workspace_bytes", "sphattn_fp8_fwd", "sphattn_fp8_grn_fwd", "sphattn_fp8_softmax_fwd",
                     "sphattn_strerror", "sphattn_version")
 
@@ -90,6 +90,10 @@ def load_library() -> ctypes.CDLL:
         lib.sphattn_bwd.argtypes = [vp] * 10 + [ip, ip, ip, ip, ip, vp]
         lib.sphattn_grn_bwd.restype = ip
         lib.sphattn_grn_bwd.argtypes = [vp] * 11 + [ip, ip, ip, ip, ip, ip, vp]
+        lib.sphattn_bwd_workspace_bytes.restype = sz
+        lib.sphattn_bwd_workspace_bytes.argtypes = [ip] * 6
+        lib.sphattn_grn_bwd_split.restype = ip
+        lib.sphattn_grn_bwd_split.argtypes = [vp] * 11 + [ip] * 6 + [vp, sz, vp]
         lib.sphattn_fp8_workspace_bytes.restype = sz
         lib.sphattn_fp8_workspace_bytes.argtypes = [ip, ip, ip, ip]
         for name in ("sphattn_fp8_fwd", "sphattn_fp8_softmax_fwd"):
@@ -299,26 +303,30 @@ def _cut_workspace_bytes(device_index, B, H, H_kv, Nq, Nk, d, code):
     return load_library().sphattn_cross_splitkv_workspace_bytes(B, H, H_kv, Nq, Nk, d, code)
 
 
+def _workspace(need, like):
+    """`need` bytes on the GPU of `like`, or None: for 0 bytes, and where memory is too short for them
+    (the uncut launches need none)."""
+    if not need:
+        return None
+    import torch
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=like.device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _launch_cross(lib, Q, K, V, mult, O, Z, B, H, H_kv, Nq, Nk, d, code, stream, own_output):
     """sphattn_cross_fwd on checked arguments.  Where the library would cut the key axis (few query
     rows against many keys) and this call allocates its output anyway, the slices' workspace comes
     from torch's allocator too: on the current stream, so its reuse is ordered behind the launch.
     A caller that brings O or a stream handle of its own gets no allocation and the unsplit launch."""
-    if own_output and stream is None:
-        need = _cut_workspace_bytes(Q.device.index, B, H, H_kv, Nq, Nk, d, code)
-        if need:
-            import torch
-            try:
-                ws = torch.empty(need, dtype=torch.uint8, device=Q.device)
-            except torch.OutOfMemoryError:
-                ws = None
-            if ws is not None:
-                _raise_on(lib.sphattn_cross_splitkv_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult),
-                                                        O.data_ptr(), _ptr(Z), B, H, H_kv, Nq, Nk, d, code,
-                                                        ws.data_ptr(), need, _stream_of(Q, None)))
-                return
-    _raise_on(lib.sphattn_cross_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), _ptr(Z),
-                                    B, H, H_kv, Nq, Nk, d, code, _stream_of(Q, stream)))
+    args = (Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), _ptr(Z), B, H, H_kv, Nq, Nk, d, code)
+    need = _cut_workspace_bytes(Q.device.index, B, H, H_kv, Nq, Nk, d, code) if own_output and stream is None else 0
+    ws = _workspace(need, Q)
+    if ws is None:
+        _raise_on(lib.sphattn_cross_fwd(*args, _stream_of(Q, stream)))
+    else:
+        _raise_on(lib.sphattn_cross_splitkv_fwd(*args, ws.data_ptr(), need, _stream_of(Q, None)))
 
 
 # ---- entry points, same names as the C ABI ----------------------------------------------------
@@ -561,20 +569,37 @@ def _check_backward(Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, code):
     return B, H, N, d, H_kv
 
 
+@functools.lru_cache(maxsize=1024)
+def _bwd_workspace_bytes(device_index, B, H, H_kv, N, d, code):
+    """Workspace of the library's choice of slices for the backward: a function of the shape and the GPU."""
+    return load_library().sphattn_bwd_workspace_bytes(B, H, H_kv, N, d, code)
+
+
+def _launch_bwd(lib, Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, code, stream, own_outputs):
+    """sphattn_grn_bwd on checked arguments, cut into slices under the conditions of _launch_cross."""
+    args = (Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), dO.data_ptr(), Z.data_ptr(),
+            dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), delta.data_ptr(), B, H, H_kv, N, d, code)
+    need = _bwd_workspace_bytes(Q.device.index, B, H, H_kv, N, d, code) if own_outputs and stream is None else 0
+    ws = _workspace(need, Q)
+    if ws is None:
+        _raise_on(lib.sphattn_grn_bwd(*args, _stream_of(Q, stream)))
+    else:
+        _raise_on(lib.sphattn_grn_bwd_split(*args, ws.data_ptr(), need, _stream_of(Q, None)))
+
+
 def sphattn_grn_bwd(Q, K, V, mult, O, dO, Z, dQ=None, dK=None, dV=None, delta=None, dtype="bf16", stream=None):
     """Gradients (dQ, dK, dV) of sum(O * dO) for O = sphattn_grn_fwd(Q, K, V, mult): per-gene
     multiplicities mult[B,N] (or None) and K, V of shape [B,H_kv,N,d]."""
     import torch
     lib, code = load_library(), _dtype_code(dtype)
+    own_outputs = dQ is None and dK is None and dV is None and delta is None
     dQ = torch.empty_like(Q) if dQ is None else dQ
     dK = torch.empty_like(K) if dK is None else dK
     dV = torch.empty_like(V) if dV is None else dV
     if delta is None:
         delta = torch.empty((2, *Q.shape[:3]), dtype=torch.float32, device=Q.device)
     B, H, N, d, H_kv = _check_backward(Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, code)
-    _raise_on(lib.sphattn_grn_bwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), dO.data_ptr(),
-                                  Z.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), delta.data_ptr(),
-                                  B, H, H_kv, N, d, code, _stream_of(Q, stream)))
+    _launch_bwd(lib, Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, code, stream, own_outputs)
     return dQ, dK, dV
 
 
@@ -582,6 +607,7 @@ def sphattn_bwd(Q, K, V, O, dO, Z, dQ=None, dK=None, dV=None, delta=None, dtype=
     """Gradients (dQ, dK, dV) of sum(O * dO) for O, Z = sphattn_fwd_z(Q, K, V); 16-bit storage."""
     import torch
     lib, code = load_library(), _dtype_code(dtype)
+    own_outputs = dQ is None and dK is None and dV is None and delta is None
     dQ = torch.empty_like(Q) if dQ is None else dQ
     dK = torch.empty_like(K) if dK is None else dK
     dV = torch.empty_like(V) if dV is None else dV
@@ -590,7 +616,5 @@ def sphattn_bwd(Q, K, V, O, dO, Z, dQ=None, dK=None, dV=None, delta=None, dtype=
     if Q.dim() == 4 and K.dim() == 4 and K.shape[1] != Q.shape[1]:
         raise ValueError(f"K must have Q's {Q.shape[1]} heads, got {K.shape[1]} (sphattn_grn_bwd takes shared heads)")
     B, H, N, d, H_kv = _check_backward(Q, K, V, None, O, dO, Z, dQ, dK, dV, delta, code)
-    _raise_on(lib.sphattn_bwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(), dO.data_ptr(), Z.data_ptr(),
-                              dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), delta.data_ptr(),
-                              B, H, N, d, code, _stream_of(Q, stream)))
+    _launch_bwd(lib, Q, K, V, None, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, code, stream, own_outputs)
     return dQ, dK, dV

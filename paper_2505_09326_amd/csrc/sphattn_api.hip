@@ -473,36 +473,79 @@ struct BwdProblem {
     hipStream_t stream;
 };
 
-template <int D, bool HALF, bool MULT, int NK>
-int launch_bwd(const BwdProblem& p)
+// Slices of the two backward kernels' streamed axes, and where their partial sums go.
+struct BwdPlan {
+    int sq = 1, keys_per_split = 0;                // dQ: slices of the keys
+    int sk = 1, tiles_per_split = 0;               // dK, dV: slices of the 64-query tiles
+    size_t bytes = 0;                              // of workspace: sq parts of dQ, then sk of dK, then sk of dV
+};
+
+// A backward problem as launched: shared K/V heads packed like the forward's (packed_group), one query head
+// of Nq = kv_group N rows per K/V head.
+struct BwdShape { int H, kv_group, Nq; };
+BwdShape bwd_shape(int H, int H_kv, int N, int d)
 {
-    constexpr int tile = kBC * D * 2;
+    const long long group = H / H_kv;
+    if (group > 1 && group * N * d * 4 <= 0x7fffffff) return BwdShape{H_kv, 1, (int)(group * N)};
+    return BwdShape{H, (int)group, N};
+}
+
+template <int D, bool HALF, bool MULT, bool PARTQ, bool PARTK>
+int launch_bwd(const BwdProblem& p, const BwdPlan& plan, float* parts)
+{
+    constexpr int NK = 2, tile = kBC * D * 2;
     constexpr int lds_dq = 2 * (2 * tile + (MULT ? kBC * 4 : 0)), lds_dkv = 2 * (2 * tile + 2 * kBC * 4) + (MULT ? kWaves * NK * 16 * 4 : 0);
-    auto kq = bwd_dq_kernel<D, HALF, MULT>;
-    auto kkv = bwd_dkv_kernel<D, HALF, MULT, NK>;
+    auto kq = bwd_dq_kernel<D, HALF, MULT, PARTQ>;
+    auto kkv = bwd_dkv_kernel<D, HALF, MULT, NK, PARTK>;
     static std::atomic<uint64_t> done_q{0}, done_kv{0};
     if (!raise_lds_limit(kq, lds_dq, done_q) || !raise_lds_limit(kkv, lds_dkv, done_kv)) return SPHATTN_ERR_LAUNCH;
-    const int n_qtiles = (p.N + 255) / 256, n_ktiles = (p.N + 64 * NK - 1) / (64 * NK);
-    const long long wg_q = (long long)p.B * p.H * n_qtiles, wg_kv = (long long)p.B * p.H_kv * n_ktiles;
+    const BwdShape sh = bwd_shape(p.H, p.H_kv, p.N, D);
+    const int n_qtiles = (sh.Nq + 255) / 256, n_ktiles = (p.N + 64 * NK - 1) / (64 * NK);
+    const long long wg_q = (long long)p.B * sh.H * n_qtiles * plan.sq, wg_kv = (long long)p.B * p.H_kv * n_ktiles * plan.sk;
     if (wg_q > 0x7fffffff || wg_kv > 0x7fffffff) return SPHATTN_ERR_SHAPE;
-    const int kv_group = p.H / p.H_kv;
     // the two planes of delta (delta_i r_i^2, then r_i) are written by the first kernel and read
     // by the second, in stream order
     float* rnorm = p.delta + (size_t)p.B * p.H * p.N;
+    const size_t nq = (size_t)p.B * p.H * p.N * D, nk = (size_t)p.B * p.H_kv * p.N * D;
+    float *parts_k = nullptr, *parts_v = nullptr;
+    if constexpr (PARTK) {
+        parts_k = parts + (PARTQ ? plan.sq * nq : 0);
+        parts_v = parts_k + plan.sk * nk;
+    }
     hipLaunchKernelGGL(kq, dim3((unsigned)wg_q), dim3(kThreads), lds_dq, p.stream,
-                       p.Q, p.K, p.V, p.mult, p.O, p.dO, p.Z, p.dQ, p.delta, rnorm, p.N, p.H, kv_group, n_qtiles, (int)wg_q);
+                       p.Q, p.K, p.V, p.mult, p.O, p.dO, p.Z, PARTQ ? (void*)parts : p.dQ, p.delta, rnorm,
+                       sh.Nq, p.N, sh.H, sh.kv_group, n_qtiles, (int)wg_q, plan.sq, plan.keys_per_split);
     if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
     hipLaunchKernelGGL(kkv, dim3((unsigned)wg_kv), dim3(kThreads), lds_dkv, p.stream,
-                       p.Q, p.K, p.V, p.mult, p.dO, (const float*)rnorm, (const float*)p.delta, p.dK, p.dV,
-                       p.N, p.H, kv_group, n_ktiles, (int)wg_kv);
-    return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
+                       p.Q, p.K, p.V, p.mult, p.dO, (const float*)rnorm, (const float*)p.delta,
+                       PARTK ? (void*)parts_k : p.dK, PARTK ? (void*)parts_v : p.dV,
+                       sh.Nq, p.N, sh.H, sh.kv_group, n_ktiles, (int)wg_kv, plan.sk, plan.tiles_per_split);
+    if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
+    if constexpr (PARTQ || PARTK) {
+        const size_t n4q = PARTQ ? nq / 4 : 0, n4k = PARTK ? nk / 4 : 0, blocks = (n4q + 2 * n4k + 255) / 256;
+        if (blocks > 0x7fffffff) return SPHATTN_ERR_SHAPE;
+        hipLaunchKernelGGL(bwd_combine_kernel<HALF>, dim3((unsigned)blocks), dim3(256), 0, p.stream,
+                           (const float*)parts, plan.sq, n4q, p.dQ, (const float*)parts_k, (const float*)parts_v, plan.sk, n4k, p.dK, p.dV);
+        if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
+    }
+    return SPHATTN_OK;
+}
+
+template <int D, bool HALF, bool MULT>
+int launch_bwd_plan(const BwdProblem& p, const BwdPlan& plan, void* workspace)
+{
+    float* parts = (float*)workspace;
+    if (plan.sq > 1 && plan.sk > 1) return launch_bwd<D, HALF, MULT, true, true>(p, plan, parts);
+    if (plan.sq > 1) return launch_bwd<D, HALF, MULT, true, false>(p, plan, parts);
+    if (plan.sk > 1) return launch_bwd<D, HALF, MULT, false, true>(p, plan, parts);
+    return launch_bwd<D, HALF, MULT, false, false>(p, plan, parts);
 }
 
 template <bool MULT>
-int dispatch_bwd(const BwdProblem& p, int d, int dtype)
+int dispatch_bwd(const BwdProblem& p, int d, int dtype, const BwdPlan& plan, void* workspace)
 {
-    if (dtype == SPHATTN_F16) return d == 128 ? launch_bwd<128, true, MULT, 2>(p) : launch_bwd<64, true, MULT, 2>(p);
-    return d == 128 ? launch_bwd<128, false, MULT, 2>(p) : launch_bwd<64, false, MULT, 2>(p);
+    if (dtype == SPHATTN_F16) return d == 128 ? launch_bwd_plan<128, true, MULT>(p, plan, workspace) : launch_bwd_plan<64, true, MULT>(p, plan, workspace);
+    return d == 128 ? launch_bwd_plan<128, false, MULT>(p, plan, workspace) : launch_bwd_plan<64, false, MULT>(p, plan, workspace);
 }
 
 size_t workspace_bytes(int B, int H, int N, int d, int n_splits)
@@ -709,6 +752,37 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
     return best;
 }
 
+// The library's choice of slices for the backward kernels.  dQ (256-row tiles, items_q of them) is cut so
+// that all slices run at once, one per CU; dK/dV (128-key tiles) likewise, or two per CU, which
+// it is built for, where the slices stay 32 tiles or longer: prologue, partial sums and their addition
+// cost a slice what 4 to 6 tiles cost, and no slice is shorter than 4.  Whole backward in us, bf16, uncut
+// against this choice (the best of a sweep over both counts within 3 %): 8 heads on 2 K/V heads of
+// 1500 x 64 129 / 42, of 1500 x 128 213 / 71; 4 on 2 of 2321 x 128 202 / 76; 4 x 1000 x 128 73 / 47;
+// 8 x 2048 x 128 127 / 87; 2 x 8192 x 128 450 / 212; 12 on 3 of 4096 x 64 330 / 171; 1 x 300 x 64 is not cut (21).
+BwdPlan plan_bwd(int B, int H, int H_kv, int N, int d)
+{
+    const BwdShape sh = bwd_shape(H, H_kv, N, d);
+    const long long cus = cu_count();
+    BwdPlan plan;
+    const long long key_tiles = ((long long)N + kBC - 1) / kBC, query_tiles = (long long)sh.kv_group * ((sh.Nq + kBC - 1) / kBC);
+    const long long items_q = (long long)B * sh.H * (((long long)sh.Nq + 255) / 256), items_k = (long long)B * H_kv * (((long long)N + 127) / 128);
+    long long sq = cus / items_q, sk = cus / items_k;
+    if (2 * cus / items_k > 1 && query_tiles / (2 * cus / items_k) >= 32) sk = 2 * cus / items_k;
+    sq = sq < key_tiles / 4 ? sq : key_tiles / 4;
+    sk = sk < query_tiles / 4 ? sk : query_tiles / 4;
+    if (sq > 1) {
+        const SplitPlan s = plan_splits(N, (int)sq);
+        plan.sq = s.n_splits;
+        plan.keys_per_split = s.keys_per_split;
+    }
+    if (sk > 1) {
+        plan.tiles_per_split = (int)((query_tiles + sk - 1) / sk);
+        plan.sk = (int)((query_tiles + plan.tiles_per_split - 1) / plan.tiles_per_split);
+    }
+    plan.bytes = ((plan.sq > 1 ? (size_t)plan.sq * B * H * N * d * 4 : 0) + (plan.sk > 1 ? (size_t)plan.sk * 2 * B * H_kv * N * d * 4 : 0) + 255) & ~(size_t)255;
+    return plan;
+}
+
 // The workspace of a split launch against its size and the other arguments.
 int check_workspace(const Problem& p, int d, int dtype, SplitPlan plan, const void* workspace, size_t size)
 {
@@ -723,6 +797,32 @@ int check_workspace(const Problem& p, int d, int dtype, SplitPlan plan, const vo
         (p.mult && overlaps(workspace, need, p.mult, (size_t)p.B * p.Nk * 4)) ||
         (p.Z && overlaps(workspace, need, p.Z, (size_t)p.B * p.H * p.Nq * 4)))
         return SPHATTN_ERR_ALIAS;
+    return SPHATTN_OK;
+}
+
+// Argument checks of the backward entry points.
+int check_bwd(const void* Q, const void* K, const void* V, const float* mult, const void* O, const void* dO, const float* Z,
+              void* dQ, void* dK, void* dV, float* delta, int B, int H, int H_kv, int N, int d, int dtype)
+{
+    if (!Q || !K || !V || !O || !dO || !Z || !dQ || !dK || !dV || !delta) return SPHATTN_ERR_NULL;
+    const int rc = check_shape(B, H, H_kv, N, N, d, dtype);
+    if (rc != SPHATTN_OK) return rc;
+    if (dtype != SPHATTN_BF16 && dtype != SPHATTN_F16) return SPHATTN_ERR_DTYPE;
+    if (((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)O | (uintptr_t)dO |
+         (uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) & 15)
+        return SPHATTN_ERR_ALIGN;
+    if (((uintptr_t)Z | (uintptr_t)delta | (uintptr_t)mult) & 3) return SPHATTN_ERR_ALIGN;
+    const size_t tq = (size_t)B * H * N * d * 2, tkv = (size_t)B * H_kv * N * d * 2, rb = (size_t)B * H * N * 4;
+    const void* ins[7] = {Q, K, V, O, dO, Z, mult};
+    const size_t in_bytes[7] = {tq, tkv, tkv, tq, tq, rb, mult ? (size_t)B * N * 4 : 0};
+    void* outs[4] = {dQ, dK, dV, delta};
+    const size_t out_bytes[4] = {tq, tkv, tkv, 2 * rb};
+    for (int o = 0; o < 4; ++o) {
+        for (int i = 0; i < 7; ++i)
+            if (ins[i] && overlaps(outs[o], out_bytes[o], ins[i], in_bytes[i])) return SPHATTN_ERR_ALIAS;
+        for (int q = o + 1; q < 4; ++q)
+            if (overlaps(outs[o], out_bytes[o], outs[q], out_bytes[q])) return SPHATTN_ERR_ALIAS;
+    }
     return SPHATTN_OK;
 }
 
@@ -938,27 +1038,37 @@ int sphattn_grn_bwd(const void* Q, const void* K, const void* V, const float* mu
                     void* dQ, void* dK, void* dV, float* delta,
                     int B, int H, int H_kv, int N, int d, int dtype, void* stream)
 {
-    if (!Q || !K || !V || !O || !dO || !Z || !dQ || !dK || !dV || !delta) return SPHATTN_ERR_NULL;
-    const int rc = check_shape(B, H, H_kv, N, N, d, dtype);
+    const int rc = check_bwd(Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, dtype);
     if (rc != SPHATTN_OK) return rc;
-    if (dtype != SPHATTN_BF16 && dtype != SPHATTN_F16) return SPHATTN_ERR_DTYPE;
-    if (((uintptr_t)Q | (uintptr_t)K | (uintptr_t)V | (uintptr_t)O | (uintptr_t)dO |
-         (uintptr_t)dQ | (uintptr_t)dK | (uintptr_t)dV) & 15)
-        return SPHATTN_ERR_ALIGN;
-    if (((uintptr_t)Z | (uintptr_t)delta | (uintptr_t)mult) & 3) return SPHATTN_ERR_ALIGN;
-    const size_t tq = (size_t)B * H * N * d * 2, tkv = (size_t)B * H_kv * N * d * 2, rb = (size_t)B * H * N * 4;
-    const void* ins[7] = {Q, K, V, O, dO, Z, mult};
-    const size_t in_bytes[7] = {tq, tkv, tkv, tq, tq, rb, mult ? (size_t)B * N * 4 : 0};
-    void* outs[4] = {dQ, dK, dV, delta};
-    const size_t out_bytes[4] = {tq, tkv, tkv, 2 * rb};
-    for (int o = 0; o < 4; ++o) {
-        for (int i = 0; i < 7; ++i)
-            if (ins[i] && overlaps(outs[o], out_bytes[o], ins[i], in_bytes[i])) return SPHATTN_ERR_ALIAS;
-        for (int q = o + 1; q < 4; ++q)
-            if (overlaps(outs[o], out_bytes[o], outs[q], out_bytes[q])) return SPHATTN_ERR_ALIAS;
+    const BwdProblem p{Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, (hipStream_t)stream};
+    return mult ? dispatch_bwd<true>(p, d, dtype, BwdPlan{}, nullptr) : dispatch_bwd<false>(p, d, dtype, BwdPlan{}, nullptr);
+}
+
+size_t sphattn_bwd_workspace_bytes(int B, int H, int H_kv, int N, int d, int dtype)
+{
+    if (check_shape(B, H, H_kv, N, N, d, dtype) != SPHATTN_OK || (dtype != SPHATTN_BF16 && dtype != SPHATTN_F16)) return 0;
+    return plan_bwd(B, H, H_kv, N, d).bytes;
+}
+
+int sphattn_grn_bwd_split(const void* Q, const void* K, const void* V, const float* mult,
+                          const void* O, const void* dO, const float* Z,
+                          void* dQ, void* dK, void* dV, float* delta,
+                          int B, int H, int H_kv, int N, int d, int dtype,
+                          void* workspace, size_t workspace_size, void* stream)
+{
+    const int rc = check_bwd(Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, dtype);
+    if (rc != SPHATTN_OK) return rc;
+    const BwdPlan plan = plan_bwd(B, H, H_kv, N, d);
+    if (plan.bytes) {
+        if (!workspace || workspace_size < plan.bytes || ((uintptr_t)workspace & 15) || wraps(workspace, plan.bytes)) return SPHATTN_ERR_WORKSPACE;
+        const size_t tq = (size_t)B * H * N * d * 2, tkv = (size_t)B * H_kv * N * d * 2, rb = (size_t)B * H * N * 4;
+        const void* others[11] = {Q, K, V, O, dO, Z, mult, dQ, dK, dV, delta};
+        const size_t bytes[11] = {tq, tkv, tkv, tq, tq, rb, (size_t)B * N * 4, tq, tkv, tkv, 2 * rb};
+        for (int i = 0; i < 11; ++i)
+            if (others[i] && overlaps(workspace, plan.bytes, others[i], bytes[i])) return SPHATTN_ERR_ALIAS;
     }
     const BwdProblem p{Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, (hipStream_t)stream};
-    return mult ? dispatch_bwd<true>(p, d, dtype) : dispatch_bwd<false>(p, d, dtype);
+    return mult ? dispatch_bwd<true>(p, d, dtype, plan, workspace) : dispatch_bwd<false>(p, d, dtype, plan, workspace);
 }
 
 int sphattn_bwd(const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* Z,

@@ -28,6 +28,11 @@
 // cost every 16-byte read twice its cycles: see block_piece_offset).  Two LDS buffers, one
 // barrier per streamed tile.
 //
+// Rows and slices.  Query heads that share a K/V head are one block of Nq = kv_group N query rows wherever
+// that fits a 32-bit buffer range (the launch then says kv_group = 1).  PART: launches that leave CUs idle cut
+// the streamed axis into slices, more workgroups of the same tiles, which leave fp32 partial sums, slice
+// after slice; bwd_combine_kernel adds them in ascending order and rounds once.
+//
 // Gene-regulatory-network options (MULT, kv_group), as in the forward: s_ij = m_j (q_i . k_j),
 // so dQ_i = sum_j ds_ij m_j k_j and dK_j = m_j sum_i ds_ij q_i (the multiplicities are data and
 // get no gradient); kv_group query heads share a K/V head, whose dK and dV sum over the
@@ -61,13 +66,13 @@ __device__ __forceinline__ float dot8(i32x4 a, i32x4 b, float acc)
 // ---------------------------------------------------------------------------
 // dQ.  Workgroup = 4 waves x 64 query rows (four blocks of 16).  Streams K/V tiles of 64 keys.
 // ---------------------------------------------------------------------------
-template <int D, bool HALF, bool MULT>
+template <int D, bool HALF, bool MULT, bool PART>
 __global__ __launch_bounds__(kThreads, 1)
 void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, const void* __restrict__ Vv,
                    const float* __restrict__ mult,
                    const void* __restrict__ Ov, const void* __restrict__ dOv, const float* __restrict__ Z,
                    void* __restrict__ dQv, float* __restrict__ delta, float* __restrict__ rnorm,
-                   int N, int H, int kv_group, int n_qtiles, int n_wg)
+                   int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
 {
     constexpr int BC = kBC, NQ = 4, BR = kWaves * 16 * NQ;
     constexpr int ROWB = D * 2, TILE = BC * ROWB;
@@ -82,10 +87,14 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n16 = lane & 15, g = lane >> 4;
     const int lid = xcd_contiguous_id(blockIdx.x, n_wg);
-    const int bh = lid / n_qtiles, qt = lid % n_qtiles;
-    const size_t head_off = (size_t)bh * N * D;
+    const int qt = lid % n_qtiles;
+    const int split = PART ? (lid / n_qtiles) % n_splits : 0;
+    const int bh = PART ? lid / (n_qtiles * n_splits) : lid / n_qtiles;
+    const size_t head_off = (size_t)bh * Nq * D;
     const int bidx = bh / H;
-    const size_t kv_off = (size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * N * D;
+    const int k0 = PART ? split * keys_per_split : 0;                 // this slice's keys: k0 .. k0 + N - 1
+    const int N = PART ? min(Nk - k0, keys_per_split) : Nk;
+    const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
     const int q0 = qt * BR + wave * 16 * NQ;
 
     // own rows: Q and dO as B operands (lane: row q0 + 16qb + n16, elements 32kk + 8g .. +7);
@@ -95,8 +104,8 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         int row = q0 + qb * 16 + n16;
-        const bool live = row < N;
-        row = live ? row : N - 1;
+        const bool live = row < Nq;
+        row = live ? row : Nq - 1;
         const size_t off = (head_off + (size_t)row * D) * 2 + 16 * g;
         float dsum = 0.f;
 #pragma unroll
@@ -107,14 +116,14 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
             dsum = dot8<HALF>(gf[qb][kk], of, dsum);
         }
         dsum = sum_across_groups(dsum);            // delta_i = dO_i . O_i
-        const float z = Z[(size_t)bh * N + row];
+        const float z = Z[(size_t)bh * Nq + row];
         const float r = z > 0.f ? 1.0f / __builtin_sqrtf(z) : 0.f;
         c1[qb] = r;
         c3[qb] = dsum * r;
         // for the dK/dV kernel: r_i and delta_i r_i^2, the factors of G_ij and s_ij in ds_ij
-        if (live && g == 0) {
-            delta[(size_t)bh * N + row] = c3[qb] * r;
-            rnorm[(size_t)bh * N + row] = r;
+        if (live && g == 0 && split == 0) {
+            delta[(size_t)bh * Nq + row] = c3[qb] * r;
+            rnorm[(size_t)bh * Nq + row] = r;
         }
     }
 
@@ -127,7 +136,7 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
     // tile copies: wave w brings rows 16w .. 16w+15 of the K and of the V tile (KBLK blocks each)
     const i32x4 krw = rsrc_words((const unsigned char*)Kv + kv_off * 2, (uint32_t)N * ROWB);
     const i32x4 vrw = rsrc_words((const unsigned char*)Vv + kv_off * 2, (uint32_t)N * ROWB);
-    const i32x4 mrw = rsrc_words(MULT ? mult + (size_t)bidx * N : nullptr, MULT ? (uint32_t)N * 4 : 0);
+    const i32x4 mrw = rsrc_words(MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, MULT ? (uint32_t)N * 4 : 0);
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     // a 1 KB copy fills two blocks: lane l lands in block l / 32, row (l % 32) / 2, piece l % 2
     const int ld_lane = (16 * wave + ((lane & 31) >> 1)) * ROWB + (lane >> 5) * 32 + (lane & 1) * 16;
@@ -230,11 +239,23 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);            // the copy of the tile past the end (zeros)
 
+    if constexpr (PART) {
+        float* dst0 = (float*)dQv + ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq * D + 4 * g;
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            const int row = q0 + qb * 16 + n16;
+            if (row < Nq) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst0 + (size_t)row * D + db * 16) = dq[db][qb] * c1[qb];
+            }
+        }
+        return;
+    }
     unsigned short* dQh = (unsigned short*)dQv + head_off;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         const int row = q0 + qb * 16 + n16;
-        if (row < N) {
+        if (row < Nq) {
             unsigned short* dst = dQh + (size_t)row * D + 4 * g;
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
@@ -258,13 +279,13 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
 // shapes): NK = 2 1.85 / 1.98 ms, NK = 3 2.29 / 2.05 ms, NK = 4 (d = 64) 2.14 ms: with one
 // wave per SIMD the second wave's latency hiding is worth more than the saved LDS reads, so
 // the library launches NK = 2.
-template <int D, bool HALF, bool MULT, int NK>
+template <int D, bool HALF, bool MULT, int NK, bool PART>
 __global__ __launch_bounds__(kThreads, NK == 2 ? 2 : 1)
 void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, const void* __restrict__ Vv,
                     const float* __restrict__ mult,
                     const void* __restrict__ dOv, const float* __restrict__ rnorm, const float* __restrict__ delta,
                     void* __restrict__ dKv, void* __restrict__ dVv,
-                    int N, int H, int kv_group, int n_ktiles, int n_wg)
+                    int Nq, int N, int H, int kv_group, int n_ktiles, int n_wg, int n_splits, int tiles_per_split)
 {
     constexpr int BC = kBC, BKEYS = kWaves * 16 * NK;
     constexpr int ROWB = D * 2, TILE = BC * ROWB;
@@ -279,7 +300,9 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     const int n16 = lane & 15, g = lane >> 4;
     const int lid = xcd_contiguous_id(blockIdx.x, n_wg);
     // lid counts (K/V head, key tile); the query heads h0 .. h0 + kv_group - 1 of batch bidx use it
-    const int kvh = lid / n_ktiles, kt = lid % n_ktiles;
+    const int kt = lid % n_ktiles;
+    const int split = PART ? (lid / n_ktiles) % n_splits : 0;
+    const int kvh = PART ? lid / (n_ktiles * n_splits) : lid / n_ktiles;
     const int H_kv = H / kv_group;
     const int bidx = kvh / H_kv, h0 = (kvh % H_kv) * kv_group;
     const size_t head_off = (size_t)kvh * N * D;   // of K, V, dK, dV
@@ -315,15 +338,15 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     // a 1 KB copy fills two blocks: lane l lands in block l / 32, row (l % 32) / 2, piece l % 2
     const int ld_lane = (16 * wave + ((lane & 31) >> 1)) * ROWB + (lane >> 5) * 32 + (lane & 1) * 16;
-    const int n_tiles = (N + BC - 1) / BC;
+    const int n_tiles = (Nq + BC - 1) / BC;
     // streamed tile `it` = tile it % n_tiles of query head h0 + it / n_tiles; each head has its
     // own descriptors, so that rows past the end of a head arrive as zeros
     struct HeadSource { i32x4 q, g, r, c; };       // buffer descriptors of Q, dO, r and delta r^2 of one query head
     auto head_source = [&](int hq) {
         const size_t qh = (size_t)(bidx * H + h0 + hq);
-        return HeadSource{rsrc_words((const unsigned char*)Qv + qh * N * D * 2, (uint32_t)N * ROWB),
-                          rsrc_words((const unsigned char*)dOv + qh * N * D * 2, (uint32_t)N * ROWB),
-                          rsrc_words(rnorm + qh * N, (uint32_t)N * 4), rsrc_words(delta + qh * N, (uint32_t)N * 4)};
+        return HeadSource{rsrc_words((const unsigned char*)Qv + qh * Nq * D * 2, (uint32_t)Nq * ROWB),
+                          rsrc_words((const unsigned char*)dOv + qh * Nq * D * 2, (uint32_t)Nq * ROWB),
+                          rsrc_words(rnorm + qh * Nq, (uint32_t)Nq * 4), rsrc_words(delta + qh * Nq, (uint32_t)Nq * 4)};
     };
     // piece 0 .. 2 KBLK - 1 of this wave's share of a tile: its 16 rows of Q (even) or dO (odd), 64-byte column block piece / 2
     auto copy_piece = [&](const HeadSource& hs, int piece, int tile, uint32_t buf) {
@@ -331,7 +354,7 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
         copy_to_lds((piece & 1) ? hs.g : hs.q, buf + ((piece & 1) ? GLDS : 0) + (wave_u * KBLK + c) * 1024, ld_lane,
                     tile * TILE + c * 64);
     };
-    // 64 r and 64 delta r^2 values: 16 lanes x 16 bytes each; queries past N arrive as 0.
+    // 64 r and 64 delta r^2 values: 16 lanes x 16 bytes each; queries past Nq arrive as 0.
     // (Under a branch, unlike the multiplicities of the other kernels: this kernel gains
     // nothing from the all-wave form, and its 48-key variant, at 512 registers, came out
     // of the compiler with 196 bytes of scratch and wrong dK with it.)
@@ -343,14 +366,17 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     const int tlane = lane * 8;
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    // this slice's streamed tiles: first .. last - 1
+    const int first = PART ? split * tiles_per_split : 0;
+    const int last = PART ? min(kv_group * n_tiles, first + tiles_per_split) : kv_group * n_tiles;
+    int next_hq = PART ? first / n_tiles : 0, next_tile = PART ? first % n_tiles : 0;   // head and tile of the copies issued in iteration j
     {
-        const HeadSource hs = head_source(0);
-        copy_planes(hs, 0, lds0);
+        const HeadSource hs = head_source(next_hq);
+        copy_planes(hs, next_tile, lds0);
 #pragma unroll
-        for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(hs, piece, 0, lds0);
+        for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(hs, piece, next_tile, lds0);
     }
-    int next_hq = 0, next_tile = 0;                // head and tile of the copies issued in iteration j
-    for (int j = 0; j < kv_group * n_tiles; ++j) {
+    for (int j = 0; j < last - first; ++j) {
         const uint32_t cur = (j & 1) * BUF_BYTES;
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0)
@@ -446,6 +472,23 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);
 
+    if constexpr (PART) {
+        const size_t off = (size_t)split * (n_wg / (n_ktiles * n_splits)) * N * D + head_off + 4 * g;
+#pragma unroll
+        for (int kb = 0; kb < NK; ++kb) {
+            const int row = k0 + kb * 16 + n16;
+            const float mk_row = mk(kb);
+            if (row < N) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    if constexpr (MULT) { dk[db][kb] *= mk_row; dv[db][kb] *= mk_row; }
+                    *reinterpret_cast<f32x4*>((float*)dKv + off + (size_t)row * D + db * 16) = dk[db][kb];
+                    *reinterpret_cast<f32x4*>((float*)dVv + off + (size_t)row * D + db * 16) = dv[db][kb];
+                }
+            }
+        }
+        return;
+    }
     unsigned short* dKh = (unsigned short*)dKv + head_off;
     unsigned short* dVh = (unsigned short*)dVv + head_off;
 #pragma unroll
@@ -463,6 +506,39 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Sums of the slices' partial gradients, rounded to the 16-bit type: first n4q groups of four values of dQ
+// over sq slices, then n4k of dK and n4k of dV over sk slices (a gradient that was not cut has none).  Slice p
+// starts 4 n4 values after slice p - 1; added in ascending order, eight slices' loads in flight.
+// ---------------------------------------------------------------------------
+template <bool HALF>
+__global__ __launch_bounds__(256)
+void bwd_combine_kernel(const float* __restrict__ pq, int sq, size_t n4q, void* __restrict__ dQ,
+                        const float* __restrict__ pk, const float* __restrict__ pv, int sk, size_t n4k,
+                        void* __restrict__ dK, void* __restrict__ dV)
+{
+    size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4q + 2 * n4k) return;
+    const bool q = i < n4q, k = !q && i < n4q + n4k;
+    i -= q ? 0 : k ? n4q : n4q + n4k;
+    const f32x4* src = reinterpret_cast<const f32x4*>(q ? pq : k ? pk : pv) + i;
+    const size_t step = q ? n4q : n4k;
+    const int n = q ? sq : sk;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int p = 0;
+    for (; p + 8 <= n; p += 8) {
+        f32x4 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = src[(size_t)(p + u) * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += x[u];
+    }
+#pragma unroll 4
+    for (; p < n; ++p) acc += src[(size_t)p * step];
+    const i32x2 o4 = {pack2<HALF>(acc[0], acc[1]), pack2<HALF>(acc[2], acc[3])};
+    *(reinterpret_cast<i32x2*>(q ? dQ : k ? dK : dV) + i) = o4;
 }
 
 }  // namespace sphattn

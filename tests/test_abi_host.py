@@ -349,3 +349,25 @@ def test_cross_split_argument_errors(lib):
     assert call(ws=0) == -9 and call(ws=0x40000008) == -9 and call(size=need - 1) == -9
     assert call(ws=0x2000000) == -7 and call(ws=0x4000000) == -7
     assert call(mult=0x5000000, ws=0x5000000) == -7 and call(Z=0x5000000, ws=0x5000000) == -7
+
+
+def test_backward_split_argument_errors(lib):
+    P = ctypes.c_void_p
+    need = lib.sphattn_bwd_workspace_bytes(1, 4, 2, 1500, 64, 1)
+    assert need > 0 and need % 256 == 0
+    assert lib.sphattn_bwd_workspace_bytes(1, 4, 3, 1500, 64, 1) == 0 and lib.sphattn_bwd_workspace_bytes(1, 4, 2, 1500, 64, 0) == 0
+    base = dict(Q=0x10000000, K=0x20000000, V=0x30000000, mult=0, O=0x40000000, dO=0x50000000, Z=0x60000000,
+                dQ=0x70000000, dK=0x80000000, dV=0x90000000, delta=0xA0000000)
+
+    def call(ws=0xB0000000, size=need, d=64, dtype=1, H_kv=2, **over):
+        a = dict(base, **over)
+        return lib.sphattn_grn_bwd_split(*(P(a[n]) for n in ("Q", "K", "V", "mult", "O", "dO", "Z", "dQ", "dK", "dV", "delta")),
+                                         1, 4, H_kv, 1500, d, dtype, P(ws), size, None)
+    for name in base:
+        if name != "mult":
+            assert call(**{name: 0}) == -1
+    assert call(H_kv=3) == -2 and call(d=96) == -3 and call(dtype=0) == -4 and call(dK=0x80000008) == -5
+    assert call(dQ=0x10000000) == -7
+    assert call(ws=0) == -9 and call(ws=0xB0000004) == -9 and call(size=need - 1) == -9
+    for name in base:
+        assert call(ws=base[name] or 0xB0000000, mult=0xB0000000) == -7       # the workspace is one of the arguments
