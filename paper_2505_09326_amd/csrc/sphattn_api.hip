@@ -731,7 +731,10 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
     const double part_us = (double)heads * (double)p.Nq * (d + 1) * 8.0 / 6e6;
     SplitPlan best = plan_splits(Nk, 1);
     double best_us = 0.0;
-    for (long long S = 1; (S * items <= cus || S == 1) && S <= tiles; ++S) {
+    // (fp32 also above one round, whose remainder cutting recovers: choose_f32 counts rounds;
+    // 1 x 21694 x 128, 170 workgroups of 128 rows, 1464 us uncut, 951 in 3 slices of 256-row workgroups)
+    const long long most = dtype == SPHATTN_F32 ? 4 * cus : cus;
+    for (long long S = 1; (S * items <= most || S == 1) && S <= tiles; ++S) {
         const SplitPlan plan = plan_splits(Nk, (int)S);
         if (plan.n_splits != S) continue;          // the same slices as a smaller count
         const double per = (double)(S == 1 ? tiles : plan.keys_per_split / kBC);
@@ -752,24 +755,47 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
     return best;
 }
 
-// The library's choice of slices for the backward kernels.  dQ (256-row tiles, items_q of them) is cut so
-// that all slices run at once, one per CU; dK/dV (128-key tiles) likewise, or two per CU, which
-// it is built for, where the slices stay 32 tiles or longer: prologue, partial sums and their addition
-// cost a slice what 4 to 6 tiles cost, and no slice is shorter than 4.  Whole backward in us, bf16, uncut
-// against this choice (the best of a sweep over both counts within 3 %): 8 heads on 2 K/V heads of
-// 1500 x 64 129 / 42, of 1500 x 128 213 / 71; 4 on 2 of 2321 x 128 202 / 76; 4 x 1000 x 128 73 / 47;
-// 8 x 2048 x 128 127 / 87; 2 x 8192 x 128 450 / 212; 12 on 3 of 4096 x 64 330 / 171; 1 x 300 x 64 is not cut (21).
+// How many slices a backward kernel's streamed axis of `tiles` 64-row tiles is cut into, for `items` tiles of
+// the other axis, `per_cu` workgroups at once on a CU, tau us per streamed tile in a full round and
+// part_us for writing and reading one slice's partial sums (6 TB/s).  A slice costs what its tiles and
+// about 5 more cost.  Below one round the fullest CU counts: one of two workgroups alone takes 0.62 of the
+// time of both, one or two of three 0.48 and 0.74; and an emptier chip clocks higher (power-bound part).  A
+// last round behind full ones costs 0.85 + 0.15 f of one if it fills the share f.  Cut for a gain of at
+// least 5 %, into slices of 4 tiles or more and at most 256 MB of sums.  Whole backward in us, bf16, uncut /
+// this choice (within 3 % of the best of a sweep over both kernels' counts): below one round 8 heads on 2
+// K/V heads of 1500 x 64 132 / 45, of 1500 x 128 217 / 71; 4 x 1000 x 128 74 / 49; 2 x 8192 x 128 449 / 224; 12 on 3
+// of 4096 x 64 327 / 179; above it 3 x 25243 x 128 (1.16 rounds in both kernels) 3240 / 2522, 9 x 8192 x 128
+// 1074 / 953, 3 x 12000 x 64 471 / 350; 12 x 4096 x 128 (0.75 of a round in both) stays uncut: 304, 332 in 4
+// slices of the keys, 330 in 4 of the queries.
+long long choose_bwd_slices(long long items, int per_cu, long long tiles, double tau, double part_us, size_t part_bytes)
+{
+    const double alone[3][3] = {{1.0, 1.0, 1.0}, {0.62, 1.0, 1.0}, {0.48, 0.74, 1.0}};
+    const long long cus = cu_count(), resident = cus * per_cu;
+    long long best = 1;
+    double best_us = 0.0;
+    for (long long S = 1; S <= 64 && (S == 1 || (tiles / S >= 4 && (size_t)S * part_bytes <= ((size_t)256 << 20))); ++S) {
+        const long long per = (tiles + S - 1) / S, n = items * S, full = n / resident;
+        const double f = (double)(n % resident) / (double)resident;
+        double rounds;
+        if (full == 0) rounds = alone[per_cu - 1][(n + cus - 1) / cus - 1] * (n < cus ? 0.75 + 0.25 * (double)n / (double)cus : 1.0);
+        else rounds = (double)full + (f > 0.0 ? 0.85 + 0.15 * f : 0.0);
+        const double us = rounds * ((double)per + 5.0) * tau + (S > 1 ? 2.0 + (double)S * part_us : 0.0);
+        if (S == 1) best_us = 0.95 * us;
+        else if (us < best_us) { best_us = us; best = S; }
+    }
+    return best;
+}
+
 BwdPlan plan_bwd(int B, int H, int H_kv, int N, int d)
 {
     const BwdShape sh = bwd_shape(H, H_kv, N, d);
-    const long long cus = cu_count();
     BwdPlan plan;
     const long long key_tiles = ((long long)N + kBC - 1) / kBC, query_tiles = (long long)sh.kv_group * ((sh.Nq + kBC - 1) / kBC);
     const long long items_q = (long long)B * sh.H * (((long long)sh.Nq + 255) / 256), items_k = (long long)B * H_kv * (((long long)N + 127) / 128);
-    long long sq = cus / items_q, sk = cus / items_k;
-    if (2 * cus / items_k > 1 && query_tiles / (2 * cus / items_k) >= 32) sk = 2 * cus / items_k;
-    sq = sq < key_tiles / 4 ? sq : key_tiles / 4;
-    sk = sk < query_tiles / 4 ? sk : query_tiles / 4;
+    const size_t bytes_q = (size_t)B * H * N * d * 4, bytes_k = 2 * (size_t)B * H_kv * N * d * 4;
+    // workgroups per CU: dQ one (d = 128) or two, dK/dV two or three; tau from launches of many rounds
+    const long long sq = choose_bwd_slices(items_q, d == 128 ? 1 : 2, key_tiles, d == 128 ? 2.2 : 1.96, (double)bytes_q * 2.0 / 6e6, bytes_q);
+    const long long sk = choose_bwd_slices(items_k, d == 128 ? 2 : 3, query_tiles, d == 128 ? 3.06 : 2.27, (double)bytes_k * 2.0 / 6e6, bytes_k);
     if (sq > 1) {
         const SplitPlan s = plan_splits(N, (int)sq);
         plan.sq = s.n_splits;
@@ -779,7 +805,7 @@ BwdPlan plan_bwd(int B, int H, int H_kv, int N, int d)
         plan.tiles_per_split = (int)((query_tiles + sk - 1) / sk);
         plan.sk = (int)((query_tiles + plan.tiles_per_split - 1) / plan.tiles_per_split);
     }
-    plan.bytes = ((plan.sq > 1 ? (size_t)plan.sq * B * H * N * d * 4 : 0) + (plan.sk > 1 ? (size_t)plan.sk * 2 * B * H_kv * N * d * 4 : 0) + 255) & ~(size_t)255;
+    plan.bytes = ((plan.sq > 1 ? (size_t)plan.sq * bytes_q : 0) + (plan.sk > 1 ? (size_t)plan.sk * bytes_k : 0) + 255) & ~(size_t)255;
     return plan;
 }
 
