@@ -494,7 +494,7 @@ template <int D, bool HALF, bool MULT, bool PARTQ, bool PARTK>
 int launch_bwd(const BwdProblem& p, const BwdPlan& plan, float* parts)
 {
     constexpr int NK = 2, tile = kBC * D * 2;
-    constexpr int lds_dq = 2 * (2 * tile + (MULT ? kBC * 4 : 0)), lds_dkv = 2 * (2 * tile + 2 * kBC * 4) + (MULT ? kWaves * NK * 16 * 4 : 0);
+    constexpr int lds_dq = bwd_dq_lds_bytes<D, MULT>(), lds_dkv = 2 * (2 * tile + 2 * kBC * 4) + (MULT ? kWaves * NK * 16 * 4 : 0);
     auto kq = bwd_dq_kernel<D, HALF, MULT, PARTQ>;
     auto kkv = bwd_dkv_kernel<D, HALF, MULT, NK, PARTK>;
     static std::atomic<uint64_t> done_q{0}, done_kv{0};

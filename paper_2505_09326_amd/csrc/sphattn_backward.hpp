@@ -63,6 +63,14 @@ __device__ __forceinline__ float dot8(i32x4 a, i32x4 b, float acc)
     return acc;
 }
 
+// LDS of the dQ kernel: two tile buffers, or one and the prologue's query blocks.
+template <int D, bool MULT>
+constexpr int bwd_dq_lds_bytes()
+{
+    constexpr int buf = 2 * kBC * D * 2 + (MULT ? kBC * 4 : 0), own = kWaves * 2 * 3 * (D / 32) * 1024;
+    return buf + (buf > own ? buf : own);
+}
+
 // ---------------------------------------------------------------------------
 // dQ.  Workgroup = 4 waves x 64 query rows (four blocks of 16).  Streams K/V tiles of 64 keys.
 // ---------------------------------------------------------------------------
@@ -98,46 +106,31 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
     const int q0 = qt * BR + wave * 16 * NQ;
 
     // own rows: Q and dO as B operands (lane: row q0 + 16qb + n16, elements 32kk + 8g .. +7);
-    // r and delta of the lane's query of every block
-    i32x4 qf[NQ][KK], gf[NQ][KK];
-    float c1[NQ], c3[NQ];                          // r_i and delta_i r_i
+    // r and delta of the lane's query of every block.  Q, dO and O come through LDS, as 1 KB block copies
+    // in the forward's K format: loaded straight into registers, an instruction's 64 lanes
+    // touch 16 rows and the 192 KB of a workgroup (d = 128) arrive at 16 bytes per cycle, 5.5 us; copied, at
+    // twice that.  Wave-private, a block of 16 queries at a time, the next one under way (two halves).
+    constexpr int STAGE = 3 * KBLK * 1024;         // one query block of Q, dO and O
+    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+    const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int own = BUF_BYTES + (int)wave_u * 2 * STAGE;   // behind tile buffer 0
+    const i32x4 own_rw[3] = {rsrc_words((const unsigned char*)Qv + head_off * 2, (uint32_t)Nq * ROWB),
+                             rsrc_words((const unsigned char*)dOv + head_off * 2, (uint32_t)Nq * ROWB),
+                             rsrc_words((const unsigned char*)Ov + head_off * 2, (uint32_t)Nq * ROWB)};
+    const int own_lane = (lane >> 2) * ROWB + block_piece_in_slot(lane) * 16;
+    auto copy_block = [&](int qb) {                // rows past the last query arrive as zeros
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-        int row = q0 + qb * 16 + n16;
-        const bool live = row < Nq;
-        row = live ? row : Nq - 1;
-        const size_t off = (head_off + (size_t)row * D) * 2 + 16 * g;
-        float dsum = 0.f;
+        for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            qf[qb][kk] = *reinterpret_cast<const i32x4*>((const unsigned char*)Qv + off + kk * 64);
-            gf[qb][kk] = *reinterpret_cast<const i32x4*>((const unsigned char*)dOv + off + kk * 64);
-            const i32x4 of = *reinterpret_cast<const i32x4*>((const unsigned char*)Ov + off + kk * 64);
-            dsum = dot8<HALF>(gf[qb][kk], of, dsum);
-        }
-        dsum = sum_across_groups(dsum);            // delta_i = dO_i . O_i
-        const float z = Z[(size_t)bh * Nq + row];
-        const float r = z > 0.f ? 1.0f / __builtin_sqrtf(z) : 0.f;
-        c1[qb] = r;
-        c3[qb] = dsum * r;
-        // for the dK/dV kernel: r_i and delta_i r_i^2, the factors of G_ij and s_ij in ds_ij
-        if (live && g == 0 && split == 0) {
-            delta[(size_t)bh * Nq + row] = c3[qb] * r;
-            rnorm[(size_t)bh * Nq + row] = r;
-        }
-    }
-
-    f32x4 dq[DB][NQ];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) dq[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c = 0; c < KBLK; ++c)
+                copy_to_lds(own_rw[t], lds0 + own + (qb & 1) * STAGE + (t * KBLK + c) * 1024, own_lane,
+                            (qt * BR + (int)wave_u * 16 * NQ + qb * 16) * ROWB + c * 64);
+    };
 
     // tile copies: wave w brings rows 16w .. 16w+15 of the K and of the V tile (KBLK blocks each)
     const i32x4 krw = rsrc_words((const unsigned char*)Kv + kv_off * 2, (uint32_t)N * ROWB);
     const i32x4 vrw = rsrc_words((const unsigned char*)Vv + kv_off * 2, (uint32_t)N * ROWB);
     const i32x4 mrw = rsrc_words(MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, MULT ? (uint32_t)N * 4 : 0);
-    const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     // a 1 KB copy fills two blocks: lane l lands in block l / 32, row (l % 32) / 2, piece l % 2
     const int ld_lane = (16 * wave + ((lane & 31) >> 1)) * ROWB + (lane >> 5) * 32 + (lane & 1) * 16;
     // piece 0 .. 2 KBLK - 1 of this wave's share of a tile: its 16 rows of K (even) or V (odd),
@@ -150,14 +143,69 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
     auto copy_mult = [&](int tile, uint32_t buf) {
         if constexpr (MULT) copy_to_lds_b32(mrw, buf + MLDS, lane * 4, tile * BC * 4);   // by every wave
     };
+
+    i32x4 qf[NQ][KK], gf[NQ][KK];
+    float c1[NQ], c3[NQ];                          // r_i and delta_i r_i
+    copy_block(0);
+    copy_block(1);
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+        if (qb == NQ - 1) {                        // tile 0 behind the last block
+            copy_mult(0, lds0);
+#pragma unroll
+            for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(piece, 0, lds0);
+        }
+        // block qb has landed; what was asked for after it (one block, or tile 0) may be under way
+        constexpr int VM = 3 * KBLK, VMT = 2 * KBLK + (MULT ? 1 : 0);
+        asm volatile("" ::: "memory");
+        if (qb < NQ - 1) __builtin_amdgcn_s_waitcnt(0x0F70 | VM);
+        else __builtin_amdgcn_s_waitcnt(0x0F70 | VMT);
+        asm volatile("" ::: "memory");
+        const SPH_LDS unsigned char* src = smem + own + (qb & 1) * STAGE + block_piece_offset(n16, g);
+        i32x4 of[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            qf[qb][kk] = lds_read_b128(src + kk * 1024);
+            gf[qb][kk] = lds_read_b128(src + (KBLK + kk) * 1024);
+            of[kk] = lds_read_b128(src + (2 * KBLK + kk) * 1024);
+        }
+        if (qb + 2 < NQ) {                         // the reads have returned before their half is overwritten
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0)
+            copy_block(qb + 2);
+        }
+        int row = q0 + qb * 16 + n16;
+        const bool live = row < Nq;
+        row = live ? row : Nq - 1;
+        float dsum = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) dsum = dot8<HALF>(gf[qb][kk], of[kk], dsum);
+        dsum = sum_across_groups(dsum);            // delta_i = dO_i . O_i
+        const float z = Z[(size_t)bh * Nq + row];
+        const float r = z > 0.f ? 1.0f / __builtin_sqrtf(z) : 0.f;
+        c1[qb] = r;
+        c3[qb] = dsum * r;
+        // for the dK/dV kernel: r_i and delta_i r_i^2, the factors of G_ij and s_ij in ds_ij
+        if (live && g == 0 && split == 0) {
+            delta[(size_t)bh * Nq + row] = c3[qb] * r;
+            rnorm[(size_t)bh * Nq + row] = r;
+        }
+    }
+
+    // the last block's reads have returned before the first barrier, behind which tile 1 lands on it
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
+
+    f32x4 dq[DB][NQ];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) dq[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
     const int alane = (g >> 1) * 512 + n16 * 32 + (g & 1) * 16;    // row-major A operand
     const int tlane = lane * 8;                                    // transposed A operand
 
     const int n_tiles = (N + BC - 1) / BC;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-    copy_mult(0, lds0);
-#pragma unroll
-    for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(piece, 0, lds0);
     for (int j = 0; j < n_tiles; ++j) {
         if constexpr (D == 64) priority_by_tile(j);   // two workgroups per CU: keep them at the same tile
         const uint32_t cur = (j & 1) * BUF_BYTES;
@@ -308,25 +356,19 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     const size_t head_off = (size_t)kvh * N * D;   // of K, V, dK, dV
     const int k0 = kt * BKEYS + wave * 16 * NK;
 
-    // own keys: K and V as B operands (lane: key k0 + 16kb + n16, elements 32kk + 8g .. +7)
-    i32x4 kf[NK][KK], vf[NK][KK];
+    i32x4 kf[NK][KK], vf[NK][KK];                  // own keys: K and V as B operands
     // The lane's keys' multiplicities wait in LDS behind the tile buffers (one float per key of
     // the workgroup, written and read by the same lanes): held in registers for the whole kernel
     // they are what pushes the d = 128 kernel out of the 256 registers of two workgroups per CU.
     constexpr int MKLDS = 2 * BUF_BYTES;
     const SPH_LDS unsigned char* mk_own = smem + MKLDS + (wave * NK * 16 + n16) * 4;
     auto mk = [&](int kb) { return MULT ? lds_read_f32(mk_own + kb * 64) : 1.f; };
+    if constexpr (MULT) {
 #pragma unroll
-    for (int kb = 0; kb < NK; ++kb) {
-        int row = k0 + kb * 16 + n16;
-        row = row < N ? row : N - 1;               // keys past the end are computed and dropped
-        if constexpr (MULT)
+        for (int kb = 0; kb < NK; ++kb) {
+            int row = k0 + kb * 16 + n16;
+            row = row < N ? row : N - 1;
             *reinterpret_cast<SPH_LDS float*>(smem + MKLDS + (wave * NK * 16 + kb * 16 + n16) * 4) = mult[(size_t)bidx * N + row];
-        const size_t off = (head_off + (size_t)row * D) * 2 + 16 * g;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            kf[kb][kk] = *reinterpret_cast<const i32x4*>((const unsigned char*)Kv + off + kk * 64);
-            vf[kb][kk] = *reinterpret_cast<const i32x4*>((const unsigned char*)Vv + off + kk * 64);
         }
     }
     f32x4 dk[DB][NK], dv[DB][NK];
@@ -371,10 +413,46 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
     const int last = PART ? min(kv_group * n_tiles, first + tiles_per_split) : kv_group * n_tiles;
     int next_hq = PART ? first / n_tiles : 0, next_tile = PART ? first % n_tiles : 0;   // head and tile of the copies issued in iteration j
     {
-        const HeadSource hs = head_source(next_hq);
-        copy_planes(hs, next_tile, lds0);
+        // Own keys (lane: key k0 + 16kb + n16, elements 32kk + 8g .. +7) through LDS, like the dQ kernel's rows:
+        // pieces of 16 keys of K or V as block copies, wave-private, two slots in tile buffer 1; then
+        // the first streamed tile.  Keys past the end arrive as zeros and are dropped.
+        constexpr int PIECE = KBLK * 1024;
+        static_assert(kWaves * 2 * PIECE <= BUF_BYTES, "the pieces fit tile buffer 1");
+        const uint32_t slots = BUF_BYTES + wave_u * 2 * PIECE;
+        const i32x4 own_rw[2] = {rsrc_words((const unsigned char*)Kv + head_off * 2, (uint32_t)N * ROWB),
+                                 rsrc_words((const unsigned char*)Vv + head_off * 2, (uint32_t)N * ROWB)};
+        const int own_lane = (lane >> 2) * ROWB + block_piece_in_slot(lane) * 16;
+        auto copy_own = [&](int p) {
 #pragma unroll
-        for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(hs, piece, next_tile, lds0);
+            for (int c = 0; c < KBLK; ++c)
+                copy_to_lds(own_rw[p & 1], lds0 + slots + (p & 1) * PIECE + c * 1024, own_lane,
+                            (kt * BKEYS + (int)(wave_u * NK + (p >> 1)) * 16) * ROWB + c * 64);
+        };
+        const HeadSource hs = head_source(next_hq);
+        copy_own(0);
+        copy_own(1);
+#pragma unroll
+        for (int p = 0; p < 2 * NK; ++p) {
+            if (p == 2 * NK - 1) {
+                copy_planes(hs, next_tile, lds0);
+#pragma unroll
+                for (int piece = 0; piece < 2 * KBLK; ++piece) copy_piece(hs, piece, next_tile, lds0);
+            }
+            // piece p has landed; what was asked for after it (a piece, or the tile) may be under way
+            asm volatile("" ::: "memory");
+            if (p < 2 * NK - 1) __builtin_amdgcn_s_waitcnt(0x0F70 | KBLK);
+            else __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * KBLK));
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) {
+                const i32x4 x = lds_read_b128(smem + slots + (p & 1) * PIECE + kk * 1024 + block_piece_offset(n16, g));
+                if (p & 1) vf[p >> 1][kk] = x;
+                else kf[p >> 1][kk] = x;
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): read before the slot is overwritten
+            if (p + 2 < 2 * NK) copy_own(p + 2);
+        }
     }
     for (int j = 0; j < last - first; ++j) {
         const uint32_t cur = (j & 1) * BUF_BYTES;

@@ -113,6 +113,12 @@ __device__ __forceinline__ void copy_to_lds(i32x4 rsrc, uint32_t lds, int voff, 
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+// non-temporal (past the L2's retention)
+__device__ __forceinline__ void copy_to_lds_nt(i32x4 rsrc, uint32_t lds, int voff, int soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
 
 // The same with 4 bytes per lane: 256 bytes per wave instruction, lane l landing at LDS byte
 // lds + 4 l.  For the per-key and per-query fp32 rows that travel with a tile (64 values): every
@@ -226,31 +232,6 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // retention (non-temporal), so that what stays in the XCD's L2 between batches of workgroups
     // is the K/V stream (measured: with ordinary loads and stores the 2 MB of O and 2 MB of Q that
     // 32 workgroups move at a batch boundary flush a 4 MB L2 completely).
-    // ---- Q fragments (B operands of S^T = K Q^T), held for the whole kernel: lane holds
-    // Q[q0 + 16qb + n16][k-slots of group g].  fp8 with d = 64 fills half of the k = 128 of
-    // the instruction: the upper 16 k-slots of every lane hold zeros on both sides.
-    constexpr int QREGS = FP8 ? 8 : 4;
-    constexpr int QSTEPS = FP8 ? 1 : KK;
-    typedef __attribute__((ext_vector_type(QREGS))) int qfrag_t;
-    qfrag_t qf[NQ][QSTEPS];
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-        int row = q0 + qb * 16 + n16;
-        row = row < Nq ? row : Nq - 1;             // rows past the end are computed and dropped
-        const unsigned char* src = Qh + (size_t)row * KROWB + 16 * g;
-#pragma unroll
-        for (int kk = 0; kk < QSTEPS; ++kk) {
-            if constexpr (FP8) {
-                const i32x4 lo = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(src));
-                i32x4 hi = {0, 0, 0, 0};
-                if constexpr (D == 128) hi = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(src + 64));
-                qf[qb][kk] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            } else {
-                qf[qb][kk] = __builtin_nontemporal_load(reinterpret_cast<const i32x4*>(src + kk * 64));
-            }
-        }
-    }
-
     f32x4 oacc[DB][NQ];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -301,19 +282,59 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
             copy_to_lds_b32(mrw, base + MLDS, lane * 4, tile * BC * 4);
     };
 
-    // ---- prologue: buffer 3 plays "tile -1" (zeros) for the first stage C; tiles 0 and 1 go
-    // to buffers 0 and 1
+    // ---- prologue.  Tiles 0 and 1 go to buffers 0 and 1; Q comes through buffers 2 and 3, each wave's rows
+    // in a region of its own, as 1 KB block copies in K's block format (straight into registers, an
+    // instruction's 64 lanes touch 16 rows and Q arrives at 16 bytes per cycle and CU: 1.9 us for the
+    // 64 KB of d = 128; copied, at twice that).
+    constexpr int QWAVE = 16 * NQ * KROWB;
+    static_assert(kWaves * QWAVE <= 2 * BUF_BYTES, "Q fits buffers 2 and 3");
+    const i32x4 qrw = rsrc_words(Qh, (uint32_t)Nq * KROWB);   // rows past the last query arrive as zeros
+    const uint32_t qlds = 2 * BUF_BYTES + wave_u * QWAVE;
+    const int qld_lane = (lane >> 2) * KROWB + block_piece_in_slot(lane) * 16;
+#pragma unroll
+    for (int c = 0; c < NST; ++c) copy_chunk(c, 0, smem);
+#pragma unroll
+    for (int c = 0; c < NQ * KBLK; ++c)
+        copy_to_lds_nt(qrw, (uint32_t)(uintptr_t)smem + qlds + c * 1024, qld_lane,
+                       (qt * tile_rows + row_off + (int)wave_u * 16 * NQ + c / KBLK * 16) * KROWB + c % KBLK * 64);
+#pragma unroll
+    for (int c = 0; c < NST; ++c) copy_chunk(c, 1, smem + BUF_BYTES);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | NST);      // this wave's share of tile 0 and its Q have landed
+    asm volatile("" ::: "memory");
+    // ---- Q fragments (B operands of S^T = K Q^T), held for the whole kernel: lane holds
+    // Q[q0 + 16qb + n16][k-slots of group g].  fp8 with d = 64 fills half of the k = 128 of
+    // the instruction: the upper 16 k-slots of every lane hold zeros on both sides.
+    constexpr int QREGS = FP8 ? 8 : 4;
+    constexpr int QSTEPS = FP8 ? 1 : KK;
+    typedef __attribute__((ext_vector_type(QREGS))) int qfrag_t;
+    qfrag_t qf[NQ][QSTEPS];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+        const SPH_LDS unsigned char* src = smem + qlds + qb * KBLK * 1024 + block_piece_offset(n16, g);
+#pragma unroll
+        for (int kk = 0; kk < QSTEPS; ++kk) {
+            if constexpr (FP8) {
+                const i32x4 lo = lds_read_b128(src);
+                i32x4 hi = {0, 0, 0, 0};
+                if constexpr (D == 128) hi = lds_read_b128(src + 1024);
+                qf[qb][kk] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            } else {
+                qf[qb][kk] = lds_read_b128(src + kk * 1024);
+            }
+        }
+    }
+    // every wave's share of tile 0 has landed, and every wave has read its Q
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // buffer 3 plays "tile -1" for the first stage C, which multiplies its second sub-step of V with P = 0
     {
         const i32x4 zero4 = {0, 0, 0, 0};
-        for (int i = tid; i < BUF_BYTES / 16; i += kThreads)
-            *reinterpret_cast<SPH_LDS i32x4*>(smem + (NBUF - 1) * BUF_BYTES + i * 16) = zero4;
+        for (int i = tid; i < VTILE / 32; i += kThreads)
+            *reinterpret_cast<SPH_LDS i32x4*>(smem + (NBUF - 1) * BUF_BYTES + KLDS + VTILE / 2 + i * 16) = zero4;
     }
-#pragma unroll
-    for (int t = 0; t < NBUF - 2; ++t)
-#pragma unroll
-        for (int c = 0; c < NST; ++c) copy_chunk(c, t, smem + t * BUF_BYTES);
-    __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wave's copies have landed
-    __syncthreads();
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) mload(kb, smem, 0);
 
@@ -401,6 +422,11 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     SPH_LDS unsigned char* bcur = smem;
     SPH_LDS unsigned char* bnxt = smem + BUF_BYTES;
     SPH_LDS unsigned char* bnn = smem + 2 * BUF_BYTES;
+    // the zeros are there for every wave
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int u = 0; u < PD; ++u) issue_reads(u, bprv, bcur, bnxt);
 
