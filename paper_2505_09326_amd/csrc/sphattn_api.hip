@@ -298,18 +298,20 @@ int launch_pipelined(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-template <int D, bool MULT, bool PARTIAL = false>
+// ROWS query rows per workgroup: 32 (four waves) or 16
+template <int D, int ROWS, bool MULT, bool PARTIAL>
 int launch_f32(const Problem& p)
 {
-    constexpr int BR = 32;                         // the four waves split the key axis
-    constexpr int lds_bytes = kWaves * 2 * 32 * (D + 4) * 4;
-    auto kern = fwd_f32_kernel<D, MULT, PARTIAL>;
+    constexpr bool SMALL = ROWS == kF32SmallRows;
+    constexpr int waves = SMALL ? f32_small_waves<D>() : kWaves;
+    constexpr int lds_bytes = waves * 2 * 32 * (D + 4) * 4;
+    constexpr auto kern = SMALL ? fwd_f32_small_kernel<D, MULT, PARTIAL> : fwd_f32_kernel<D, MULT, PARTIAL>;
     static std::atomic<uint64_t> done{0};
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
-    const int n_qtiles = (p.Nq + BR - 1) / BR;
+    const int n_qtiles = (p.Nq + ROWS - 1) / ROWS;
     const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
     if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
-    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kThreads), lds_bytes, p.stream,
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(64 * waves), lds_bytes, p.stream,
                        (const float*)p.Q, (const float*)p.K, (const float*)p.V, (float*)p.O, p.mult, p.Z,
                        p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
                        p.n_splits, p.keys_per_split);
@@ -332,23 +334,23 @@ int launch_f32x3(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// fp32 storage has three workgroup shapes: 32 rows on the fp32 matrix instruction with the keys dealt
-// to the four waves (the least latency: the launches that cannot give every CU more than that), and 128
+// fp32 storage has four workgroup shapes: 16 or 32 rows on the fp32 matrix instruction with the keys dealt
+// to the waves (the least latency: the launches that cannot give every CU more than that), and 128
 // or 256 rows on six bf16 products.  Time of one round per 32-key tile, in us, as measured on launches
-// that fill a small and the whole part of the CUs (f): d = 128 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
-// 0.68, 1.1 to 1.3, 1.85 to 2.25.  Rounds times that picks the shape (8 heads of 4096 x 128: 704, 328
-// and 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 364, 551, 897;
-// 4 x 1000 x 128 52, 73, 119).  S slices: S times the items, 1 / S of the tiles.
+// that fill a small and the whole part of the CUs (f): d = 128 0.9, 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
+// 0.35, 0.68, 1.1 to 1.3, 1.85 to 2.25.  Rounds times that picks the shape (32, 128 and 256 rows: 8 heads of
+// 4096 x 128 704, 328, 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 352, 553,
+// 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
 struct F32Choice { int rows; double us; };
 F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d)
 {
     const double cus = (double)cu_count(), tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
     F32Choice best{32, 1e30};
-    for (const int rows : {32, 128, 256}) {
+    for (const int rows : {16, 32, 128, 256}) {
         const double items = (double)(heads * ((Nq + rows - 1) / rows) * S);
         const double f = items < cus ? items / cus : 1.0;
-        const double tau = d == 128 ? (rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
-                                    : (rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
+        const double tau = d == 128 ? (rows == 16 ? 0.9 : rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
+                                    : (rows == 16 ? 0.35 : rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
         const double us = __builtin_ceil(items / cus) * tiles * tau;
         if (us < best.us) best = F32Choice{rows, us};
     }
@@ -361,7 +363,7 @@ int launch_f32_any(const Problem& p)
     const int rows = choose_f32((long long)p.B * p.H, p.Nq, PARTIAL ? p.keys_per_split : p.Nk, p.n_splits, D).rows;
     if (rows == 128) return launch_f32x3<D, 1, MULT, PARTIAL>(p);
     if (rows == 256) return launch_f32x3<D, 2, MULT, PARTIAL>(p);
-    return launch_f32<D, MULT, PARTIAL>(p);
+    return rows == 16 ? launch_f32<D, 16, MULT, PARTIAL>(p) : launch_f32<D, 32, MULT, PARTIAL>(p);
 }
 
 template <int D>

@@ -206,7 +206,8 @@ __device__ __forceinline__ void store_tile(const SPH_LDS unsigned char* stage, _
 }
 
 // ---------------------------------------------------------------------------
-// fp32 Q/K/V/O kernel on the fp32 matrix instruction v_mfma_f32_32x32x2_f32.
+// fp32 Q/K/V/O kernel on the fp32 matrix instruction v_mfma_f32_32x32x2_f32, for launches that do not fill
+// the chip (larger ones: sphattn_f32.hpp).
 // Same mapping as above with k = 2 per instruction: lane l holds row/column
 // (l & 31) and k index (l >> 5), so accumulator register 4g+t of S^T (key
 // 8g + 4h + t) is directly the B operand of the k-step that pairs it with the
@@ -369,6 +370,176 @@ void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                 o4[t] = acc * inv;
             }
             if (row < Nq) *reinterpret_cast<f32x4*>(dst + 8 * g) = o4;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same for the smallest launches, 16 query rows per workgroup, on v_mfma_f32_16x16x4_f32:
+// lane (n16, g) owns query n16 and, in register t of a 16-key block, key 4g + t, which is the B operand of
+// the k-step that pairs it with V rows 4g + t of all four lane groups; V needs no transpose
+// (one scalar per lane).  The k-steps of a score take d = 16m + 4g + e, so that Q comes as 16-byte
+// loads and one 16-byte LDS read of K serves four of them.
+//
+// Half the rows and, at d = 64, where LDS holds eight waves' tiles, half the keys per wave: for one head
+// of 256 x 64 a wave spends 0.85 us on matrix instructions instead of 3.4.  One head of 256 x 64 11.4 us with
+// 32 rows, 6.5 with 16; of 256 x 128 20.6 / 10.6; 4 x 1000 x 64 27.3 / 15.7; 4 x 1000 x 128 52 / 33.  It
+// stages a tile for half the rows, so it loses where both shapes fill the CUs (2 x 4096 x 64 91 / 95,
+// 1 x 8192 x 128 352 / 467).
+// ---------------------------------------------------------------------------
+template <int D>
+constexpr int f32_small_waves() { return D == 64 ? 8 : 4; }
+constexpr int kF32SmallRows = 16;
+
+template <int D>
+constexpr int f32_small_lds_bytes() { return f32_small_waves<D>() * 2 * 32 * (D + 4) * 4; }
+
+// Nq, Nk, Zv, PARTIAL, n_splits and keys_per_split as in fwd_pipelined_kernel.
+template <int D, bool MULT, bool PARTIAL = false>
+__global__ __launch_bounds__(64 * f32_small_waves<D>(), 1)
+void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                    const float* __restrict__ V, float* __restrict__ O,
+                    const float* __restrict__ mult, float* __restrict__ Zv,
+                    int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg,
+                    int n_splits, int keys_per_split)
+{
+    constexpr int W = f32_small_waves<D>();
+    constexpr int BC = 32;                         // keys per tile
+    constexpr int ROWF = D + 4;                    // padded row, in floats: conflict-free columns
+    constexpr int TILE_F = BC * ROWF;
+    constexpr int WAVE_F = 2 * TILE_F;             // K tile then V tile, private to a wave
+    constexpr int DB = D / 16, M = D / 16;
+    constexpr int LD = BC * D / 4 / 64;            // float4 loads per lane per tensor per tile
+    constexpr int PART = (DB * 4 + 1) * 64;        // a wave's partial: DB float4 per lane, then z
+    static_assert(W * PART <= W * WAVE_F, "partials fit the staging space");
+
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    SPH_LDS float* smem = (SPH_LDS float*)smem_raw;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int n16 = lane & 15, g = lane >> 4;
+    const int lid = xcd_contiguous_id(blockIdx.x, n_wg);
+    const int qt = lid % n_qtiles;
+    const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
+    const int bh = PARTIAL ? lid / (n_qtiles * n_splits) : lid / n_qtiles;
+    const int bidx = bh / H;
+    const int k0 = PARTIAL ? split * keys_per_split : 0;
+    const int N = PARTIAL ? min(Nk - k0, keys_per_split) : Nk;      // keys k0 .. k0 + N - 1
+    const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
+    const float* Kh = K + kv_off;
+    const float* Vh = V + kv_off;
+    const float* mrow = MULT ? mult + (size_t)bidx * Nk + k0 : nullptr;
+    const int q0 = qt * kF32SmallRows;
+
+    SPH_LDS float* kb_ = smem + wave * WAVE_F;
+    SPH_LDS float* vb_ = kb_ + TILE_F;
+    f32x4 kreg[LD], vreg[LD];
+    auto load_tile = [&](int j0) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int id = lane + i * 64;
+            const int r = id / (D / 4), c = id % (D / 4);
+            if (j0 + r < N) {
+                kreg[i] = *reinterpret_cast<const f32x4*>(Kh + (size_t)(j0 + r) * D + 4 * c);
+                vreg[i] = *reinterpret_cast<const f32x4*>(Vh + (size_t)(j0 + r) * D + 4 * c);
+            } else {                               // zero keys add nothing to o or z
+                kreg[i] = f32x4{0, 0, 0, 0};
+                vreg[i] = f32x4{0, 0, 0, 0};
+            }
+        }
+    };
+    auto store_tile = [&]() {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int id = lane + i * 64;
+            const int r = id / (D / 4), c = id % (D / 4);
+            *reinterpret_cast<SPH_LDS f32x4*>(kb_ + r * ROWF + 4 * c) = kreg[i];
+            *reinterpret_cast<SPH_LDS f32x4*>(vb_ + r * ROWF + 4 * c) = vreg[i];
+        }
+    };
+
+    const int n_tiles = (N + BC - 1) / BC;
+    if (wave < n_tiles) load_tile(wave * BC);
+    // Q as B operand of S^T = K Q^T: lane holds Q[q0 + n16][16m + 4g + e]
+    f32x4 qf[M];
+    {
+        int row = q0 + n16;
+        row = row < Nq ? row : Nq - 1;             // rows past the end are computed and dropped
+        const float* src = Q + ((size_t)bh * Nq + row) * D + 4 * g;
+#pragma unroll
+        for (int m = 0; m < M; ++m) qf[m] = *reinterpret_cast<const f32x4*>(src + 16 * m);
+    }
+    f32x4 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float z = 0.f;
+
+    for (int jt = wave; jt < n_tiles; jt += W) {
+        // LDS executes one wave's operations in order: the reads of the previous tile are done
+        // before these writes land, and the reads below see them
+        store_tile();
+        if (jt + W < n_tiles) load_tile((jt + W) * BC);
+        // S^T: two blocks of 16 keys x 16 queries
+        f32x4 s[2] = {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}};
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            f32x4 kf[2];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+                kf[kb] = *reinterpret_cast<const SPH_LDS f32x4*>(kb_ + (16 * kb + n16) * ROWF + 16 * m + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], qf[m][e], s[kb], 0, 0, 0);
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if constexpr (MULT) {              // s_ij = m_j (q_i . k_j); keys past N are zero
+                    const int key = jt * BC + 16 * kb + 4 * g + t;
+                    s[kb][t] *= key < N ? mrow[key] : 0.f;
+                }
+                z = __builtin_fmaf(s[kb][t], s[kb][t], z);
+            }
+        // O^T (D x 16 queries) += V^T S^T: the k-step of register t of block kb takes keys 16 kb + 4g + t
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    oacc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb_[(16 * kb + 4 * g + t) * ROWF + db * 16 + n16], s[kb][t], oacc[db], 0, 0, 0);
+    }
+
+    // ---- add the waves' partial (o, z): block db of wave w at part[w][db][lane], z at part[w][DB][lane]
+    __syncthreads();                               // every wave is done with its staging space
+    SPH_LDS float* part = smem;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) *reinterpret_cast<SPH_LDS f32x4*>(part + wave * PART + db * 256 + lane * 4) = oacc[db];
+    part[wave * PART + DB * 256 + lane] = z;
+    __syncthreads();
+
+    // wave w finishes the output blocks w, w + W, ... (16 columns of the head dimension each)
+    if (wave < DB) {
+        float zt = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) zt += part[w * PART + DB * 256 + lane];
+        zt += __shfl_xor(zt, 16);
+        zt += __shfl_xor(zt, 32);
+        const float inv = PARTIAL ? 1.f : zt > 0.f ? 1.0f / __builtin_sqrtf(zt) : 0.f;
+        const int row = q0 + n16;
+        // partial: the fp32 pair (o, z) of this key slice, slice-major
+        const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq
+                                     : (size_t)bh * Nq;
+        if (wave == 0 && g == 0 && row < Nq && (PARTIAL || Zv != nullptr)) Zv[rows0 + row] = zt;
+        for (int db = wave; db < DB; db += W) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < W; ++w) acc += *reinterpret_cast<const SPH_LDS f32x4*>(part + w * PART + db * 256 + lane * 4);
+            if (row < Nq) *reinterpret_cast<f32x4*>(O + (rows0 + row) * D + db * 16 + 4 * g) = acc * inv;
         }
     }
 }

@@ -1,5 +1,5 @@
-"""fp32 storage on three-part bf16 products (sphattn_f32.hpp), the shapes that choose it: 128- and
-256-row workgroups, ragged queries and keys, multiplicities, shared heads, accumulators.  The bound is
+"""fp32 storage: three-part bf16 products (sphattn_f32.hpp) in 128- and 256-row workgroups, and the fp32
+instruction in 16- and 32-row ones, on shapes that choose each: ragged queries and keys, multiplicities, shared heads, accumulators.  The bound is
 that of fp32 arithmetic itself, not the 1e-4 of the entry point: relative 2-norm error against 64 bits
 at most 3e-8 sqrt(N_k) / 4 + 2e-7, which the fp32 matrix instruction measures at (2.1e-7 at 256 keys,
 6.1e-7 at 4096) and which one missing low part (2^-17) or a rounded score would exceed tenfold."""
@@ -38,7 +38,10 @@ def _reference(q, k, v, mult):
 CASES = [(1, 9, 9, 4000, 33, 128, False, 1.0, 1.0), (1, 17, 17, 4097, 97, 128, True, 1.0, 1.0),
          (1, 12, 4, 3001, 700, 64, True, 1.0, 1.0), (2, 16, 16, 2100, 1025, 64, False, 1.0, 1.0),
          (1, 8, 8, 2049, 1, 128, False, 1.0, 1.0), (1, 8, 8, 4096, 4100, 128, False, 1e15, 1e-20),
-         (1, 16, 16, 4096, 640, 128, False, 1e-12, 1e30)]
+         (1, 16, 16, 4096, 640, 128, False, 1e-12, 1e30),
+         # 16 rows: one tile, fewer tiles than waves, several per wave; 32 rows: between 4096 and 8192 rows
+         (1, 1, 1, 1, 33, 64, False, 1.0, 1.0), (2, 4, 2, 100, 333, 64, True, 1.0, 1.0), (1, 3, 3, 257, 130, 128, True, 1.0, 1.0),
+         (1, 2, 1, 17, 600, 128, False, 1.0, 1.0), (1, 5, 5, 1400, 70, 64, True, 1.0, 1.0), (1, 5, 5, 1399, 40, 128, False, 1.0, 1.0)]
 
 
 @pytest.mark.parametrize("B,H,H_kv,Nq,Nk,d,with_mult,sq,sv", CASES)
