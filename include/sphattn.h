@@ -355,10 +355,10 @@ int sphattn_grn_bwd_split(const void* Q, const void* K, const void* V, const flo
  *   O        : device, [B,H,N,d] bfloat16, written by the call, must not overlap the inputs.
  *   workspace: device scratch owned by the caller, 16-byte aligned, at least
  *              sphattn_fp8_workspace_bytes(B, H_kv, N, d) bytes (a transposed copy of V padded
- *              to whole 128-key tiles, and the largest key norm of every K/V head); overwritten by the
+ *              to whole 128-key tiles, and the largest key norms of every K/V head); overwritten by the
  *              call, must not overlap Q, K, V or O.  A NULL, misaligned or short workspace
  *              returns SPHATTN_ERR_WORKSPACE.  Calls that share a workspace must be ordered.
- * Three launches on `stream` (clear, prepare, attention); no allocation, no synchronisation.
+ * Two or three launches on `stream` ((clear,) prepare, attention); no allocation, no synchronisation.
  * Other errors as sphattn_fwd.  sphattn_fp8_workspace_bytes returns 0 for an invalid shape.
  */
 size_t sphattn_fp8_workspace_bytes(int B, int H_kv, int N, int d);

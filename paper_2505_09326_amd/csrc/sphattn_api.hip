@@ -393,7 +393,8 @@ int launch_softmax32(const Problem& p)
 //             Not for fp8 Q/K at d = 128, whose score instruction needs four query blocks a slot.
 //   128 rows: 4 x 8192 x 128 103 against 151 of 256 rows, 1 x 32768 x 128 378 against 529; at d = 64, where
 //             two fit a CU, up to one and a half per CU (5 x 8192 x 64, 320 workgroups, 84 against 88 us,
-//             7 x 8192, 448, 95 against 94, 12 x 5003 fp16, 480, 66 against 63).
+//             7 x 8192, 448, 95 against 94, 12 x 5003 fp16, 480, 66 against 63); fp8 Q/K, which spills there, one
+//             and a quarter (28 x 1555 x 64, 364, 21.4 against 21.0).
 // With more items than that they take two rounds and lose (5 x 8192 x 128, 160 tiles of 256 rows: 152 against
 // 136 us): a partly filled single round costs less than its share of idle CUs suggests, because the
 // part is power-bound and idle CUs give their share of the budget to the rest.
@@ -402,7 +403,7 @@ int rows_per_workgroup(long long heads, long long Nq, long long n_splits, int d,
     const long long cus = cu_count(), slices = heads * n_splits;
     if (slices * ((Nq + 255) / 256) >= cus) return 256;
     if (!(fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
-    return slices * ((Nq + 127) / 128) <= (d == 64 ? cus * 3 / 2 : cus) ? 128 : 256;
+    return slices * ((Nq + 127) / 128) <= (d == 128 ? cus : fp8 ? cus * 5 / 4 : cus * 3 / 2) ? 128 : 256;
 }
 
 template <int D, QKType QKT, bool MULT, bool PARTIAL>
@@ -594,7 +595,7 @@ int launch_fp8(const void* Q, const void* K, const unsigned char* VT, const floa
     const long long n_wg = (long long)B * H * n_qtiles;
     hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kThreads), lds_bytes, st,
                        (const unsigned char*)Q, (const unsigned char*)K, VT, kmax, mult, (unsigned short*)O,
-                       N, H, H / H_kv, n_tiles, n_qtiles, (int)n_wg, stream_period(kern, lds_bytes, period));
+                       N, H, H / H_kv, n_tiles, n_qtiles, (int)n_wg, stream_period(kern, lds_bytes, period), fp8_chunks((long long)B * H_kv, n_tiles));
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
@@ -630,17 +631,20 @@ int fp8_forward(const void* Q, const void* K, const void* V, const float* mult, 
     if ((long long)heads * n_tiles > 0x7fffffff) return SPHATTN_ERR_SHAPE;
     if ((long long)B * H * ((N + 255) / 256) > 0x7fffffff) return SPHATTN_ERR_SHAPE;
     if ((unsigned __int128)d * n_tiles * kFp8Tile > 0x7fffffff) return SPHATTN_ERR_SHAPE;   // one head of V^T: a 32-bit range
-    // three launches; the attention kernel's attribute (the one thing that can fail without a
+    // two or three launches; the attention kernel's attribute (the one thing that can fail without a
     // launch) is set by its launcher before it enqueues anything, so a refusal there leaves the
     // workspace written and nothing else
-    hipLaunchKernelGGL(fp8_clear_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, kmax, heads);
-    if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
-    if (d == 128)
-        hipLaunchKernelGGL(fp8_prepare_kernel<128>, dim3((unsigned)(heads * n_tiles)), dim3(256), 0, st,
-                           (const unsigned char*)K, (const unsigned char*)V, mult, VT, kmax, N, n_tiles, H_kv);
-    else
-        hipLaunchKernelGGL(fp8_prepare_kernel<64>, dim3((unsigned)(heads * n_tiles)), dim3(256), 0, st,
-                           (const unsigned char*)K, (const unsigned char*)V, mult, VT, kmax, N, n_tiles, H_kv);
+    const int n_chunks = fp8_chunks(heads, n_tiles);
+    if (n_chunks == 0) {
+        hipLaunchKernelGGL(fp8_clear_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, kmax, heads);
+        if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
+    }
+    const long long prep_wg = (long long)heads * (n_tiles + n_chunks);
+    if (prep_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
+    auto prepare = d == 128 ? (n_chunks ? fp8_prepare_kernel<128, true> : fp8_prepare_kernel<128, false>)
+                            : (n_chunks ? fp8_prepare_kernel<64, true> : fp8_prepare_kernel<64, false>);
+    hipLaunchKernelGGL(prepare, dim3((unsigned)prep_wg), dim3(256), 0, st,
+                       (const unsigned char*)K, (const unsigned char*)V, mult, VT, kmax, N, n_tiles, H_kv, heads, n_chunks);
     if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
     if (d == 128) {
         if (softmax) return launch_fp8<128, true, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);

@@ -66,17 +66,84 @@ namespace sphattn {
 
 constexpr int kFp8Tile = 128;          // keys per tile (one k of the second contraction)
 
-// ---- preparation: V^T copy and the largest key norm per K/V head -------------------------
+// ---- preparation: V^T copy and the largest key norms of every K/V head -----------------------
 //
-// grid = (heads) x (tiles of 128 keys).  VT[head][c][Np] (E4M3, Np = tiles * 128, zero past
-// N) receives V transposed; kmax[head] receives max_j |k_j| through an integer atomic max on
-// the bits of the non-negative float (kmax must be zero before the launch).  With multiplicities
-// (mult [B, N], heads_per_batch K/V heads per batch entry) the norm of key j counts mult_j times.
-template <int D>
+// heads x n_tiles workgroups transpose V: VT[head][c][Np] (E4M3, Np = tiles * 128, zero past N), a tile of 128
+// keys each.  The largest |k_j| of a head (with multiplicities, mult [B, N], heads_per_batch K/V heads per
+// batch entry, the norm of key j counts |mult_j| times) is found in one of two ways:
+//   n_chunks > 0  heads x n_chunks more workgroups, in front, take a chunk of a head's keys each and write the
+//                 largest norm among them to kmax[head][chunk]; the forward kernel takes the largest of a
+//                 head's chunks.  No launch to clear anything: 8 heads on 4 of 8000 x 128 with
+//                 multiplicities 115.7 us with the other way, 113.3 with this.
+//   n_chunks = 0  the transposing workgroups take their own tile's keys and an integer atomic max on the bits
+//                 of the non-negative float gathers kmax[head], which a launch before has cleared.
+// The workspace has room for one float per head and what rounding that up to 256 bytes leaves, so many
+// heads of many keys would get one long chunk each: 64 heads of 16384 x 128 106 us for the preparation against 89
+// with atomics.  Chunks of at most 1024 keys take no longer than the transposition beside them (6 us).
+constexpr int kFp8MaxChunks = 64;      // chunks per head at most: one lane each in the forward kernel
+constexpr int kFp8ChunkKeys = 1024;    // keys per chunk at most
+
+// chunks per head, or 0 for the atomic way
+inline int fp8_chunks(long long heads, int n_tiles)
+{
+    const long long fit = ((heads * 4 + 255) / 256 * 64) / heads;
+    long long c = fit < kFp8MaxChunks ? fit : kFp8MaxChunks;
+    c = c < n_tiles ? c : n_tiles;
+    return (n_tiles + c - 1) / c * kFp8Tile <= kFp8ChunkKeys ? (int)c : 0;
+}
+
+// The largest |k_j| (times |mult_j|) of keys first .. last - 1, in thread 0; two threads per key, `U` times
+// 128 keys in flight (U = 1: at most 128 keys).
+template <int D, int U>
+__device__ __forceinline__ float largest_key_norm(const unsigned char* __restrict__ Kh, const float* __restrict__ mrow,
+                                                  int first, int last, float (&wmax)[4])
+{
+    const int tid = threadIdx.x;
+    float best = 0.f;
+    auto take = [&](int base) {
+        i32x4 w[U][D / 32];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = base + u * kFp8Tile + (tid >> 1);
+#pragma unroll
+            for (int c = 0; c < D / 32; ++c)
+                w[u][c] = row < last ? *reinterpret_cast<const i32x4*>(Kh + (size_t)row * D + (D / 2) * (tid & 1) + 16 * c) : i32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = base + u * kFp8Tile + (tid >> 1);
+            float ss = 0.f;
+#pragma unroll
+            for (int c = 0; c < D / 32; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float a = __builtin_amdgcn_cvt_f32_fp8(w[u][c][r], 0), b = __builtin_amdgcn_cvt_f32_fp8(w[u][c][r], 1);
+                    const float c2 = __builtin_amdgcn_cvt_f32_fp8(w[u][c][r], 2), e = __builtin_amdgcn_cvt_f32_fp8(w[u][c][r], 3);
+                    ss += a * a + b * b + c2 * c2 + e * e;
+                }
+            ss += __shfl_xor(ss, 1);
+            if (mrow != nullptr && row < last) {
+                const float m = mrow[row];
+                ss *= m * m;
+            }
+            best = fmaxf(best, ss);
+        }
+    };
+    if constexpr (U == 1) take(first);             // one tile: no loop, so that its loads go out with the caller's
+    else
+        for (int base = first; base < last; base += U * kFp8Tile) take(base);
+#pragma unroll
+    for (int m = 2; m < 64; m <<= 1) best = fmaxf(best, __shfl_xor(best, m));
+    if ((tid & 63) == 0) wmax[tid >> 6] = best;
+    __syncthreads();
+    return __builtin_sqrtf(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3])));
+}
+
+template <int D, bool CHUNKS>
 __global__ __launch_bounds__(256)
 void fp8_prepare_kernel(const unsigned char* __restrict__ K, const unsigned char* __restrict__ V,
                         const float* __restrict__ mult, unsigned char* __restrict__ VT,
-                        float* __restrict__ kmax, int N, int n_tiles, int heads_per_batch)
+                        float* __restrict__ kmax, int N, int n_tiles, int heads_per_batch, int n_heads, int n_chunks)
 {
     // rows of D + 4 bytes: the 16 rows that one output piece gathers from then start in different
     // banks (with a 16-byte-aligned stride they would all start in the same bank)
@@ -84,11 +151,21 @@ void fp8_prepare_kernel(const unsigned char* __restrict__ K, const unsigned char
     __shared__ __attribute__((aligned(16))) unsigned char tile[T * LROW];
     __shared__ float wmax[4];
     const int tid = threadIdx.x;
-    const int head = blockIdx.x / n_tiles, kt = blockIdx.x % n_tiles;
+    const int n_norm = CHUNKS ? n_heads * n_chunks : 0;
+    if (CHUNKS && (int)blockIdx.x < n_norm) {
+        const int head = blockIdx.x / n_chunks, chunk = blockIdx.x % n_chunks;
+        const int per = (n_tiles + n_chunks - 1) / n_chunks * T;
+        const int first = chunk * per, last = min(N, first + per);
+        const float m = largest_key_norm<D, 2>(K + (size_t)head * N * D, mult != nullptr ? mult + (size_t)(head / heads_per_batch) * N : nullptr,
+                                               first, last, wmax);
+        if (tid == 0) kmax[blockIdx.x] = m;
+        return;
+    }
+    const int blk = blockIdx.x - n_norm;
+    const int head = blk / n_tiles, kt = blk % n_tiles;
     const int key0 = kt * T;
     const size_t Np = (size_t)n_tiles * T;
     const unsigned char* Vh = V + (size_t)head * N * D;
-    const unsigned char* Kh = K + (size_t)head * N * D;
 
     for (int id = tid; id < T * (D / 16); id += 256) {
         const int row = id / (D / 16), c16 = id % (D / 16);
@@ -97,36 +174,12 @@ void fp8_prepare_kernel(const unsigned char* __restrict__ K, const unsigned char
 #pragma unroll
         for (int r = 0; r < 4; ++r) *reinterpret_cast<int*>(tile + row * LROW + 16 * c16 + 4 * r) = v[r];
     }
-    // |k_j|^2 of row tid/2, half tid%2 of the row
-    float ss = 0.f;
-    {
-        const int row = tid >> 1, half = tid & 1;
-        if (key0 + row < N) {
-            const unsigned char* src = Kh + (size_t)(key0 + row) * D + (D / 2) * half;
-#pragma unroll
-            for (int c = 0; c < D / 32; ++c) {
-                const i32x4 w = *reinterpret_cast<const i32x4*>(src + 16 * c);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float a = __builtin_amdgcn_cvt_f32_fp8(w[r], 0), b = __builtin_amdgcn_cvt_f32_fp8(w[r], 1);
-                    const float c2 = __builtin_amdgcn_cvt_f32_fp8(w[r], 2), e = __builtin_amdgcn_cvt_f32_fp8(w[r], 3);
-                    ss += a * a + b * b + c2 * c2 + e * e;
-                }
-            }
-        }
-        ss += __shfl_xor(ss, 1);
-        if (mult != nullptr && key0 + row < N) {
-            const float m = mult[(size_t)(head / heads_per_batch) * N + key0 + row];
-            ss *= m * m;
-        }
-#pragma unroll
-        for (int m = 2; m < 64; m <<= 1) ss = fmaxf(ss, __shfl_xor(ss, m));
-        if ((tid & 63) == 0) wmax[tid >> 6] = ss;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        const float m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-        atomicMax(reinterpret_cast<int*>(kmax + head), __float_as_int(__builtin_sqrtf(m)));
+    if constexpr (!CHUNKS) {
+        const float m = largest_key_norm<D, 1>(K + (size_t)head * N * D, mult != nullptr ? mult + (size_t)(head / heads_per_batch) * N : nullptr,
+                                               key0, min(N, key0 + T), wmax);
+        if (tid == 0) atomicMax(reinterpret_cast<int*>(kmax + head), __float_as_int(m));
+    } else {
+        __syncthreads();                           // (largest_key_norm has one)
     }
     // 16-byte pieces of V^T: column c of d, keys key0 + 16q .. +15
     unsigned char* VTh = VT + (size_t)head * D * Np;
@@ -172,7 +225,7 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
                     const unsigned char* __restrict__ VT, const float* __restrict__ kmax,
                     const float* __restrict__ mult,
                     unsigned short* __restrict__ O, int N, int H, int kv_group, int n_tiles, int n_qtiles, int n_wg,
-                    int stream_period)
+                    int stream_period, int n_chunks)
 {
     constexpr int BC = kFp8Tile, NQ = 4;
     constexpr int BR = kWaves * 16 * NQ;
@@ -235,7 +288,15 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     float qdiv[NQ];                                // 2^e_i: the scores of row i are divided by it on conversion
     float qshift[NQ];
     constexpr float kSoftmaxScaleLog2 = 1.4426950408889634f * (D == 128 ? 0.08838834764831845f : 0.125f);   // log2(e) / sqrt(d)
-    const float km = kmax[kvh];
+    // the head's largest key norm: the largest of its chunks', a lane each
+    float km;
+    if (n_chunks == 0) {
+        km = kmax[kvh];
+    } else {
+        km = lane < n_chunks ? kmax[kvh * n_chunks + lane] : 0.f;
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) km = fmaxf(km, __shfl_xor(km, m));
+    }
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         int row = q0 + qb * 16 + n16;
