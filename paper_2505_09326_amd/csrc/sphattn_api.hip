@@ -342,9 +342,9 @@ int launch_f32x3(const Problem& p)
 // 4096 x 128 704, 328, 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 352, 553,
 // 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
 struct F32Choice { int rows; double us; };
-F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d)
+F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d, long long n_cus)
 {
-    const double cus = (double)cu_count(), tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
+    const double cus = (double)n_cus, tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
     F32Choice best{32, 1e30};
     for (const int rows : {16, 32, 128, 256}) {
         const double items = (double)(heads * ((Nq + rows - 1) / rows) * S);
@@ -360,7 +360,7 @@ F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, lo
 template <int D, bool MULT, bool PARTIAL>
 int launch_f32_any(const Problem& p)
 {
-    const int rows = choose_f32((long long)p.B * p.H, p.Nq, PARTIAL ? p.keys_per_split : p.Nk, p.n_splits, D).rows;
+    const int rows = choose_f32((long long)p.B * p.H, p.Nq, PARTIAL ? p.keys_per_split : p.Nk, p.n_splits, D, cu_count()).rows;
     if (rows == 128) return launch_f32x3<D, 1, MULT, PARTIAL>(p);
     if (rows == 256) return launch_f32x3<D, 2, MULT, PARTIAL>(p);
     return rows == 16 ? launch_f32<D, 16, MULT, PARTIAL>(p) : launch_f32<D, 32, MULT, PARTIAL>(p);
@@ -398,9 +398,9 @@ int launch_softmax32(const Problem& p)
 // With more items than that they take two rounds and lose (5 x 8192 x 128, 160 tiles of 256 rows: 152 against
 // 136 us): a partly filled single round costs less than its share of idle CUs suggests, because the
 // part is power-bound and idle CUs give their share of the budget to the rest.
-int rows_per_workgroup(long long heads, long long Nq, long long n_splits, int d, bool fp8)
+int rows_per_workgroup(long long heads, long long Nq, long long n_splits, int d, bool fp8, long long cus)
 {
-    const long long cus = cu_count(), slices = heads * n_splits;
+    const long long slices = heads * n_splits;
     if (slices * ((Nq + 255) / 256) >= cus) return 256;
     if (!(fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
     return slices * ((Nq + 127) / 128) <= (d == 128 ? cus : fp8 ? cus * 5 / 4 : cus * 3 / 2) ? 128 : 256;
@@ -410,7 +410,7 @@ template <int D, QKType QKT, bool MULT, bool PARTIAL>
 int launch_spherical(const Problem& p)
 {
     const int rows = p.tile_rows != 0 ? p.tile_rows
-                                      : rows_per_workgroup((long long)p.B * p.H, p.Nq, p.n_splits, D, QKT == QKType::Fp8);
+                                      : rows_per_workgroup((long long)p.B * p.H, p.Nq, p.n_splits, D, QKT == QKType::Fp8, cu_count());
     // a row's sums in the 256-row kernel's order, on the narrower form of that kernel (bf16 has one)
     if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
         if (p.one_key_order && rows < 256) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
@@ -740,15 +740,19 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
     // (fp32 also above one round, whose remainder cutting recovers: choose_f32 counts rounds;
     // 1 x 21694 x 128, 170 workgroups of 128 rows, 1464 us uncut, 951 in 3 slices of 256-row workgroups)
     const long long most = dtype == SPHATTN_F32 ? 4 * cus : cus;
-    for (long long S = 1; (S * items <= most || S == 1) && S <= tiles; ++S) {
-        const SplitPlan plan = plan_splits(Nk, (int)S);
-        if (plan.n_splits != S) continue;          // the same slices as a smaller count
+    long long last = 0;
+    // (every count up to 16, then in steps of an eighth: this runs on every call that may be cut)
+    for (long long want = 1; (want * items <= most || want == 1) && want <= tiles; want += want < 16 ? 1 : want / 8) {
+        const SplitPlan plan = plan_splits(Nk, (int)want);
+        const long long S = plan.n_splits;
+        if (S == last) continue;                   // the same slices as a smaller count
+        last = S;
         const double per = (double)(S == 1 ? tiles : plan.keys_per_split / kBC);
         double us;
         if (dtype == SPHATTN_F32) {
-            us = 6.0 + choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d).us;
+            us = 6.0 + choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d, cus).us;
         } else {
-            const int rows = rows_per_workgroup(heads, p.Nq, S, d, dtype == SPHATTN_FP8QK_BF16V);
+            const int rows = rows_per_workgroup(heads, p.Nq, S, d, dtype == SPHATTN_FP8QK_BF16V, cus);
             const double f = (double)(S * heads * ((p.Nq + rows - 1) / rows)) / (double)cus;
             const double tau = d == 128 ? (rows == 64 ? 0.40 + 0.08 * f : 0.55 + 0.17 * f)
                                         : (rows == 64 ? 0.25 + 0.03 * f : 0.36 + 0.08 * f);
@@ -779,7 +783,7 @@ long long choose_bwd_slices(long long items, int per_cu, long long tiles, double
     const long long cus = cu_count(), resident = cus * per_cu;
     long long best = 1;
     double best_us = 0.0;
-    for (long long S = 1; S <= 64 && (S == 1 || (tiles / S >= 4 && (size_t)S * part_bytes <= ((size_t)256 << 20))); ++S) {
+    for (long long S = 1; S <= 64 && (S == 1 || (tiles / S >= 4 && (size_t)S * part_bytes <= ((size_t)256 << 20))); S += S < 16 ? 1 : S / 8) {
         const long long per = (tiles + S - 1) / S, n = items * S, full = n / resident;
         const double f = (double)(n % resident) / (double)resident;
         double rounds;
