@@ -284,7 +284,7 @@ int launch_pipelined(const Problem& p)
                 hipLaunchKernelGGL(kern, dim3((unsigned)resident), dim3(kThreads), lds_bytes, p.stream,
                                    p.Q, p.K, p.V, p.O, p.mult, p.Z,
                                    p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
-                                   p.n_splits, p.keys_per_split, scale_log2, 0, n_main, 0);
+                                   p.n_splits, p.keys_per_split, scale_log2, 0, n_main);
                 if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
                 return launch_halves<D, QKT>(p, n_qtiles, (int)n_wg, n_main, full % 2 == 1, false) >= 0 ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
             }
@@ -294,7 +294,7 @@ int launch_pipelined(const Problem& p)
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds_bytes, p.stream,
                        p.Q, p.K, p.V, p.O, p.mult, p.Z,
                        p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
-                       p.n_splits, p.keys_per_split, scale_log2, 0, (int)n_wg, 0);
+                       p.n_splits, p.keys_per_split, scale_log2, 0, (int)n_wg);
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 

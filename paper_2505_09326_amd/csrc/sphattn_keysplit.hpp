@@ -37,7 +37,8 @@ constexpr int keysplit_lds_bytes()
     return kNBuf * kBC * (D * (QKT == QKType::Fp8 ? 1 : 2) + D * 2) + (MULT ? kSplitMultRing * kBC * 4 : 0);
 }
 
-// One work item; arguments as fwd_pipelined_item.
+// One work item; arguments as fwd_pipelined_item, and: query tiles are tile_rows apart (the workgroup's rows, or
+// twice as many when the item is one half, starting at row_off, of a wider tile).
 template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL>
 __device__ __forceinline__
 void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
