@@ -42,6 +42,14 @@ constexpr int f32_flags_at() { return 2 * 6 * kF32Tile * D * 2 + 2 * kF32Tile * 
 template <int D>
 constexpr int f32_lds_bytes() { return f32_flags_at<D>() + kF32Waves * 4; }
 
+// Byte of a head's K or V at which row `row` of tile `tile` starts.  Heads are at most 2^31 - 1 bytes (the entry
+// points refuse longer ones), which a tile past the last one may pass: such a tile is not asked for.
+template <int D>
+constexpr int f32_tile_byte(int tile, int row) { return (tile * kF32Tile + row) * D * 4; }
+constexpr int kF32MostKeys128 = 0x7fffffff / (128 * 4), kF32MostKeys64 = 0x7fffffff / (64 * 4);
+static_assert(f32_tile_byte<128>((kF32MostKeys128 - 1) / kF32Tile, kF32Tile - 1) > 0 &&
+              f32_tile_byte<64>((kF32MostKeys64 - 1) / kF32Tile, kF32Tile - 1) > 0, "offsets of the longest head's last tile fit");
+
 __device__ __forceinline__ uint32_t doubled_bits(float x) { return __builtin_bit_cast(uint32_t, x) << 1; }
 
 // The lanes whose x is subnormal.  (The compiler's form of this goes through a vector register.)
@@ -164,11 +172,13 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
     const i32x4 vrw = rsrc_words(V + kv_off, (uint32_t)N * D * 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
     const int ld_lane = (lane >> 3) * D * 4 + (lane & 7) * 16;
-    auto copy_tile = [&](int t) {
+    const int n_tiles = (N + BC - 1) / BC;
+    auto copy_tile = [&](int t) {                  // past the last tile: that one again, which nothing uses
+        const int tile = min(t, n_tiles - 1);
 #pragma unroll
         for (int u = 0; u < UPW; ++u) {
             const int idx = wave * UPW + u, in = idx % (4 * KK);   // row group in / KK, column group in % KK
-            copy_to_lds(idx < 4 * KK ? krw : vrw, lds0 + RAW + idx * 1024, ld_lane, (t * BC + in / KK * 8) * D * 4 + in % KK * 128);
+            copy_to_lds(idx < 4 * KK ? krw : vrw, lds0 + RAW + idx * 1024, ld_lane, f32_tile_byte<D>(tile, in / KK * 8) + in % KK * 128);
         }
     };
     uint64_t outside = 0;                          // lanes that met a value out of the parts' range
@@ -230,7 +240,6 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
     for (int qb = 0; qb < NQ; ++qb) zacc[qb][0] = zacc[qb][1] = 0.f;
 
     const __amdgpu_buffer_rsrc_t mrs = make_rsrc(MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, MULT ? (uint32_t)N * 4 : 0);
-    const int n_tiles = (N + BC - 1) / BC;
     wait_copies();
 #pragma unroll
     for (int u = 0; u < UPW; ++u) split_unit(u, 0);

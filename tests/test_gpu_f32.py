@@ -164,3 +164,28 @@ def test_fp32_product_is_good_to_a_rounding(pkg):
     err = ((o[..., 0].double() - exact) / exact).abs().max().item()
     print(f"  largest error {err:.2e}", flush=True)
     assert err <= 3 * 2.0 ** -24
+
+
+def test_fp32_longest_key_axis(pkg):
+    """4 194 303 keys of 128, the most that a head's 2^31 - 1 bytes hold: the byte offsets of the last tiles are
+    the largest there are.  Sampled rows against 64 bits (32 keys left out would show as 2.8e-3)."""
+    Nq, Nk, d = 16384, 0x7fffffff // 512, 128
+    print(f"case f32 longest Nq={Nq} Nk={Nk} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    q = torch.randn((1, 1, Nq, d), generator=g, device=DEV)
+    k, v = (torch.randn((1, 1, Nk, d), generator=g, device=DEV) for _ in range(2))
+    op, zp = pkg.sphattn_partial_fwd(q, k, v, dtype="f32")
+    torch.cuda.synchronize()
+    rows = torch.tensor([0, 1, 777, 8191, 16383], device=DEV)
+    o, z = torch.zeros((5, d), dtype=torch.float64, device=DEV), torch.zeros(5, dtype=torch.float64, device=DEV)
+    for i in range(0, Nk, 1 << 19):
+        S = q[0, 0, rows].double() @ k[0, 0, i:i + (1 << 19)].double().t().contiguous()
+        o += S @ v[0, 0, i:i + (1 << 19)].double()
+        z += (S * S).sum(-1)
+    # z: a lane adds the squares of Nk / 8 keys one after the other, half a rounding of the running sum each on the
+    # average over its growth at worst (they have one sign, so nothing averages out as it does in o)
+    bound, bound_z = 0.75e-8 * math.sqrt(Nk) + 2e-7, Nk / 8 * 2.0 ** -25
+    err_o = ((op[0, 0, rows].double() - o).norm() / o.norm()).item()
+    err_z = ((zp[0, 0, rows].double() - z).norm() / z.norm()).item()
+    print(f"  o rel {err_o:.2e} of {bound:.2e}, z rel {err_z:.2e} of {bound_z:.2e}", flush=True)
+    assert err_o <= bound and err_z <= bound_z
