@@ -205,9 +205,13 @@ int sphattn_combine(const float* o_parts, const float* z_parts, int n_parts, voi
 
 /*
  * sphattn_grn_fwd with the key axis cut into n_splits slices that run as separate workgroups
- * (sphattn_partial_fwd per slice, then sphattn_combine, in two launches; with one slice it is
- * sphattn_grn_fwd itself and the workspace is not touched).  It pays when B * H * N / 256 is
+ * (sphattn_partial_fwd per slice, then sphattn_combine, in two launches).  It pays when B * H * N / 256 is
  * below the number of workgroups the device runs at once, i.e. few heads of moderate length.
+ * One slice is one launch that does not touch the workspace: sphattn_grn_fwd itself where the library
+ * chose it (n_splits 0).  Asked for as n_splits = 1 with 16-bit or fp8 Q/K storage it is sphattn_grn_fwd itself too
+ * where that takes 256 query rows per workgroup; a smaller launch, for which sphattn_grn_fwd takes 64 or
+ * 128 rows and adds the two halves of every key tile separately, then adds every row's terms in
+ * the order of the 256-row workgroups (bit for bit sphattn_fwd_tile_rows with 256), which is slower.
  *
  *   n_splits       : slices asked for; 0 lets sphattn_splitkv_heuristic choose.  Slices are
  *                    whole 64-key tiles of equal size, so fewer than asked may be used (any

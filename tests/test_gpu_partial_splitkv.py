@@ -194,7 +194,8 @@ def test_splitkv_parity(pkg, oracle, B, H, H_kv, N, d, dtype, with_mult, n_split
 
 
 def test_splitkv_single_slice_equals_unsplit_call(pkg):
-    """One slice runs the same arithmetic in the same order as the unsplit 256-row kernel."""
+    """One slice asked for by name, on a launch below one round, runs the same arithmetic in the same
+    order as the unsplit 256-row kernel."""
     B, H, N, d = 1, 3, 900, 128
     q, k, v = (t.to(DEV) for t in si.make_qkv(B, H, N, d, "bf16", seed=1300))
     ws, _ = _workspace(pkg, B, H, N, d, 1)
@@ -202,6 +203,38 @@ def test_splitkv_single_slice_equals_unsplit_call(pkg):
     b, _ = pkg.sphattn_fwd_tile_rows(q, k, v, dtype="bf16", tile_rows=256)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("H,N,d,dtype", [(3, 900, 64, "bf16"), (2, 1999, 128, "f16"), (2, 700, 64, "fp8qk_bf16v"), (5, 450, 128, "fp8qk_bf16v")])
+def test_one_slice_below_a_round_keeps_the_order_of_256_rows(pkg, H, N, d, dtype):
+    """n_splits = 1 on launches that the plain call runs in 64- or 128-row workgroups."""
+    print(f"case one slice H={H} N={N} d={d} {dtype}", flush=True)
+    q, k, v = (t.to(DEV) for t in si.make_qkv(1, H, N, d, dtype, seed=1310 + N))
+    ws, _ = _workspace(pkg, 1, H, N, d, 1)
+    a = pkg.sphattn_splitkv_fwd(q, k, v, ws, n_splits=1, dtype=dtype)
+    b, _ = pkg.sphattn_fwd_tile_rows(q, k, v, dtype=dtype, tile_rows=256)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("H,H_kv,N,d,dtype,with_mult", [(66, 66, 1900, 64, "f16", False), (70, 35, 1850, 64, "bf16", False),
+                                                        (34, 34, 1900, 128, "bf16", False), (36, 12, 2000, 128, "f16", True)])
+def test_one_slice_from_a_round_on_is_the_plain_call(pkg, H, H_kv, N, d, dtype, with_mult):
+    """More 256-row tiles than CUs, a remainder behind a round of two per CU among them (half tiles), by name
+    and by the library's choice where that is one slice: the bits of sphattn_grn_fwd."""
+    print(f"case one slice H={H} H_kv={H_kv} N={N} d={d} {dtype}", flush=True)
+    q, _, _ = (t.to(DEV) for t in si.make_qkv(1, H, N, d, dtype, seed=1320 + N))
+    _, k, v = (t.to(DEV) for t in si.make_qkv(1, H_kv, N, d, dtype, seed=1330 + N))
+    mult = _mult(1, N, 1340).to(DEV) if with_mult else None
+    ws, _ = _workspace(pkg, 1, H, N, d, 1)
+    plain = pkg.sphattn_grn_fwd(q, k, v, mult, O=torch.empty_like(q), dtype=dtype)
+    chosen = [1] + ([0] if pkg.sphattn_splitkv_heuristic(1, H, N, d, dtype) == 1 else [])
+    for n_splits in chosen:
+        a = pkg.sphattn_splitkv_fwd(q, k, v, ws, mult=mult, n_splits=n_splits, dtype=dtype)
+        b = torch.empty_like(q)
+        pkg.sphattn_splitkv_fwd_noalloc(q, k, v, b, mult=mult, n_splits=n_splits, dtype=dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(a, plain) and torch.equal(b, plain)
 
 
 def test_splitkv_is_deterministic(pkg):
