@@ -288,16 +288,24 @@ def test_splitkv_few_heads_at_full_length(pkg, oracle):
 CROSS_SHAPES = [(1, 2, 2, 1, 700, 128, "bf16", False), (2, 4, 2, 300, 77, 64, "bf16", True),
                 (1, 2, 1, 513, 2049, 128, "f16", True), (1, 3, 3, 64, 1000, 64, "fp8qk_bf16v", False),
                 (2, 2, 1, 257, 130, 128, "f32", True), (1, 1, 1, 1000, 1, 64, "bf16", False),
-                # 528 query tiles of d = 64 for 512 resident workgroups, shared K/V heads: one full
-                # round, then the 16 remaining tiles as 128-row halves (the last ones half empty)
+                # 33 pairs of heads of 3800 rows, the two heads of a pair packed into one block: 495 tiles, just below
+                # the 512 of d = 64 that run at once
                 (1, 66, 33, 1900, 300, 64, "f16", False)]
+# More tiles than the 512, by at most half a round: one full round, then the remaining tiles as 128-row halves.
+# 66 heads of 8 tiles (528), whose last tiles have no second half; 35 pairs of heads packed into 15 tiles (525)
+# whose last tiles have a ragged second half (3800 rows) or none (3700)
+HALF_TILE_SHAPES = [(1, 66, 66, 1900, 300, 64, "f16", False), (1, 70, 35, 1900, 300, 64, "f16", False),
+                    (1, 70, 35, 1850, 130, 64, "f16", False), (1, 70, 35, 1900, 65, 64, "bf16", False)]
 
 
-@pytest.mark.parametrize("B,H,H_kv,Nq,Nk,d,dtype,with_mult", CROSS_SHAPES)
+@pytest.mark.parametrize("B,H,H_kv,Nq,Nk,d,dtype,with_mult", CROSS_SHAPES + HALF_TILE_SHAPES)
 def test_cross_forward_parity(pkg, oracle, B, H, H_kv, Nq, Nk, d, dtype, with_mult):
     """N_q query rows against N_k keys (sphattn_cross_fwd), with and without multiplicities and
     shared K/V heads; O and z against the oracle's accumulator followed by its tail."""
     print(f"case cross B={B} H={H} H_kv={H_kv} Nq={Nq} Nk={Nk} d={d} {dtype} mult={with_mult}", flush=True)
+    if (B, H, H_kv, Nq, Nk, d, dtype, with_mult) in HALF_TILE_SHAPES:    # heads that share K and V are one block of rows
+        assert 2 * torch.cuda.get_device_properties(DEV).multi_processor_count == 512
+        assert 512 < B * H_kv * -(-(H // H_kv * Nq) // 256) <= 768
     q, _, _ = si.make_qkv(B, H, Nq, d, dtype, seed=700 + Nq)
     _, k, v = si.make_qkv(B, H_kv, Nk, d, dtype, seed=800 + Nk)
     mult = None
