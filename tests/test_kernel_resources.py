@@ -84,6 +84,30 @@ def test_d128_forward_is_one_wave_per_simd_without_scratch(usage):
         assert _num(v, "VGPRs") + _num(v, "AGPRs") <= 512, name
 
 
+def test_key_split_forward(usage):
+    # the rule that picks 128 and 64 rows counts two workgroups per CU at d = 64; scratch only with fp8 Q/K
+    # there (20 to 56 bytes, written and read once per item)
+    for d, nq in ((128, 4), (128, 2), (64, 4), (64, 2)):
+        for qk in (0, 1, 2):
+            if (d, nq, qk) == (128, 2, 1):
+                continue                           # fp8 Q/K has no 64-row form there
+            for name, v in _find(usage, "fwd_keysplit_kernel", f"ILi{d}ELi{nq}ELNS_6QKTypeE{qk}E").items():
+                assert _num(v, "ScratchSize [bytes/lane]") <= (60 if (d, nq, qk) == (64, 4, 1) else 0), name
+                assert _num(v, "Occupancy [waves/SIMD]") >= (1 if (d, nq) == (128, 4) else 2), name
+
+
+def test_f32_kernels(usage):
+    # workgroups of eight waves, two per SIMD; at d = 64 in 128 rows two such workgroups per CU
+    for d, nq, waves in ((128, 1, 2), (128, 2, 2), (64, 1, 4), (64, 2, 2)):
+        for name, v in _find(usage, "fwd_f32x3_kernel", f"ILi{d}ELi{nq}E").items():
+            assert _num(v, "ScratchSize [bytes/lane]") == 0 and _num(v, "Occupancy [waves/SIMD]") >= waves, name
+    for d, waves in ((128, 1), (64, 2)):
+        for kernel in ("fwd_f32_kernel", "fwd_f32_small_kernel"):
+            for name, v in _find(usage, f"{kernel}ILi{d}E").items():
+                assert _num(v, "ScratchSize [bytes/lane]") == 0, name
+                assert _num(v, "Occupancy [waves/SIMD]") >= (waves if "small" in kernel else 1), name
+
+
 def test_backward_kernels(usage):
     # dK/dV: two workgroups per CU at d = 128, with and without multiplicities, (almost) no scratch
     for name, v in _find(usage, "bwd_dkv_kernelILi128E").items():
