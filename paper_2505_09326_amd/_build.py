@@ -17,6 +17,11 @@ HIPCC_FLAGS = [
     # allocator move long-lived accumulators/operands to AGPRs; without it every MFMA result
     # lands in AGPRs and the score registers must be copied out before the VALU can touch them
     "-mllvm", "-amdgpu-mfma-vgpr-form",
+    # Tile loops begin on an instruction cache line.  One wave per SIMD has nothing to cover the fetch behind the
+    # branch back, so where a loop happens to land counts: the d = 128 forward 4 bytes before the end of a line
+    # took 60 cycles more per tile (9 x 8192 x 128 272.8 us, 3 x 25243 x 128 811) than in the middle of one or at
+    # its start (265 and 790).
+    "-falign-loops=64",
     "-Wno-unused-command-line-argument",
 ]
 

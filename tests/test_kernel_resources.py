@@ -18,14 +18,15 @@ API = os.path.join(CSRC, "sphattn_api.hip")
 
 
 @pytest.fixture(scope="module")
-def usage(tmp_path_factory):
+def compiled(tmp_path_factory):
+    """The resource remarks by kernel, and the assembly."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not os.path.exists(hipcc):
         pytest.skip("no hipcc")
     flags = [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
-    out = tmp_path_factory.mktemp("res") / "dev.o"
+    out = tmp_path_factory.mktemp("res") / "dev.s"
     res = subprocess.run([hipcc, *flags, "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
-                          "-c", "-o", str(out), API], capture_output=True, text=True)
+                          "-S", "-o", str(out), API], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     kernels, cur = {}, None
     for line in res.stderr.splitlines():
@@ -40,7 +41,12 @@ def usage(tmp_path_factory):
             k, v = t.split(":", 1)
             kernels[cur][k.strip()] = v.strip()
     assert kernels, "no resource remarks in the compiler's output"
-    return kernels
+    return kernels, out.read_text()
+
+
+@pytest.fixture(scope="module")
+def usage(compiled):
+    return compiled[0]
 
 
 def _find(usage, *parts):
@@ -127,3 +133,23 @@ def test_all_e4m3_kernels(usage):
     # d = 64 without multiplicities: two workgroups per CU
     for name, v in _find(usage, "fwd_fp8_kernelILi64ELb0ELb0E").items():
         assert _num(v, "Occupancy [waves/SIMD]") >= 2 and _num(v, "ScratchSize [bytes/lane]") == 0, name
+
+
+def test_loops_begin_on_an_instruction_cache_line(compiled):
+    """A tile loop that lands just before the end of a line is 2.5 % slower in the d = 128 forward."""
+    lines = compiled[1].splitlines()
+    loops = 0
+    for i, line in enumerate(lines):
+        if not re.match(r"\.LBB\d+_\d+:", line):
+            continue
+        label, matrix = line.split(":")[0], 0
+        for x in lines[i + 1:]:
+            if re.match(r"\.LBB\d+_\d+:|\s*s_endpgm", x):
+                break
+            matrix += "v_mfma" in x
+            if re.match(r"\s*s_c?branch", x) and x.split()[-1] == label:   # back to the top: a loop of one stretch
+                if matrix >= 24:
+                    loops += 1
+                    assert re.search(r"\.p2align\s+6", lines[i - 1]), label
+                break
+    assert loops >= 40                             # the forward and backward kernels in all their forms
