@@ -788,9 +788,9 @@ long long choose_bwd_slices(long long items, int per_cu, long long tiles, double
         const double f = (double)(n % resident) / (double)resident;
         double rounds;
         if (full == 0) rounds = alone[per_cu - 1][(n + cus - 1) / cus - 1] * (n < cus ? 0.75 + 0.25 * (double)n / (double)cus : 1.0);
-        else rounds = (double)full + (f > 0.0 ? 0.85 + 0.15 * f : 0.0);
+        else rounds = (double)full + (f == 0.0 ? 0.0 : per_cu == 1 ? 0.85 + 0.15 * f : alone[per_cu - 1][(n % resident + cus - 1) / cus - 1]);
         const double us = rounds * ((double)per + 5.0) * tau + (S > 1 ? 2.0 + (double)S * part_us : 0.0);
-        if (S == 1) best_us = 0.95 * us;
+        if (S == 1) best_us = (full == 0 ? 0.95 : 0.98) * us;
         else if (us < best_us) { best_us = us; best = S; }
     }
     return best;

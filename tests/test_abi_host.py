@@ -371,3 +371,15 @@ def test_backward_split_argument_errors(lib):
     assert call(ws=0) == -9 and call(ws=0xB0000004) == -9 and call(size=need - 1) == -9
     for name in base:
         assert call(ws=base[name] or 0xB0000000, mult=0xB0000000) == -7       # the workspace is one of the arguments
+
+
+def test_backward_cuts_only_what_gains(lib):
+    """Above one round (256 CUs): dK/dV stays whole where the remainder puts a workgroup more on most CUs, each
+    alone there and done in half a round's time; shapes measured on both sides of the line."""
+    need = lambda *a: lib.sphattn_bwd_workspace_bytes(*a, 1)
+    for shape in ((1, 16, 16, 8192, 64), (1, 24, 24, 5200, 64), (3, 4, 4, 10066, 64), (2, 20, 20, 3300, 128)):
+        assert need(*shape) == 0, shape            # 2 to 5 % slower in slices
+    B, H, Hk, N, d = 1, 16, 16, 5200, 128          # dQ gains 4 % by two slices, dK/dV loses as much
+    assert need(B, H, Hk, N, d) == 2 * B * H * N * d * 4
+    for shape in ((1, 9, 9, 8192, 128), (1, 3, 3, 25243, 128), (1, 17, 17, 8192, 64), (1, 13, 13, 8192, 64), (1, 12, 12, 6000, 128)):
+        assert need(*shape) > 0, shape             # 4 to 20 % faster in slices
