@@ -459,13 +459,11 @@ int launch_combine(const float* o_parts, const float* z_parts, int n_parts, void
     const size_t threads = rows * (D / 4);
     const size_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return SPHATTN_ERR_SHAPE;
-    const dim3 grid((unsigned)blocks), block(256);
-    if (dtype == SPHATTN_F32)
-        hipLaunchKernelGGL((combine_kernel<D, 0>), grid, block, 0, stream, o_parts, z_parts, n_parts, O, Z, rows);
-    else if (dtype == SPHATTN_F16)
-        hipLaunchKernelGGL((combine_kernel<D, 2>), grid, block, 0, stream, o_parts, z_parts, n_parts, O, Z, rows);
-    else
-        hipLaunchKernelGGL((combine_kernel<D, 1>), grid, block, 0, stream, o_parts, z_parts, n_parts, O, Z, rows);
+    const bool resident = parts_resident((size_t)n_parts, rows * D * 4);
+    const auto kern = dtype == SPHATTN_F32 ? (resident ? combine_kernel<D, 0, true> : combine_kernel<D, 0, false>)
+                    : dtype == SPHATTN_F16 ? (resident ? combine_kernel<D, 2, true> : combine_kernel<D, 2, false>)
+                                           : (resident ? combine_kernel<D, 1, true> : combine_kernel<D, 1, false>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, stream, o_parts, z_parts, n_parts, O, Z, rows);
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
@@ -527,7 +525,10 @@ int launch_bwd(const BwdProblem& p, const BwdPlan& plan, float* parts)
     if constexpr (PARTQ || PARTK) {
         const size_t n4q = PARTQ ? nq / 4 : 0, n4k = PARTK ? nk / 4 : 0, blocks = (n4q + 2 * n4k + 255) / 256;
         if (blocks > 0x7fffffff) return SPHATTN_ERR_SHAPE;
-        hipLaunchKernelGGL(bwd_combine_kernel<HALF>, dim3((unsigned)blocks), dim3(256), 0, p.stream,
+        const size_t most = (size_t)(plan.sq > plan.sk ? plan.sq : plan.sk);
+        const bool resident = parts_resident(most, plan.bytes / most);
+        const auto kern = resident ? bwd_combine_kernel<HALF, true> : bwd_combine_kernel<HALF, false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, p.stream,
                            (const float*)parts, plan.sq, n4q, p.dQ, (const float*)parts_k, (const float*)parts_v, plan.sk, n4k, p.dK, p.dV);
         if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
     }
@@ -768,15 +769,17 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
 // How many slices a backward kernel's streamed axis of `tiles` 64-row tiles is cut into, for `items` tiles of
 // the other axis, `per_cu` workgroups at once on a CU, tau us per streamed tile in a full round and
 // part_us for writing and reading one slice's partial sums (6 TB/s).  A slice costs what its tiles and
-// about 5 more cost.  Below one round the fullest CU counts: one of two workgroups alone takes 0.62 of the
-// time of both, one or two of three 0.48 and 0.74; and an emptier chip clocks higher (power-bound part).  A
-// last round behind full ones costs 0.85 + 0.15 f of one if it fills the share f.  Cut for a gain of at
-// least 5 %, into slices of 4 tiles or more and at most 256 MB of sums.  Whole backward in us, bf16, uncut /
-// this choice (within 3 % of the best of a sweep over both kernels' counts): below one round 8 heads on 2
-// K/V heads of 1500 x 64 132 / 45, of 1500 x 128 217 / 71; 4 x 1000 x 128 74 / 49; 2 x 8192 x 128 449 / 224; 12 on 3
-// of 4096 x 64 327 / 179; above it 3 x 25243 x 128 (1.16 rounds in both kernels) 3240 / 2522, 9 x 8192 x 128
-// 1074 / 953, 3 x 12000 x 64 471 / 350; 12 x 4096 x 128 (0.75 of a round in both) stays uncut: 304, 332 in 4
-// slices of the keys, 330 in 4 of the queries.
+// about 5 more cost.  Where a round does not give every CU its `per_cu` the fullest CU counts: one of two workgroups
+// alone takes 0.62 of the time of both, one or two of three 0.48 and 0.74.  Below one round an emptier chip
+// also clocks higher (power-bound part); a last round of one workgroup per CU behind full ones costs 0.85 + 0.15 f
+// of one if it fills the share f.  Cut for a gain of at least 5 % below one round and 2 % above it, into slices
+// of 4 tiles or more and at most 256 MB of sums.  Whole backward in us, bf16, uncut / this choice: below one
+// round 8 heads on 2 K/V heads of 1500 x 64 126 / 41, of 1500 x 128 207 / 62; 4 x 1000 x 128 68 / 44; 2 x 8192 x 128
+// 438 / 210; 12 on 3 of 4096 x 64 325 / 168; 12 x 4096 x 128 (0.75 of a round in both) stays uncut: 304, 332 in 4
+// slices of the keys, 330 in 4 of the queries.  Above it 3 x 25243 x 128 (1.16 rounds in both kernels) 3255 / 2560,
+// 9 x 8192 x 128 1077 / 945, 17 x 8192 x 64 895 / 840 (dQ alone, 1.06 rounds); left alone where the
+// remainder is a workgroup more on most CUs: dK/dV of 16 x 8192 x 64 (1.33 rounds of three per CU) 708, in two
+// slices 725, and of 16 x 5200 x 128 (1.28 of two) 696, 729.
 long long choose_bwd_slices(long long items, int per_cu, long long tiles, double tau, double part_us, size_t part_bytes)
 {
     const double alone[3][3] = {{1.0, 1.0, 1.0}, {0.62, 1.0, 1.0}, {0.48, 0.74, 1.0}};

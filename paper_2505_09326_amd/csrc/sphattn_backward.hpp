@@ -589,9 +589,9 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
 // ---------------------------------------------------------------------------
 // Sums of the slices' partial gradients, rounded to the 16-bit type: first n4q groups of four values of dQ
 // over sq slices, then n4k of dK and n4k of dV over sk slices (a gradient that was not cut has none).  Slice p
-// starts 4 n4 values after slice p - 1; added in ascending order, eight slices' loads in flight.
+// starts 4 n4 values after slice p - 1; added in ascending order, small sums with eight slices' loads in flight.
 // ---------------------------------------------------------------------------
-template <bool HALF>
+template <bool HALF, bool RESIDENT>
 __global__ __launch_bounds__(256)
 void bwd_combine_kernel(const float* __restrict__ pq, int sq, size_t n4q, void* __restrict__ dQ,
                         const float* __restrict__ pk, const float* __restrict__ pv, int sk, size_t n4k,
@@ -606,14 +606,20 @@ void bwd_combine_kernel(const float* __restrict__ pq, int sq, size_t n4q, void* 
     const int n = q ? sq : sk;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     int p = 0;
-    for (; p + 8 <= n; p += 8) {
-        f32x4 x[8];
+    auto take = [&](auto count) {
+        constexpr int U = decltype(count)::value;
+        for (; p + U <= n; p += U) {
+            f32x4 x[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = src[(size_t)(p + u) * step];
+            for (int u = 0; u < U; ++u) x[u] = src[(size_t)(p + u) * step];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += x[u];
+            for (int u = 0; u < U; ++u) acc += x[u];
+        }
+    };
+    if constexpr (RESIDENT) {                      // (as in combine_kernel)
+        take(std::integral_constant<int, 8>{});
+        take(std::integral_constant<int, 4>{});
     }
-#pragma unroll 4
     for (; p < n; ++p) acc += src[(size_t)p * step];
     const i32x2 o4 = {pack2<HALF>(acc[0], acc[1]), pack2<HALF>(acc[2], acc[3])};
     *(reinterpret_cast<i32x2*>(q ? dQ : k ? dK : dV) + i) = o4;
