@@ -391,29 +391,51 @@ int launch_softmax32(const Problem& p)
 //   64 rows:  4 x 1999 x 128 17.8 us against 23.6 of 128 rows (38 of 256), 1 x 8192 x 128 56 against 76,
 //             2 x 8192 x 64 39 against 50; one and a half per CU no more (12 x 1999 x 64 16.6 against 16.1).
 //             Not for fp8 Q/K at d = 128, whose score instruction needs four query blocks a slot.
-//   128 rows: 4 x 8192 x 128 103 against 151 of 256 rows, 1 x 32768 x 128 378 against 529; at d = 64, where
-//             two fit a CU, up to one and a half per CU (5 x 8192 x 64, 320 workgroups, 84 against 88 us,
-//             7 x 8192, 448, 95 against 94, 12 x 5003 fp16, 480, 66 against 63); fp8 Q/K, which spills there, one
-//             and a quarter (28 x 1555 x 64, 364, 21.4 against 21.0).
+//   128 rows: 4 x 8192 x 128 103 against 151 of 256 rows, 1 x 32768 x 128 378 against 529.  At d = 64, where two
+//             fit a CU, a quarter more than one per CU with counts or fp8 Q/K and at least 40 tiles (10 x 3400 x 64
+//             with counts, 270 workgroups, 42.9 against 44.1, fp8 35.6 against 36.7; of 33 tiles 29.3 against 28.9, of 5
+//             tiles fp8 10.1 against 8.2; 12 x 4000, 384, with counts 54.3 against 51.9).  Without them only for long key
+//             axes (bf16 4 x 8300, 260, 82 against 92, 5 x 8192, 320, 85 against 88, f16 88 against 88; but 8 x 5000, 320,
+//             53.7 against 50.2, f16 4 x 9000, 284, 94 against 87, 100 x 300, 300, 8.9 against 8.1).
 // With more items than that they take two rounds and lose (5 x 8192 x 128, 160 tiles of 256 rows: 152 against
 // 136 us): a partly filled single round costs less than its share of idle CUs suggests, because the
 // part is power-bound and idle CUs give their share of the budget to the rest.
-int rows_per_workgroup(long long heads, long long Nq, long long n_splits, int d, bool fp8, long long cus)
+struct RowsRule { bool half, fp8, counts; };       // storage and options of the launch
+int rows_per_workgroup(long long heads, long long Nq, long long n_splits, long long tiles, int d, RowsRule r, long long cus)
 {
-    const long long slices = heads * n_splits;
+    const long long slices = heads * n_splits, wg = slices * ((Nq + 127) / 128);
     if (slices * ((Nq + 255) / 256) >= cus) return 256;
-    if (!(fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
-    return slices * ((Nq + 127) / 128) <= (d == 128 ? cus : fp8 ? cus * 5 / 4 : cus * 3 / 2) ? 128 : 256;
+    if (!(r.fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
+    const bool more = d == 64 && (r.fp8 || r.counts ? tiles >= 40 : tiles >= 120);
+    return wg <= (!more ? cus : r.half && !r.counts ? cus * 33 / 32 : cus * 5 / 4) ? 128 : 256;
+}
+
+// bf16 without counts also has 128 rows as four waves of 32 over all keys (fwd_pipelined_kernel with NQ = 2).  It reads
+// every fragment for two query blocks only, but starts with less: no exchange of halves, no second ring.  Where
+// 64-row workgroups do not fit the chip it wins on short key axes (us, key-split / this): d = 128 64 x 300
+// 9.9 / 8.1, 40 x 500 11.1 / 9.8, 20 x 1000 16.1 / 14.6, 10 x 2000 25.5 / 23.6, 8 x 3000 34.1 / 33.0, then 6 x 4000 43.8 / 51.1; with
+// CUs nearly all taken up to 28 tiles (20 x 1500 23.5 / 23.5, 16 x 2000 28.2 / 28.8, 10 x 3200 41.7 / 46.9).  At d = 64
+// 64 x 300 6.8 / 5.9, 30 x 700 9.1 / 8.5, 20 x 1000 10.5 / 10.5, then 12 x 1500 13.3 / 13.5; of more than one per CU (256
+// rows / this) 100 x 300 8.1 / 7.4, 48 x 900 14.6 / 13.9, 16 x 2100 24.0 / 24.0, then 12 x 2900 30.9 / 31.4.  And a single
+// tile of keys: 16 x 64 x 128 5.4 of 64 rows / 5.1.
+bool narrow_pays(long long heads, long long Nq, long long tiles, int d, long long cus)
+{
+    const long long wg = heads * ((Nq + 127) / 128);
+    if (heads * ((Nq + 255) / 256) >= cus || wg > (d == 64 ? 2 * cus : cus)) return false;
+    if (heads * ((Nq + 63) / 64) <= cus) return tiles == 1;
+    return tiles <= (d == 64 ? (wg > cus ? 33 : 16) : wg > cus * 3 / 4 ? 28 : 52);
 }
 
 template <int D, QKType QKT, bool MULT, bool PARTIAL>
 int launch_spherical(const Problem& p)
 {
+    const long long heads = (long long)p.B * p.H, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
     const int rows = p.tile_rows != 0 ? p.tile_rows
-                                      : rows_per_workgroup((long long)p.B * p.H, p.Nq, p.n_splits, D, QKT == QKType::Fp8, cu_count());
-    // the 256-row kernel's order on the narrower form of that kernel (bf16 has one): 4 x 1999 x 128 22.3 us, 38.2 on 256 rows
+                                      : rows_per_workgroup(heads, p.Nq, p.n_splits, tiles, D, RowsRule{QKT == QKType::F16, QKT == QKType::Fp8, MULT}, cus);
+    // (with one_key_order, which has the 256-row kernel's order, as this has: 4 x 1999 x 128 22.3 us, 38.2 on 256 rows)
     if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
-        if (p.one_key_order && rows < 256) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+        if (p.tile_rows == 0 && ((p.one_key_order && rows < 256) || narrow_pays(heads, p.Nq, tiles, D, cus)))
+            return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
     if (rows == 256 || p.one_key_order) return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
     if constexpr (QKT != QKType::Fp8 || D == 64)
         if (rows == 64) return launch_keysplit<D, 2, QKT, MULT, PARTIAL>(p);
@@ -753,7 +775,7 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
         if (dtype == SPHATTN_F32) {
             us = 6.0 + choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d, cus).us;
         } else {
-            const int rows = rows_per_workgroup(heads, p.Nq, S, d, dtype == SPHATTN_FP8QK_BF16V, cus);
+            const int rows = rows_per_workgroup(heads, p.Nq, S, (long long)per, d, RowsRule{dtype == SPHATTN_F16, dtype == SPHATTN_FP8QK_BF16V, false}, cus);
             const double f = (double)(S * heads * ((p.Nq + rows - 1) / rows)) / (double)cus;
             const double tau = d == 128 ? (rows == 64 ? 0.40 + 0.08 * f : 0.55 + 0.17 * f)
                                         : (rows == 64 ? 0.25 + 0.03 * f : 0.36 + 0.08 * f);

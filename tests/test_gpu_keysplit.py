@@ -61,6 +61,31 @@ def test_both_widths_against_the_oracle(pkg, oracle, N, d, dtype, tile_rows):
         np.testing.assert_allclose(Z.cpu().double().numpy(), ref_z, rtol=2e-4, atol=1e-7 * ref_z.max())
 
 
+@pytest.mark.parametrize("H,Nq,Nk,d", [(64, 300, 300, 128), (12, 1500, 1500, 128), (100, 300, 300, 64), (20, 129, 1000, 128),
+                                       (3, 50, 64, 128), (2, 64, 1, 64), (30, 1050, 640, 64)])
+def test_short_key_axes_take_the_narrow_form_of_the_256_row_kernel(pkg, H, Nq, Nk, d):
+    """bf16 launches that 64-row workgroups would overfill, with few key tiles, and single tiles: every element
+    within what rounding each score and the result to bf16 (2^-8 of them at most) allows against 64 bits, and
+    bit for bit what 256 rows give (the key-split kernel adds the halves of a tile separately and does not)."""
+    print(f"case narrow H={H} Nq={Nq} Nk={Nk} d={d}", flush=True)
+    q, _, _ = si.make_qkv(1, H, Nq, d, "bf16", seed=4800 + Nq)
+    _, k, v = si.make_qkv(1, H, Nk, d, "bf16", seed=4900 + Nk)
+    q, k, v = q.to(DEV), k.to(DEV), v.to(DEV)
+    Z = torch.empty((1, H, Nq), dtype=torch.float32, device=DEV)
+    O = pkg.sphattn_cross_fwd(q, k, v, O=torch.empty_like(q), Z=Z, dtype="bf16")
+    torch.cuda.synchronize()
+    for h in range(H):
+        V, S = v[0, h].double(), q[0, h].double() @ k[0, h].double().t().contiguous()
+        z = (S * S).sum(1, keepdim=True)
+        ref = S @ V / z.sqrt()
+        bound = 2.0 ** -8 * (ref.abs() + S.abs() @ V.abs() / z.sqrt()) + 1e-5
+        assert ((O[0, h].double() - ref).abs() <= bound).all(), h
+        assert ((Z[0, h].double() - z[:, 0]).abs() <= 2e-4 * z[:, 0] + 1e-7 * z.max()).all(), h
+    if Nq == Nk:
+        whole, _ = pkg.sphattn_fwd_tile_rows(q, k, v, tile_rows=256)
+        assert torch.equal(O, whole)
+
+
 @pytest.mark.parametrize("Nq,Nk,d,dtype", [(130, 1, 64, "f16"), (127, 65, 128, "f16"), (200, 191, 128, "bf16"),
                                            (129, 448, 64, "bf16"), (300, 130, 128, "fp8qk_bf16v"), (1, 320, 64, "fp8qk_bf16v")])
 def test_partial_accumulators_with_multiplicities(pkg, oracle, Nq, Nk, d, dtype):

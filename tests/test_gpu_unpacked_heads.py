@@ -63,8 +63,8 @@ def test_forward(pkg, G, Nq, Nk, d, dtype, with_mult, partial):
         norm = S.norm(dim=1, keepdim=True)
         ref = S @ V / norm
         if partial:
-            # every element: each score is rounded to bf16 (2^-9 of it) before its product with V; fp32 sums beside that
-            bound = 2.0 ** -9 * (S.abs() @ V.abs()) + 1e-5 * norm
+            # every element: each score is rounded to bf16 (2^-8 of it at most) before its product with V; fp32 sums beside that
+            bound = 2.0 ** -8 * (S.abs() @ V.abs()) + 1e-5 * norm
             excess = ((got[0, h].double() - S @ V).abs() - bound).max().item()
             assert excess <= 0.0, (h, excess)
         else:
