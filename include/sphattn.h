@@ -275,7 +275,9 @@ size_t sphattn_splitkv_workspace_bytes(int B, int H, int N, int d, int n_splits)
  * fill their rounds on the compute units of the current device (256 when no device can be
  * asked) or when cutting is not expected to gain at least 3 %; otherwise the count, in slices of at least
  * 8 tiles, with the lowest estimated run time: rounds of workgroups, how full they are, the
- * slices' prologues and the combine step are priced from measurements on one MI355X.
+ * slices' prologues and the combine step are priced from measurements on one MI355X, for
+ * workgroups of 256 rows (32 in fp32); the narrower ones, which the unsplit launch may take, are priced at 0.6 of
+ * these or not at all, so n_splits given or sphattn_cross_splitkv_fwd, whose own choice knows them, can be faster.
  * Launches nothing. */
 int sphattn_splitkv_heuristic(int B, int H, int N, int d, int dtype);
 

@@ -5,6 +5,15 @@ include/sphattn.h; this module only marshals torch tensors (device memory and
 streams) into that ABI.  There is no fallback: if the library has not been
 built, importing the entry points raises.
 
+Every entry point has a function of its name here except sphattn_cross_splitkv_fwd, sphattn_grn_bwd_split and
+their _workspace_bytes: the forward and backward functions call those themselves where the library would cut
+the launch into slices, provided that they allocate all outputs (no O, no gradients, no delta given) and no
+stream handle is given.  The slices' workspace then comes from torch's allocator, at most 17 MB for a
+forward call (68 MB in fp32) and 512 MiB for a backward call; where it gives none the call runs the uncut launch
+without a word, as does a call that brings an output or a stream.  Cut and uncut launches agree to rounding,
+not bit for bit, so sphattn_fwd_tile_rows, sphattn_normalized_fwd with "l2" and the like, which never cut, may
+differ from sphattn_fwd in the last place.
+
 The C ABI cannot see how large a buffer behind a pointer is, so the binding checks what it
 can see before any launch: every tensor's shape against the shapes the entry point's header
 states, its torch dtype against the `dtype` code, contiguity and device.  A mismatch raises
@@ -317,8 +326,8 @@ def _workspace(need, like):
 
 def _launch_cross(lib, Q, K, V, mult, O, Z, B, H, H_kv, Nq, Nk, d, code, stream, own_output):
     """sphattn_cross_fwd on checked arguments.  Where the library would cut the key axis (few query
-    rows against many keys) and this call allocates its output anyway, the slices' workspace comes
-    from torch's allocator too: on the current stream, so its reuse is ordered behind the launch.
+    rows against many keys) and this call allocates its output anyway, the slices' workspace (17 MB at most, 68
+    in fp32) comes from torch's allocator too: on the current stream, so its reuse is ordered behind the launch.
     A caller that brings O or a stream handle of its own gets no allocation and the unsplit launch."""
     args = (Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), _ptr(Z), B, H, H_kv, Nq, Nk, d, code)
     need = _cut_workspace_bytes(Q.device.index, B, H, H_kv, Nq, Nk, d, code) if own_output and stream is None else 0
@@ -366,7 +375,7 @@ def sphattn_fwd_z(Q, K, V, O=None, Z=None, dtype="bf16", stream=None):
 
 
 def sphattn_fwd_tile_rows(Q, K, V, O=None, Z=None, dtype="bf16", tile_rows=0, stream=None):
-    """sphattn_fwd_z with the workgroup shape forced to 128 or 256 query rows (0: the library's
+    """sphattn_fwd_z in one launch, with the workgroup shape forced to 128 or 256 query rows (0: the library's
     choice); returns (O, Z), Z being None unless given."""
     lib, code = load_library(), _dtype_code(dtype)
     if O is None:
@@ -576,7 +585,8 @@ def _bwd_workspace_bytes(device_index, B, H, H_kv, N, d, code):
 
 
 def _launch_bwd(lib, Q, K, V, mult, O, dO, Z, dQ, dK, dV, delta, B, H, H_kv, N, d, code, stream, own_outputs):
-    """sphattn_grn_bwd on checked arguments, cut into slices under the conditions of _launch_cross."""
+    """sphattn_grn_bwd on checked arguments, cut into slices under the conditions of _launch_cross (up to
+    256 MiB of partial sums for dQ and as much for dK and dV)."""
     args = (Q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(mult), O.data_ptr(), dO.data_ptr(), Z.data_ptr(),
             dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), delta.data_ptr(), B, H, H_kv, N, d, code)
     need = _bwd_workspace_bytes(Q.device.index, B, H, H_kv, N, d, code) if own_outputs and stream is None else 0

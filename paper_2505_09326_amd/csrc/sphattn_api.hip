@@ -304,7 +304,7 @@ int launch_f32(const Problem& p)
 {
     constexpr bool SMALL = ROWS == kF32SmallRows;
     constexpr int waves = SMALL ? f32_small_waves<D>() : kWaves;
-    constexpr int lds_bytes = waves * 2 * 32 * (D + 4) * 4;
+    constexpr int lds_bytes = SMALL ? f32_small_lds_bytes<D>() : waves * 2 * 32 * (D + 4) * 4;
     constexpr auto kern = SMALL ? fwd_f32_small_kernel<D, MULT, PARTIAL> : fwd_f32_kernel<D, MULT, PARTIAL>;
     static std::atomic<uint64_t> done{0};
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
@@ -337,7 +337,7 @@ int launch_f32x3(const Problem& p)
 // fp32 storage has four workgroup shapes: 16 or 32 rows on the fp32 matrix instruction with the keys dealt
 // to the waves (the least latency: the launches that cannot give every CU more than that), and 128
 // or 256 rows on six bf16 products.  Time of one round per 32-key tile, in us, as measured on launches
-// that fill a small and the whole part of the CUs (f): d = 128 0.9, 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
+// that fill a small and the whole part of the CUs (f), the bf16 ones without the watch that adds 2 %: d = 128 0.9, 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
 // 0.35, 0.68, 1.1 to 1.3, 1.85 to 2.25.  Rounds times that picks the shape (32, 128 and 256 rows: 8 heads of
 // 4096 x 128 704, 328, 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 352, 553,
 // 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
@@ -679,15 +679,19 @@ int fp8_forward(const void* Q, const void* K, const void* V, const float* mult, 
                 : launch_fp8<64, false, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
 }
 
-// Key slices for `heads` heads of Nq query rows against Nk keys: 1 where cutting is not expected to
-// gain at least 3 %, otherwise the count with the lowest estimated run time.
+// Key slices for `heads` heads of Nq query rows against Nk keys, as sphattn_splitkv_fwd chooses them: 1 where
+// cutting is not expected to gain at least 3 %, otherwise the count with the lowest estimated run time.  The
+// estimate is of 256-row workgroups (32-row ones in fp32) and of an unsplit launch from before there were 64-row ones;
+// plan_cross below prices the shapes that launches take.  In us, unsplit / this choice / plan_cross's: 1 x 8192 x 128 54 / 50 / 38,
+// 1 x 8192 x 64 36 / 34 / 23, 1 x 2048 x 128 17 / 12.7 / 14, fp32 1 x 8192 x 128 348 / 348 / 151, fp32 4 x 1000 x 64 15.7 / 20.1 / 15.7; only this one
+// cuts 16-bit launches above one round (1 x 40000 x 128 642 / 532).
 int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
 {
     const long long cus = cu_count();
     const long long tiles = (Nk + kBC - 1) / kBC;
     const long long most = (tiles + 7) / 8;        // no slice shorter than 8 tiles
     if (dtype == SPHATTN_F32) {
-        // the fp32 kernel's workgroups hold 32 query rows: enough slices to give every CU one
+        // workgroups of 32 query rows: enough slices to give every CU one
         const long long wg = heads * ((Nq + 31) / 32);
         if (wg >= cus) return 1;
         const long long want = (cus + wg - 1) / wg;
@@ -701,7 +705,7 @@ int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
     // keys: main(S) = (0.5 rounds / S + 0.5 wg / resident) (1 + 3.5 / tiles per slice); the combine
     // step adds its launch (about 3 tile times) and S passes over wg / resident of the rows, 300 / Nk
     // of a round each.  Unsplit, a launch of at most `resident` 128-row workgroups costs
-    // 0.6 (0.5 + wg / resident) on the same scale.  Measured against these (bf16, one GPU):
+    // 0.6 (0.5 + wg / resident) on the same scale.  Measured against these (bf16, one GPU, unsplit as it was then):
     // 1 x 8192 x 128: S = 8 44 us (4: 57, unsplit 99); 2 x 8192 x 128: S = 4; 1 x 32768 x 128: S = 2;
     // 8 x 4096 x 128: unsplit; 1 x 40000 x 128 (157 tiles): S = 3 533 us (2: 645, unsplit 629);
     // 3 x 16384 x 128 (192 tiles): S = 4 291 us (2: 300, unsplit 298); 5 x 16384 x 64: S = 3 251 (unsplit 285).
