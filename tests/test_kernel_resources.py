@@ -153,3 +153,18 @@ def test_loops_begin_on_an_instruction_cache_line(compiled):
                     assert re.search(r"\.p2align\s+6", lines[i - 1]), label
                 break
     assert loops >= 40                             # the forward and backward kernels in all their forms
+
+
+def test_forward_tile_loops_do_not_drain_their_reads(compiled):
+    """The loop's first wait leaves the later slots' LDS reads under way (with the reads ahead of the loop in another
+    order it waited for all of them, in every tile)."""
+    text = compiled[1]
+    for d, qk, counts in ((128, 0, 0), (128, 0, 1), (128, 2, 1), (64, 0, 0), (64, 2, 1), (128, 1, 0)):
+        name = f"_ZN7sphattn20fwd_pipelined_kernelILi{d}ELi4ELNS_6QKTypeE{qk}ELNS_4NormE0ELb{counts}ELb0E"
+        start = text.index("\n" + name) + 1
+        body = text[start:text.index(".end_amdhsa_kernel", start)]
+        loops = [x for x in re.split(r"^\.LBB\d+_\d+:.*$", body, flags=re.M) if x.count("v_mfma") >= 64]
+        assert loops, name
+        for x in loops:
+            wait = re.search(r"s_waitcnt lgkmcnt\((\d+)\)", x)
+            assert wait and int(wait.group(1)) >= 4, (name, wait and wait.group(0))
