@@ -168,3 +168,14 @@ def test_forward_tile_loops_do_not_drain_their_reads(compiled):
         for x in loops:
             wait = re.search(r"s_waitcnt lgkmcnt\((\d+)\)", x)
             assert wait and int(wait.group(1)) >= 4, (name, wait and wait.group(0))
+
+
+def test_fp8_preparation_takes_a_keys_loads_together(compiled):
+    """All of a key's loads for its norm stand in one block, without a wait between them (a branch each made two trips)."""
+    text = compiled[1]
+    for d, chunks, keys in ((128, 0, 1), (128, 1, 2), (64, 0, 1), (64, 1, 2)):
+        start = text.index(f"\n_ZN7sphattn18fp8_prepare_kernelILi{d}ELb{chunks}E") + 1
+        body = text[start:text.index(".end_amdhsa_kernel", start)]
+        blocks = re.split(r"^\.LBB\d+_\d+:.*$|^\s+s_cbranch.*$|^\s+s_waitcnt vmcnt.*$", body, flags=re.M)
+        together = [n for n in (x.count("global_load_dwordx4") for x in blocks) if n > 1]
+        assert together and all(n == d // 32 for n in together) and len(together) >= keys, (d, chunks, together)
