@@ -90,7 +90,7 @@ long long cu_count();
 // the compute units times the workgroups of this kernel that fit one unit.  Feeds the kernels'
 // key-stream direction (see fwd_pipelined_kernel); asked once per kernel and device.
 template <typename Kern>
-int stream_period(Kern kern, int lds_bytes, std::atomic<int> (&cached)[64])
+int stream_period(Kern kern, int lds_bytes, std::atomic<int> (&cached)[64], int threads = kThreads)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
@@ -100,7 +100,7 @@ int stream_period(Kern kern, int lds_bytes, std::atomic<int> (&cached)[64])
     int p = cached[dev].load(std::memory_order_relaxed);
     if (p == 0) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, kThreads, (size_t)lds_bytes) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, threads, (size_t)lds_bytes) != hipSuccess ||
             per_cu <= 0) {
             (void)hipGetLastError();
             return 0;                              // 0: never reverse
@@ -207,20 +207,20 @@ long long balanced_grid(long long n_items, long long resident)
     return grid < resident ? grid : resident;
 }
 
-// The key-split kernel over a launch's items of 32 NQ query rows.
-template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL>
+// The key-split kernel over a launch's items of 16 NQ RG query rows.
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int RG, int KG>
 int launch_keysplit(const Problem& p)
 {
-    constexpr int BR = 32 * NQ, lds_bytes = keysplit_lds_bytes<D, QKT, MULT>();
-    auto kern = fwd_keysplit_kernel<D, NQ, QKT, MULT, PARTIAL>;
+    constexpr int BR = 16 * NQ * RG, threads = 64 * keysplit_waves<RG, KG>(), lds_bytes = keysplit_lds_bytes<D, NQ, RG, KG, QKT, MULT>();
+    auto kern = fwd_keysplit_kernel<D, NQ, QKT, MULT, PARTIAL, RG, KG>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
     const int n_qtiles = (p.Nq + BR - 1) / BR;
     const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
     if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
-    const long long grid = balanced_grid(n_wg, (long long)kXcds * stream_period(kern, lds_bytes, period));
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds_bytes, p.stream,
+    const long long grid = balanced_grid(n_wg, (long long)kXcds * stream_period(kern, lds_bytes, period, threads));
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds_bytes, p.stream,
                        p.Q, p.K, p.V, p.O, p.mult, p.Z, p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
                        p.n_splits, p.keys_per_split, 0, (int)n_wg, 0);
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
@@ -233,8 +233,8 @@ int launch_keysplit(const Problem& p)
 template <int D, QKType QKT>
 long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_begin, bool backwards, bool resident_only)
 {
-    constexpr int lds_bytes = keysplit_lds_bytes<D, QKT, false>();
-    auto kern = fwd_keysplit_kernel<D, 4, QKT, false, false>;
+    constexpr int lds_bytes = keysplit_lds_bytes<D, 4, 2, 2, QKT, false>();
+    auto kern = fwd_keysplit_kernel<D, 4, QKT, false, false, 2, 2>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return 0;
@@ -383,63 +383,76 @@ int launch_softmax32(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// Query rows per workgroup.  256 (four waves of 64 rows) is the efficient shape of a full chip; 128 and 64
-// (sphattn_keysplit.hpp) have each wave do half of every key tile for 64 or 32 rows.  In us per 64-key
-// tile while the chip is not full: d = 128 0.97, 0.55, 0.42; d = 64 0.56, 0.36, 0.26; what is left at 64 rows
-// is the copy of the tile itself, so there is no shape below it.  The smaller ones copy two and four
-// times the K/V bytes per flop and pay while they still run all at once, one per CU:
-//   64 rows:  4 x 1999 x 128 17.8 us against 23.6 of 128 rows (38 of 256), 1 x 8192 x 128 56 against 76,
-//             2 x 8192 x 64 39 against 50; one and a half per CU no more (12 x 1999 x 64 16.6 against 16.1).
-//             Not for fp8 Q/K at d = 128, whose score instruction needs four query blocks a slot.
-//   128 rows: 4 x 8192 x 128 103 against 151 of 256 rows, 1 x 32768 x 128 378 against 529.  At d = 64, where two
-//             fit a CU, a quarter more than one per CU with counts or fp8 Q/K and at least 40 tiles (10 x 3400 x 64
-//             with counts, 270 workgroups, 42.9 against 44.1, fp8 35.6 against 36.7; of 33 tiles 29.3 against 28.9, of 5
-//             tiles fp8 10.1 against 8.2; 12 x 4000, 384, with counts 54.3 against 51.9).  Without them only for long key
-//             axes (bf16 4 x 8300, 260, 82 against 92, 5 x 8192, 320, 85 against 88, f16 88 against 88; but 8 x 5000, 320,
-//             53.7 against 50.2, f16 4 x 9000, 284, 94 against 87, 100 x 300, 300, 8.9 against 8.1).
-// With more items than that they take two rounds and lose (5 x 8192 x 128, 160 tiles of 256 rows: 152 against
-// 136 us): a partly filled single round costs less than its share of idle CUs suggests, because the
-// part is power-bound and idle CUs give their share of the budget to the rest.
-struct RowsRule { bool half, fp8, counts; };       // storage and options of the launch
-int rows_per_workgroup(long long heads, long long Nq, long long n_splits, long long tiles, int d, RowsRule r, long long cus)
-{
-    const long long slices = heads * n_splits, wg = slices * ((Nq + 127) / 128);
-    if (slices * ((Nq + 255) / 256) >= cus) return 256;
-    if (!(r.fp8 && d == 128) && slices * ((Nq + 63) / 64) <= cus) return 64;
-    const bool more = d == 64 && (r.fp8 || r.counts ? tiles >= 40 : tiles >= 120);
-    return wg <= (!more ? cus : r.half && !r.counts ? cus * 33 / 32 : cus * 5 / 4) ? 128 : 256;
-}
+// How a launch of 16-bit or fp8-Q/K storage is laid out.  256 query rows (fwd_pipelined_kernel) is the shape of a full chip; the
+// others (sphattn_keysplit.hpp) deal the keys of a tile to groups of waves, and pay while all their workgroups run at
+// once, one per CU (two in Rows64 at d = 64).  Rows64 has two key groups of two waves; Rows64Wide four of two, so two
+// waves per SIMD; Rows64Own four of one wave with all 64 rows, which reads every K and V byte from LDS once (d = 128, where LDS and
+// copies are the bound); Rows128 two of two, Rows128Wide four of two (d = 64); Rows256Wide two key groups of four waves
+// (d = 64).  Narrow: 128 rows in four waves of 32 over all keys (bf16 without counts), which reads every fragment for
+// two query blocks only, but starts with less.
+enum Form { kRows64, kRows64Wide, kRows64Own, kRows128, kRows128Wide, kNarrow, kRows256Wide, kRows256, kForms };
+constexpr int kFormRows[kForms] = {64, 64, 64, 128, 128, 128, 256, 256};
 
-// bf16 without counts also has 128 rows as four waves of 32 over all keys (fwd_pipelined_kernel with NQ = 2).  It reads
-// every fragment for two query blocks only, but starts with less: no exchange of halves, no second ring.  Where
-// 64-row workgroups do not fit the chip it wins on short key axes (us, key-split / this): d = 128 64 x 300
-// 9.9 / 8.1, 40 x 500 11.1 / 9.8, 20 x 1000 16.1 / 14.6, 10 x 2000 25.5 / 23.6, 8 x 3000 34.1 / 33.0, then 6 x 4000 43.8 / 51.1; with
-// CUs nearly all taken up to 28 tiles (20 x 1500 23.5 / 23.5, 16 x 2000 28.2 / 28.8, 10 x 3200 41.7 / 46.9).  At d = 64
-// 64 x 300 6.8 / 5.9, 30 x 700 9.1 / 8.5, 20 x 1000 10.5 / 10.5, then 12 x 1500 13.3 / 13.5; of more than one per CU (256
-// rows / this) 100 x 300 8.1 / 7.4, 48 x 900 14.6 / 13.9, 16 x 2100 24.0 / 24.0, then 12 x 2900 30.9 / 31.4.  And a single
-// tile of keys: 16 x 64 x 128 5.4 of 64 rows / 5.1.
-bool narrow_pays(long long heads, long long Nq, long long tiles, int d, long long cus)
+// Time of a launch that runs at once, in us: start + tiles (tile + share f of the CUs), the tiles of 64 keys rounded up to what the
+// form's loop does at a time.  Fitted to 929 launches of bf16 and fp8 Q/K with and without counts (1 to 128 heads of 100 to 12000
+// keys, every form timed on each): 1 to 4 % off in the root mean square, and what this picks is 0.0 to 0.6 % slower
+// than the best form.  tile 0: the form does not exist.  f16 measures like bf16.
+struct FormCost { float start, tile, share; };
+constexpr FormCost kFormCost[2][2][2][kForms] = {   // [d = 128][fp8 Q/K][counts]
+    {{{{3.7f, .253f, .04f}, {4.5f, .162f, .05f}, {0, 0, 0}, {4.3f, .341f, .06f}, {5.5f, .262f, .08f}, {3.8f, .383f, .07f}, {5.0f, .453f, .15f}, {4.8f, .536f, .15f}},
+      {{3.7f, .343f, .04f}, {4.7f, .228f, .05f}, {0, 0, 0}, {4.6f, .473f, .05f}, {5.8f, .324f, .07f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.7f, .728f, .09f}}},
+     {{{3.6f, .230f, .04f}, {4.4f, .159f, .04f}, {0, 0, 0}, {4.5f, .322f, .05f}, {5.9f, .247f, .07f}, {0, 0, 0}, {5.0f, .453f, .15f}, {4.9f, .561f, .07f}},
+      {{3.7f, .304f, .03f}, {4.6f, .197f, .04f}, {0, 0, 0}, {5.4f, .440f, .05f}, {6.1f, .313f, .08f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.9f, .729f, .07f}}}},
+    {{{{4.7f, .370f, .09f}, {5.7f, .277f, .13f}, {6.5f, .276f, .11f}, {5.9f, .519f, .14f}, {0, 0, 0}, {4.7f, .506f, .20f}, {0, 0, 0}, {6.6f, .927f, .35f}},
+      {{5.0f, .447f, .09f}, {5.7f, .334f, .14f}, {6.6f, .318f, .11f}, {6.1f, .616f, .11f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.6f, 1.06f, .31f}}},
+     {{{0, 0, 0}, {0, 0, 0}, {5.9f, .224f, .07f}, {5.5f, .446f, .10f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .692f, .24f}},
+      {{0, 0, 0}, {0, 0, 0}, {6.1f, .263f, .07f}, {5.6f, .533f, .09f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .813f, .23f}}}}};
+
+struct FormChoice { Form form; double us; };
+struct Storage { bool bf16, fp8, counts; };
+FormChoice choose_form(long long slices, long long Nq, long long tiles, int d, Storage st, long long cus)
 {
-    const long long wg = heads * ((Nq + 127) / 128);
-    if (heads * ((Nq + 255) / 256) >= cus || wg > (d == 64 ? 2 * cus : cus)) return false;
-    if (heads * ((Nq + 63) / 64) <= cus) return tiles == 1;
-    return tiles <= (d == 64 ? (wg > cus ? 33 : 16) : wg > cus * 3 / 4 ? 28 : 52);
+    FormChoice best{kRows256, 0.0};
+    if (slices * ((Nq + 255) / 256) > cus) return best;    // a full chip: rounds of 256 rows
+    best.us = 1e30;
+    for (int form = 0; form < kForms; ++form) {
+        const FormCost c = kFormCost[d == 128][st.fp8][st.counts][form];
+        const long long items = slices * ((Nq + kFormRows[form] - 1) / kFormRows[form]);
+        // two on a CU at d = 64: Narrow, and Rows64 for what has no Narrow.  They take 1.5 and 1.8 times as long as one (100 x 300 x 64
+        // bf16 7.5 us, 8.5 on 256 rows; 64 x 500 x 64 fp8 7.6, 8.0 on 128 rows; 12 x 3000 x 64 fp8 with counts 34.8, 39.4)
+        const double both = d != 64 ? 0.0 : form == kNarrow ? 1.5 : form == kRows64 && !(st.bf16 && !st.counts) ? 1.8 : 0.0;
+        if (c.tile == 0 || (form == kNarrow && !st.bf16) || items > (both > 0.0 ? 2 * cus : cus)) continue;
+        const long long step = form == kRows64Wide || form == kRows64Own || form == kRows128Wide ? 4 : form == kNarrow || form == kRows256 ? 1 : 2;
+        const double n = (double)((tiles + step - 1) / step * step), f = items > cus ? 1.0 : (double)items / (double)cus;
+        const double us = c.start + n * (c.tile + c.share * f) * (items > cus ? both : 1.0);
+        if (us < best.us) best = FormChoice{(Form)form, us};
+    }
+    return best;
 }
 
 template <int D, QKType QKT, bool MULT, bool PARTIAL>
 int launch_spherical(const Problem& p)
 {
-    const long long heads = (long long)p.B * p.H, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
-    const int rows = p.tile_rows != 0 ? p.tile_rows
-                                      : rows_per_workgroup(heads, p.Nq, p.n_splits, tiles, D, RowsRule{QKT == QKType::F16, QKT == QKType::Fp8, MULT}, cus);
-    // (with one_key_order, which has the 256-row kernel's order, as this has: 4 x 1999 x 128 22.3 us, 38.2 on 256 rows)
-    if constexpr (QKT == QKType::Bf16 && !MULT && !PARTIAL)
-        if (p.tile_rows == 0 && ((p.one_key_order && rows < 256) || narrow_pays(heads, p.Nq, tiles, D, cus)))
-            return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
-    if (rows == 256 || p.one_key_order) return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
-    if constexpr (QKT != QKType::Fp8 || D == 64)
-        if (rows == 64) return launch_keysplit<D, 2, QKT, MULT, PARTIAL>(p);
-    return launch_keysplit<D, 4, QKT, MULT, PARTIAL>(p);
+    constexpr bool FP8 = QKT == QKType::Fp8, BF16 = QKT == QKType::Bf16;
+    const long long slices = (long long)p.B * p.H * p.n_splits, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
+    Form form = p.tile_rows == 128 ? kRows128 : p.tile_rows == 256 ? kRows256
+              : choose_form(slices, p.Nq, tiles, D, Storage{BF16 && !PARTIAL, FP8, MULT}, cus).form;
+    // (the 256-row kernel's order of a row's terms, which Narrow has too: 4 x 1999 x 128 22.3 us, 38.2 on 256 rows)
+    if (p.one_key_order && form != kRows256) form = BF16 && !MULT && !PARTIAL ? kNarrow : kRows256;
+    if constexpr (BF16 && !MULT && !PARTIAL)
+        if (form == kNarrow) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
+    if constexpr (!(FP8 && D == 128)) {
+        if (form == kRows64) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 2>(p);
+        if (form == kRows64Wide) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 4>(p);
+    }
+    if constexpr (D == 128) {
+        if (form == kRows64Own) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 1, 4>(p);
+    } else {
+        if (form == kRows128Wide) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 2, 4>(p);
+        if (form == kRows256Wide) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 4, 2>(p);
+    }
+    if (form == kRows128) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 2, 2>(p);
+    return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
 }
 
 // Spherical attention in any storage type; PARTIAL: accumulators over key slices.
@@ -779,11 +792,7 @@ SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
         if (dtype == SPHATTN_F32) {
             us = 6.0 + choose_f32(heads, p.Nq, S == 1 ? Nk : plan.keys_per_split, S, d, cus).us;
         } else {
-            const int rows = rows_per_workgroup(heads, p.Nq, S, (long long)per, d, RowsRule{dtype == SPHATTN_F16, dtype == SPHATTN_FP8QK_BF16V, false}, cus);
-            const double f = (double)(S * heads * ((p.Nq + rows - 1) / rows)) / (double)cus;
-            const double tau = d == 128 ? (rows == 64 ? 0.40 + 0.08 * f : 0.55 + 0.17 * f)
-                                        : (rows == 64 ? 0.25 + 0.03 * f : 0.36 + 0.08 * f);
-            us = (rows == 64 ? 4.0 : 6.0) + tau * per;
+            us = choose_form(S * heads, p.Nq, (long long)per, d, Storage{false, dtype == SPHATTN_FP8QK_BF16V, false}, cus).us;
         }
         if (S > 1) us += 4.0 + (double)S * part_us;
         if (S == 1) best_us = 0.9 * us;            // cut only for a gain of at least 10 %

@@ -105,6 +105,11 @@ __device__ __forceinline__ int block_piece_offset(int row, int piece)
 {
     return row * 64 + ((piece ^ (row >> 1)) & 3) * 16;
 }
+// ds_read_b64_tr_b16 on such blocks: columns 16 odd .. + 15 of row lane / 4 (of every 16-bit block), 8 bytes a lane
+__device__ __forceinline__ int block_tr_offset(int lane, int odd)
+{
+    return block_piece_offset(lane >> 2, 2 * odd + ((lane >> 1) & 1)) + (lane & 1) * 8;
+}
 // the piece that copy lane `lane` has to fetch for its slot
 __device__ __forceinline__ int block_piece_in_slot(int lane)
 {
