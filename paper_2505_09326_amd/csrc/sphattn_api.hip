@@ -318,11 +318,11 @@ int launch_f32(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-template <int D, int NQ, bool MULT, bool PARTIAL>
-int launch_f32x3(const Problem& p)
+template <int D, int NQ, bool MULT, bool PARTIAL, bool TWO>
+int launch_f32_parts(const Problem& p)
 {
     constexpr int BR = kF32Waves * 16 * NQ, lds_bytes = f32_lds_bytes<D>();
-    auto kern = fwd_f32x3_kernel<D, NQ, MULT, PARTIAL>;
+    constexpr auto kern = TWO ? fwd_f32x2_kernel<D, NQ, MULT, PARTIAL> : fwd_f32x3_kernel<D, NQ, MULT, PARTIAL>;
     static std::atomic<uint64_t> done{0};
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
     const int n_qtiles = (p.Nq + BR - 1) / BR;
@@ -336,21 +336,30 @@ int launch_f32x3(const Problem& p)
 
 // fp32 storage has four workgroup shapes: 16 or 32 rows on the fp32 matrix instruction with the keys dealt
 // to the waves (the least latency: the launches that cannot give every CU more than that), and 128
-// or 256 rows on six bf16 products.  Time of one round per 32-key tile, in us, as measured on launches
-// that fill a small and the whole part of the CUs (f), the bf16 ones without the watch that adds 2 %: d = 128 0.9, 1.42, 2.05 to 2.55, 3.5 to 4.3; d = 64
-// 0.35, 0.68, 1.1 to 1.3, 1.85 to 2.25.  Rounds times that picks the shape (32, 128 and 256 rows: 8 heads of
-// 4096 x 128 704, 328, 452 us; 16 heads 1396, 652, 551; 4 heads of 4096 x 64 167, 150, 243; 1 x 8192 x 128 352, 553,
-// 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
+// or 256 rows in two fp16 or three bf16 parts.  Time of one round per 32-key tile, in us, as measured on launches
+// that fill a small and the whole part of the CUs (f): d = 128 0.9, 1.42 on the fp32 instruction, 1.4 to 1.7, 2.0 to 2.6 in two
+// parts, 2.05 to 2.55, 3.5 to 4.3 in three (without the watch that adds 2 %); d = 64 0.35, 0.68; 0.69 to 0.87, 1.0 to 1.38; 1.1 to 1.3, 1.85 to 2.25.
+// Rounds times that picks the shape (32 rows, 128 and 256 in two parts, in three: 8 heads of 4096 x 128 704, 217 and
+// 275, 328 and 452 us; 16 heads 1396, 433 and 333, 652 and 551; 4 heads of 4096 x 64 167, 99 and 150, 150 and 243; in three parts 1 x 8192 x
+// 128 352, 553, 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
+//
+// Two parts wherever the results are then no further from 64 bits.  Error of O (relative 2-norm) with three / two parts:
+// d = 128 1.73e-7 / 1.79e-7 at 200 keys, 1.85 / 1.84 at 500, 2.01 / 1.92 at 1000, 2.98 / 2.45 at 5000; d = 64
+// 1.62 / 1.71 at 1000, 1.77 / 1.79 at 1500, 2.10 / 1.95 at 2500; z from 200 keys on closer with two.
+bool f32_two_parts(long long keys, int d) { return keys >= (d == 128 ? 512 : 1792); }
 struct F32Choice { int rows; double us; };
 F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d, long long n_cus)
 {
     const double cus = (double)n_cus, tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
+    const bool two = f32_two_parts(keys_per_slice, d);
     F32Choice best{32, 1e30};
     for (const int rows : {16, 32, 128, 256}) {
         const double items = (double)(heads * ((Nq + rows - 1) / rows) * S);
         const double f = items < cus ? items / cus : 1.0;
-        const double tau = d == 128 ? (rows == 16 ? 0.9 : rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
-                                    : (rows == 16 ? 0.35 : rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
+        double tau = d == 128 ? (rows == 16 ? 0.9 : rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
+                              : (rows == 16 ? 0.35 : rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
+        if (two && rows == 128) tau = d == 128 ? 1.4 + 0.28 * f : 0.69 + 0.18 * f;
+        if (two && rows == 256) tau = d == 128 ? 2.0 + 0.6 * f : 1.0 + 0.38 * f;
         const double us = __builtin_ceil(items / cus) * tiles * tau;
         if (us < best.us) best = F32Choice{rows, us};
     }
@@ -361,8 +370,9 @@ template <int D, bool MULT, bool PARTIAL>
 int launch_f32_any(const Problem& p)
 {
     const int rows = choose_f32((long long)p.B * p.H, p.Nq, PARTIAL ? p.keys_per_split : p.Nk, p.n_splits, D, cu_count()).rows;
-    if (rows == 128) return launch_f32x3<D, 1, MULT, PARTIAL>(p);
-    if (rows == 256) return launch_f32x3<D, 2, MULT, PARTIAL>(p);
+    const bool two = f32_two_parts(PARTIAL ? p.keys_per_split : p.Nk, D);
+    if (rows == 128) return two ? launch_f32_parts<D, 1, MULT, PARTIAL, true>(p) : launch_f32_parts<D, 1, MULT, PARTIAL, false>(p);
+    if (rows == 256) return two ? launch_f32_parts<D, 2, MULT, PARTIAL, true>(p) : launch_f32_parts<D, 2, MULT, PARTIAL, false>(p);
     return rows == 16 ? launch_f32<D, 16, MULT, PARTIAL>(p) : launch_f32<D, 32, MULT, PARTIAL>(p);
 }
 

@@ -1,7 +1,33 @@
-// Forward for fp32 storage on the bf16 matrix instructions.
+// Forward for fp32 storage on the 16-bit matrix instructions, in two fp16 parts or three bf16 parts.
 //
-// The fp32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at 1/16 of the bf16 one's rate.  An fp32
-// value is the exact sum of three bf16 values, x = x0 + x1 + x2 (each the rest before it, rounded to bf16), so
+// The fp32 matrix instruction (v_mfma_f32_32x32x2_f32) runs at 1/16 of the 16-bit ones' rate, so an fp32 product is
+// taken apart.
+//
+// Two parts.  x = x0 + x1, each the rest before it rounded to fp16.  The rest has 12 bits and x1 holds 11, so x is off by
+// 2^-23 of its power of two in one value of four and exact in the others: 2^-24 in the root mean square.
+// x y = x0 y0 + (x0 y1 + x1 y0), three products; the one left out is at most 2^-22 |x y| and 2^-25 in the
+// root mean square.  x1 has steps of 2^-24 at least, so all values are brought near the top of fp16's range by powers of two,
+// which cost no bit: each row of Q to a largest element below 2^14, K to a mean magnitude below 2^7 over its first
+// 32 keys, each column of V likewise, and a score with its count by 2^-18 / the mean count.  The end takes
+// them back.  What makes up for the parts' rounding is sums from zero: a score takes 12 additions at full size where three
+// parts take 24 and the fp32 instruction 64; z receives four squares at a time, o 64 keys.  Error of O against 64 bits
+// (relative 2-norm, normal values, d = 128) with three / two parts: 2.0e-7 / 1.9e-7 at 1000 keys, 3.0 / 2.5 at 5000,
+// 5.2 / 3.8 at 20000; of z a half to two thirds.  Below 512 keys (d = 64: 1792) three parts are as close or closer, and such
+// launches take them (f32_two_parts).
+//
+// The scales come from 32 keys, so the end asks whether they did: every row has z >= N / 16 in scaled scores (or
+// is a row of zeros in Q); z without the scales is in [2^-100, 2^100]; the row of o is 2^4 a column or more in scaled
+// values, or zero (the keys that have the scores are not those without the values); all is finite; and every
+// column of V has a mean magnitude of 1, no element counted as more than 32, or is all zeros.  If any
+// wave of a workgroup sees one of these fail, after 512 keys or at the end, the workgroup does its rows again in three parts,
+// and from there with the fp32 instruction.  Normal values pass with factors of 5 to 60; a first key a hundred times the others, later keys a hundred
+// times the first with values a thousandth, values that only unscored keys have, fail.
+//
+// 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
+// more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products alone are 82 us of the 178 at 2.5 PFLOP/s; between them each SIMD splits the next
+// tile and the scores.
+//
+// Three parts.  An fp32 value is the exact sum of three bf16 values, x = x0 + x1 + x2 (each the rest before it, rounded to bf16), so
 //     x y = x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) + (x1 y2 + x2 y1 + x2 y2),
 // six bf16 products, each exact in fp32, summed by the matrix cores in fp32.  |x1| <= 2^-8 and |x2| <= 2^-17 of
 // x0's power of two, so the three left out come to at most 2^-24 |x y| and measure 5.5e-8 at most and 5.8e-9 in
@@ -19,15 +45,17 @@
 // leaves NaN) and no o is below 2^-100.  If any wave of a workgroup saw one, for Q and the first tile before
 // the loop, the workgroup does its rows again with the fp32 instruction (f32_exact_rows): V scaled by 1e-36,
 // Q by 1e-36 against K by 1e36, infinities, subnormals and the largest fp32 values come out as they do there.
-// The watch costs 2 % (8 x 4096 x 128 282.3 us without it, 288.7 with; 16 x 4096 x 64 283.8, 289.1).
+// The watch costs 2 % (8 x 4096 x 128 in three parts 282.3 us without it, 288.7 with; 16 x 4096 x 64 283.8, 289.1).
 // Done again from the first tile on, 8 x 4096 x 128 takes 707 us (702 on fwd_f32_kernel); from the last tile, 953.
 //
-// A workgroup is 8 waves (two per SIMD) x 16 NQ query rows; Q's three parts stay in registers.
+// A workgroup is 8 waves (two per SIMD) x 16 NQ query rows; Q's parts stay in registers.
 // K and V tiles of 32 keys arrive as they are through direct global -> LDS copies (each wave's share in
 // a region of its own), are split by the wave that copied them, a unit at a time between its matrix
-// instructions, and go to LDS as three bf16 images in
+// instructions, and go to LDS as 16-bit images in
 // the block formats of the other kernels: K as 16 x 64-byte blocks with permuted pieces (row-major
-// reads), V as 16 x 32-byte blocks (transposing reads).  Two image buffers, one barrier per tile.
+// reads), V as 16 x 32-byte blocks (transposing reads).  One barrier per tile.  Three parts: two buffers of six
+// images.  Two parts: tiles go in pairs, the scores of both and then o from both, so K has two buffers and V
+// three, and copies run two tiles ahead.
 #pragma once
 #include "sphattn_pipelined.hpp"
 
@@ -36,11 +64,13 @@ namespace sphattn {
 constexpr int kF32Waves = 8;
 constexpr int kF32Tile = 32;           // keys per tile
 
-// Two sets of six images, one tile as copied, and a word per wave.
+// LDS, in images of one part of a K or V tile.  Three parts: two sets of six, and one tile as copied (four).  Two parts: two
+// tiles of K and three of V, two images each, and two tiles as copied.  Then a word per wave, sums over the
+// first tile (of K per wave, of V per column in two halves) and the columns' powers of two.
 template <int D>
-constexpr int f32_flags_at() { return 2 * 6 * kF32Tile * D * 2 + 2 * kF32Tile * D * 4; }
+constexpr int f32_flags_at() { return 18 * kF32Tile * D * 2; }
 template <int D>
-constexpr int f32_lds_bytes() { return f32_flags_at<D>() + kF32Waves * 4; }
+constexpr int f32_lds_bytes() { return f32_flags_at<D>() + 2 * kF32Waves * 4 + 3 * D * 4; }
 
 // Byte of a head's K or V at which row `row` of tile `tile` starts.  Heads are at most 2^31 - 1 bytes (the entry
 // points refuse longer ones), which a tile past the last one may pass: such a tile is not asked for.
@@ -135,18 +165,42 @@ void f32_exact_rows(const float* __restrict__ Qh, __amdgpu_buffer_rsrc_t ks, __a
     }
 }
 
-// Nq, Nk, Zv, PARTIAL, n_splits and keys_per_split as in fwd_pipelined_kernel.
-template <int D, int NQ, bool MULT, bool PARTIAL>
-__global__ __launch_bounds__(64 * kF32Waves, 2)
-void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
-                      float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
-                      int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
+// The same pair, already scaled, as two packed pairs of fp16.
+struct Split2 { int p0, p1; };
+__device__ __forceinline__ Split2 split2(float a, float b)
 {
-    constexpr int BC = kF32Tile, BR = kF32Waves * 16 * NQ;
+    Split2 r;
+    r.p0 = pack2<true>(a, b);
+    const f16x2 h = __builtin_bit_cast(f16x2, r.p0);
+    r.p1 = pack2<true>(a - (float)h[0], b - (float)h[1]);
+    return r;
+}
+
+// 2^e for an e that keeps it a normal number, and the e that brings a positive x to [2^(to - 1), 2^to); most for zero.
+__device__ __forceinline__ float power_of_two(int e) { return __builtin_bit_cast(float, (uint32_t)(e + 127) << 23); }
+__device__ __forceinline__ int exponent_to(float x, int to, int most)
+{
+    const int e = to - __builtin_amdgcn_frexp_expf(x);
+    return x > 0.f ? max(-126, min(126, e)) : most;
+}
+
+// What a workgroup works on: its head's rows of Q, O and Z (null: not wanted), its keys, and its first row.
+struct F32Rows {
+    const float* Q; const float* K; const float* V; const float* mult; float* O; float* Z;
+    int Nq, N, q0;
+};
+
+// Two parts: 8 waves x 16 NQ rows from p.q0 on; false, with nothing stored, where the values do not allow it.
+// Every thread of the workgroup calls it and gets the same answer.
+template <int D, int NQ, bool MULT, bool PARTIAL>
+__device__ __forceinline__
+bool f32_two_part_rows(const F32Rows& p)
+{
+    constexpr int BC = kF32Tile;
     constexpr int KK = D / 32, DB = D / 16;
-    constexpr int IMG = BC * D * 2;                // one bf16 image of a K or V tile
-    constexpr int SET = 6 * IMG;                   // K0 K1 K2 V0 V1 V2
-    constexpr int RAW = 2 * SET, FLAGS = f32_flags_at<D>();
+    constexpr int IMG = BC * D * 2;                // one 16-bit image of a K or V tile
+    constexpr int VRING = 4 * IMG;                 // V behind two tiles of K
+    constexpr int RAW = 10 * IMG, FLAGS = f32_flags_at<D>(), SUMS = FLAGS + kF32Waves * 4, COLS = SUMS + kF32Waves * 4, POWERS = COLS + 2 * D * 4;
     constexpr int UNITS = 2 * 4 * KK;              // 1 KB units (8 rows x 32 columns of fp32) of K and V
     constexpr int UPW = UNITS / kF32Waves;         // per wave
     static_assert(UNITS % kF32Waves == 0, "units are dealt evenly");
@@ -154,54 +208,53 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     SPH_LDS unsigned char* smem = (SPH_LDS unsigned char*)smem_raw;
 
+    const int Nq = p.Nq, N = p.N;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, g = lane >> 4;
-    const int lid = xcd_contiguous_id(blockIdx.x, n_wg);
-    const int qt = lid % n_qtiles;
-    const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
-    const int bh = PARTIAL ? lid / (n_qtiles * n_splits) : lid / n_qtiles;
-    const int bidx = bh / H;
-    const int k0 = PARTIAL ? split * keys_per_split : 0;
-    const int N = PARTIAL ? min(Nk - k0, keys_per_split) : Nk;
-    const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
-    const int q0 = qt * BR + (int)wave * 16 * NQ;
+    const int q0 = p.q0 + (int)wave * 16 * NQ;
 
-    // ---- tile copies: unit u of this wave, rows past the last key as zeros
-    const i32x4 krw = rsrc_words(K + kv_off, (uint32_t)N * D * 4);
-    const i32x4 vrw = rsrc_words(V + kv_off, (uint32_t)N * D * 4);
+    // ---- tile copies: unit u of this wave, rows past the last key as zeros.  Waves 0 to 3 have K, the others V; a
+    // wave's units are one group of 32 columns, so that a lane has the same four columns in all of them
+    const i32x4 krw = rsrc_words(p.K, (uint32_t)N * D * 4);
+    const i32x4 vrw = rsrc_words(p.V, (uint32_t)N * D * 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
     const int ld_lane = (lane >> 3) * D * 4 + (lane & 7) * 16;
     const int n_tiles = (N + BC - 1) / BC;
-    auto copy_tile = [&](int t) {                  // past the last tile: that one again, which nothing uses
-        const int tile = min(t, n_tiles - 1);
+    const bool is_k = wave < 4;
+    const int cg = (wave & 3) % KK, rg0 = (wave & 3) / KK * UPW;   // column group, first row group
+    auto copy_tile = [&](int t) {                  // past the last tile zeros: no byte is in range
 #pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            const int idx = wave * UPW + u, in = idx % (4 * KK);   // row group in / KK, column group in % KK
-            copy_to_lds(idx < 4 * KK ? krw : vrw, lds0 + RAW + idx * 1024, ld_lane, f32_tile_byte<D>(tile, in / KK * 8) + in % KK * 128);
-        }
+        for (int u = 0; u < UPW; ++u)
+            copy_to_lds(is_k ? krw : vrw, lds0 + RAW + (t & 1) * 4 * IMG + (wave * UPW + u) * 1024, ld_lane,
+                        t >= n_tiles ? N * D * 4 : f32_tile_byte<D>(t, (rg0 + u) * 8) + cg * 128);
     };
-    uint64_t outside = 0;                          // lanes that met a value out of the parts' range
+    auto raw_unit = [&](int u, int buffer) {
+        return __builtin_bit_cast(f32x4, lds_read_b128(smem + RAW + buffer * 4 * IMG + (wave * UPW + u) * 1024 + lane * 16));
+    };
     // whether any wave of the workgroup says so (a barrier between the two)
     auto say = [&](bool yes) { *reinterpret_cast<SPH_LDS int*>(smem + FLAGS + wave * 4) = __any(yes); };
     auto anyone = [&]() -> bool {
         const i32x4 a = lds_read_b128(smem + FLAGS), b = lds_read_b128(smem + FLAGS + 16);
         return __builtin_amdgcn_readfirstlane(a[0] | a[1] | a[2] | a[3] | b[0] | b[1] | b[2] | b[3]) != 0;
     };
-    // the same units split into the three images of set `set`
+    // factors of the lane's four columns (of K: all the same), and what V's columns amount to
+    f32x4 scale = {1.f, 1.f, 1.f, 1.f}, colsum = {0.f, 0.f, 0.f, 0.f};
+    // The same units split into the images of the set at `set` (K's, V's): a row group is 8 rows of a 16-row block, whose other 8 rows lie 512 bytes
+    // on in a K block (the same permutation of pieces) and 256 in a V block; the next block row D * 32.
+    static_assert(UPW % 2 == 0, "rg0 is even");
     const int rowin = lane >> 3, c4 = lane & 7;    // row and float4 of the unit
-    auto split_unit = [&](int u, int set) {
-            const int idx = wave * UPW + u, in = idx % (4 * KK), rg = in / KK, c = in % KK;
-            const f32x4 x = __builtin_bit_cast(f32x4, lds_read_b128(smem + RAW + idx * 1024 + lane * 16));
-            const Split3 lo = split3(x[0], x[1], outside), hi = split3(x[2], x[3], outside);
-            const int row = (rg & 1) * 8 + rowin;
-            const bool is_k = idx < 4 * KK;
-            const int koff = ((rg >> 1) * KK + c) * 1024 + block_piece_offset(row, c4 >> 1) + (c4 & 1) * 8;
-            const int voff = 3 * IMG + ((rg >> 1) * DB + 2 * c + (c4 >> 2)) * 512 + row * 32 + (c4 & 3) * 8;
-            SPH_LDS unsigned char* dst = smem + set * SET + (is_k ? koff : voff);
+    const int odd_rows = is_k ? 512 : 256;
+    const int at = cg * 1024 + (is_k ? block_piece_offset(rowin, c4 >> 1) + (c4 & 1) * 8 : (c4 >> 2) * 512 + rowin * 32 + (c4 & 3) * 8);
+    auto split_unit = [&](int u, int buffer, int kset, int vset) {
+            f32x4 x = raw_unit(u, buffer);
+            SPH_LDS unsigned char* dst = smem + (is_k ? kset : vset) + at + ((rg0 + u) >> 1) * D * 32 + (u & 1) * odd_rows;
+            x *= scale;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) colsum[e] += fminf(__builtin_fabsf(x[e]), 32.f);
+            const Split2 lo = split2(x[0], x[1]), hi = split2(x[2], x[3]);
             *reinterpret_cast<SPH_LDS i32x2*>(dst) = i32x2{lo.p0, hi.p0};
             *reinterpret_cast<SPH_LDS i32x2*>(dst + IMG) = i32x2{lo.p1, hi.p1};
-            *reinterpret_cast<SPH_LDS i32x2*>(dst + 2 * IMG) = i32x2{lo.p2, hi.p2};
     };
     auto wait_copies = [&]() {
         asm volatile("" ::: "memory");
@@ -209,26 +262,40 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
         asm volatile("" ::: "memory");
     };
     copy_tile(0);
+    copy_tile(1);
 
-    // ---- Q in three parts as B operands: row n16 of the block, elements 32 kk + 8 g .. + 7
-    i32x4 qf[NQ][KK][3];
+    // ---- Q in parts as B operands: row n16 of the block, elements 32 kk + 8 g .. + 7
+    i32x4 qf[NQ][KK][2];
+    int eq[NQ];                                    // the row's power of two
+    bool qzero[NQ];
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         int row = q0 + qb * 16 + n16;
         row = row < Nq ? row : Nq - 1;             // rows past the end are computed and dropped
-        const float* src = Q + ((size_t)bh * Nq + row) * D + 8 * g;
+        const float* src = p.Q + (size_t)row * D + 8 * g;
+        f32x4 x[KK][2];
+        float most = 0.f;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            const f32x4 a = *reinterpret_cast<const f32x4*>(src + 32 * kk), b = *reinterpret_cast<const f32x4*>(src + 32 * kk + 4);
+        for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                x[kk][h] = *reinterpret_cast<const f32x4*>(src + 32 * kk + 4 * h);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) most = fmaxf(most, __builtin_fabsf(x[kk][h][e]));
+            }
+        most = max_across_groups(most);
+        eq[qb] = exponent_to(most, 14, 0);
+        qzero[qb] = most == 0.f;
+        const float f = power_of_two(eq[qb]);
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const f32x4& ab = e < 2 ? a : b;
-                const Split3 s = split3(ab[2 * (e & 1)], ab[2 * (e & 1) + 1], outside);
+                const float a = x[kk][e >> 1][2 * (e & 1)], b = x[kk][e >> 1][2 * (e & 1) + 1];
+                const Split2 s = split2(a * f, b * f);
                 qf[qb][kk][0][e] = s.p0;
                 qf[qb][kk][1][e] = s.p1;
-                qf[qb][kk][2][e] = s.p2;
             }
-        }
     }
     f32x4 oacc[DB][NQ];
 #pragma unroll
@@ -239,158 +306,301 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) zacc[qb][0] = zacc[qb][1] = 0.f;
 
-    const __amdgpu_buffer_rsrc_t mrs = make_rsrc(MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, MULT ? (uint32_t)N * 4 : 0);
-    wait_copies();
+    const __amdgpu_buffer_rsrc_t mrs = make_rsrc(p.mult, MULT ? (uint32_t)N * 4 : 0);
+    auto load_counts = [&](int j, int kb) -> f32x4 {   // of the lane's keys 16 kb + 4 g + t; past the last key 0
+        f32x4 m;
 #pragma unroll
-    for (int u = 0; u < UPW; ++u) split_unit(u, 0);
-    say(outside != 0);
+        for (int t = 0; t < 4; ++t)
+            m[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, (j * BC + 16 * kb + 4 * g + t) * 4, 0, 0));
+        return m;
+    };
+    wait_copies();
+    int ek, ep = -18;                              // K's power of two; P = 2^ep (Q' K'), Q' and K' scaled
+    {
+        // Powers of two from means over the first tile, which an outlier does not move far: of K, and of each column of V.
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < UPW; ++u) {
+            const f32x4 x = raw_unit(u, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += __builtin_fabsf(x[e]);
+        }
+#pragma unroll
+        for (int w = 8; w < 64; w *= 2)            // over the unit's rows
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], w);
+        if (is_k) {
+            float all = sum[0] + sum[1] + sum[2] + sum[3];
+#pragma unroll
+            for (int w = 1; w < 8; w *= 2) all += __shfl_xor(all, w);
+            if (lane == 0) *reinterpret_cast<SPH_LDS float*>(smem + SUMS + wave * 4) = all;
+        } else if (lane < 8) {
+            *reinterpret_cast<SPH_LDS f32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = sum;
+        }
+        __syncthreads();
+        const float rows = (float)min(N, BC);
+        const f32x4 ks = __builtin_bit_cast(f32x4, lds_read_b128(smem + SUMS));
+        ek = __builtin_amdgcn_readfirstlane(exponent_to((ks[0] + ks[1] + ks[2] + ks[3]) / (rows * D), 7, 126));
+        if constexpr (MULT) {
+            const f32x4 m0 = load_counts(0, 0), m1 = load_counts(0, 1);
+            float m = 0.f;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) m += __builtin_fabsf(m0[t]) + __builtin_fabsf(m1[t]);
+            ep = max(-126, ep + __builtin_amdgcn_readfirstlane(exponent_to(sum_across_groups(m) / rows, 1, 0)));
+        }
+        if (is_k) {
+            const float f = power_of_two(ek);
+            scale = f32x4{f, f, f, f};
+        } else {
+            const SPH_LDS unsigned char* sums = smem + COLS + (cg * 32 + c4 * 4) * 4;
+            f32x4 cs = __builtin_bit_cast(f32x4, lds_read_b128(sums));
+            if constexpr (KK == 2) cs += __builtin_bit_cast(f32x4, lds_read_b128(sums + D * 4));
+            i32x4 ev;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                ev[e] = exponent_to(cs[e] / rows, 7, 126);
+                scale[e] = power_of_two(ev[e]);
+            }
+            if (lane < 8) *reinterpret_cast<SPH_LDS i32x4*>(smem + POWERS + (cg * 32 + c4 * 4) * 4) = ev;   // (at KK = 2 by two waves, the same)
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < UPW; ++u) split_unit(u, 0, 0, VRING);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0): the copied bytes are read, the images written
-    copy_tile(1);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    bool in_range = !anyone();
 
-    // which part of the left and of the right operand each of the six products takes, smallest first
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-    const int klane = block_piece_offset(n16, g), vlane = 3 * IMG + lane * 8;
+    // which part of the left and of the right operand each product takes, smallest first
+    constexpr int PRODUCTS = 3, PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+    const int klane = block_piece_offset(n16, g);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; in_range && j < n_tiles; ++j) {
-        const SPH_LDS unsigned char* set = smem + (j & 1) * SET;
+    // Steps of a few fragments, read a step ahead, and their matrix instructions: KK score steps (both 16-key blocks of a
+    // k-step), then output steps.  The next tile is split a unit at a time in between.
+    // Tiles in pairs: the scores of both, then o += V^T P of both as one sum that is formed from zero, so o is rounded once
+    // in 64 keys.  Copies run two tiles ahead; the second tile of a pair may be one past the end, all zeros.
+    const float pscale = power_of_two(ep);
+    int vring[3] = {VRING, VRING + 2 * IMG, VRING + 4 * IMG};   // V of the pair's tiles and of the next one
+    i32x4 pf[2][NQ][2];
+    auto tile_phase = [&](auto second, int j) __attribute__((always_inline)) {
+        constexpr int SECOND = decltype(second)::value;
+        constexpr int STEPS = KK + (SECOND ? DB : 0);
+        // units from this step on, so many steps apart: the second tile's copies were asked for in the short first phase
+        constexpr int FROM = SECOND ? 2 : 0, EVERY = SECOND ? (STEPS - FROM) / UPW : KK / UPW;
+        static_assert(EVERY >= 1 && FROM + (UPW - 1) * EVERY < STEPS, "every unit has its step");
+        const SPH_LDS unsigned char* kset = smem + SECOND * 2 * IMG;
         f32x4 mk[2];
-        if constexpr (MULT) {                      // of the lane's keys 16 kb + 4 g + t; past the last key 0
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    mk[kb][t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, (j * BC + 16 * kb + 4 * g + t) * 4, 0, 0));
+        if constexpr (MULT) {
+            mk[0] = load_counts(j, 0);
+            mk[1] = load_counts(j, 1);
         }
-        // Steps of 12 NQ matrix instructions on six fragments, which are read a step ahead: KK score
-        // steps (both 16-key blocks of a k-step), then DB / 2 output steps (two 16-column blocks).
-        // The next tile is split a unit at a time in between; its copied bytes have had most of a
-        // tile's time to land, and their successors are asked for when the last unit is read.
-        constexpr int STEPS = KK + DB / 2, EVERY = STEPS / UPW;
-        i32x4 fr[2][2][3];
+        copy_tile(j + 2);
+        i32x4 fr[2][2][2];                     // [step][key block, or tile of the pair][part]
         auto load_step = [&](int st) {
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) {
+                for (int q = 0; q < 2; ++q) {
                     if (st < KK) {
-                        fr[st & 1][u][p] = lds_read_b128(set + p * IMG + (u * KK + st) * 1024 + klane);
+                        fr[st & 1][u][q] = lds_read_b128(kset + q * IMG + (u * KK + st) * 1024 + klane);
                     } else {
-                        const SPH_LDS unsigned char* a = set + vlane + p * IMG + (2 * (st - KK) + u) * 512;
+                        const SPH_LDS unsigned char* a = smem + vring[u] + lane * 8 + q * IMG + (st - KK) * 512;
                         const i32x2 lo = lds_read_tr64(a), hi = lds_read_tr64(a + DB * 512);
-                        fr[st & 1][u][p] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+                        fr[st & 1][u][q] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
                     }
                 }
         };
         f32x4 s[2][NQ];
-        i32x4 pf[NQ][3];
         load_step(0);
-        wait_copies();
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             if (st + 1 < STEPS) load_step(st + 1);
-            if (st % EVERY == 0) split_unit(st / EVERY, (j + 1) & 1);
+            if (st == FROM) {                  // the next tile has landed; the one after it may be under way
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_waitcnt(0x0F70 | UPW);
+                asm volatile("" ::: "memory");
+            }
+            if (st >= FROM && (st - FROM) % EVERY == 0 && (st - FROM) / EVERY < UPW)
+                split_unit((st - FROM) / EVERY, 1 - SECOND, (1 - SECOND) * 2 * IMG, vring[1 + SECOND]);
             if (st < KK) {
                 // S^T = K Q^T
 #pragma unroll
-                for (int m = 0; m < 6; ++m)
+                for (int m = 0; m < PRODUCTS; ++m)
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                         for (int qb = 0; qb < NQ; ++qb)
-                            s[kb][qb] = mfma16x16<false>(fr[st & 1][kb][PA[m]], qf[qb][st][PB[m]], st == 0 && m == 0 ? zero : s[kb][qb]);
+                            s[kb][qb] = mfma16x16<true>(fr[st & 1][kb][PA[m]], qf[qb][st][PB[m]], st == 0 && m == 0 ? zero : s[kb][qb]);
                 if (st == KK - 1) {
-                    // z, and the scores in three parts: registers 2 kb, 2 kb + 1 of the B operands
+                    // z, and the scores in parts: registers 2 kb, 2 kb + 1 of the B operands
 #pragma unroll
                     for (int qb = 0; qb < NQ; ++qb) {
+                        float zt[2] = {0.f, 0.f};      // (from zero as well: one rounding of z in four squares)
 #pragma unroll
                         for (int kb = 0; kb < 2; ++kb) {
-                            if constexpr (MULT) s[kb][qb] *= mk[kb];
+                            if constexpr (MULT) s[kb][qb] *= mk[kb] * pscale;
+                            else s[kb][qb] *= pscale;
 #pragma unroll
                             for (int c = 0; c < 2; ++c) {
                                 const float a = s[kb][qb][2 * c], b = s[kb][qb][2 * c + 1];
-                                zacc[qb][0] = __builtin_fmaf(a, a, zacc[qb][0]);
-                                zacc[qb][1] = __builtin_fmaf(b, b, zacc[qb][1]);
-                                const Split3 x = split3(a, b, outside);
-                                pf[qb][0][2 * kb + c] = x.p0;
-                                pf[qb][1][2 * kb + c] = x.p1;
-                                pf[qb][2][2 * kb + c] = x.p2;
+                                zt[0] = __builtin_fmaf(a, a, zt[0]);
+                                zt[1] = __builtin_fmaf(b, b, zt[1]);
+                                const Split2 x = split2(a, b);
+                                pf[SECOND][qb][0][2 * kb + c] = x.p0;
+                                pf[SECOND][qb][1][2 * kb + c] = x.p1;
                             }
                         }
+                        zacc[qb][0] += zt[0];
+                        zacc[qb][1] += zt[1];
                     }
                 }
             } else {
-                // O^T += V^T P; the tile's sum is formed from zero and added once
-                f32x4 t[2][NQ];
+                // O^T += V^T P over the pair's 64 keys
+                f32x4 t[NQ];
 #pragma unroll
-                for (int m = 0; m < 6; ++m)
+                for (int m = 0; m < PRODUCTS; ++m)
 #pragma unroll
                     for (int u = 0; u < 2; ++u)
 #pragma unroll
                         for (int qb = 0; qb < NQ; ++qb)
-                            t[u][qb] = mfma16x16<false>(fr[st & 1][u][PA[m]], pf[qb][PB[m]], m == 0 ? zero : t[u][qb]);
+                            t[qb] = mfma16x16<true>(fr[st & 1][u][PA[m]], pf[u][qb][PB[m]], m == 0 && u == 0 ? zero : t[qb]);
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int qb = 0; qb < NQ; ++qb) oacc[2 * (st - KK) + u][qb] += t[u][qb];
+                for (int qb = 0; qb < NQ; ++qb) oacc[st - KK][qb] += t[qb];
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (st == (UPW - 1) * EVERY) {
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): the copied bytes have been read
-                copy_tile(j + 2);
-            }
         }
-        // the other set is whole, this one may be overwritten
+        // the other K set and the next V are whole, this K set and the copied bytes may be overwritten
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0)
+        __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);            // the copies past the end must not outlive the workgroup's LDS
-
-    const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq : (size_t)bh * Nq;
-    if (in_range) {
-        constexpr uint32_t LEAST = (27u << 24) - 1, INFINITE = 0xff000000u;   // doubled bits: of 2^-100, less one; of infinity
-        uint32_t least = ~0u, most = 0;            // a zero becomes the largest of all by the subtraction
+    };
+    // Whether the sums over the first `keys` keys are what two parts hold, for the workgroup.
+    float z[NQ];
+    auto in_range = [&](int keys) __attribute__((always_inline)) -> bool {
+        bool bad = false;
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
-            most = max(most, doubled_bits(zacc[qb][0] + zacc[qb][1]));
+            z[qb] = sum_across_groups(zacc[qb][0] + zacc[qb][1]);
+            // the row's scores against the parts' resolution, and z as it is without the powers of two
+            const float whole = __builtin_ldexpf(z[qb], -2 * (ep + eq[qb] + ek));
+            bad |= !qzero[qb] && !(z[qb] >= 0x1p-4f * (float)keys && whole >= 0x1p-100f && whole <= 0x1p100f);
+            uint32_t most = doubled_bits(z[qb]);   // nothing infinite, no NaN
+            float size = 0.f;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const uint32_t bits = doubled_bits(oacc[db][qb][t]);
-                    least = min(least, bits - 1);
-                    most = max(most, bits);
+                    most = max(most, doubled_bits(oacc[db][qb][t]));
+                    size = __builtin_fmaf(oacc[db][qb][t], oacc[db][qb][t], size);
                 }
+            bad |= most >= 0xff000000u;
+            // the row of O against the resolution of P and V: the keys with the scores are not those without the values
+            size = sum_across_groups(size);
+            bad |= !qzero[qb] && !(size == 0.f || size >= 0x1p8f * (float)D * z[qb]);
         }
-        say(outside != 0 || least < LEAST || most >= INFINITE);
+        if (!is_k) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float all = colsum[e];
+#pragma unroll
+                for (int w = 8; w < 64; w *= 2) all += __shfl_xor(all, w);
+                bad |= !(all == 0.f || all >= (float)keys / (KK == 2 ? 2 : 1));   // (at KK = 2 of half of the rows)
+            }
+        }
+        say(bad);
         __syncthreads();
-        in_range = !anyone();
+        return !anyone();
+    };
+    // Asked at the end, and on long key axes once early, so that values that two parts cannot hold cost little more than
+    // three parts do (a loop in a loop: asked inside one, d = 64 lost 4 %).
+    constexpr int EARLY = 16;                      // tiles
+    bool held;
+    for (int j = 0, stop = n_tiles < 2 * EARLY ? n_tiles : EARLY;; stop = n_tiles) {
+        for (; j < stop; j += 2) {
+            tile_phase(std::integral_constant<int, 0>{}, j);
+            tile_phase(std::integral_constant<int, 1>{}, j + 1);
+            const int next = vring[2];
+            vring[2] = vring[1];
+            vring[1] = vring[0];
+            vring[0] = next;
+        }
+        held = in_range(min(N, stop * BC));
+        if (!held || stop == n_tiles) break;
+        __syncthreads();                           // the answer is read
     }
-    if (!in_range) {
-        const __amdgpu_buffer_rsrc_t ks = make_rsrc(K + kv_off, (uint32_t)N * D * 4), vs = make_rsrc(V + kv_off, (uint32_t)N * D * 4);
-#pragma unroll 1
-        for (int qb = 0; qb < NQ; ++qb)
-            f32_exact_rows<D, MULT, PARTIAL>(Q + (size_t)bh * Nq * D, ks, vs, mrs, O + rows0 * D,
-                                             Zv != nullptr ? Zv + rows0 : nullptr, Nq, N, q0 + qb * 16);
-        return;
+    __builtin_amdgcn_s_waitcnt(0x0F70);            // the copies past the end must not land in what follows
+    if (!held) {
+        __syncthreads();                           // the flags are read, the LDS is free
+        return false;
     }
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-        const float z = sum_across_groups(zacc[qb][0] + zacc[qb][1]);
-        const float inv = PARTIAL ? 1.f : z > 0.f ? 1.0f / __builtin_sqrtf(z) : 0.f;
+        const int back = -(ep + eq[qb] + ek);      // a score is 2^back of what z and o were summed of
+        const float inv = PARTIAL ? 1.f : z[qb] > 0.f ? 1.0f / __builtin_sqrtf(z[qb]) : 0.f;
         const int row = q0 + qb * 16 + n16;
         if (row < Nq) {
-            if (g == 0 && (PARTIAL || Zv != nullptr)) Zv[rows0 + row] = z;
-            float* dst = O + (rows0 + row) * D + 4 * g;
+            if (g == 0 && (PARTIAL || p.Z != nullptr)) p.Z[row] = __builtin_ldexpf(z[qb], 2 * back);
+            float* dst = p.O + (size_t)row * D + 4 * g;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4*>(dst + db * 16) = oacc[db][qb] * inv;
+            for (int db = 0; db < DB; ++db) {
+                f32x4 o = oacc[db][qb] * inv;
+                const i32x4 ev = __builtin_bit_cast(i32x4, lds_read_b128(smem + POWERS + (db * 16 + 4 * g) * 4));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t] = __builtin_ldexpf(o[t], (PARTIAL ? back : 0) - ev[t]);
+                *reinterpret_cast<f32x4*>(dst + db * 16) = o;
+            }
         }
+    }
+    return true;
+}
+
+// Three parts.  Nq, Nk, Zv, PARTIAL, n_splits and keys_per_split as in fwd_pipelined_kernel.
+template <int D, int NQ, bool MULT, bool PARTIAL>
+__global__ __launch_bounds__(64 * kF32Waves, 2)
+void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                      float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
+                      int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
+{
+    constexpr int TILE = kF32Waves * 16 * NQ, first = 0;
+#include "sphattn_f32_three.inc"
+}
+
+// The same for a call from a kernel.
+template <int D, int NQ, int TILE, bool MULT, bool PARTIAL>
+__device__ __forceinline__
+void f32_three_part_rows(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                         float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
+                         int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split, int first)
+{
+#include "sphattn_f32_three.inc"
+}
+
+// Two parts, and three where two do not hold the values.
+template <int D, int NQ, bool MULT, bool PARTIAL>
+__global__ __launch_bounds__(64 * kF32Waves, 2)
+void fwd_f32x2_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                      float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
+                      int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
+{
+    constexpr int TILE = kF32Waves * 16 * NQ;
+    {
+        const int lid = xcd_contiguous_id(blockIdx.x, n_wg), qt = lid % n_qtiles;
+        const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
+        const int bh = PARTIAL ? lid / (n_qtiles * n_splits) : lid / n_qtiles, bidx = bh / H;
+        const int k0 = PARTIAL ? split * keys_per_split : 0;
+        const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
+        const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq : (size_t)bh * Nq;
+        const F32Rows p{Q + (size_t)bh * Nq * D, K + kv_off, V + kv_off, MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, O + rows0 * D,
+                        Zv != nullptr ? Zv + rows0 : nullptr, Nq, PARTIAL ? min(Nk - k0, keys_per_split) : Nk, qt * TILE};
+        if (f32_two_part_rows<D, NQ, MULT, PARTIAL>(p)) return;
+    }
+    // (256 rows of d = 128 in three parts do not fit the registers beside what the call above leaves: 128 at a time)
+    constexpr int NB = D == 128 ? 1 : NQ;
+#pragma unroll 1
+    for (int first = 0; first < TILE; first += kF32Waves * 16 * NB) {
+        f32_three_part_rows<D, NB, TILE, MULT, PARTIAL>(Q, K, V, O, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_wg, n_splits, keys_per_split, first);
+        __syncthreads();                           // every wave has read the LDS that the next rows overwrite
     }
 }
 

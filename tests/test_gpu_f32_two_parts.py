@@ -1,0 +1,81 @@
+"""fp32 storage in two fp16 parts (sphattn_f32.hpp): the shortest key axes that take them, odd numbers of tiles, parts of
+one, and values that a pair of fp16 numbers holds only with the powers of two of rows, keys and columns, or not at all
+(then three bf16 parts or the fp32 instruction do the work).  Every output column of a head is compared with 64 bits on
+its own.  With A = sqrt(q^2 . k^2) for the size of a score's terms, a score is off by rounding q and k (2^-24 in the root mean square of each) and by
+at most 12 to 24 additions (2^-25 each in the root mean square): 1.5e-7 A.  Independent errors of the scores move an
+output by sqrt(sum A^2 v^2) / n and, through n, by o sum |S| A / n^2, and adding up 57 groups of keys moves it by 2^-25 sqrt(57)
+of its own size, 2.3e-7.
+5e-7 of the three together is asked for.  A single z has no mean over rows: each of 24 additions may be 2^-24 short
+of a partial sum of twice A, so 3e-6 of 2 sum |S| A."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2505_09326_amd as p
+    p.load_library()
+    return p
+
+
+def _inputs(kind, H, Nq, Nk, d, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q, k, v = (torch.randn((1, H, n, d), generator=g, device=DEV) for n in (Nq, Nk, Nk))
+    m = None
+    if kind == "columns":                          # every column of V in a binade of its own
+        v *= torch.pow(2.0, torch.arange(d, device=DEV) % 61 - 30.0)
+    elif kind == "zero columns":
+        v[..., 5::16] = 0.0
+    elif kind == "rows":                           # rows of Q far apart, all keys small; a row of zeros
+        q *= torch.pow(2.0, torch.arange(Nq, device=DEV) % 41 - 20.0)[:, None]
+        q[:, :, 7] = 0.0
+        k *= 1e-9
+    elif kind == "outliers":                       # the first key a hundred times the others, its value a thousand
+        k[:, :, 0] *= 100.0
+        v[:, :, 0] *= 1000.0
+    elif kind == "unseen value":                   # a value of 1e7 that no score touches
+        k[:, :, 0] = 0.0
+        v[:, :, 0] = 1e7
+    elif kind == "unscored":                       # the same of every other key, the others' values a thousandth
+        k[:, :, ::2], v[:, :, ::2], v[:, :, 1::2] = 0.0, 100.0, v[:, :, 1::2] * 1e-3
+    elif kind == "unvalued":                       # every other value zero, the other keys a thousandth
+        v[:, :, ::2], k[:, :, 1::2] = 0.0, k[:, :, 1::2] * 1e-3
+    elif kind == "growing":                        # later keys a hundred times the first, later values a thousandth
+        k[:, :, Nk // 2:] *= 100.0
+        v[:, :, Nk // 3:] *= 1e-3
+    elif kind == "late":                           # one late key beyond fp16 at the first tile's scale
+        k[:, :, -1] *= 1e6
+    elif kind == "counts":
+        m = torch.poisson(torch.full((1, Nk), 1.5, device=DEV), generator=g)
+        m[:, 0], m[:, Nk // 2] = 2.0, 5000.0
+    return q, k, v, m
+
+
+@pytest.mark.parametrize("kind", ["plain", "columns", "zero columns", "rows", "outliers", "unseen value", "unscored", "unvalued", "growing", "late", "counts"])
+@pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 512, 128), (40, 391, 577, 128), (130, 300, 640, 128), (32, 512, 1792, 64), (64, 257, 1825, 64)])
+def test_columns_against_64_bits(pkg, H, Nq, Nk, d, kind):
+    print(f"case two parts {H} x {Nq} of {Nk} x {d} {kind}", flush=True)
+    q, k, v, m = _inputs(kind, H, Nq, Nk, d, 6000 + Nk + d)
+    O, Z = torch.empty_like(q), torch.empty((1, H, Nq), device=DEV)
+    pkg.sphattn_cross_fwd(q, k, v, m, O=O, Z=Z, dtype="f32")
+    o, z = pkg.sphattn_partial_fwd(q, k, v, m, dtype="f32")
+    torch.cuda.synchronize()
+    for h in (0, H // 2, H - 1):
+        kh = k[0, h].double() * m[0].double()[:, None] if m is not None else k[0, h].double()
+        S = q[0, h].double() @ kh.t().contiguous()
+        A = ((q[0, h].double() ** 2) @ (kh ** 2).t().contiguous()).sqrt()
+        n2, dz = (S * S).sum(1), 2.0 * (S.abs() * A).sum(1)
+        n = n2.sqrt()[:, None].clamp_min(1e-140)
+        V = v[0, h].double()
+        ref = S @ V / n
+        size = (ref.abs() + (A * A @ V ** 2).sqrt() / n + ref.abs() * dz[:, None] / 2.0 / n ** 2).norm(dim=0)
+        for got in (O[0, h].double(), o[0, h].double() / n):
+            assert torch.isfinite(got).all()
+            err = (got - ref).norm(dim=0)
+            assert (err <= 5e-7 * size).all(), (h, (err / size).max().item())
+        for got in (Z[0, h].double(), z[0, h].double()):
+            assert ((got - n2).abs() <= 3e-6 * dz).all(), (h, ((got - n2).abs() / dz.clamp_min(1e-300)).max().item())
