@@ -401,7 +401,7 @@ int launch_softmax32(const Problem& p)
 // (d = 64).  Narrow: 128 rows in four waves of 32 over all keys (bf16 without counts), which reads every fragment for
 // two query blocks only, but starts with less.
 enum Form { kRows64, kRows64Wide, kRows64Own, kRows128, kRows128Wide, kNarrow, kRows256Wide, kRows256, kForms };
-constexpr int kFormRows[kForms] = {64, 64, 64, 128, 128, 128, 256, 256};
+constexpr int kFormRowsLog2[kForms] = {6, 6, 6, 7, 7, 7, 8, 8};
 
 // Time of a launch that runs at once, in us: start + tiles (tile + share f of the CUs), the tiles of 64 keys rounded up to what the
 // form's loop does at a time.  Fitted to 929 launches of bf16 and fp8 Q/K with and without counts (1 to 128 heads of 100 to 12000
@@ -425,15 +425,16 @@ FormChoice choose_form(long long slices, long long Nq, long long tiles, int d, S
     FormChoice best{kRows256, 0.0};
     if (slices * ((Nq + 255) / 256) > cus) return best;    // a full chip: rounds of 256 rows
     best.us = 1e30;
+    const double per_cu = 1.0 / (double)cus;   // (no divisions by variables: this runs on every call)
     for (int form = 0; form < kForms; ++form) {
         const FormCost c = kFormCost[d == 128][st.fp8][st.counts][form];
-        const long long items = slices * ((Nq + kFormRows[form] - 1) / kFormRows[form]);
+        const long long items = slices * ((Nq + (1 << kFormRowsLog2[form]) - 1) >> kFormRowsLog2[form]);
         // two on a CU at d = 64: Narrow, and Rows64 for what has no Narrow.  They take 1.5 and 1.8 times as long as one (100 x 300 x 64
         // bf16 7.5 us, 8.5 on 256 rows; 64 x 500 x 64 fp8 7.6, 8.0 on 128 rows; 12 x 3000 x 64 fp8 with counts 34.8, 39.4)
         const double both = d != 64 ? 0.0 : form == kNarrow ? 1.5 : form == kRows64 && !(st.bf16 && !st.counts) ? 1.8 : 0.0;
         if (c.tile == 0 || (form == kNarrow && !st.bf16) || items > (both > 0.0 ? 2 * cus : cus)) continue;
         const long long step = form == kRows64Wide || form == kRows64Own || form == kRows128Wide ? 4 : form == kNarrow || form == kRows256 ? 1 : 2;
-        const double n = (double)((tiles + step - 1) / step * step), f = items > cus ? 1.0 : (double)items / (double)cus;
+        const double n = (double)((tiles + step - 1) & -step), f = items > cus ? 1.0 : (double)items * per_cu;
         const double us = c.start + n * (c.tile + c.share * f) * (items > cus ? both : 1.0);
         if (us < best.us) best = FormChoice{(Form)form, us};
     }
