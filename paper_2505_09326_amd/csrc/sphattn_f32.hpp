@@ -20,12 +20,12 @@
 // values, or zero (the keys that have the scores are not those without the values); all is finite; and every
 // column of V has a mean magnitude of 1, no element counted as more than 32, or is all zeros.  If any
 // wave of a workgroup sees one of these fail, after 512 keys or at the end, the workgroup does its rows again in three parts,
-// and from there with the fp32 instruction.  Normal values pass with factors of 5 to 60; a first key a hundred times the others, later keys a hundred
-// times the first with values a thousandth, values that only unscored keys have, fail.
+// and from there with the fp32 instruction.  Normal values pass with factors of 5 to 60; a first key a hundred times
+// the others, later keys a hundred times the first with values a thousandth, values that only unscored keys have, fail.
 //
 // 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
-// more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products alone are 82 us of the 178 at 2.5 PFLOP/s; between them each SIMD splits the next
-// tile and the scores.
+// more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products
+// alone are 82 us of the 178 at 2.5 PFLOP/s; between them each SIMD splits the next tile and the scores.
 //
 // Three parts.  An fp32 value is the exact sum of three bf16 values, x = x0 + x1 + x2 (each the rest before it, rounded to bf16), so
 //     x y = x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) + (x1 y2 + x2 y1 + x2 y2),
