@@ -15,13 +15,16 @@
 // 5.2 / 3.8 at 20000; of z a half to two thirds.  Below 512 keys (d = 64: 1792) three parts are as close or closer, and such
 // launches take them (f32_two_parts).
 //
-// The scales come from 32 keys, so the end asks whether they did: every row has z >= N / 16 in scaled scores (or
-// is a row of zeros in Q); z without the scales is in [2^-100, 2^100]; the row of o is 2^4 a column or more in scaled
-// values, or zero (the keys that have the scores are not those without the values); all is finite; and every
-// column of V has a mean magnitude of 1, no element counted as more than 32, or is all zeros.  If any
-// wave of a workgroup sees one of these fail, after 512 keys or at the end, the workgroup does its rows again in three parts,
-// and from there with the fp32 instruction.  Normal values pass with factors of 5 to 60; a first key a hundred times
-// the others, later keys a hundred times the first with values a thousandth, values that only unscored keys have, fail.
+// The scales come from 32 keys and P has one for all of them, so the end asks what each element of O was formed of.  Below a
+// power of two of 2^-2 a part's last bit is 2^-24 whatever the value, so P is off by up to 2^-25 (by rounding, and at most 2^-23.3
+// through K and Q), V by 2^-25, and an element by 2^-25 |column of V| and 2^-25 sqrt(z), all scaled, at random signs.  It is in doubt
+// unless o^2 >= 2^-6 |column|^2 + 2^-8 z: then all that is at most 2^-20.9 of it in the worst case, 2^-22 in the usual one.  Of normal values 0.4 to
+// 1 % are in doubt, by chance.  More than three eighths of a wave's rows of one column, or an eighth (and four) of a
+// row's columns, are not chance but keys whose scores or values the scales do not fit and which carry that column or row: a
+// key with 1e4 times the others' scores, say, and no value in some columns, which are then formed of the other
+// keys.  Also asked: every row has z >= N / 16 in scaled scores (or is a row of zeros in Q); z without the scales is in
+// [2^-100, 2^100]; no element is NaN (a value beyond fp16 leaves inf - inf).  If any wave of a workgroup sees one of these fail, after
+// 512 keys or at the end, the workgroup does its rows again in three parts, and from there with the fp32 instruction.
 //
 // 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
 // more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products
@@ -184,6 +187,10 @@ __device__ __forceinline__ int exponent_to(float x, int to, int most)
     return x > 0.f ? max(-126, min(126, e)) : most;
 }
 
+// x of the lane N further on in the lane's row of 16.
+template <int N>
+__device__ __forceinline__ int lane_rotated(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x120 + N, 0xf, 0xf, true); }
+
 // What a workgroup works on: its head's rows of Q, O and Z (null: not wanted), its keys, and its first row.
 struct F32Rows {
     const float* Q; const float* K; const float* V; const float* mult; float* O; float* Z;
@@ -238,8 +245,9 @@ bool f32_two_part_rows(const F32Rows& p)
         const i32x4 a = lds_read_b128(smem + FLAGS), b = lds_read_b128(smem + FLAGS + 16);
         return __builtin_amdgcn_readfirstlane(a[0] | a[1] | a[2] | a[3] | b[0] | b[1] | b[2] | b[3]) != 0;
     };
-    // factors of the lane's four columns (of K: all the same), and what V's columns amount to
-    f32x4 scale = {1.f, 1.f, 1.f, 1.f}, colsum = {0.f, 0.f, 0.f, 0.f};
+    // factors of the lane's four columns (of K: all the same), and the squares of V's columns, scaled (an element below 1
+    // counts as itself, so that only a column of zeros is 0)
+    f32x4 scale = {1.f, 1.f, 1.f, 1.f}, colsq = {0.f, 0.f, 0.f, 0.f};
     // The same units split into the images of the set at `set` (K's, V's): a row group is 8 rows of a 16-row block, whose other 8 rows lie 512 bytes
     // on in a K block (the same permutation of pieces) and 256 in a V block; the next block row D * 32.
     static_assert(UPW % 2 == 0, "rg0 is even");
@@ -251,7 +259,7 @@ bool f32_two_part_rows(const F32Rows& p)
             SPH_LDS unsigned char* dst = smem + (is_k ? kset : vset) + at + ((rg0 + u) >> 1) * D * 32 + (u & 1) * odd_rows;
             x *= scale;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) colsum[e] += fminf(__builtin_fabsf(x[e]), 32.f);
+            for (int e = 0; e < 4; ++e) colsq[e] = __builtin_fmaf(__builtin_fabsf(x[e]), fmaxf(__builtin_fabsf(x[e]), 1.f), colsq[e]);
             const Split2 lo = split2(x[0], x[1]), hi = split2(x[2], x[3]);
             *reinterpret_cast<SPH_LDS i32x2*>(dst) = i32x2{lo.p0, hi.p0};
             *reinterpret_cast<SPH_LDS i32x2*>(dst + IMG) = i32x2{lo.p1, hi.p1};
@@ -478,36 +486,84 @@ bool f32_two_part_rows(const F32Rows& p)
     // Whether the sums over the first `keys` keys are what two parts hold, for the workgroup.
     float z[NQ];
     auto in_range = [&](int keys) __attribute__((always_inline)) -> bool {
+        if (!is_k) {
+            f32x4 all;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)            // over the unit's rows
+                all[e] = sum_across_groups(colsq[e] + __builtin_bit_cast(float, lane_rotated<8>(__builtin_bit_cast(int, colsq[e]))));
+            if (lane < 8) *reinterpret_cast<SPH_LDS f32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = all;
+        }
+        __syncthreads();
         bool bad = false;
+        // An element of O is in doubt where it is not well above what the last bits of P (2^-25, times the column) and of V (times the row's
+        // scores) come to.  Rows past the end, rows of zeros and columns of zeros have none.
+        constexpr float NONE = -__builtin_inff();
+        float zmin[NQ], finite = 0.f;
+        int rows = 0, columns = 0;
+        uint32_t doubts[NQ];                       // of the lane's columns, a bit each
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
             z[qb] = sum_across_groups(zacc[qb][0] + zacc[qb][1]);
             // the row's scores against the parts' resolution, and z as it is without the powers of two
             const float whole = __builtin_ldexpf(z[qb], -2 * (ep + eq[qb] + ek));
             bad |= !qzero[qb] && !(z[qb] >= 0x1p-4f * (float)keys && whole >= 0x1p-100f && whole <= 0x1p100f);
-            uint32_t most = doubled_bits(z[qb]);   // nothing infinite, no NaN
-            float size = 0.f;
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    most = max(most, doubled_bits(oacc[db][qb][t]));
-                    size = __builtin_fmaf(oacc[db][qb][t], oacc[db][qb][t], size);
-                }
-            bad |= most >= 0xff000000u;
-            // the row of O against the resolution of P and V: the keys with the scores are not those without the values
-            size = sum_across_groups(size);
-            bad |= !qzero[qb] && !(size == 0.f || size >= 0x1p8f * (float)D * z[qb]);
+            const bool counts = q0 + qb * 16 + n16 < Nq && !qzero[qb];
+            zmin[qb] = counts ? 0x1p-8f * z[qb] : NONE;
+            finite += z[qb];
+            rows += __builtin_popcountll(__ballot(counts) & 0xffff);
+            doubts[qb] = 0;
         }
-        if (!is_k) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float all = colsum[e];
+        for (int db = 0; db < DB; ++db) {
+            const SPH_LDS unsigned char* sums = smem + COLS + (db * 16 + 4 * g) * 4;
+            f32x4 cs = __builtin_bit_cast(f32x4, lds_read_b128(sums));
+            if constexpr (KK == 2) cs += __builtin_bit_cast(f32x4, lds_read_b128(sums + D * 4));
 #pragma unroll
-                for (int w = 8; w < 64; w *= 2) all += __shfl_xor(all, w);
-                bad |= !(all == 0.f || all >= (float)keys / (KK == 2 ? 2 : 1));   // (at KK = 2 of half of the rows)
+            for (int t = 0; t < 4; ++t) {
+                const float vmin = cs[t] == 0.f ? NONE : 0x1p-6f * cs[t];
+                columns += cs[t] == 0.f ? 0 : 1;
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    const float above = __builtin_fmaf(oacc[db][qb][t], oacc[db][qb][t], -(vmin + zmin[qb]));
+                    doubts[qb] += doubts[qb] + (above >= 0.f ? 0u : 1u);
+                    finite += above;               // (infinite where there is nothing to doubt)
+                }
             }
         }
+        bad |= finite != finite;
+        // In doubt at most: an eighth of a row's columns and four, and three eighths of the wave's rows of a column, counted bit by bit over the rows
+        const float most = sum_across_groups((float)columns) * 0.125f + 4.f;
+        uint32_t n[6] = {doubts[0], 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) bad |= sum_across_groups((float)__builtin_popcount(doubts[qb])) > most;
+        if constexpr (NQ == 2) {
+            n[1] = doubts[0] & doubts[1];
+            n[0] = doubts[0] ^ doubts[1];
+        }
+        auto add_rotated = [&](auto by, int digits) __attribute__((always_inline)) {
+            uint32_t carry = 0;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                if (i >= digits) { n[i] = i == digits ? carry : 0; continue; }
+                const uint32_t m = lane_rotated<decltype(by)::value>(n[i]), x = n[i] ^ m;
+                const uint32_t c = (n[i] & m) | (carry & x);
+                n[i] = x ^ carry;
+                carry = c;
+            }
+        };
+        add_rotated(std::integral_constant<int, 8>{}, NQ);
+        add_rotated(std::integral_constant<int, 4>{}, NQ + 1);
+        add_rotated(std::integral_constant<int, 2>{}, NQ + 2);
+        add_rotated(std::integral_constant<int, 1>{}, NQ + 3);
+        const int limit = max(2, rows * 3 / 8);
+        uint32_t more = 0, same = ~0u;             // columns whose count is above the limit, or equal so far
+#pragma unroll
+        for (int i = NQ + 3; i >= 0; --i) {
+            const uint32_t bit = (limit >> i) & 1 ? ~0u : 0u;
+            more |= same & n[i] & ~bit;
+            same &= ~(n[i] ^ bit);
+        }
+        bad |= more != 0;
         say(bad);
         __syncthreads();
         return !anyone();

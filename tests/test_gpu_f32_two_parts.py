@@ -79,3 +79,60 @@ def test_columns_against_64_bits(pkg, H, Nq, Nk, d, kind):
             assert (err <= 5e-7 * size).all(), (h, (err / size).max().item())
         for got in (Z[0, h].double(), z[0, h].double()):
             assert ((got - n2).abs() <= 3e-6 * dz).all(), (h, ((got - n2).abs() / dz.clamp_min(1e-300)).max().item())
+
+
+def _one_key(kind, size, value, H, Nq, Nk, d, seed):
+    """Inputs in which one key among the first has `size` times the others' scores (by its elements, by its count, or for one
+    query row alone) and `value` times their values in a quarter of V's columns."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q, k, v = (torch.randn((1, H, n, d), generator=g, device=DEV) for n in (Nq, Nk, Nk))
+    m = None
+    if kind == "key":
+        q += 2.0
+        k[:, :, 3] = k[:, :, 3].abs() * size
+    elif kind == "late key":
+        q += 2.0
+        k[:, :, Nk - 3] = k[:, :, Nk - 3].abs() * size
+    elif kind == "count":
+        m = torch.poisson(torch.full((1, Nk), 1.5, device=DEV), generator=g)
+        m[:, 3] = size
+    elif kind == "one row":                        # element 0 belongs to this key and this row
+        q[..., 0] = 0.0
+        q[:, :, 21, 0] = size
+        k[..., 0] = 0.0
+        k[:, :, 3, 0] = 1.0
+    v[:, :, Nk - 3 if kind == "late key" else 3, :d // 4] *= value
+    return q, k, v, m
+
+
+@pytest.mark.parametrize("kind,size", [("key", 1e2), ("key", 1e4), ("key", 1e5), ("key", 1e6), ("key", 1e7), ("key", 1e9), ("key", 1e11),
+                                       ("late key", 1e5), ("count", 1e3), ("count", 1e5), ("count", 1e7), ("one row", 1e3), ("one row", 1e5), ("one row", 1e8)])
+@pytest.mark.parametrize("value", [0.0, 1e-6])
+@pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 512, 128), (16, 4000, 1100, 128), (64, 257, 1825, 64), (16, 4000, 1900, 64)])
+def test_columns_without_the_largest_key(pkg, H, Nq, Nk, d, kind, size, value):
+    """Columns as above.  Rows over the quarter of the columns: a row's errors in the scores are common to its columns, so its
+    norm over 16 or 32 of them scatters; twice the bound.  The largest key's products may all have one sign, so partial sums reach the
+    score itself as well as twice A: z within 3e-6 of 2 sum |S| (A + |S|)."""
+    print(f"case two parts {H} x {Nq} of {Nk} x {d} {kind} {size:g}, {value:g}", flush=True)
+    q, k, v, m = _one_key(kind, size, value, H, Nq, Nk, d, 6100 + Nk + d)
+    O, Z = torch.empty_like(q), torch.empty((1, H, Nq), device=DEV)
+    pkg.sphattn_cross_fwd(q, k, v, m, O=O, Z=Z, dtype="f32")
+    o, z = pkg.sphattn_partial_fwd(q, k, v, m, dtype="f32")
+    torch.cuda.synchronize()
+    for h in (0, H - 1):
+        kh = k[0, h].double() * m[0].double()[:, None] if m is not None else k[0, h].double()
+        S = q[0, h].double() @ kh.t().contiguous()
+        A = ((q[0, h].double() ** 2) @ (kh ** 2).t().contiguous()).sqrt()
+        n2, dz = (S * S).sum(1), 2.0 * (S.abs() * A).sum(1)
+        n = n2.sqrt()[:, None]
+        V = v[0, h].double()
+        ref = S @ V / n
+        size = ref.abs() + (A * A @ V ** 2).sqrt() / n + ref.abs() * dz[:, None] / 2.0 / n ** 2
+        for got in (O[0, h].double(), o[0, h].double() / n):
+            err = got - ref
+            columns = err.norm(dim=0) / size.norm(dim=0)
+            rows = err[:, :d // 4].norm(dim=1) / size[:, :d // 4].norm(dim=1)
+            print(f"  columns {columns.max().item():.2e} rows {rows.max().item():.2e}", flush=True)
+            assert (columns <= 5e-7).all() and (rows <= 1e-6).all()
+        for got in (Z[0, h].double(), z[0, h].double()):
+            assert ((got - n2).abs() <= 3e-6 * (dz + 2.0 * n2)).all()
