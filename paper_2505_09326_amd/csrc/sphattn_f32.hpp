@@ -489,8 +489,10 @@ bool f32_two_part_rows(const F32Rows& p)
         if (!is_k) {
             f32x4 all;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)            // over the unit's rows
-                all[e] = sum_across_groups(colsq[e] + __builtin_bit_cast(float, lane_rotated<8>(__builtin_bit_cast(int, colsq[e]))));
+            for (int e = 0; e < 4; ++e) {          // over the unit's rows
+                const float sum = colsq[e];        // (a bit cast of the vector's element itself takes element 0)
+                all[e] = sum_across_groups(sum + __builtin_bit_cast(float, lane_rotated<8>(__builtin_bit_cast(int, sum))));
+            }
             if (lane < 8) *reinterpret_cast<SPH_LDS f32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = all;
         }
         __syncthreads();

@@ -136,3 +136,45 @@ def test_columns_without_the_largest_key(pkg, H, Nq, Nk, d, kind, size, value):
             assert (columns <= 5e-7).all() and (rows <= 1e-6).all()
         for got in (Z[0, h].double(), z[0, h].double()):
             assert ((got - n2).abs() <= 3e-6 * (dz + 2.0 * n2)).all()
+
+
+def _ordinary(kind, H, Nq, Nk, d, seed):
+    """Inputs that programs have."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q, k, v = (torch.randn((1, H, n, d), generator=g, device=DEV) for n in (Nq, Nk, Nk))
+    m = None
+    if kind == "zero columns":
+        v[..., 5::16] = 0.0
+    elif kind == "late key":                       # (not ordinary: fp16 does not hold it)
+        k[:, :, -1] *= 1e6
+    return q, k.contiguous(), v.contiguous(), m
+
+
+@pytest.mark.parametrize("kind", ["plain", "zero columns", "late key"])
+@pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 1024, 128), (16, 4000, 1100, 128), (64, 257, 1825, 64), (16, 4000, 1900, 64)])
+def test_ordinary_values_take_two_parts(pkg, H, Nq, Nk, d, kind):
+    """A value of 1e30 in the last row of column 0 sends every workgroup to three parts, whose other columns do not
+    depend on it: results that differ from them in their last bits were formed in two.  And the bound of the columns."""
+    print(f"case two parts {H} x {Nq} of {Nk} x {d} {kind}", flush=True)
+    q, k, v, m = _ordinary(kind, H, Nq, Nk, d, 6200 + Nk + d)
+    three = v.clone()
+    three[:, :, -1, 0] = 1e30
+    O, T = torch.empty_like(q), torch.empty_like(q)
+    pkg.sphattn_cross_fwd(q, k, v, m, O=O, dtype="f32")
+    pkg.sphattn_cross_fwd(q, k, three, m, O=T, dtype="f32")
+    torch.cuda.synchronize()
+    # of every 128 rows (whole workgroups take one way or the other)
+    differs = (O[0, :, :, 1:] != T[0, :, :, 1:]).any(-1).float()
+    blocks = [differs[:, r:r + 128].mean(1) for r in range(0, Nq, 128)]
+    for share in blocks:
+        print("  rows in two parts", share.min().item(), share.max().item(), flush=True)
+        assert (share > 0.5).all() if kind != "late key" else (share == 0.0).all()
+    for h in (0, H - 1):
+        kh = k[0, h].double() * m[0].double()[:, None] if m is not None else k[0, h].double()
+        S = q[0, h].double() @ kh.t().contiguous()
+        A = ((q[0, h].double() ** 2) @ (kh ** 2).t().contiguous()).sqrt()
+        dz, n = 2.0 * (S.abs() * A).sum(1)[:, None], S.norm(dim=1, keepdim=True)
+        V = v[0, h].double()
+        ref = S @ V / n
+        size = (ref.abs() + (A * A @ V ** 2).sqrt() / n + ref.abs() * dz / 2.0 / n ** 2).norm(dim=0)
+        assert ((O[0, h].double() - ref).norm(dim=0) <= 5e-7 * size).all()
