@@ -7,8 +7,8 @@
 // 2^-23 of its power of two in one value of four and exact in the others: 2^-24 in the root mean square.
 // x y = x0 y0 + (x0 y1 + x1 y0), three products; the one left out is at most 2^-22 |x y| and 2^-25 in the
 // root mean square.  x1 has steps of 2^-24 at least, so all values are brought near the top of fp16's range by powers of two,
-// which cost no bit: each row of Q to a largest element below 2^14, K to a mean magnitude below 2^7 over its first
-// 32 keys, each column of V likewise, and a score with its count by 2^-18 / the mean count.  The end takes
+// which cost no bit: each row of Q to a largest element below 2^14, K to a mean exponent of 6 over 32 keys spread over the axis, each
+// column of V likewise (zeros not counted), and a score with its count by 2^-17 and the power of two of the mean count.  The end takes
 // them back.  What makes up for the parts' rounding is sums from zero: a score takes 12 additions at full size where three
 // parts take 24 and the fp32 instruction 64; z receives four squares at a time, o 64 keys.  Error of O against 64 bits
 // (relative 2-norm, normal values, d = 128) with three / two parts: 2.0e-7 / 1.9e-7 at 1000 keys, 3.0 / 2.5 at 5000,
@@ -16,15 +16,15 @@
 // launches take them (f32_two_parts).
 //
 // The scales come from 32 keys and P has one for all of them, so the end asks what each element of O was formed of.  Below a
-// power of two of 2^-2 a part's last bit is 2^-24 whatever the value, so P is off by up to 2^-25 (by rounding, and at most 2^-23.3
-// through K and Q), V by 2^-25, and an element by 2^-25 |column of V| and 2^-25 sqrt(z), all scaled, at random signs.  It is in doubt
-// unless o^2 >= 2^-6 |column|^2 + 2^-8 z: then all that is at most 2^-20.9 of it in the worst case, 2^-22 in the usual one.  Of normal values 0.4 to
-// 1 % are in doubt, by chance.  More than three eighths of a wave's rows of one column, or an eighth (and four) of a
-// row's columns, are not chance but keys whose scores or values the scales do not fit and which carry that column or row: a
-// key with 1e4 times the others' scores, say, and no value in some columns, which are then formed of the other
-// keys.  Also asked: every row has z >= N / 16 in scaled scores (or is a row of zeros in Q); z without the scales is in
+// power of two of 2^-2 a part's last bit is 2^-24 whatever the value.  So P is off by up to 2^-25 and, through K's last bits,
+// 2^-17 2^-25 |row of Q|, 2^-24.5 at most; V by 2^-25; and an element of O by 2^-24.5 |column of V| and 2^-25 sqrt(z), all scaled, at random
+// signs.  It is in doubt unless o^2 >= 2^-6 |column|^2 + 2^-8 z, above which that is 2^-21 of it in the worst case and 2^-22.5 in the
+// root mean square.  Of normal values 0.4 to 1 % are in doubt, by chance, of one-hot V 2 to 5 %.  More than three eighths of a wave's rows of one column, or an
+// eighth (and four) of a row's columns, are not chance but keys whose scores or values the scales do not fit and which carry that column
+// or row: a key with 1e4 times the others' scores, say, and no value in some columns, which are then formed of
+// the other keys.  Also asked: every row has z >= N / 16 in scaled scores (or is a row of zeros in Q); z without the scales is in
 // [2^-100, 2^100]; no element is NaN (a value beyond fp16 leaves inf - inf).  If any wave of a workgroup sees one of these fail, after
-// 512 keys or at the end, the workgroup does its rows again in three parts, and from there with the fp32 instruction.
+// 512 keys (columns not yet) or at the end, the workgroup does its rows again in three parts, and from there with the fp32 instruction.
 //
 // 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
 // more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products
@@ -179,12 +179,12 @@ __device__ __forceinline__ Split2 split2(float a, float b)
     return r;
 }
 
-// 2^e for an e that keeps it a normal number, and the e that brings a positive x to [2^(to - 1), 2^to); most for zero.
+// 2^e for an e that keeps it a normal number, and the e that brings a positive x to [2^(to - 1), 2^to); 0 for zero.
 __device__ __forceinline__ float power_of_two(int e) { return __builtin_bit_cast(float, (uint32_t)(e + 127) << 23); }
-__device__ __forceinline__ int exponent_to(float x, int to, int most)
+__device__ __forceinline__ int exponent_to(float x, int to)
 {
     const int e = to - __builtin_amdgcn_frexp_expf(x);
-    return x > 0.f ? max(-126, min(126, e)) : most;
+    return x > 0.f ? max(-126, min(126, e)) : 0;
 }
 
 // x of the lane N further on in the lane's row of 16.
@@ -269,6 +269,15 @@ bool f32_two_part_rows(const F32Rows& p)
         __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0)
         asm volatile("" ::: "memory");
     };
+    // 32 keys spread over the axis, this wave's columns of K or V of 8 UPW of them: what the powers of two are taken from
+    auto sampled_key = [&](int i) -> int { return (int)((uint32_t)i * (uint32_t)N >> 5); };
+    f32x4 sample[UPW];
+    {
+        const float* src = is_k ? p.K : p.V;
+#pragma unroll
+        for (int u = 0; u < UPW; ++u)
+            sample[u] = *reinterpret_cast<const f32x4*>(src + (size_t)sampled_key((rg0 + u) * 8 + rowin) * D + cg * 32 + c4 * 4);
+    }
     copy_tile(0);
     copy_tile(1);
 
@@ -292,7 +301,7 @@ bool f32_two_part_rows(const F32Rows& p)
                 for (int e = 0; e < 4; ++e) most = fmaxf(most, __builtin_fabsf(x[kk][h][e]));
             }
         most = max_across_groups(most);
-        eq[qb] = exponent_to(most, 14, 0);
+        eq[qb] = exponent_to(most, 14);
         qzero[qb] = most == 0.f;
         const float f = power_of_two(eq[qb]);
 #pragma unroll
@@ -323,50 +332,64 @@ bool f32_two_part_rows(const F32Rows& p)
         return m;
     };
     wait_copies();
-    int ek, ep = -18;                              // K's power of two; P = 2^ep (Q' K'), Q' and K' scaled
+    int ek, ep = -17;                              // K's power of two; P = 2^ep (Q' K'), Q' and K' scaled
     {
-        // Powers of two from means over the first tile, which an outlier does not move far: of K, and of each column of V.
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        // Powers of two from the mean exponent of the sample's elements other than zero, which neither an outlier nor zeros
+        // (padding, one-hot values, values cut at zero) move far: of K, and of each column of V.  Sums in one word:
+        // the elements, from bit 20 on, and their exponents + 256, of 1024 at most.
+        auto exponent_word = [](float x) -> int { return x != 0.f ? (1 << 20) + 256 + __builtin_amdgcn_frexp_expf(x) : 0; };
+        auto mean_exponent = [](int elements, int sum) -> int {   // of at least one element
+            return (int)__builtin_rintf((float)sum * __builtin_amdgcn_rcpf((float)elements)) - 256;
+        };
+        i32x4 word = {0, 0, 0, 0};
 #pragma unroll
-        for (int u = 0; u < UPW; ++u) {
-            const f32x4 x = raw_unit(u, 0);
+        for (int u = 0; u < UPW; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += __builtin_fabsf(x[e]);
-        }
+            for (int e = 0; e < 4; ++e) word[e] += exponent_word(sample[u][e]);
 #pragma unroll
         for (int w = 8; w < 64; w *= 2)            // over the unit's rows
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += __shfl_xor(sum[e], w);
-        if (is_k) {
-            float all = sum[0] + sum[1] + sum[2] + sum[3];
+            for (int e = 0; e < 4; ++e) word[e] += __shfl_xor(word[e], w);
+        int all = word[0] + word[1] + word[2] + word[3];
 #pragma unroll
-            for (int w = 1; w < 8; w *= 2) all += __shfl_xor(all, w);
-            if (lane == 0) *reinterpret_cast<SPH_LDS float*>(smem + SUMS + wave * 4) = all;
-        } else if (lane < 8) {
-            *reinterpret_cast<SPH_LDS f32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = sum;
-        }
+        for (int w = 1; w < 8; w *= 2) all += __shfl_xor(all, w);
+        if (lane == 0) *reinterpret_cast<SPH_LDS int*>(smem + SUMS + wave * 4) = all;
+        if (!is_k && lane < 8) *reinterpret_cast<SPH_LDS i32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = word;
         __syncthreads();
-        const float rows = (float)min(N, BC);
-        const f32x4 ks = __builtin_bit_cast(f32x4, lds_read_b128(smem + SUMS));
-        ek = __builtin_amdgcn_readfirstlane(exponent_to((ks[0] + ks[1] + ks[2] + ks[3]) / (rows * D), 7, 126));
-        if constexpr (MULT) {
-            const f32x4 m0 = load_counts(0, 0), m1 = load_counts(0, 1);
-            float m = 0.f;
+        const i32x4 ks = lds_read_b128(smem + SUMS), vs = lds_read_b128(smem + SUMS + 16);
+        constexpr int LOW = (1 << 20) - 1;
+        int kn = 0, ksum = 0, vn = 0, vsum = 0;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) m += __builtin_fabsf(m0[t]) + __builtin_fabsf(m1[t]);
-            ep = max(-126, ep + __builtin_amdgcn_readfirstlane(exponent_to(sum_across_groups(m) / rows, 1, 0)));
+        for (int e = 0; e < 4; ++e) {
+            kn += ks[e] >> 20;
+            ksum += ks[e] & LOW;
+            vn += vs[e] >> 20;
+            vsum += vs[e] & LOW;
+        }
+        ek = __builtin_amdgcn_readfirstlane(kn > 0 ? max(-126, min(126, 6 - mean_exponent(kn, ksum))) : 0);
+        if constexpr (MULT) {
+            const int key = sampled_key(lane & 31);
+            int m = exponent_word(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, key * 4, 0, 0)));
+#pragma unroll
+            for (int w = 1; w < 32; w *= 2) m += __shfl_xor(m, w);
+            if (m != 0) ep = max(-126, ep + 1 - mean_exponent(m >> 20, m & LOW));
+            ep = __builtin_amdgcn_readfirstlane(ep);
         }
         if (is_k) {
             const float f = power_of_two(ek);
             scale = f32x4{f, f, f, f};
         } else {
             const SPH_LDS unsigned char* sums = smem + COLS + (cg * 32 + c4 * 4) * 4;
-            f32x4 cs = __builtin_bit_cast(f32x4, lds_read_b128(sums));
-            if constexpr (KK == 2) cs += __builtin_bit_cast(f32x4, lds_read_b128(sums + D * 4));
+            i32x4 cs = lds_read_b128(sums);
+            if constexpr (KK == 2) cs += lds_read_b128(sums + D * 4);
+            // A column with few values in the sample is not brought up further than the others (one small value says little of the
+            // rest), one with none not brought down either, so that no value of it becomes zero.
+            const int others = vn > 0 ? 6 - mean_exponent(vn, vsum) : 0;
             i32x4 ev;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                ev[e] = exponent_to(cs[e] / rows, 7, 126);
+                const int elements = cs[e] >> 20, own = elements > 0 ? 6 - mean_exponent(elements, cs[e] & LOW) : max(0, others);
+                ev[e] = max(-126, min(126, elements > 0 && elements < 8 ? min(own, others) : own));
                 scale[e] = power_of_two(ev[e]);
             }
             if (lane < 8) *reinterpret_cast<SPH_LDS i32x4*>(smem + POWERS + (cg * 32 + c4 * 4) * 4) = ev;   // (at KK = 2 by two waves, the same)
@@ -483,9 +506,10 @@ bool f32_two_part_rows(const F32Rows& p)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // Whether the sums over the first `keys` keys are what two parts hold, for the workgroup.
+    // Whether the sums over the first `keys` keys are what two parts hold, for the workgroup.  Before the end a row without any score (left
+    // padding) is not asked yet.
     float z[NQ];
-    auto in_range = [&](int keys) __attribute__((always_inline)) -> bool {
+    auto in_range = [&](int keys, bool end) __attribute__((always_inline)) -> bool {
         if (!is_k) {
             f32x4 all;
 #pragma unroll
@@ -508,8 +532,9 @@ bool f32_two_part_rows(const F32Rows& p)
             z[qb] = sum_across_groups(zacc[qb][0] + zacc[qb][1]);
             // the row's scores against the parts' resolution, and z as it is without the powers of two
             const float whole = __builtin_ldexpf(z[qb], -2 * (ep + eq[qb] + ek));
-            bad |= !qzero[qb] && !(z[qb] >= 0x1p-4f * (float)keys && whole >= 0x1p-100f && whole <= 0x1p100f);
-            const bool counts = q0 + qb * 16 + n16 < Nq && !qzero[qb];
+            const bool asked = !qzero[qb] && (end || z[qb] != 0.f);
+            bad |= asked && !(z[qb] >= 0x1p-4f * (float)keys && whole >= 0x1p-100f && whole <= 0x1p100f);
+            const bool counts = q0 + qb * 16 + n16 < Nq && asked;
             zmin[qb] = counts ? 0x1p-8f * z[qb] : NONE;
             finite += z[qb];
             rows += __builtin_popcountll(__ballot(counts) & 0xffff);
@@ -557,7 +582,8 @@ bool f32_two_part_rows(const F32Rows& p)
         add_rotated(std::integral_constant<int, 4>{}, NQ + 1);
         add_rotated(std::integral_constant<int, 2>{}, NQ + 2);
         add_rotated(std::integral_constant<int, 1>{}, NQ + 3);
-        const int limit = max(2, rows * 3 / 8);
+        // (not before the end: the squares of V are a tile ahead, and a column may have its first values there)
+        const int limit = end ? max(2, rows * 3 / 8) : 16 * NQ;
         uint32_t more = 0, same = ~0u;             // columns whose count is above the limit, or equal so far
 #pragma unroll
         for (int i = NQ + 3; i >= 0; --i) {
@@ -583,7 +609,7 @@ bool f32_two_part_rows(const F32Rows& p)
             vring[1] = vring[0];
             vring[0] = next;
         }
-        held = in_range(min(N, stop * BC));
+        held = in_range(min(N, stop * BC), stop == n_tiles);
         if (!held || stop == n_tiles) break;
         __syncthreads();                           // the answer is read
     }

@@ -139,18 +139,37 @@ def test_columns_without_the_largest_key(pkg, H, Nq, Nk, d, kind, size, value):
 
 
 def _ordinary(kind, H, Nq, Nk, d, seed):
-    """Inputs that programs have."""
+    """Inputs that programs have, with zeros where a sample of the first keys would look."""
     g = torch.Generator(device=DEV).manual_seed(seed)
     q, k, v = (torch.randn((1, H, n, d), generator=g, device=DEV) for n in (Nq, Nk, Nk))
     m = None
-    if kind == "zero columns":
+    if kind.startswith("left padding"):
+        n = int(kind.split()[-1])
+        k[:, :, :n], v[:, :, :n] = 0.0, 0.0
+    elif kind == "right padding":
+        k[:, :, 100:], v[:, :, 100:] = 0.0, 0.0
+    elif kind == "no values at first":
+        v[:, :, :40] = 0.0
+    elif kind == "one late column":
+        v[:, :, :40, 5] = 0.0
+    elif kind == "cut at one":
+        v = (v - 1.0).clamp_min(0.0)
+    elif kind == "one value in twenty":
+        v = v * (torch.rand(v.shape, generator=g, device=DEV) < 0.05)
+    elif kind == "one-hot":
+        v = torch.nn.functional.one_hot(torch.randint(0, d, v.shape[:3], generator=g, device=DEV), d).float()
+    elif kind == "no counts at first":
+        m = torch.poisson(torch.full((1, Nk), 1.5, device=DEV), generator=g)
+        m[:, :100] = 0.0
+    elif kind == "zero columns":
         v[..., 5::16] = 0.0
     elif kind == "late key":                       # (not ordinary: fp16 does not hold it)
         k[:, :, -1] *= 1e6
     return q, k.contiguous(), v.contiguous(), m
 
 
-@pytest.mark.parametrize("kind", ["plain", "zero columns", "late key"])
+@pytest.mark.parametrize("kind", ["plain", "zero columns", "left padding 31", "left padding 100", "left padding 600", "right padding", "no values at first", "one late column",
+                                  "cut at one", "one value in twenty", "one-hot", "no counts at first", "late key"])
 @pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 1024, 128), (16, 4000, 1100, 128), (64, 257, 1825, 64), (16, 4000, 1900, 64)])
 def test_ordinary_values_take_two_parts(pkg, H, Nq, Nk, d, kind):
     """A value of 1e30 in the last row of column 0 sends every workgroup to three parts, whose other columns do not
