@@ -19,12 +19,16 @@
 // power of two of 2^-2 a part's last bit is 2^-24 whatever the value.  So P is off by up to 2^-25 and, through K's last bits,
 // 2^-17 2^-25 |row of Q|, 2^-24.5 at most; V by 2^-25; and an element of O by 2^-24.5 |column of V| and 2^-25 sqrt(z), all scaled, at random
 // signs.  It is in doubt unless o^2 >= 2^-6 |column|^2 + 2^-8 z, above which that is 2^-21 of it in the worst case and 2^-22.5 in the
-// root mean square.  Of normal values 0.4 to 1 % are in doubt, by chance, of one-hot V 2 to 5 %.  More than three eighths of a wave's rows of one column, or an
-// eighth (and four) of a row's columns, are not chance but keys whose scores or values the scales do not fit and which carry that column
-// or row: a key with 1e4 times the others' scores, say, and no value in some columns, which are then formed of
-// the other keys.  Also asked: every row has z >= N / 16 in scaled scores (or is a row of zeros in Q); z without the scales is in
+// root mean square.  Of normal values 0.4 to 1 % are in doubt, by chance, of one-hot V 2 to 5 %.  More than three eighths of a wave's rows of one
+// column, or an eighth (and four) of a row's columns, are not chance but keys whose scores or values the scales do not fit and which
+// carry that column or row: a key with 1e4 times the others' scores, say, and no value in some columns, which are then
+// formed of the other keys.  (So that every wave has rows to count, rows past the last query are the head's first ones again; and a
+// column whose squares come to zero is looked at a second time, as those of values below 2^-75 do: with a quarter of
+// the columns zeros 1.5 to 3 % of the time, 6 % with zeros in all places.  Told apart in the loop by a second instruction per value: 1.6 % of every call.)
+// Also asked: every row has z >= N / 16 in scaled scores (or is a row of zeros in Q); z without the scales is in
 // [2^-100, 2^100]; no element is NaN (a value beyond fp16 leaves inf - inf).  If any wave of a workgroup sees one of these fail, after
-// 512 keys (columns not yet) or at the end, the workgroup does its rows again in three parts, and from there with the fp32 instruction.
+// 512 keys (columns not yet; not on axes below 1024 keys) or at the end, the workgroup does its rows again in three parts, and from there with the fp32
+// instruction.
 //
 // 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
 // more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products
@@ -191,6 +195,12 @@ __device__ __forceinline__ int exponent_to(float x, int to)
 template <int N>
 __device__ __forceinline__ int lane_rotated(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x120 + N, 0xf, 0xf, true); }
 
+// One more bit at the low end of `bits`: whether a >= b does not hold.
+__device__ __forceinline__ void append_unless(uint32_t& bits, float a, float b)
+{
+    asm("v_cmp_nge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(a), "v"(b) : "vcc");
+}
+
 // What a workgroup works on: its head's rows of Q, O and Z (null: not wanted), its keys, and its first row.
 struct F32Rows {
     const float* Q; const float* K; const float* V; const float* mult; float* O; float* Z;
@@ -239,14 +249,14 @@ bool f32_two_part_rows(const F32Rows& p)
     auto raw_unit = [&](int u, int buffer) {
         return __builtin_bit_cast(f32x4, lds_read_b128(smem + RAW + buffer * 4 * IMG + (wave * UPW + u) * 1024 + lane * 16));
     };
-    // whether any wave of the workgroup says so (a barrier between the two)
-    auto say = [&](bool yes) { *reinterpret_cast<SPH_LDS int*>(smem + FLAGS + wave * 4) = __any(yes); };
-    auto anyone = [&]() -> bool {
+    // what the waves of the workgroup say, together (a barrier between the two)
+    auto say = [&](int what) { *reinterpret_cast<SPH_LDS int*>(smem + FLAGS + wave * 4) = what; };
+    auto heard = [&]() -> int {
         const i32x4 a = lds_read_b128(smem + FLAGS), b = lds_read_b128(smem + FLAGS + 16);
-        return __builtin_amdgcn_readfirstlane(a[0] | a[1] | a[2] | a[3] | b[0] | b[1] | b[2] | b[3]) != 0;
+        return __builtin_amdgcn_readfirstlane(a[0] | a[1] | a[2] | a[3] | b[0] | b[1] | b[2] | b[3]);
     };
-    // factors of the lane's four columns (of K: all the same), and the squares of V's columns, scaled (an element below 1
-    // counts as itself, so that only a column of zeros is 0)
+    constexpr int OUTSIDE = 1, ZEROS = 2;
+    // factors of the lane's four columns (of K: all the same), and the squares of V's columns, scaled
     f32x4 scale = {1.f, 1.f, 1.f, 1.f}, colsq = {0.f, 0.f, 0.f, 0.f};
     // The same units split into the images of the set at `set` (K's, V's): a row group is 8 rows of a 16-row block, whose other 8 rows lie 512 bytes
     // on in a K block (the same permutation of pieces) and 256 in a V block; the next block row D * 32.
@@ -259,7 +269,7 @@ bool f32_two_part_rows(const F32Rows& p)
             SPH_LDS unsigned char* dst = smem + (is_k ? kset : vset) + at + ((rg0 + u) >> 1) * D * 32 + (u & 1) * odd_rows;
             x *= scale;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) colsq[e] = __builtin_fmaf(__builtin_fabsf(x[e]), fmaxf(__builtin_fabsf(x[e]), 1.f), colsq[e]);
+            for (int e = 0; e < 4; ++e) colsq[e] = __builtin_fmaf(x[e], x[e], colsq[e]);
             const Split2 lo = split2(x[0], x[1]), hi = split2(x[2], x[3]);
             *reinterpret_cast<SPH_LDS i32x2*>(dst) = i32x2{lo.p0, hi.p0};
             *reinterpret_cast<SPH_LDS i32x2*>(dst + IMG) = i32x2{lo.p1, hi.p1};
@@ -288,7 +298,8 @@ bool f32_two_part_rows(const F32Rows& p)
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
         int row = q0 + qb * 16 + n16;
-        row = row < Nq ? row : Nq - 1;             // rows past the end are computed and dropped
+        if (p.q0 + kF32Waves * 16 * NQ > Nq)       // past the end the head's first rows again: computed, asked like any other, and dropped
+            row = row < Nq ? row : row % Nq;
         const float* src = p.Q + (size_t)row * D + 8 * g;
         f32x4 x[KK][2];
         float most = 0.f;
@@ -506,26 +517,28 @@ bool f32_two_part_rows(const F32Rows& p)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    // Whether the sums over the first `keys` keys are what two parts hold, for the workgroup.  Before the end a row without any score (left
+    // For the workgroup: OUTSIDE where the sums over the first `keys` keys are not what two parts hold, ZEROS where squares of V came to zero.  Before the end a row without any score (left
     // padding) is not asked yet.
     float z[NQ];
-    auto in_range = [&](int keys, bool end) __attribute__((always_inline)) -> bool {
+    auto in_range = [&](int keys, bool end) __attribute__((always_inline)) -> int {
+        bool bad = false, zero = false;
         if (!is_k) {
             f32x4 all;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {          // over the unit's rows
                 const float sum = colsq[e];        // (a bit cast of the vector's element itself takes element 0)
                 all[e] = sum_across_groups(sum + __builtin_bit_cast(float, lane_rotated<8>(__builtin_bit_cast(int, sum))));
+                zero |= all[e] == 0.f;
             }
             if (lane < 8) *reinterpret_cast<SPH_LDS f32x4*>(smem + COLS + ((wave & 3) / KK * D + cg * 32 + c4 * 4) * 4) = all;
         }
         __syncthreads();
-        bool bad = false;
         // An element of O is in doubt where it is not well above what the last bits of P (2^-25, times the column) and of V (times the row's
-        // scores) come to.  Rows past the end, rows of zeros and columns of zeros have none.
+        // scores) come to.  Rows of zeros and columns of zeros have none.
         constexpr float NONE = -__builtin_inff();
         float zmin[NQ], finite = 0.f;
-        int rows = 0, columns = 0;
+        int rows = 0;
+        uint32_t zeros = 0;
         uint32_t doubts[NQ];                       // of the lane's columns, a bit each
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
@@ -534,10 +547,9 @@ bool f32_two_part_rows(const F32Rows& p)
             const float whole = __builtin_ldexpf(z[qb], -2 * (ep + eq[qb] + ek));
             const bool asked = !qzero[qb] && (end || z[qb] != 0.f);
             bad |= asked && !(z[qb] >= 0x1p-4f * (float)keys && whole >= 0x1p-100f && whole <= 0x1p100f);
-            const bool counts = q0 + qb * 16 + n16 < Nq && asked;
-            zmin[qb] = counts ? 0x1p-8f * z[qb] : NONE;
+            zmin[qb] = asked ? 0x1p-8f * z[qb] : NONE;
             finite += z[qb];
-            rows += __builtin_popcountll(__ballot(counts) & 0xffff);
+            rows += __builtin_popcountll(__ballot(asked) & 0xffff);
             doubts[qb] = 0;
         }
 #pragma unroll
@@ -547,19 +559,20 @@ bool f32_two_part_rows(const F32Rows& p)
             if constexpr (KK == 2) cs += __builtin_bit_cast(f32x4, lds_read_b128(sums + D * 4));
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const float vmin = cs[t] == 0.f ? NONE : 0x1p-6f * cs[t];
-                columns += cs[t] == 0.f ? 0 : 1;
+                const float above_zero = cs[t] == 0.f ? -NONE : -0x1p-6f * cs[t];
+                append_unless(zeros, cs[t], 0x1p-149f);
 #pragma unroll
                 for (int qb = 0; qb < NQ; ++qb) {
-                    const float above = __builtin_fmaf(oacc[db][qb][t], oacc[db][qb][t], -(vmin + zmin[qb]));
-                    doubts[qb] += doubts[qb] + (above >= 0.f ? 0u : 1u);
-                    finite += above;               // (infinite where there is nothing to doubt)
+                    const float above = __builtin_fmaf(oacc[db][qb][t], oacc[db][qb][t], above_zero);
+                    append_unless(doubts[qb], above, zmin[qb]);
+                    // (a value that fp16 does not hold leaves NaN in its column of every row, a score in its whole row)
+                    if (qb == 0 || (db == 0 && t == 0)) finite += above;
                 }
             }
         }
         bad |= finite != finite;
         // In doubt at most: an eighth of a row's columns and four, and three eighths of the wave's rows of a column, counted bit by bit over the rows
-        const float most = sum_across_groups((float)columns) * 0.125f + 4.f;
+        const float most = ((float)D - sum_across_groups((float)__builtin_popcount(zeros))) * 0.125f + 4.f;
         uint32_t n[6] = {doubts[0], 0, 0, 0, 0, 0};
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) bad |= sum_across_groups((float)__builtin_popcount(doubts[qb])) > most;
@@ -583,7 +596,7 @@ bool f32_two_part_rows(const F32Rows& p)
         add_rotated(std::integral_constant<int, 2>{}, NQ + 2);
         add_rotated(std::integral_constant<int, 1>{}, NQ + 3);
         // (not before the end: the squares of V are a tile ahead, and a column may have its first values there)
-        const int limit = end ? max(2, rows * 3 / 8) : 16 * NQ;
+        const int limit = end ? rows * 3 / 8 : 16 * NQ;
         uint32_t more = 0, same = ~0u;             // columns whose count is above the limit, or equal so far
 #pragma unroll
         for (int i = NQ + 3; i >= 0; --i) {
@@ -592,14 +605,14 @@ bool f32_two_part_rows(const F32Rows& p)
             same &= ~(n[i] ^ bit);
         }
         bad |= more != 0;
-        say(bad);
+        say((__any(bad) ? OUTSIDE : 0) | (__any(zero) ? ZEROS : 0));
         __syncthreads();
-        return !anyone();
+        return heard();
     };
     // Asked at the end, and on long key axes once early, so that values that two parts cannot hold cost little more than
     // three parts do (a loop in a loop: asked inside one, d = 64 lost 4 %).
     constexpr int EARLY = 16;                      // tiles
-    bool held;
+    int found;
     for (int j = 0, stop = n_tiles < 2 * EARLY ? n_tiles : EARLY;; stop = n_tiles) {
         for (; j < stop; j += 2) {
             tile_phase(std::integral_constant<int, 0>{}, j);
@@ -609,12 +622,36 @@ bool f32_two_part_rows(const F32Rows& p)
             vring[1] = vring[0];
             vring[0] = next;
         }
-        held = in_range(min(N, stop * BC), stop == n_tiles);
-        if (!held || stop == n_tiles) break;
+        found = in_range(min(N, stop * BC), stop == n_tiles);
+        if ((found & OUTSIDE) || stop == n_tiles) break;
         __syncthreads();                           // the answer is read
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);            // the copies past the end must not land in what follows
-    if (!held) {
+    // Squares of values below 2^-75 vanish: are these columns zeros?  All waves look at the 32 columns around each again.
+    if (found == ZEROS) {
+        __syncthreads();                           // the answer is read
+        bool values = false;
+#pragma unroll 1
+        for (int group = 0; group < KK; ++group) {
+            const int column = group * 32 + c4 * 4;
+            f32x4 sums = __builtin_bit_cast(f32x4, lds_read_b128(smem + COLS + column * 4));
+            if constexpr (KK == 2) sums += __builtin_bit_cast(f32x4, lds_read_b128(smem + COLS + (D + column) * 4));
+            if (!__any(sums[0] == 0.f || sums[1] == 0.f || sums[2] == 0.f || sums[3] == 0.f)) continue;
+            uint32_t bits[4] = {0, 0, 0, 0};
+#pragma unroll 8
+            for (int key = wave * 8 + rowin; key < N; key += 64) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p.V + (size_t)key * D + column);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bits[e] |= doubled_bits(x[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) values |= sums[e] == 0.f && bits[e] != 0;
+        }
+        say(__any(values) ? OUTSIDE : 0);
+        __syncthreads();
+        found = heard();
+    }
+    if (found & OUTSIDE) {
         __syncthreads();                           // the flags are read, the LDS is free
         return false;
     }

@@ -49,13 +49,16 @@ def _inputs(kind, H, Nq, Nk, d, seed):
         v[:, :, Nk // 3:] *= 1e-3
     elif kind == "late":                           # one late key beyond fp16 at the first tile's scale
         k[:, :, -1] *= 1e6
+    elif kind == "tiny column":                    # a column whose one value vanishes beside the others
+        v[..., 5] = 0.0
+        v[:, :, 7, 5] = 1e-30
     elif kind == "counts":
         m = torch.poisson(torch.full((1, Nk), 1.5, device=DEV), generator=g)
         m[:, 0], m[:, Nk // 2] = 2.0, 5000.0
     return q, k, v, m
 
 
-@pytest.mark.parametrize("kind", ["plain", "columns", "zero columns", "rows", "outliers", "unseen value", "unscored", "unvalued", "growing", "late", "counts"])
+@pytest.mark.parametrize("kind", ["plain", "columns", "zero columns", "rows", "outliers", "unseen value", "unscored", "unvalued", "growing", "late", "tiny column", "counts"])
 @pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 512, 128), (40, 391, 577, 128), (130, 300, 640, 128), (32, 512, 1792, 64), (64, 257, 1825, 64)])
 def test_columns_against_64_bits(pkg, H, Nq, Nk, d, kind):
     print(f"case two parts {H} x {Nq} of {Nk} x {d} {kind}", flush=True)
