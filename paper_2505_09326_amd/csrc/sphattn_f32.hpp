@@ -30,8 +30,8 @@
 // 512 keys (columns not yet; not on axes below 1024 keys) or at the end, the workgroup does its rows again in three parts, and from there with the fp32
 // instruction.
 //
-// 8 x 4096 x 128: 284 us in three parts, 178 in two (given up after 512 keys and done in three: 11 %
-// more than three parts alone; d = 64 14 %); 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  The products
+// 8 x 4096 x 128: 284 us in three parts, 178 in two; 8 x 4096 x 64 171 and 109, 16 x 4000 x 128 534 and 324.  Given up after 512
+// keys and done in three parts 10 to 13 % more than three parts alone; given up at the end, as is everything below 1024 keys, 60 to 65 %.  The products
 // alone are 82 us of the 178 at 2.5 PFLOP/s; between them each SIMD splits the next tile and the scores.
 //
 // Three parts.  An fp32 value is the exact sum of three bf16 values, x = x0 + x1 + x2 (each the rest before it, rounded to bf16), so
@@ -683,16 +683,15 @@ void fwd_f32x3_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
                       float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
                       int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
 {
-    constexpr int TILE = kF32Waves * 16 * NQ, first = 0;
 #include "sphattn_f32_three.inc"
 }
 
 // The same for a call from a kernel.
-template <int D, int NQ, int TILE, bool MULT, bool PARTIAL>
+template <int D, int NQ, bool MULT, bool PARTIAL>
 __device__ __forceinline__
 void f32_three_part_rows(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
                          float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
-                         int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split, int first)
+                         int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
 {
 #include "sphattn_f32_three.inc"
 }
@@ -704,7 +703,6 @@ void fwd_f32x2_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
                       float* __restrict__ O, const float* __restrict__ mult, float* __restrict__ Zv,
                       int Nq, int Nk, int H, int kv_group, int n_qtiles, int n_wg, int n_splits, int keys_per_split)
 {
-    constexpr int TILE = kF32Waves * 16 * NQ;
     {
         const int lid = xcd_contiguous_id(blockIdx.x, n_wg), qt = lid % n_qtiles;
         const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
@@ -713,16 +711,11 @@ void fwd_f32x2_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
         const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
         const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq : (size_t)bh * Nq;
         const F32Rows p{Q + (size_t)bh * Nq * D, K + kv_off, V + kv_off, MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, O + rows0 * D,
-                        Zv != nullptr ? Zv + rows0 : nullptr, Nq, PARTIAL ? min(Nk - k0, keys_per_split) : Nk, qt * TILE};
+                        Zv != nullptr ? Zv + rows0 : nullptr, Nq, PARTIAL ? min(Nk - k0, keys_per_split) : Nk, qt * (kF32Waves * 16 * NQ)};
         if (f32_two_part_rows<D, NQ, MULT, PARTIAL>(p)) return;
     }
-    // (256 rows of d = 128 in three parts do not fit the registers beside what the call above leaves: 128 at a time)
-    constexpr int NB = D == 128 ? 1 : NQ;
-#pragma unroll 1
-    for (int first = 0; first < TILE; first += kF32Waves * 16 * NB) {
-        f32_three_part_rows<D, NB, TILE, MULT, PARTIAL>(Q, K, V, O, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_wg, n_splits, keys_per_split, first);
-        __syncthreads();                           // every wave has read the LDS that the next rows overwrite
-    }
+    // (All rows at once, which keeps 20 bytes a lane in scratch for 256 rows of d = 128: 128 at a time, without, took 18 % longer.)
+    f32_three_part_rows<D, NQ, MULT, PARTIAL>(Q, K, V, O, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_wg, n_splits, keys_per_split);
 }
 
 }  // namespace sphattn

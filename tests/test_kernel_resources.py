@@ -114,6 +114,14 @@ def test_f32_kernels(usage):
                 assert _num(v, "Occupancy [waves/SIMD]") >= (waves if "small" in kernel else 1), name
 
 
+def test_f32_kernels_in_two_parts(usage):
+    # the same shapes; scratch only in 256 rows of d = 128, once per tile of the way out to three parts
+    for d, nq, waves in ((128, 1, 2), (128, 2, 2), (64, 1, 4), (64, 2, 2)):
+        for name, v in _find(usage, "fwd_f32x2_kernel", f"ILi{d}ELi{nq}E").items():
+            assert _num(v, "ScratchSize [bytes/lane]") <= (20 if (d, nq) == (128, 2) else 0), name
+            assert _num(v, "Occupancy [waves/SIMD]") >= waves, name
+
+
 def test_backward_kernels(usage):
     # dK/dV: two workgroups per CU at d = 128, with and without multiplicities, (almost) no scratch
     for name, v in _find(usage, "bwd_dkv_kernelILi128E").items():
