@@ -8,6 +8,7 @@
 #include "sphattn_softmax32.hpp"
 #include "sphattn_backward.hpp"
 #include "sphattn_fp8.hpp"
+#include "sphattn_choice.hpp"
 #include "../../include/sphattn.h"
 
 #include <stdint.h>
@@ -19,6 +20,8 @@ namespace {
 using namespace sphattn;
 
 constexpr int kVersion = 510;   // 0.5.1
+
+static_assert(kBC == kChoiceTile && kF32Tile == kChoiceF32Tile, "times per tile of the kernels' tiles");
 
 // [a, a+an) and [b, b+bn) share a byte.  Written with differences, so that a range reaching the
 // top of the address space cannot wrap the comparison.
@@ -334,38 +337,6 @@ int launch_f32_parts(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// fp32 storage has four workgroup shapes: 16 or 32 rows on the fp32 matrix instruction with the keys dealt
-// to the waves (the least latency: the launches that cannot give every CU more than that), and 128
-// or 256 rows in two fp16 or three bf16 parts.  Time of one round per 32-key tile, in us, as measured on launches
-// that fill a small and the whole part of the CUs (f): d = 128 0.9, 1.42 on the fp32 instruction, 1.4 to 1.7, 2.0 to 2.6 in two
-// parts, 2.05 to 2.55, 3.5 to 4.3 in three (without the watch that adds 2 %); d = 64 0.35, 0.68; 0.69 to 0.87, 1.0 to 1.38; 1.1 to 1.3, 1.85 to 2.25.
-// Rounds times that picks the shape (32 rows, 128 and 256 in two parts, in three: 8 heads of 4096 x 128 704, 217 and
-// 275, 328 and 452 us; 16 heads 1396, 433 and 333, 652 and 551; 4 heads of 4096 x 64 167, 99 and 150, 150 and 243; in three parts 1 x 8192 x
-// 128 352, 553, 888, 16 rows 467; 4 x 1000 x 128 52, 73, 119, 16 rows 33).  S slices: S times the items, 1 / S of the tiles.
-//
-// Two parts wherever the results are then no further from 64 bits.  Error of O (relative 2-norm) with three / two parts:
-// d = 128 1.73e-7 / 1.79e-7 at 200 keys, 1.85 / 1.84 at 500, 2.01 / 1.92 at 1000, 2.98 / 2.45 at 5000; d = 64
-// 1.62 / 1.71 at 1000, 1.77 / 1.79 at 1500, 2.10 / 1.95 at 2500; z from 200 keys on closer with two.
-bool f32_two_parts(long long keys, int d) { return keys >= (d == 128 ? 512 : 1792); }
-struct F32Choice { int rows; double us; };
-F32Choice choose_f32(long long heads, long long Nq, long long keys_per_slice, long long S, int d, long long n_cus)
-{
-    const double cus = (double)n_cus, tiles = (double)((keys_per_slice + kF32Tile - 1) / kF32Tile);
-    const bool two = f32_two_parts(keys_per_slice, d);
-    F32Choice best{32, 1e30};
-    for (const int rows : {16, 32, 128, 256}) {
-        const double items = (double)(heads * ((Nq + rows - 1) / rows) * S);
-        const double f = items < cus ? items / cus : 1.0;
-        double tau = d == 128 ? (rows == 16 ? 0.9 : rows == 32 ? 1.42 : rows == 128 ? 2.05 + 0.5 * f : 3.5 + 0.8 * f)
-                              : (rows == 16 ? 0.35 : rows == 32 ? 0.68 : rows == 128 ? 1.1 + 0.2 * f : 1.85 + 0.4 * f);
-        if (two && rows == 128) tau = d == 128 ? 1.4 + 0.28 * f : 0.69 + 0.18 * f;
-        if (two && rows == 256) tau = d == 128 ? 2.0 + 0.6 * f : 1.0 + 0.38 * f;
-        const double us = __builtin_ceil(items / cus) * tiles * tau;
-        if (us < best.us) best = F32Choice{rows, us};
-    }
-    return best;
-}
-
 template <int D, bool MULT, bool PARTIAL>
 int launch_f32_any(const Problem& p)
 {
@@ -391,54 +362,6 @@ int launch_softmax32(const Problem& p)
     hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kThreads), lds_bytes, p.stream,
                        p.Q, p.K, p.V, p.O, p.Nq, n_qtiles, (int)n_wg, scale_log2);
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
-}
-
-// How a launch of 16-bit or fp8-Q/K storage is laid out.  256 query rows (fwd_pipelined_kernel) is the shape of a full chip; the
-// others (sphattn_keysplit.hpp) deal the keys of a tile to groups of waves, and pay while all their workgroups run at
-// once, one per CU (two in Rows64 at d = 64).  Rows64 has two key groups of two waves; Rows64Wide four of two, so two
-// waves per SIMD; Rows64Own four of one wave with all 64 rows, which reads every K and V byte from LDS once (d = 128, where LDS and
-// copies are the bound); Rows128 two of two, Rows128Wide four of two (d = 64); Rows256Wide two key groups of four waves
-// (d = 64).  Narrow: 128 rows in four waves of 32 over all keys (bf16 without counts), which reads every fragment for
-// two query blocks only, but starts with less.
-enum Form { kRows64, kRows64Wide, kRows64Own, kRows128, kRows128Wide, kNarrow, kRows256Wide, kRows256, kForms };
-constexpr int kFormRowsLog2[kForms] = {6, 6, 6, 7, 7, 7, 8, 8};
-
-// Time of a launch that runs at once, in us: start + tiles (tile + share f of the CUs), the tiles of 64 keys rounded up to what the
-// form's loop does at a time.  Fitted to 929 launches of bf16 and fp8 Q/K with and without counts (1 to 128 heads of 100 to 12000
-// keys, every form timed on each): 1 to 4 % off in the root mean square, and what this picks is 0.0 to 0.6 % slower
-// than the best form.  tile 0: the form does not exist.  f16 measures like bf16.
-struct FormCost { float start, tile, share; };
-constexpr FormCost kFormCost[2][2][2][kForms] = {   // [d = 128][fp8 Q/K][counts]
-    {{{{3.7f, .253f, .04f}, {4.5f, .162f, .05f}, {0, 0, 0}, {4.3f, .341f, .06f}, {5.5f, .262f, .08f}, {3.8f, .383f, .07f}, {5.0f, .453f, .15f}, {4.8f, .536f, .15f}},
-      {{3.7f, .343f, .04f}, {4.7f, .228f, .05f}, {0, 0, 0}, {4.6f, .473f, .05f}, {5.8f, .324f, .07f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.7f, .728f, .09f}}},
-     {{{3.6f, .230f, .04f}, {4.4f, .159f, .04f}, {0, 0, 0}, {4.5f, .322f, .05f}, {5.9f, .247f, .07f}, {0, 0, 0}, {5.0f, .453f, .15f}, {4.9f, .561f, .07f}},
-      {{3.7f, .304f, .03f}, {4.6f, .197f, .04f}, {0, 0, 0}, {5.4f, .440f, .05f}, {6.1f, .313f, .08f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.9f, .729f, .07f}}}},
-    {{{{4.7f, .370f, .09f}, {5.7f, .277f, .13f}, {6.5f, .276f, .11f}, {5.9f, .519f, .14f}, {0, 0, 0}, {4.7f, .506f, .20f}, {0, 0, 0}, {6.6f, .927f, .35f}},
-      {{5.0f, .447f, .09f}, {5.7f, .334f, .14f}, {6.6f, .318f, .11f}, {6.1f, .616f, .11f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.6f, 1.06f, .31f}}},
-     {{{0, 0, 0}, {0, 0, 0}, {5.9f, .224f, .07f}, {5.5f, .446f, .10f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .692f, .24f}},
-      {{0, 0, 0}, {0, 0, 0}, {6.1f, .263f, .07f}, {5.6f, .533f, .09f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .813f, .23f}}}}};
-
-struct FormChoice { Form form; double us; };
-struct Storage { bool bf16, fp8, counts; };
-FormChoice choose_form(long long slices, long long Nq, long long tiles, int d, Storage st, long long cus)
-{
-    FormChoice best{kRows256, 0.0};
-    if (slices * ((Nq + 255) / 256) > cus) return best;    // a full chip: rounds of 256 rows
-    best.us = 1e30;
-    const double per_cu = 1.0 / (double)cus;   // (no divisions by variables: this runs on every call)
-    for (int form = 0; form < kForms; ++form) {
-        const FormCost c = kFormCost[d == 128][st.fp8][st.counts][form];
-        const long long items = slices * ((Nq + (1 << kFormRowsLog2[form]) - 1) >> kFormRowsLog2[form]);
-        // two on a CU at d = 64: Narrow, and Rows64 for what has no Narrow.  They take 1.5 and 1.8 times as long as one (100 x 300 x 64
-        // bf16 7.5 us, 8.5 on 256 rows; 64 x 500 x 64 fp8 7.6, 8.0 on 128 rows; 12 x 3000 x 64 fp8 with counts 34.8, 39.4)
-        const double both = d != 64 ? 0.0 : form == kNarrow ? 1.5 : form == kRows64 && !(st.bf16 && !st.counts) ? 1.8 : 0.0;
-        if (c.tile == 0 || (form == kNarrow && !st.bf16) || items > (both > 0.0 ? 2 * cus : cus)) continue;
-        const long long step = form == kRows64Wide || form == kRows64Own || form == kRows128Wide ? 4 : form == kNarrow || form == kRows256 ? 1 : 2;
-        const double n = (double)((tiles + step - 1) & -step), f = items > cus ? 1.0 : (double)items * per_cu;
-        const double us = c.start + n * (c.tile + c.share * f) * (items > cus ? both : 1.0);
-        if (us < best.us) best = FormChoice{(Form)form, us};
-    }
-    return best;
 }
 
 template <int D, QKType QKT, bool MULT, bool PARTIAL>

@@ -1,0 +1,52 @@
+"""csrc/sphattn_choice.hpp, the code that picks a launch's kernel, compiled for the host: which form a call takes on a device of
+256 compute units."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+from paper_2505_09326_amd._build import CSRC
+
+FORMS = ("Rows64", "Rows64Wide", "Rows64Own", "Rows128", "Rows128Wide", "Narrow", "Rows256Wide", "Rows256")
+ROWS = (64, 64, 64, 128, 128, 128, 256, 256)
+CUS = 256
+
+SOURCE = """
+#include "sphattn_choice.hpp"
+using namespace sphattn;
+extern "C" int form(long long slices, long long Nq, long long Nk, int d, int bf16, int fp8, int counts)
+{
+    return choose_form(slices, Nq, (Nk + kChoiceTile - 1) / kChoiceTile, d, Storage{bf16 != 0, fp8 != 0, counts != 0}, %d).form;
+}
+extern "C" int f32_rows(long long heads, long long Nq, long long Nk, int d) { return choose_f32(heads, Nq, Nk, 1, d, %d).rows; }
+extern "C" int two_parts(long long Nk, int d) { return f32_two_parts(Nk, d); }
+""" % (CUS, CUS)
+
+
+@functools.lru_cache(maxsize=None)
+def _library():
+    with tempfile.TemporaryDirectory() as tmp:
+        src, out = os.path.join(tmp, "choice.cpp"), os.path.join(tmp, "choice.so")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", out, src], check=True)
+        lib = ctypes.CDLL(out)
+    lib.form.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
+    lib.f32_rows.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
+    lib.two_parts.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    return lib
+
+
+def form(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
+    """The form's name, and whether two of its workgroups share a CU.  Query heads of one K/V head are one block of rows."""
+    rows = Nq * (H // H_kv)
+    f = _library().form(H_kv, rows, Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts)
+    return FORMS[f], f != len(FORMS) - 1 and H_kv * -(-rows // ROWS[f]) > CUS
+
+
+def f32_rows(H, Nq, Nk, d):
+    """Query rows per workgroup of an fp32 launch, and whether it works in two parts."""
+    lib = _library()
+    rows = lib.f32_rows(H, Nq, Nk, d)
+    return rows, rows >= 128 and bool(lib.two_parts(Nk, d))

@@ -59,7 +59,7 @@ def _inputs(kind, H, Nq, Nk, d, seed):
 
 
 @pytest.mark.parametrize("kind", ["plain", "columns", "zero columns", "rows", "outliers", "unseen value", "unscored", "unvalued", "growing", "late", "tiny column", "counts"])
-@pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 512, 128), (40, 391, 577, 128), (130, 300, 640, 128), (32, 512, 1792, 64), (64, 257, 1825, 64)])
+@pytest.mark.parametrize("H,Nq,Nk,d", [(32, 512, 512, 128), (40, 391, 577, 128), (130, 300, 640, 128), (16, 4000, 1100, 128), (32, 512, 1792, 64), (64, 257, 1825, 64), (16, 4000, 1900, 64)])
 def test_columns_against_64_bits(pkg, H, Nq, Nk, d, kind):
     print(f"case two parts {H} x {Nq} of {Nk} x {d} {kind}", flush=True)
     q, k, v, m = _inputs(kind, H, Nq, Nk, d, 6000 + Nk + d)

@@ -15,10 +15,13 @@ DEV = "cuda:0"
 U = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11, "fp8qk_bf16v": 2.0 ** -8}
 
 # H, H_kv, N_q, N_k, d
-SHAPES = [(2, 2, 64, 641, 64), (3, 3, 130, 575, 64), (4, 2, 200, 1025, 64), (256, 256, 33, 700, 64),   # 64 rows, four key groups
+# (what each takes depends on storage and counts as well; test_launch_choice.py holds that every form of every storage is among them)
+SHAPES = [(2, 2, 64, 641, 64), (3, 3, 130, 575, 64), (4, 2, 200, 1025, 64), (256, 256, 33, 700, 64),   # 64 rows, two and four key groups
           (2, 2, 63, 900, 128), (4, 1, 65, 1153, 128), (250, 250, 64, 1600, 128),
-          (1, 1, 70, 150, 128), (2, 2, 64, 257, 128), (50, 50, 300, 4600, 128), (128, 64, 17, 4097, 128),   # one row group
-          (20, 20, 999, 1300, 64), (6, 3, 3000, 1281, 64),                                             # 128 rows, four key groups
+          (1, 1, 70, 150, 128), (2, 2, 64, 257, 128), (50, 50, 300, 4600, 128), (128, 64, 17, 4097, 128),   # the same, and one row group
+          (20, 20, 999, 1300, 64), (6, 3, 3000, 1281, 64),                                             # 128 rows, four key groups with counts
+          (64, 64, 290, 1985, 64), (64, 64, 289, 310, 64), (16, 8, 2000, 1990, 128), (64, 64, 290, 61, 128),   # four without, and two
+          (64, 64, 290, 61, 64), (1, 1, 33, 60, 64), (1, 1, 33, 61, 128),                              # two workgroups on a CU; a single tile
           (100, 100, 400, 1000, 64), (64, 64, 1024, 449, 64), (12, 3, 5003, 129, 64)]                  # 256 rows, two key groups
 
 

@@ -1,0 +1,40 @@
+"""The GPU tests of the forward's forms and of fp32 in two parts run the kernels that they are there for (no GPU needed)."""
+import itertools
+
+import pytest
+
+import launch_choice
+import test_gpu_f32_two_parts as two_parts
+import test_gpu_forward_forms as forms
+
+
+@pytest.mark.parametrize("partial", [False, True])
+@pytest.mark.parametrize("counts", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "fp8qk_bf16v"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_every_form_has_a_shape(d, dtype, counts, partial):
+    """Whatever a launch may take, over a grid of sizes, one of the tested shapes takes too."""
+    reached = {launch_choice.form(h, h, nq, nk, d, dtype, counts, partial)
+               for h, nq, nk in itertools.product((1, 2, 4, 8, 12, 20, 40, 64, 100, 200), (33, 64, 100, 300, 500, 999, 2000, 4000),
+                                                  (60, 150, 300, 500, 700, 1000, 1300, 2000, 3000, 4600, 7000))}
+    tested = {launch_choice.form(H, H_kv, Nq, Nk, d, dtype, counts, partial) for H, H_kv, Nq, Nk, dd in forms.SHAPES if dd == d}
+    reached.discard(("Rows256", False))            # (fwd_pipelined_kernel has tests of its own)
+    assert len(reached) >= (2 if dtype == "fp8qk_bf16v" and d == 128 else 3)
+    assert reached <= tested, reached - tested
+
+
+def _shapes(test):
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0].startswith("H,Nq,Nk,d"))
+
+
+@pytest.mark.parametrize("test", [two_parts.test_columns_against_64_bits, two_parts.test_columns_without_the_largest_key,
+                                  two_parts.test_ordinary_values_take_two_parts])
+def test_fp32_shapes_take_two_parts(test):
+    """128 rows and 256 rows at both head dims, ragged in the second half of 256; and at d = 128 an axis with the early check (1024 keys)."""
+    shapes = _shapes(test)
+    taken = {(d, launch_choice.f32_rows(H, Nq, Nk, d)) for H, Nq, Nk, d in shapes}
+    assert taken == {(d, (rows, True)) for d in (64, 128) for rows in (128, 256)}
+    for H, Nq, Nk, d in shapes:
+        if launch_choice.f32_rows(H, Nq, Nk, d)[0] == 256:
+            assert Nq % 256 > 128
+    assert any(d == 128 and Nk >= 1024 for H, Nq, Nk, d in shapes)
