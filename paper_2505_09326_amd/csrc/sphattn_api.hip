@@ -371,8 +371,7 @@ int launch_spherical(const Problem& p)
     const long long slices = (long long)p.B * p.H * p.n_splits, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
     Form form = p.tile_rows == 128 ? kRows128 : p.tile_rows == 256 ? kRows256
               : choose_form(slices, p.Nq, tiles, D, Storage{BF16 && !PARTIAL, FP8, MULT}, cus).form;
-    // (the 256-row kernel's order of a row's terms, which Narrow has too: 4 x 1999 x 128 22.3 us, 38.2 on 256 rows)
-    if (p.one_key_order && form != kRows256) form = BF16 && !MULT && !PARTIAL ? kNarrow : kRows256;
+    if (p.one_key_order) form = in_one_key_order(form, tiles, BF16 && !MULT && !PARTIAL);
     if constexpr (BF16 && !MULT && !PARTIAL)
         if (form == kNarrow) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
     if constexpr (!(FP8 && D == 128)) {

@@ -54,6 +54,15 @@ inline FormChoice choose_form(long long slices, long long Nq, long long tiles, i
     return best;
 }
 
+// The same for a launch that has to add a row's terms in the order of kRows256, as Narrow does too (where the launch has it).  Narrow where it is one
+// workgroup per CU (4 x 1999 x 128 22.3 us, 38.2 on 256 rows); two on a CU in place of kRows256Wide, on short key axes only (Narrow / 256 rows,
+// d = 64: 32 x 2048 30.7 / 31.6, 24 x 2500 35.5 / 36.1, then 20 x 3000 39.2 / 37.1, 8 x 6000 65.2 / 60.3, 3 x 20000 235 / 226).
+inline Form in_one_key_order(Form form, long long tiles, bool has_narrow)
+{
+    if (form == kRows256 || !has_narrow) return kRows256;
+    return form != kRows256Wide || tiles <= 40 ? kNarrow : kRows256;
+}
+
 // fp32 storage has four workgroup shapes: 16 or 32 rows on the fp32 matrix instruction with the keys dealt
 // to the waves (the least latency: the launches that cannot give every CU more than that), and 128
 // or 256 rows in two fp16 or three bf16 parts.  Time of one round per 32-key tile, in us, as measured on launches

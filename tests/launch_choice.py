@@ -19,6 +19,7 @@ extern "C" int form(long long slices, long long Nq, long long Nk, int d, int bf1
 {
     return choose_form(slices, Nq, (Nk + kChoiceTile - 1) / kChoiceTile, d, Storage{bf16 != 0, fp8 != 0, counts != 0}, %d).form;
 }
+extern "C" int form_in_one_order(int form, long long Nk) { return in_one_key_order((Form)form, (Nk + kChoiceTile - 1) / kChoiceTile, true); }
 extern "C" int f32_rows(long long heads, long long Nq, long long Nk, int d) { return choose_f32(heads, Nq, Nk, 1, d, %d).rows; }
 extern "C" int two_parts(long long Nk, int d) { return f32_two_parts(Nk, d); }
 """ % (CUS, CUS)
@@ -33,6 +34,7 @@ def _library():
         subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", out, src], check=True)
         lib = ctypes.CDLL(out)
     lib.form.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
+    lib.form_in_one_order.argtypes = [ctypes.c_int, ctypes.c_longlong]
     lib.f32_rows.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     lib.two_parts.argtypes = [ctypes.c_longlong, ctypes.c_int]
     return lib
@@ -43,6 +45,11 @@ def form(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
     rows = Nq * (H // H_kv)
     f = _library().form(H_kv, rows, Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts)
     return FORMS[f], f != len(FORMS) - 1 and H_kv * -(-rows // ROWS[f]) > CUS
+
+
+def bf16_form_in_one_key_order(H, N, d):
+    """The form of a bf16 self-attention launch without counts that keeps the 256-row kernel's order of a row's terms."""
+    return FORMS[_library().form_in_one_order(FORMS.index(form(H, H, N, N, d, "bf16", False)[0]), N)]
 
 
 def f32_rows(H, Nq, Nk, d):

@@ -23,6 +23,13 @@ def test_every_form_has_a_shape(d, dtype, counts, partial):
     assert reached <= tested, reached - tested
 
 
+@pytest.mark.parametrize("H,N,d,name", [(8, 6000, 64, "Rows256"), (12, 5000, 64, "Rows256"), (20, 3000, 64, "Rows256"), (3, 20000, 64, "Rows256"),
+                                        (32, 2048, 64, "Narrow"), (4, 8192, 64, "Narrow"), (4, 1999, 128, "Narrow"), (40, 4096, 64, "Rows256")])
+def test_one_key_order_takes_the_faster_of_two(H, N, d, name):
+    """Two workgroups of 128 rows on a CU lose 6 to 8 % against one of 256 on long key axes."""
+    assert launch_choice.bf16_form_in_one_key_order(H, N, d) == name
+
+
 def _shapes(test):
     return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0].startswith("H,Nq,Nk,d"))
 
