@@ -8,7 +8,7 @@ constexpr int kChoiceTile = 64, kChoiceF32Tile = 32;   // keys that the times be
 
 // How a launch of 16-bit or fp8-Q/K storage is laid out.  256 query rows (fwd_pipelined_kernel) is the shape of a full chip; the
 // others (sphattn_keysplit.hpp) deal the keys of a tile to groups of waves, and pay while all their workgroups run at
-// once, one per CU (two in Rows64 at d = 64).  Rows64 has two key groups of two waves; Rows64Wide four of two, so two
+// once, one per CU (two in Rows64 and Narrow at d = 64).  Rows64 has two key groups of two waves; Rows64Wide four of two, so two
 // waves per SIMD; Rows64Own four of one wave with all 64 rows, which reads every K and V byte from LDS once (d = 128, where LDS and
 // copies are the bound); Rows128 two of two, Rows128Wide four of two (d = 64); Rows256Wide two key groups of four waves
 // (d = 64).  Narrow: 128 rows in four waves of 32 over all keys (bf16 without counts), which reads every fragment for
@@ -17,15 +17,16 @@ enum Form { kRows64, kRows64Wide, kRows64Own, kRows128, kRows128Wide, kNarrow, k
 constexpr int kFormRowsLog2[kForms] = {6, 6, 6, 7, 7, 7, 8, 8};
 
 // Time of a launch that runs at once, in us: start + tiles (tile + share f of the CUs), the tiles of 64 keys rounded up to what the
-// form's loop does at a time.  Fitted to 929 launches of bf16 and fp8 Q/K with and without counts (1 to 128 heads of 100 to 12000
-// keys, every form timed on each): 1 to 4 % off in the root mean square, and what this picks is 0.0 to 0.6 % slower
-// than the best form.  tile 0: the form does not exist.  f16 measures like bf16.
+// form's loop does at a time.  Fitted to 928 launches of bf16 and fp8 Q/K with and without counts (1 to 128 heads of 100 to 12000
+// keys, every form timed on each; profiles/forward_forms_launches.txt): 1 to 4 % off in the root mean square, and what this picks is 0.0 to
+// 0.3 % slower than the best form in the mean, 23 % at most (128 x 500 x 64).  Of Rows256Wide with fp8 Q/K, timed on 56 launches later, only the start is a fit (100 x 500
+// with counts 12.0 us, 11.5 of Rows256; 24 x 2000 27.7, 28.7), the rest is bf16's.  tile 0: the form does not exist.  f16 measures like bf16.
 struct FormCost { float start, tile, share; };
 constexpr FormCost kFormCost[2][2][2][kForms] = {   // [d = 128][fp8 Q/K][counts]
     {{{{3.7f, .253f, .04f}, {4.5f, .162f, .05f}, {0, 0, 0}, {4.3f, .341f, .06f}, {5.5f, .262f, .08f}, {3.8f, .383f, .07f}, {5.0f, .453f, .15f}, {4.8f, .536f, .15f}},
       {{3.7f, .343f, .04f}, {4.7f, .228f, .05f}, {0, 0, 0}, {4.6f, .473f, .05f}, {5.8f, .324f, .07f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.7f, .728f, .09f}}},
-     {{{3.6f, .230f, .04f}, {4.4f, .159f, .04f}, {0, 0, 0}, {4.5f, .322f, .05f}, {5.9f, .247f, .07f}, {0, 0, 0}, {5.0f, .453f, .15f}, {4.9f, .561f, .07f}},
-      {{3.7f, .304f, .03f}, {4.6f, .197f, .04f}, {0, 0, 0}, {5.4f, .440f, .05f}, {6.1f, .313f, .08f}, {0, 0, 0}, {5.2f, .631f, .10f}, {4.9f, .729f, .07f}}}},
+     {{{3.6f, .230f, .04f}, {4.4f, .159f, .04f}, {0, 0, 0}, {4.5f, .322f, .05f}, {5.9f, .247f, .07f}, {0, 0, 0}, {5.4f, .453f, .15f}, {4.9f, .561f, .07f}},
+      {{3.7f, .304f, .03f}, {4.6f, .197f, .04f}, {0, 0, 0}, {5.4f, .440f, .05f}, {6.1f, .313f, .08f}, {0, 0, 0}, {6.0f, .631f, .10f}, {4.9f, .729f, .07f}}}},
     {{{{4.7f, .370f, .09f}, {5.7f, .277f, .13f}, {6.5f, .276f, .11f}, {5.9f, .519f, .14f}, {0, 0, 0}, {4.7f, .506f, .20f}, {0, 0, 0}, {6.6f, .927f, .35f}},
       {{5.0f, .447f, .09f}, {5.7f, .334f, .14f}, {6.6f, .318f, .11f}, {6.1f, .616f, .11f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.6f, 1.06f, .31f}}},
      {{{0, 0, 0}, {0, 0, 0}, {5.9f, .224f, .07f}, {5.5f, .446f, .10f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .692f, .24f}},
