@@ -28,7 +28,7 @@ constexpr FormCost kFormCost[2][2][2][kForms] = {   // [d = 128][fp8 Q/K][counts
      {{{3.6f, .230f, .04f}, {4.4f, .159f, .04f}, {0, 0, 0}, {4.5f, .322f, .05f}, {5.9f, .247f, .07f}, {0, 0, 0}, {5.4f, .453f, .15f}, {4.9f, .561f, .07f}},
       {{3.7f, .304f, .03f}, {4.6f, .197f, .04f}, {0, 0, 0}, {5.4f, .440f, .05f}, {6.1f, .313f, .08f}, {0, 0, 0}, {6.0f, .631f, .10f}, {4.9f, .729f, .07f}}}},
     {{{{4.7f, .370f, .09f}, {5.7f, .277f, .13f}, {6.5f, .276f, .11f}, {5.9f, .519f, .14f}, {0, 0, 0}, {4.7f, .506f, .20f}, {0, 0, 0}, {6.6f, .927f, .35f}},
-      {{5.0f, .447f, .09f}, {5.7f, .334f, .14f}, {6.6f, .318f, .11f}, {6.1f, .616f, .11f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.6f, 1.06f, .31f}}},
+      {{4.7f, .447f, .09f}, {5.7f, .334f, .14f}, {6.6f, .318f, .11f}, {6.1f, .616f, .11f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.6f, 1.06f, .31f}}},
      {{{0, 0, 0}, {0, 0, 0}, {5.9f, .224f, .07f}, {5.5f, .446f, .10f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .692f, .24f}},
       {{0, 0, 0}, {0, 0, 0}, {6.1f, .263f, .07f}, {5.6f, .533f, .09f}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {6.0f, .813f, .23f}}}}};
 

@@ -329,7 +329,10 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
         const int i = u % SLOTS;
         const int tt = u < SLOTS ? t : t + 1, set = u < SLOTS ? par : par ^ 1;
         const SPH_LDS unsigned char* kp = smem + ((tt + 1) & (NBUF - 1)) * KTILE + klane;
-        const SPH_LDS unsigned char* a = smem + v_buffer(t, u < SLOTS ? -1 : 0) + vfrag(i);
+        // (named by the tile read where that schedules the loop better: two key groups with counts 4 to 5 % on short key axes; not with four,
+        // 1 x 12000 x 64 39.2 us for 38.2, nor in 256 rows with counts, 1 %)
+        constexpr bool BY_TILE = KG == 2 && (RG == 2 || !MULT);
+        const SPH_LDS unsigned char* a = smem + (BY_TILE ? v_buffer(tt, -1) : v_buffer(t, u < SLOTS ? -1 : 0)) + vfrag(i);
         const i32x2 lo = lds_read_tr64(a);
         const i32x2 hi = lds_read_tr64(a + DB * 512);
         vf[i % RING] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
@@ -545,9 +548,11 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
         return;
     }
 
-    // the workgroup's rows as a whole go through LDS, so that every store instruction writes whole rows
+    // the rows go through LDS, so that every store instruction writes whole rows: the wave's own, with four key groups (a wave may
+    // have parts of rows) the workgroup's
     const __amdgpu_buffer_rsrc_t orw = make_rsrc((unsigned short*)Ov + head_off, (uint32_t)Nq * D * 2);
     constexpr int ROWS = 16 * NQ * RG, WROWS = ROWS / WAVES;
+    static_assert(FOUR || WROWS == 16 * FQ, "a wave's rows");
     __syncthreads();                               // every wave has taken its share
 #pragma unroll
     for (int q = 0; q < FQ; ++q) {
@@ -561,8 +566,12 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
             put_piece<D * 2>(smem, wrow + q * 16 + n16, (db0 + db) * 32 + 8 * g, o4);
         }
     }
-    __syncthreads();
-    store_tile<WROWS, D * 2>(smem + wave_u * WROWS * (D * 2 + 16), orw, tile_row0 + (int)wave_u * WROWS, Nq, lane, stream_out);
+    if constexpr (FOUR) {
+        __syncthreads();
+        store_tile<WROWS, D * 2>(smem + wave_u * WROWS * (D * 2 + 16), orw, tile_row0 + (int)wave_u * WROWS, Nq, lane, stream_out);
+    } else {                                       // (whole rows, the wave's own)
+        store_tile<WROWS, D * 2>(smem + wrow * (D * 2 + 16), orw, row0, Nq, lane, stream_out);
+    }
 }
 
 // Persistent workgroups over the items, every other batch streaming the keys backwards, and the
