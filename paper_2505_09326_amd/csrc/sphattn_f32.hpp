@@ -383,7 +383,7 @@ bool f32_two_part_rows(const F32Rows& p)
             int m = exponent_word(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(mrs, key * 4, 0, 0)));
 #pragma unroll
             for (int w = 1; w < 32; w *= 2) m += __shfl_xor(m, w);
-            if (m != 0) ep = max(-126, ep + 1 - mean_exponent(m >> 20, m & LOW));
+            if (m != 0) ep = max(-126, min(126, ep + 1 - mean_exponent(m >> 20, m & LOW)));
             ep = __builtin_amdgcn_readfirstlane(ep);
         }
         if (is_k) {
