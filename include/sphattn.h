@@ -32,11 +32,21 @@ extern "C" {
 
 /* Storage formats.  Arithmetic is MFMA with fp32 accumulation in every case. */
 typedef enum {
-    SPHATTN_F32 = 0,         /* Q,K,V,O fp32; fp32 matrix instruction, or bf16 ones on exact three-part values */
+    SPHATTN_F32 = 0,         /* Q,K,V,O fp32 (see below) */
     SPHATTN_BF16 = 1,        /* Q,K,V,O bfloat16 */
     SPHATTN_FP8QK_BF16V = 2, /* Q,K OCP E4M3 (finite-only) bytes; V,O bfloat16 */
     SPHATTN_F16 = 3          /* Q,K,V,O IEEE half (the paper's precision); scores must stay below 65504 */
 } sphattn_dtype;
+
+/*
+ * SPHATTN_F32 runs on the fp32 matrix instruction (small launches), on bf16 ones with every value as three
+ * parts that are exactly it, or, from 512 keys (d = 64: 1792) on, on fp16 ones with every value as two parts: scaled
+ * by powers of two and rounded to 22 to 23 bits, sums in fp32 throughout.  Results of the last are as close to 64 bits as those of the
+ * other two on values of ordinary spread (relative 2-norm error of O 1.8e-7 to 3.8e-7 at 512 to 20000 keys).  Every workgroup checks what the rows and
+ * columns of its results were formed of and does them again in three parts where two do not hold the values (outliers
+ * and mixed magnitudes that carry a row or a column of O); such calls take 10 to 65 % longer than in three parts
+ * alone.
+ */
 
 /* Return codes. */
 enum {
@@ -209,9 +219,10 @@ int sphattn_combine(const float* o_parts, const float* z_parts, int n_parts, voi
  * below the number of workgroups the device runs at once, i.e. few heads of moderate length.
  * One slice is one launch that does not touch the workspace: sphattn_grn_fwd itself where the library
  * chose it (n_splits 0).  Asked for as n_splits = 1 with 16-bit or fp8 Q/K storage it is sphattn_grn_fwd itself too
- * where that takes 256 query rows per workgroup; a smaller launch, for which sphattn_grn_fwd takes 64 or
- * 128 rows and adds the two halves of every key tile separately, then adds every row's terms in
- * the order of the 256-row workgroups (bit for bit sphattn_fwd_tile_rows with 256), which is slower.
+ * where the launch has more workgroups of 256 query rows than the device has compute units; a smaller launch, for
+ * which sphattn_grn_fwd may deal the keys of a tile to two or four groups of waves and add their sums at the end, then adds
+ * every row's terms in the order of the 256-row workgroups (bit for bit sphattn_fwd_tile_rows with 256), which is
+ * slower.
  *
  *   n_splits       : slices asked for; 0 lets sphattn_splitkv_heuristic choose.  Slices are
  *                    whole 64-key tiles of equal size, so fewer than asked may be used (any

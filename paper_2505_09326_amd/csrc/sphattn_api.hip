@@ -693,12 +693,11 @@ int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
 
 // The library's choice of slices for a rectangular problem, in the launch's terms (packed_group).
 // A launch is cut only while all its slices still run at once as workgroups of 128 rows or fewer, one
-// per CU (at d = 64 as well: 1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  In us,
-// from launches of one to many slices: a workgroup spends 4 (64 rows) or 6 on its first and last bytes
-// and tau on each 64-key tile, tau growing with the share f of the CUs in use (the part is power-bound); the
-// second launch costs 4, and each part is written and read at 6 TB/s together.  Measured with the
-// slices this picks against one: 1 x 8192 x 128 39 against 56 us, 1 x 8192 x 64 24 against 37; not cut:
-// 4 x 1999 x 128 (22.7 at best against 17.8), 8 x 1000 x 128 (18.1 against 10.9).
+// per CU (1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  Either side is priced as the launch it would be
+// (choose_form, choose_f32), as without counts, which the plan does not know and which raise both, and without Narrow, which parts have not
+// and with which no plan over 2535 shapes differs; the second launch costs 4 us, and each part is written and read at 6 TB/s together.
+// Measured with the slices this picks against one: 1 x 8192 x 128 38 against 44 us, 1 x 8192 x 64 24 against 27.5; not cut:
+// 4 x 1999 x 128 (22.7 at best against 15.7), 8 x 1000 x 128 (18.1 against 10.9).
 SplitPlan plan_cross(int B, int H, int H_kv, int Nq, int Nk, int d, int dtype)
 {
     Problem p{};

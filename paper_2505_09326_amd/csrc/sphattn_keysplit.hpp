@@ -21,7 +21,7 @@
 //             (0.22 against 0.45 of 128 rows: 5 x 3000 with counts 31.6 -> 21.6).
 //   4  2  4   128 rows, two waves per SIMD, d = 64: 0.26 against 0.34 (4 x 8192 58.5 -> 54.5, 6 x 4000 with counts 33.9 -> 28.3).
 //   4  4  2   256 rows, two waves per SIMD, d = 64: 0.45 against 0.54 of fwd_pipelined_kernel alone on its CU (3 x 12000
-//             115.6 -> 94.7, 8 x 6000 with counts 75 -> 69, 4 x 8 x 2048 28 -> 26.7).
+//             115.6 -> 94.7, 8 x 6000 with counts 75 -> 69, 32 x 2048 29.5 -> 28 with the call, 27.4 -> 26.2 of the kernel).
 //
 // Copies.  K and V have rings of their own, each tile's buffer free again as soon as its one reader iteration is
 // over.  With NBUF buffers of K and NVB of V:
@@ -304,8 +304,9 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
             }
         }
     }
-    // K_1 has landed, everywhere; every wave has read Q, where V_1 and V_2 go, and K_0, where K_4
-    // goes.  The rest of group 2 follows in slots 0 .. SLOTS - PD - 1 of iteration 0.
+    // K_1 has landed, everywhere; every wave has read Q, where V_0, or V_1 and V_2, go (QLDS), and K_0, where K_NBUF
+    // goes.  The copies that follow here are those of iterations 1 - NBUF .. -1 that the prologue has not issued, the last of them in
+    // part: the rest goes with slots 0 .. SLOTS - PD - 1 of iteration 0.
     asm volatile("" ::: "memory");
     {
         constexpr int VM = YOUNGER;

@@ -1,4 +1,4 @@
-"""fp32 storage: three-part bf16 products (sphattn_f32.hpp) in 128- and 256-row workgroups, and the fp32
+"""fp32 storage: three-part bf16 products (sphattn_f32.hpp; from 512 keys, d = 64 1792, on two-part fp16 ones) in 128- and 256-row workgroups, and the fp32
 instruction in 16- and 32-row ones, on shapes that choose each: ragged queries and keys, multiplicities, shared heads, accumulators.  The bound is
 that of fp32 arithmetic itself, not the 1e-4 of the entry point: relative 2-norm error against 64 bits
 at most 3e-8 sqrt(N_k) / 4 + 2e-7, which the fp32 matrix instruction measures at (2.1e-7 at 256 keys,

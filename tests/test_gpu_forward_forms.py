@@ -1,5 +1,5 @@
 """Launches that take the key-split kernel's forms of four key groups, of one row group and of 256 rows (choose_form in
-sphattn_api.hip), at the sizes where they can go wrong: a single step of 128 keys and parts of one, odd numbers of
+sphattn_choice.hpp), at the sizes where they can go wrong: a single step of 128 keys and parts of one, odd numbers of
 tiles, ragged last rows, as many workgroups as CUs, whole results and partial accumulators, with and without counts.
 Every element is compared with 64 bits within what the storage type allows: one rounding of every score and of the
 result (u of them at most), 2e-4 of z, and for E4M3 scores the matrix instruction's own error, 2^-16 of the sum of the

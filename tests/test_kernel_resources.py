@@ -102,6 +102,17 @@ def test_key_split_forward(usage):
                 assert _num(v, "Occupancy [waves/SIMD]") >= (1 if (d, nq) == (128, 4) else 2), name
 
 
+def test_key_split_forward_by_form(usage):
+    # Li<D>E Li<NQ>E .. Li<RG>E Li<KG>E: the forms of eight waves run two per SIMD, four waves of 64 rows (and of 128 at d = 64) two workgroups
+    # per CU at d = 64, one row group one wave per SIMD
+    for d, nq, rg, kg, waves in ((64, 2, 2, 2, 2), (64, 2, 2, 4, 2), (64, 4, 2, 2, 2), (64, 4, 2, 4, 2), (64, 4, 4, 2, 2),
+                                 (128, 2, 2, 2, 2), (128, 2, 2, 4, 2), (128, 4, 2, 2, 1), (128, 4, 1, 4, 1)):
+        kernels = [(n, v) for n, v in _find(usage, "fwd_keysplit_kernel", f"ILi{d}ELi{nq}E").items() if f"ELi{rg}ELi{kg}EEE" in n]
+        assert len(kernels) >= (8 if (d, nq) == (128, 2) else 12), (d, nq, rg, kg, len(kernels))
+        for name, v in kernels:
+            assert _num(v, "Occupancy [waves/SIMD]") >= waves, name
+
+
 def test_f32_kernels(usage):
     # workgroups of eight waves, two per SIMD; at d = 64 in 128 rows two such workgroups per CU
     for d, nq, waves in ((128, 1, 2), (128, 2, 2), (64, 1, 4), (64, 2, 2)):
