@@ -40,12 +40,13 @@ typedef enum {
 
 /*
  * SPHATTN_F32 runs on the fp32 matrix instruction (small launches), on bf16 ones with every value as three
- * parts that are exactly it, or, from 512 keys (d = 64: 1792) on, on fp16 ones with every value as two parts: scaled
- * by powers of two and rounded to 22 to 23 bits, sums in fp32 throughout.  Results of the last are as close to 64 bits as those of the
- * other two on values of ordinary spread (relative 2-norm error of O 1.8e-7 to 3.8e-7 at 512 to 20000 keys).  Every workgroup checks what the rows and
- * columns of its results were formed of and does them again in three parts where two do not hold the values (outliers
- * and mixed magnitudes that carry a row or a column of O); such calls take 10 to 65 % longer than in three parts
- * alone.
+ * parts that are exactly it, or, from 512 keys (d = 64: 1792) on, on fp16 ones with every value as two parts:
+ * scaled by powers of two and rounded to 22 to 23 bits, sums in fp32 throughout.  Results of the last are as close
+ * to 64 bits as those of the other two on values of ordinary spread (relative 2-norm error of O 1.8e-7 to 3.8e-7 at
+ * 512 to 20000 keys); where a row's scores cancel against an offset that all keys have, the rounding of Q shows as
+ * it would in inputs of 23 bits.  Every workgroup checks what the rows and columns of its results were formed of
+ * and does them again in three parts where two do not hold the values (outliers and mixed magnitudes that carry a
+ * row or a column of O); such calls take 10 to 65 % longer than in three parts alone.
  */
 
 /* Return codes. */
