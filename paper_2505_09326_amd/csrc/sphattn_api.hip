@@ -551,21 +551,39 @@ int run_splitkv(Problem p, int d, int dtype, int requested, SplitPlan plan, void
                     : launch_combine<64>(o_parts, z_parts, plan.n_splits, O, Z, rows, dtype, p.stream);
 }
 
-template <int D, bool SOFTMAX, bool MULT>
-int launch_fp8(const void* Q, const void* K, const unsigned char* VT, const float* kmax, const float* mult,
-                      void* O, int B, int H, int H_kv, int N, int n_tiles, hipStream_t st)
+struct Fp8Problem {
+    const unsigned char* Q; const unsigned char* K; const unsigned char* VT; const float* kmax; const float* mult; unsigned short* O;
+    int B, H, H_kv, N, n_tiles;
+    hipStream_t stream;
+};
+
+template <int D, bool SOFTMAX, bool MULT, int NQ, int WAVES>
+int launch_fp8_shape(const Fp8Problem& p)
 {
-    constexpr int lds_bytes = 4 * (2 * kFp8Tile * D + (MULT ? kFp8Tile * 4 : 0));
+    constexpr int lds_bytes = 4 * (2 * kFp8Tile * D + (MULT ? kFp8Tile * 4 : 0)), BR = 16 * NQ * WAVES;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
-    auto kern = fwd_fp8_kernel<D, SOFTMAX, MULT>;
+    auto kern = fwd_fp8_kernel<D, SOFTMAX, MULT, NQ, WAVES>;
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
-    const int n_qtiles = (N + 255) / 256;
-    const long long n_wg = (long long)B * H * n_qtiles;
-    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(kThreads), lds_bytes, st,
-                       (const unsigned char*)Q, (const unsigned char*)K, VT, kmax, mult, (unsigned short*)O,
-                       N, H, H / H_kv, n_tiles, n_qtiles, (int)n_wg, stream_period(kern, lds_bytes, period), fp8_chunks((long long)B * H_kv, n_tiles));
+    const int n_qtiles = (p.N + BR - 1) / BR;
+    const long long n_wg = (long long)p.B * p.H * n_qtiles;   // (fits: check_shape counts 32-row tiles)
+    hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(64 * WAVES), lds_bytes, p.stream,
+                       p.Q, p.K, p.VT, p.kmax, p.mult, p.O, p.N, p.H, p.H / p.H_kv, p.n_tiles, n_qtiles, (int)n_wg,
+                       stream_period(kern, lds_bytes, period, 64 * WAVES), fp8_chunks((long long)p.B * p.H_kv, p.n_tiles));
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
+}
+
+template <int D, bool MULT>
+int launch_fp8(const Fp8Problem& p)
+{
+    const Fp8Shape shape = choose_fp8((long long)p.B * p.H, p.N, D, MULT, cu_count());
+    if (shape.nq == 1) return shape.waves == 4 ? launch_fp8_shape<D, false, MULT, 1, 4>(p) : launch_fp8_shape<D, false, MULT, 1, 8>(p);
+    if constexpr (D == 64) {
+        if (shape.waves == 4 && shape.nq == 2) return launch_fp8_shape<D, false, MULT, 2, 4>(p);
+        if constexpr (!MULT)
+            if (shape.nq == 4) return launch_fp8_shape<D, false, MULT, 4, 4>(p);
+    }
+    return launch_fp8_shape<D, false, MULT, 2, 8>(p);
 }
 
 int fp8_forward(const void* Q, const void* K, const void* V, const float* mult, void* O, void* workspace,
@@ -615,14 +633,11 @@ int fp8_forward(const void* Q, const void* K, const void* V, const float* mult, 
     hipLaunchKernelGGL(prepare, dim3((unsigned)prep_wg), dim3(256), 0, st,
                        (const unsigned char*)K, (const unsigned char*)V, mult, VT, kmax, N, n_tiles, H_kv, heads, n_chunks);
     if (hipGetLastError() != hipSuccess) return SPHATTN_ERR_LAUNCH;
-    if (d == 128) {
-        if (softmax) return launch_fp8<128, true, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
-        return mult ? launch_fp8<128, false, true>(Q, K, VT, kmax, mult, O, B, H, H_kv, N, n_tiles, st)
-                    : launch_fp8<128, false, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
-    }
-    if (softmax) return launch_fp8<64, true, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
-    return mult ? launch_fp8<64, false, true>(Q, K, VT, kmax, mult, O, B, H, H_kv, N, n_tiles, st)
-                : launch_fp8<64, false, false>(Q, K, VT, kmax, nullptr, O, B, H, H_kv, N, n_tiles, st);
+    const Fp8Problem p{(const unsigned char*)Q, (const unsigned char*)K, VT, kmax, mult, (unsigned short*)O, B, H, H_kv, N, n_tiles, st};
+    if (softmax)                                   // (the shape of the spherical kernel's large launches)
+        return d == 128 ? launch_fp8_shape<128, true, false, 2, 8>(p) : launch_fp8_shape<64, true, false, 4, 4>(p);
+    if (d == 128) return mult ? launch_fp8<128, true>(p) : launch_fp8<128, false>(p);
+    return mult ? launch_fp8<64, true>(p) : launch_fp8<64, false>(p);
 }
 
 // Key slices for `heads` heads of Nq query rows against Nk keys, as sphattn_splitkv_fwd chooses them: 1 where

@@ -96,4 +96,26 @@ inline F32Choice choose_f32(long long heads, long long Nq, long long keys_per_sl
     return best;
 }
 
+// The all-E4M3 forward's workgroup (sphattn_fp8.hpp): query blocks of 16 rows per wave, and waves.  64 rows while every CU gets at most
+// one such workgroup, else 128 likewise, else 256: over 300 launches of 1 to 64 heads of 190 to 23000 keys, every shape timed on each, that is 0 to
+// 0.5 % slower than the best shape in the mean and 4 % at most, and 0.68 to 0.76 of 256 rows in four waves (geometric mean; nowhere slower).
+// At d = 64 above one round of 256 rows two workgroups share a CU, but not two of eight waves: the shape follows from rounds of two and a last
+// round of one or two, in the units of a tile's time measured for them.  Without counts 256 rows in four waves, two on a CU 1.84, one 1.08,
+// or 128 rows, 0.985 and 0.66 (8 x 9000 131.8 and 126.4 us, 12 x 5725 101.5 and 109.6; for a gain of 4 %); with counts 256 rows in eight waves, 1.11
+// alone, or 128 rows, 1.16 and 0.74 (8 x 9000 165.3 and 138.5, 48 x 2149 57.6 and 58.2).
+struct Fp8Shape { int nq, waves; };
+inline Fp8Shape choose_fp8(long long heads, long long N, int d, bool counts, long long cus)
+{
+    if (heads * ((N + 63) / 64) <= cus) return Fp8Shape{1, 4};
+    const long long n128 = heads * ((N + 127) / 128), n256 = heads * ((N + 255) / 256);
+    if (n128 <= cus) return Fp8Shape{1, 8};
+    if (d == 128 || n256 <= cus) return Fp8Shape{2, 8};
+    auto cost = [cus](long long n, double two, double one) {   // rounds of two workgroups per CU and what is left
+        const long long rest = n % (2 * cus);
+        return (double)(n / (2 * cus)) * two + (rest == 0 ? 0.0 : rest <= cus ? one : two);
+    };
+    if (counts) return cost(n128, 1.16, 0.74) < 1.11 * (double)((n256 + cus - 1) / cus) ? Fp8Shape{2, 4} : Fp8Shape{2, 8};
+    return cost(n128, 0.985, 0.66) < 0.96 * cost(n256, 1.84, 1.08) ? Fp8Shape{2, 4} : Fp8Shape{4, 4};
+}
+
 }  // namespace sphattn

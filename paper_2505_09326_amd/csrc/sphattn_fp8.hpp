@@ -19,8 +19,8 @@
 //     (v_cvt_scalef32_pk_fp8_f32), which rounds to nearest even.
 //   * z_i = sum_j p_ij^2 is taken from the ROUNDED scores p_ij, on the matrix cores as well:
 //     it is the diagonal of P^T P, and P's register image serves as A and as B operand alike.
-//     One extra matrix instruction per query block and tile replaces 128 VALU FMAs, which
-//     a single wave per SIMD cannot issue in the shadow of the matrix instructions.
+//     One extra matrix instruction per query block and tile replaces 128 VALU FMAs, for which
+//     there is no room in the shadow of the matrix instructions.
 //
 // Matrix-core mapping.  With k = 128 both contractions have the same shape,
 //     S^T block kb (16 keys x 16 queries) = K frag (A: 16 keys x 128 of d) * Q frag (B: 128 x 16 queries)
@@ -52,9 +52,9 @@
 // (512 bytes per 128 keys, copied into LDS behind K and V^T) and reach the lanes through one
 // 16-byte LDS read per slot, a slot ahead of their use.
 //
-// Pipeline.  A slot = one score block row kb of the current tile (4 matrix instructions, one
-// per query block) + one V^T fragment db of the previous tile (4 more) + the conversion of the
-// block row finished in the slot before (one convert instruction and at most one LDS read
+// Pipeline.  A slot = one score block row kb of the current tile (NQ matrix instructions, one
+// per query block) + one V^T fragment db of the previous tile (NQ more) + the conversion of the
+// block row finished in the slot before (one convert instruction and one LDS read, two at NQ = 1,
 // behind every matrix instruction, in a fixed order).  P is complete one slot into the next tile,
 // so the second contraction of tile T runs in slots 1..7 of tile T+1 and slot 0 of tile T+2.
 // Tiles of 128 keys rotate through four 32 KB LDS buffers, filled straight from HBM/L2
@@ -211,8 +211,19 @@ __global__ void fp8_clear_kernel(float* __restrict__ p, int n)
 
 // ---- the forward kernel ------------------------------------------------------------------
 //
-// One workgroup = 4 wavefronts = 256 query rows of one (b, h); a wavefront owns NQ = 4 blocks
+// One workgroup = WAVES wavefronts = 16 NQ WAVES query rows of one (b, h); a wavefront owns NQ blocks
 // of 16 rows.  VT and kmax come from fp8_prepare_kernel (same stream, earlier).
+//
+// Shapes (choose_fp8 picks; whole calls in us, with counts / without).  A wave alone on its SIMD stops the matrix pipe for
+// its own conversions, multiplications, register moves and LDS reads (busy 0.61 / 0.72 of the time); two fill each other's gaps, though
+// every fragment read from LDS then feeds two matrix instructions instead of four:
+//   256 rows  NQ 2, 8 waves  8 on 4 x 8000 x 128 108.5 / 100.5 (4 waves of 64 rows, which was the only shape: 114.9 / 103.2), 24 heads on 6
+//             of 3001 76.3 (89.4), 8 x 8000 x 64 81.4 / 72.1 (85.4 / 75.8); 64 x 16384 x 128 as before, 2970, at the power limit
+//   256 rows  NQ 4, 4 waves  d = 64 without counts above one round, where two such workgroups share a CU: 8 x 32768 947 (8 waves 1037)
+//   128 rows  NQ 1, 8 waves  half of the CUs: 8 x 3000 x 128 28.1 / 25.6 (256 rows 38.0 / 35.4; NQ 2, 4 waves 30.1 / 27.9)
+//   128 rows  NQ 2, 4 waves  d = 64, two on a CU, where 256 rows leave their last round thin: 8 x 9000 138 / 126 (165 / 132)
+//   64 rows   NQ 1, 4 waves  few rows: 4 x 1000 x 128 13.1 / 12.3 (18.5 / 17.8), 8 x 2048 x 64 15.2 / 14.4 (24.0 / 21.8)
+// (More waves of 64 rows do not fit: o, Q, P and the fragments of such a wave take 350 registers.)
 //
 // SOFTMAX: the comparison twin.  O = softmax(Q K^T / sqrt(d)) V on the same skeleton, made as
 // cheap as a SoftMax can be here: the shift of row i is not a running maximum but the bound
@@ -223,18 +234,16 @@ __global__ void fp8_clear_kernel(float* __restrict__ p, int n)
 // the row sums come from the matrix cores as well (an all-ones A fragment against P).  A row
 // whose largest score is more than about 12 sqrt(d) below its bound underflows to zero weights
 // and gives 0: a twin for timing on inputs of moderate size, not a general SoftMax.
-// d = 64: two workgroups per CU (64 KB of LDS each) where the registers allow it without
-// spilling much (not with multiplicities: 624 bytes of scratch per lane)
-template <int D, bool SOFTMAX, bool MULT>
-__global__ __launch_bounds__(kThreads, (D == 64 && !MULT) ? 2 : 1)
+template <int D, bool SOFTMAX, bool MULT, int NQ, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2)
 void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __restrict__ K,
                     const unsigned char* __restrict__ VT, const float* __restrict__ kmax,
                     const float* __restrict__ mult,
                     unsigned short* __restrict__ O, int N, int H, int kv_group, int n_tiles, int n_qtiles, int n_wg,
                     int stream_period, int n_chunks)
 {
-    constexpr int BC = kFp8Tile, NQ = 4;
-    constexpr int BR = kWaves * 16 * NQ;
+    constexpr int BC = kFp8Tile, THREADS = 64 * WAVES;
+    constexpr int BR = WAVES * 16 * NQ;
     constexpr int KH = D / 64;                     // 1 KB blocks per K block row (64-byte halves of the key rows)
     constexpr int DB = D / 16;                     // V^T fragments per tile = 16-column blocks of O
     constexpr int KTILE = BC * D;                  // K tile; the V^T tile (D rows of 128 keys) has the same size
@@ -244,14 +253,16 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     constexpr int SLOTS = 8;                       // per tile: score block rows kb (and, d = 128, V^T fragments db)
     constexpr int PD = 2;                          // LDS prefetch distance in slots (measured best of 1, 2, 3)
     constexpr int RING = 4;
-    constexpr int KCOPY = 2 * KH;                  // 1 KB copies per wave per tile: of K ...
-    constexpr int VPW = DB / 4;                    // ... V^T fragments per wave, two copies each
-    constexpr int NCOPY = KCOPY + 2 * VPW;         // 8 (d = 128) or 4 (d = 64)
-    constexpr int NCOPY_ALL = NCOPY + (MULT ? 1 : 0);   // and one 512-byte copy (wave 0) of multiplicities
+    constexpr int RPG = NQ == 1 ? 2 : 1;           // parts of a slot's reads per group
+    constexpr int KPW = 8 / WAVES;                 // K block rows per wave
+    constexpr int KCOPY = KPW * KH;                // 1 KB copies per wave per tile: of K ...
+    constexpr int VCOPY = 2 * DB / WAVES;          // ... and of V^T (halves of fragments)
+    constexpr int NCOPY = KCOPY + VCOPY;           // four waves: 8 (d = 128) or 4 (d = 64)
+    constexpr int NCOPY_ALL = NCOPY + (MULT ? 1 : 0);   // and 256 bytes of multiplicities
     static_assert(D == 64 || D == 128, "head dimension 128 or 64");
     static_assert((2 * SLOTS) % RING == 0 && PD < RING, "ring indices must repeat");
     static_assert(!(SOFTMAX && MULT), "multiplicities belong to the spherical variant");
-    static_assert(2 * PD <= NCOPY, "the prologue issues whole copies of tile 1");
+    static_assert((WAVES == 4 || WAVES == 8) && (NQ == 4 || NQ == 2 || NQ == 1), "whole block rows per wave; four parts of a slot's reads");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     SPH_LDS unsigned char* smem = (SPH_LDS unsigned char*)smem_raw;
@@ -280,12 +291,13 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     constexpr int HALF1 = 1024;                    // second half of the rows: the next block
     // copies: lane l fills row l/4, slot l%4 of a block, with piece p = block_piece_in_slot(l)
     //   K   block (kb, h): tile row key(kb, l/4), bytes 64 h + 16 p of the key row;
-    //                      wave w copies the block rows kb = 2w, 2w+1
+    //                      wave w copies the block rows kb = KPW w .. KPW w + KPW - 1
     //   V^T block (db, h): row 16db + l/4 of V^T, keys 64 h + 16 p of the tile;
-    //                      wave w copies the fragments db = VPW w .. VPW w + VPW - 1
+    //                      wave w copies the blocks 2 db + h = VCOPY w .. VCOPY w + VCOPY - 1
     const int p = lane >> 2;
-    const int kld_lane = (16 * (p >> 2) + (p & 3) + 64 * (wave >> 1) + 8 * (wave & 1)) * D + block_piece_in_slot(lane) * 16;
-    const int vld_lane = (int)((16 * VPW * wave + p) * Np) + block_piece_in_slot(lane) * 16;
+    const int kld_lane = (16 * (p >> 2) + (p & 3) + 64 * (wave * KPW >> 2) + 4 * (wave * KPW & 3)) * D + block_piece_in_slot(lane) * 16;
+    // (a V^T fragment's two blocks may be two waves': the lane offset has the wave's first half)
+    const int vld_lane = (int)((16 * (wave * VCOPY >> 1) + p) * Np) + (wave * VCOPY & 1) * 64 + block_piece_in_slot(lane) * 16;
 
     // ---- Q fragments and the row factors a_i.  Q is read once and O written once by this
     // workgroup only: non-temporal, so that the L2 keeps the K/V stream instead.
@@ -349,16 +361,16 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
         const uint32_t base = (uint32_t)(uintptr_t)buf;
         const int tile = src_tile(t);
         if (c < KCOPY) {
-            const int r = c / KH, h = c % KH;      // block row 2 wave + r, half h
-            copy_to_lds(krw, base + ((wave_u * 2 + r) * KH + h) * 1024, kld_lane, tile * KTILE + r * 4 * D + h * 64);
+            const int r = c / KH, h = c % KH;      // block row KPW wave + r, half h
+            copy_to_lds(krw, base + ((wave_u * KPW + r) * KH + h) * 1024, kld_lane, tile * KTILE + r * 4 * D + h * 64);
         } else if (c < NCOPY) {
-            const int f = (c - KCOPY) >> 1, h = (c - KCOPY) & 1;   // fragment VPW wave + f, half h
-            copy_to_lds(vrw, base + KTILE + ((wave_u * VPW + f) * 2 + h) * 1024, vld_lane,
-                        tile * BC + (int)(f * 16 * Np) + h * 64);
+            const int b = c - KCOPY;               // block VCOPY wave + b
+            copy_to_lds(vrw, base + KTILE + (wave_u * VCOPY + b) * 1024, vld_lane,
+                        tile * BC + (int)((b >> 1) * 16 * Np) + (b & 1) * 64);
         } else if (MULT && c == NCOPY) {
-            // the tile's 128 multiplicities: two 256-byte copies, by every wave (no branch)
-            copy_to_lds_b32(mrw, base + MLDS, lane * 4, tile * BC * 4);
-            copy_to_lds_b32(mrw, base + MLDS + 256, lane * 4, tile * BC * 4 + 256);
+            // 64 of the tile's 128 multiplicities, by every other wave (no branch)
+            const int half = (wave_u & 1) * 256;
+            copy_to_lds_b32(mrw, base + MLDS + half, lane * 4, tile * BC * 4 + half);
         }
     };
 
@@ -366,7 +378,7 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     // entirely, and of tile 1 the copies that the loop would have issued before its first slot
     {
         const i32x4 zero4 = {0, 0, 0, 0};
-        for (int i = tid; i < BUF_BYTES / 16; i += kThreads)
+        for (int i = tid; i < BUF_BYTES / 16; i += THREADS)
             *reinterpret_cast<SPH_LDS i32x4*>(smem + (NBUF - 1) * BUF_BYTES + i * 16) = zero4;
     }
 #pragma unroll
@@ -506,10 +518,11 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
             s16x2 wlo;
 #pragma unroll
             for (int m = 0; m < 2 * NQ; ++m) {
+#pragma unroll
+                for (int part = m * RPG; part < (m + 1) * RPG && part < 4; ++part) read_part(i + PD, part, bnn, bprv, bcur, bnxt);
                 if (m < NQ) {
                     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
                     Sn[m] = mfma8(kfr, qf[m], zero);
-                    read_part(i + PD, m, bnn, bprv, bcur, bnxt);
                 } else if (has_v(i)) {
                     oacc[(i + 7) % 8 % DB][m - NQ] = mfma8(vfr, Pr[m - NQ], oacc[(i + 7) % 8 % DB][m - NQ]);
                 }
@@ -572,7 +585,7 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     // through a per-wave LDS stage, so that every store instruction writes whole rows (the tile
     // buffers are free once every wave has read its last tile)
     constexpr int ROWS = 16 * NQ;
-    static_assert(kWaves * ROWS * (D * 2 + 16) <= NBUF * BUF_BYTES, "the output stage fits the tile buffers");
+    static_assert(WAVES * ROWS * (D * 2 + 16) <= NBUF * BUF_BYTES, "the output stage fits the tile buffers");
     SPH_LDS unsigned char* stage = smem + wave * ROWS * (D * 2 + 16);
     __syncthreads();
 #pragma unroll
