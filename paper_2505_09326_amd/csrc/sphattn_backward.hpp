@@ -227,6 +227,9 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
         // are issued, and the VALU work on a key block's scores is issued behind the first
         // matrix instructions of the following step, so that neither the LDS latency nor the
         // matrix pipeline's is waited for in the open.
+        // A fragment meets all query blocks in turn, and every other output step takes them in reverse: operands that stay from one
+        // matrix instruction to the next cost no power.  (Scores and dO V^T in turns: whole backward of 2 x 16 x 8192 x 128 2869 us, 2843
+        // with this and the same in the other kernel, 1 x 8 x 32768 x 64 5868 and 5831, 2 x 8 x 4096 x 128 376.1 and 373.1.)
         constexpr int QG = 2 * KK, PER_SUB = QG + DB, STEPS = 2 * PER_SUB;
         i32x4 fa[2], fb[2];
         auto load_step = [&](int st) {
@@ -271,16 +274,18 @@ void bwd_dq_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, con
                 const int kb = u / KK, kk = u % KK;
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb) {
-                    sc[kb][qb] = mfma16x16<HALF>(fa[st & 1], qf[qb][kk], kk == 0 ? zero : sc[kb][qb]);
-                    gg[kb][qb] = mfma16x16<HALF>(fb[st & 1], gf[qb][kk], kk == 0 ? zero : gg[kb][qb]);
-                }
+                for (int qb = 0; qb < NQ; ++qb) sc[kb][qb] = mfma16x16<HALF>(fa[st & 1], qf[qb][kk], kk == 0 ? zero : sc[kb][qb]);
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) gg[kb][qb] = mfma16x16<HALF>(fb[st & 1], gf[qb][kk], kk == 0 ? zero : gg[kb][qb]);
                 if (kb == 1 && kk == 0) finish_block(sub, 0);      // behind the next block's first step
                 if (u == QG - 1) finish_block(sub, 1);             // the output steps need it now
             } else {
                 const int db = u - QG;
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb) dq[db][qb] = mfma16x16<HALF>(fa[st & 1], dsp[qb], dq[db][qb]);
+                for (int i = 0; i < NQ; ++i) {
+                    const int qb = db % 2 == 0 ? i : NQ - 1 - i;
+                    dq[db][qb] = mfma16x16<HALF>(fa[st & 1], dsp[qb], dq[db][qb]);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -475,6 +480,7 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
         // instructions of step st are issued.  Per 32-query sub-step:
         //   2 KK score steps (query block qb, k-step kk): S = Q K^T, G = dO V^T
         //   DB output steps (column block db): dV^T += dO^T W, dK^T += Q^T dS
+        // in the dQ kernel's order of operands.
         constexpr int QG = 2 * KK, PER_SUB = QG + DB, STEPS = 2 * PER_SUB;
         i32x4 fa[2], fb[2];
         auto load_step = [&](int st) {
@@ -525,10 +531,9 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
                 const int qb = u / KK, kk = u % KK;
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kb = 0; kb < NK; ++kb) {
-                    s[qb][kb] = mfma16x16<HALF>(fa[st & 1], kf[kb][kk], kk == 0 ? zero : s[qb][kb]);
-                    gg[qb][kb] = mfma16x16<HALF>(fb[st & 1], vf[kb][kk], kk == 0 ? zero : gg[qb][kb]);
-                }
+                for (int kb = 0; kb < NK; ++kb) s[qb][kb] = mfma16x16<HALF>(fa[st & 1], kf[kb][kk], kk == 0 ? zero : s[qb][kb]);
+#pragma unroll
+                for (int kb = 0; kb < NK; ++kb) gg[qb][kb] = mfma16x16<HALF>(fb[st & 1], vf[kb][kk], kk == 0 ? zero : gg[qb][kb]);
                 // W and dS of a query block are formed right behind its last score step, so that its
                 // S and G are dead before the next block's are written (16 registers that this
                 // kernel, which sits at the 256 of two workgroups per CU, does not have: with them
@@ -540,9 +545,10 @@ void bwd_dkv_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv, co
             } else {
                 const int db = u - QG;
 #pragma unroll
-                for (int kb = 0; kb < NK; ++kb) {
-                    dv[db][kb] = mfma16x16<HALF>(fb[st & 1], wp[kb], dv[db][kb]);
-                    dk[db][kb] = mfma16x16<HALF>(fa[st & 1], dsp[kb], dk[db][kb]);
+                for (int i = 0; i < 2 * NK; ++i) {
+                    const int at = db % 2 == 0 ? i : 2 * NK - 1 - i, kb = at % NK;
+                    if (at < NK) dv[db][kb] = mfma16x16<HALF>(fb[st & 1], wp[kb], dv[db][kb]);
+                    else dk[db][kb] = mfma16x16<HALF>(fa[st & 1], dsp[kb], dk[db][kb]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);

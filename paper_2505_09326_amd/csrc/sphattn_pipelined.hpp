@@ -382,6 +382,12 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
         }
     }
 
+    // Order of the matrix instructions.  Operands that stay from one to the next cost no power, and power is what bounds this loop, so a
+    // fragment meets all query blocks in turn, and where the scheduler has room (16-bit without counts) two slots'
+    // scores and two slots' outputs lie together, the second of each in reverse, so that the block at the seam stays as well: 2 x 16 x 8192 x 128
+    // 720.8 -> 713.7 us, fp16 756.5 -> 751.5, 1 x 8 x 32768 x 64 0.2 to 0.5 %; fp8 Q/K 0, with counts
+    // 757.8 -> 783.1; the key-split kernel, which waits for results rather than for power, 1 to 6 % slower.
+    constexpr bool SNAKE = !FP8 && !MULT && NORM == Norm::Spherical;
     // Fragment registers.  16-bit: one K fragment per slot, in a ring.  fp8: the K fragment of
     // key block kb arrives as two 16-byte halves with the V^T fragment of the first slot that
     // uses it; two sets alternate between consecutive sub-steps.
@@ -411,7 +417,7 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
                 kf8[hh & 1][kb][1] = k8hi(kp + klane + kb * KBLK * 1024);
             }
         } else {
-            const int kb = i / KK, kk = i % KK;
+            const int kb = SNAKE ? i % 2 : i / KK, kk = SNAKE ? i / 2 : i % KK;
             kf[u % RING] = lds_read_b128(kp + klane + (kb * KBLK + kk) * 1024);
         }
     };
@@ -476,26 +482,31 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
             }
 
             // A: next sub-step's scores
-            if constexpr (FP8) {
+            auto scores = [&]() __attribute__((always_inline)) {
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (FP8) {
 #pragma unroll
-                for (int u = 0; u < QKM; ++u) {
-                    const int idx = i * QKM + u, kb = idx / NQ, qb = idx % NQ;
-                    const qfrag_t kfr = k8frag(kf8[hf][kb][0], kf8[hf][kb][1]);
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    Sn[kb][qb] = mfma_qk(kfr, qf[qb][0], zero);
-                }
-            } else {
-                const int kb = i / KK, kk = i % KK;
+                    for (int u = 0; u < QKM; ++u) {
+                        const int idx = i * QKM + u, kb = idx / NQ, qb = idx % NQ;
+                        Sn[kb][qb] = mfma_qk(k8frag(kf8[hf][kb][0], kf8[hf][kb][1]), qf[qb][0], zero);
+                    }
+                } else {
+                    const int kb = SNAKE ? i % 2 : i / KK, kk = SNAKE ? i / 2 : i % KK;
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb) {
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    Sn[kb][qb] = mfma_qk(kf[s % RING], qf[qb][kk], kk == 0 ? zero : Sn[kb][qb]);
+                    for (int u = 0; u < NQ; ++u) {
+                        const int qb = SNAKE && i % 2 == 1 ? NQ - 1 - u : u;
+                        Sn[kb][qb] = mfma_qk(kf[s % RING], qf[qb][kk], kk == 0 ? zero : Sn[kb][qb]);
+                    }
                 }
-            }
+            };
             // C: V^T fragment i (columns 16i .. 16i+15 of d) against the previous sub-step's P
+            if (!SNAKE || i % 2 == 1) scores();
 #pragma unroll
-            for (int qb = 0; qb < NQ; ++qb)
+            for (int u = 0; u < NQ; ++u) {
+                const int qb = SNAKE && i % 2 == 0 ? NQ - 1 - u : u;
                 oacc[i][qb] = mfma16x16<HALF>(vf[s % RING], Pp[qb], oacc[i][qb]);
+            }
+            if (SNAKE && i % 2 == 0) scores();
 
             // B: PAIRS register pairs of the current sub-step's scores.  Pair p = (block p/2,
             // registers 2(p%2), 2(p%2)+1); block = (kb, qb); the pair becomes register
