@@ -14,6 +14,10 @@ without a word, as does a call that brings an output or a stream.  Cut and uncut
 not bit for bit, so sphattn_fwd_tile_rows, sphattn_normalized_fwd with "l2" and the like, which never cut, may
 differ from sphattn_fwd in the last place.
 
+Calls that allocate their outputs and give no stream go through _marshal (csrc/marshal.cpp), which does in C++ what the
+functions here do in Python and does nothing where anything about a call is not as it has to be; the Python below it then
+finds out what, and takes the calls that bring an output or a stream.
+
 The C ABI cannot see how large a buffer behind a pointer is, so the binding checks what it
 can see before any launch: every tensor's shape against the shapes the entry point's header
 states, its torch dtype against the `dtype` code, contiguity and device.  A mismatch raises
@@ -25,7 +29,7 @@ import ctypes
 import functools
 import os
 
-from ._build import LIB_PATH, build_library
+from ._build import LIB_PATH, MARSHAL_PATH, build_library
 
 SPHATTN_F32 = 0
 SPHATTN_BF16 = 1
@@ -47,6 +51,7 @@ EXPORTED_SYMBOLS = ("sphattn_fwd", "sphattn_fwd_z", "sphattn_fwd_tile_rows", "sp
 NORMALIZERS = {"l2": 0, "softmax": 1, "l1": 2, "sqrelu": 3}
 
 _lib = None
+_fast = None                                       # _marshal, bound to _lib's entry points
 
 
 class SphattnError(RuntimeError):
@@ -57,7 +62,7 @@ class SphattnError(RuntimeError):
 
 def load_library() -> ctypes.CDLL:
     """Load the built library; raise if it is missing (no CPU fallback exists)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         path = os.environ.get("SPHATTN_LIBRARY", LIB_PATH)   # another build of the same library
         if not os.path.exists(path):
@@ -115,7 +120,15 @@ def load_library() -> ctypes.CDLL:
         lib.sphattn_strerror.argtypes = [ip]
         lib.sphattn_version.restype = ip
         lib.sphattn_version.argtypes = []
-        _lib = lib
+        if not os.path.exists(MARSHAL_PATH):
+            raise ImportError(
+                f"{MARSHAL_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+        import torch  # noqa: F401  (whose libraries _marshal links against)
+        from . import _marshal
+        names = ("sphattn_cross_fwd", "sphattn_cross_splitkv_fwd", "sphattn_cross_splitkv_workspace_bytes", "sphattn_grn_bwd",
+                 "sphattn_grn_bwd_split", "sphattn_bwd_workspace_bytes", "sphattn_fp8_grn_fwd")
+        _marshal.bind(_raise_on, *(ctypes.cast(getattr(lib, name), vp).value for name in names))
+        _lib, _fast = lib, _marshal
     return _lib
 
 
@@ -344,6 +357,9 @@ def sphattn_fwd(Q, K, V, O=None, dtype="bf16", stream=None):
     """O = (Q K^T) V with each score row divided by its L2 norm; tensors are [B,H,N,d]."""
     lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
+        done = _fast.forward(Q, K, V, None, None, code, True, True, False) if stream is None else None
+        if done is not None:
+            return done
         O = _alloc_out(Q, dtype)
     B, H, N, d, _, _ = _check_forward(Q, K, V, O, None, None, code, same_h=True)
     _launch_cross(lib, Q, K, V, None, O, None, B, H, H, N, N, d, code, stream, own_output)
@@ -366,6 +382,9 @@ def sphattn_fwd_z(Q, K, V, O=None, Z=None, dtype="bf16", stream=None):
     import torch
     lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
+        done = _fast.forward(Q, K, V, None, Z, code, True, True, Z is None) if stream is None else None
+        if done is not None:
+            return done if Z is None else (done, Z)
         O = _alloc_out(Q, dtype)
     if Z is None:
         Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
@@ -391,6 +410,9 @@ def sphattn_grn_fwd(Q, K, V, mult=None, O=None, dtype="bf16", stream=None):
     None) and K, V of shape [B,H_kv,N,d] shared by groups of H/H_kv query heads."""
     lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
+        done = _fast.forward(Q, K, V, mult, None, code, True, False, False) if stream is None else None
+        if done is not None:
+            return done
         O = _alloc_out(Q, dtype)
     B, H, N, d, H_kv, _ = _check_forward(Q, K, V, O, mult, None, code)
     _launch_cross(lib, Q, K, V, mult, O, None, B, H, H_kv, N, N, d, code, stream, own_output)
@@ -414,10 +436,24 @@ def sphattn_cross_fwd(Q, K, V, mult=None, O=None, Z=None, dtype="bf16", stream=N
     multiplicities mult [B,N_k], optional row aggregates Z [B,H,N_q]); returns O [B,H,N_q,d]."""
     lib, code, own_output = load_library(), _dtype_code(dtype), O is None
     if O is None:
+        done = _fast.forward(Q, K, V, mult, Z, code, False, False, False) if stream is None else None
+        if done is not None:
+            return done
         O = _alloc_out(Q, dtype)
     B, H, Nq, d, H_kv, Nk = _check_forward(Q, K, V, O, mult, Z, code, same_n=False)
     _launch_cross(lib, Q, K, V, mult, O, Z, B, H, H_kv, Nq, Nk, d, code, stream, own_output)
     return O
+
+
+def _cross_fwd_z(Q, K, V, mult, dtype):
+    """sphattn_cross_fwd of a self-attention shape that also returns the row aggregates: (O, Z)."""
+    import torch
+    load_library()
+    done = _fast.forward(Q, K, V, mult, None, _dtype_code(dtype), True, False, True)
+    if done is not None:
+        return done
+    Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
+    return sphattn_cross_fwd(Q, K, V, mult, Z=Z, dtype=dtype), Z
 
 
 def sphattn_partial_fwd(Q, K, V, mult=None, o_part=None, z_part=None, dtype="bf16", stream=None):
@@ -530,6 +566,9 @@ def sphattn_fp8_fwd(Q, K, V, workspace, O=None, stream=None, _entry="sphattn_fp8
     import torch
     lib = load_library()
     if O is None:
+        done = _fast.fp8_forward(Q, K, V, None, workspace) if stream is None and _entry == "sphattn_fp8_fwd" else None
+        if done is not None:
+            return done
         O = torch.empty(Q.shape, dtype=torch.bfloat16, device=Q.device)
     ws_bytes = _need_workspace(workspace)
     B, H, N, d, H_kv = _check_fp8(Q, K, V, O, None)
@@ -550,6 +589,9 @@ def sphattn_fp8_grn_fwd(Q, K, V, mult, workspace, O=None, stream=None):
     import torch
     lib = load_library()
     if O is None:
+        done = _fast.fp8_forward(Q, K, V, mult, workspace) if stream is None else None
+        if done is not None:
+            return done
         O = torch.empty(Q.shape, dtype=torch.bfloat16, device=Q.device)
     ws_bytes = _need_workspace(workspace)
     B, H, N, d, H_kv = _check_fp8(Q, K, V, O, mult)
@@ -603,6 +645,10 @@ def sphattn_grn_bwd(Q, K, V, mult, O, dO, Z, dQ=None, dK=None, dV=None, delta=No
     import torch
     lib, code = load_library(), _dtype_code(dtype)
     own_outputs = dQ is None and dK is None and dV is None and delta is None
+    if own_outputs and stream is None:
+        done = _fast.backward(Q, K, V, mult, O, dO, Z, code, False)
+        if done is not None:
+            return done
     dQ = torch.empty_like(Q) if dQ is None else dQ
     dK = torch.empty_like(K) if dK is None else dK
     dV = torch.empty_like(V) if dV is None else dV
@@ -618,6 +664,10 @@ def sphattn_bwd(Q, K, V, O, dO, Z, dQ=None, dK=None, dV=None, delta=None, dtype=
     import torch
     lib, code = load_library(), _dtype_code(dtype)
     own_outputs = dQ is None and dK is None and dV is None and delta is None
+    if own_outputs and stream is None:
+        done = _fast.backward(Q, K, V, None, O, dO, Z, code, True)
+        if done is not None:
+            return done
     dQ = torch.empty_like(Q) if dQ is None else dQ
     dK = torch.empty_like(K) if dK is None else dK
     dV = torch.empty_like(V) if dV is None else dV

@@ -7,6 +7,7 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB_PATH = os.path.join(_HERE, "libsphattn.so")
+MARSHAL_PATH = os.path.join(_HERE, "_marshal.so")
 SOURCES = [os.path.join(CSRC, "sphattn_api.hip")]
 
 HIPCC_FLAGS = [
@@ -38,3 +39,22 @@ def build_library(verbose: bool = False) -> str:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed building libsphattn.so")
     return LIB_PATH
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile the CPython extension in front of the library (csrc/marshal.cpp; host code only) and return its path."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{base}/include", f"-I{base}/include/torch/csrc/api/include", "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}",
+           "-o", MARSHAL_PATH, os.path.join(CSRC, "marshal.cpp"), f"-L{base}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if verbose or res.returncode != 0:
+        print(" ".join(cmd))
+        print(res.stdout)
+        print(res.stderr)
+    if res.returncode != 0:
+        raise RuntimeError("the compiler failed building _marshal.so")
+    return MARSHAL_PATH

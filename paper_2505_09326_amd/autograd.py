@@ -10,7 +10,7 @@ two backward kernels.  Nothing is computed here.
 """
 import torch
 
-from . import sphattn_bwd, sphattn_cross_fwd, sphattn_fwd_z, sphattn_grn_bwd
+from . import _cross_fwd_z, sphattn_bwd, sphattn_fwd_z, sphattn_grn_bwd
 
 _DTYPES = {torch.bfloat16: "bf16", torch.float16: "f16"}
 
@@ -26,11 +26,7 @@ class _SphericalAttention(torch.autograd.Function):
         dtype = _DTYPES[Q.dtype]
         Q, K, V = Q.contiguous(), K.contiguous(), V.contiguous()
         plain = mult is None and K.shape[1] == Q.shape[1]
-        if plain:
-            O, Z = sphattn_fwd_z(Q, K, V, dtype=dtype)
-        else:
-            Z = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-            O = sphattn_cross_fwd(Q, K, V, mult, Z=Z, dtype=dtype)
+        O, Z = sphattn_fwd_z(Q, K, V, dtype=dtype) if plain else _cross_fwd_z(Q, K, V, mult, dtype)
         ctx.save_for_backward(Q, K, V, O, Z)
         ctx.mult, ctx.plain, ctx.dtype = mult, plain, dtype
         return O
