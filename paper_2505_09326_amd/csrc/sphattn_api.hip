@@ -251,13 +251,12 @@ long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_be
     return hipGetLastError() == hipSuccess ? resident : -1;
 }
 
-template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL = false>
+template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL = false, int WAVES = kWaves>
 int launch_pipelined(const Problem& p)
 {
-    constexpr int BR = kWaves * 16 * NQ;
-    constexpr int EQ = QKT == QKType::Fp8 ? 1 : 2;
-    constexpr int lds_bytes = kNBuf * kBC * (D * EQ + D * 2 + (MULT ? 4 : 0));
-    auto kern = fwd_pipelined_kernel<D, NQ, QKT, NORM, MULT, PARTIAL>;
+    constexpr int BR = WAVES * 16 * NQ, threads = 64 * WAVES;
+    constexpr int lds_bytes = pipelined_lds_bytes<D, NQ, QKT, MULT, WAVES>();
+    auto kern = fwd_pipelined_kernel<D, NQ, QKT, NORM, MULT, PARTIAL, WAVES>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
@@ -267,7 +266,7 @@ int launch_pipelined(const Problem& p)
     const float scale_log2 = 1.4426950408889634f / __builtin_sqrtf((float)D);
     // persistent workgroups: as many as the chip runs at once (a multiple of the XCD count), or
     // one per item if that is fewer
-    const long long resident = (long long)kXcds * stream_period(kern, lds_bytes, period);
+    const long long resident = (long long)kXcds * stream_period(kern, lds_bytes, period, threads);
     // d = 64, a remainder of at most half a round behind at least one full round: the full rounds
     // run here and the remaining tiles as two 128-row halves each in a launch of their own, which
     // fills twice as many CUs for 0.6 of the time.  In full rounds, with f = remainder / resident:
@@ -276,7 +275,7 @@ int launch_pipelined(const Problem& p)
     // 8192 x 64 (640 tiles, 1.25 rounds) 273 against 306 us, 12 x 12345 x 64 387 against 425 us.
     // At d = 128 the 128-row kernel is too much slower per row for this (8 x 41472 x 128: 4.84
     // against 4.66 ms, 4 x 20000 x 128: 649 against 632 us), and the balanced grid stays.
-    constexpr bool HAS_HALVES = D == 64 && NQ == 4 && !PARTIAL && !MULT && NORM == Norm::Spherical && QKT != QKType::Fp8;
+    constexpr bool HAS_HALVES = D == 64 && NQ == 4 && WAVES == kWaves && !PARTIAL && !MULT && NORM == Norm::Spherical && QKT != QKType::Fp8;
     if constexpr (HAS_HALVES) {
         const long long full = resident > 0 ? n_wg / resident : 0, rem = resident > 0 ? n_wg % resident : 0;
         if (p.tile_rows == 0 && full >= 1 && rem > 0) {
@@ -294,7 +293,7 @@ int launch_pipelined(const Problem& p)
         }
     }
     const long long grid = balanced_grid(n_wg, resident);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds_bytes, p.stream,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds_bytes, p.stream,
                        p.Q, p.K, p.V, p.O, p.mult, p.Z,
                        p.Nq, p.Nk, p.H, p.H / p.H_kv, n_qtiles, (int)n_wg,
                        p.n_splits, p.keys_per_split, scale_log2, 0, (int)n_wg);
@@ -385,6 +384,8 @@ int launch_spherical(const Problem& p)
         if (form == kRows256Wide) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 4, 2>(p);
     }
     if (form == kRows128) return launch_keysplit<D, 4, QKT, MULT, PARTIAL, 2, 2>(p);
+    if constexpr (D == 64 && !(FP8 && MULT))
+        if (p.tile_rows == 0 && rows512_pay(slices, p.Nq, tiles, Storage{BF16, FP8, MULT}, !PARTIAL, cus)) return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL, 8>(p);
     return launch_pipelined<D, 4, QKT, Norm::Spherical, MULT, PARTIAL>(p);
 }
 

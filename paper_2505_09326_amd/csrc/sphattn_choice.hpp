@@ -55,6 +55,27 @@ inline FormChoice choose_form(long long slices, long long Nq, long long tiles, i
     return best;
 }
 
+// d = 64, launches of more 256-row workgroups than CUs: 512 rows in eight waves, one workgroup per CU, in place of two of 256 rows in four
+// waves, which share nothing: each byte of K and V is copied to LDS once per CU and not twice, and the waves of a SIMD stay at one tile by themselves.  8 x
+// 32768 1354.5 -> 1326.7 us, 32 x 8192 370 -> 350, 9 x 8192 (one round, half filled) 152 -> 135, with counts 20 x 8192 358 -> 332, fp8 Q/K 289 -> 266;
+// fp8 Q/K with counts, which spills, 2 to 5 % slower.  Above one round it is the thinner last round that decides (a round filled to f
+// costs 0.5 + 0.5 f; 256-row launches of 16-bit storage without counts may run theirs as halves, launch_pipelined): 8 x 17000 481 us, 547 with this,
+// 8 x 24576 856 and 879.  Not on short key axes there (260 x 512 with counts 26.2, 33.8; 200 x 700 41.4, 40.3).  Rows are added up in the
+// same order either way.
+inline bool rows512_pay(long long slices, long long Nq, long long tiles, Storage st, bool whole, long long cus)
+{
+    const long long n256 = slices * ((Nq + 255) / 256), n512 = slices * ((Nq + 511) / 512);
+    if (n256 <= cus || (st.fp8 && st.counts)) return false;
+    if (n512 <= cus) return true;
+    const long long full = n256 / (2 * cus), rest = n256 % (2 * cus);
+    double cost256 = 0.5 * (double)(full + (rest != 0)) + 0.25 * (double)n256 / (double)cus;
+    if (whole && !st.fp8 && !st.counts && full >= 1 && rest > 0 && rest <= cus) {
+        const double halves = (double)full + 0.3 + 0.3 * (double)rest / (double)cus;
+        cost256 = halves < cost256 ? halves : cost256;
+    }
+    return tiles >= 10 && 0.5 * (double)((n512 + cus - 1) / cus) + 0.5 * (double)n512 / (double)cus <= 1.02 * cost256;
+}
+
 // The same for a launch that has to add a row's terms in the order of kRows256, as Narrow does too (where the launch has it).  Narrow where it is one
 // workgroup per CU (4 x 1999 x 128 22.3 us, 38.2 on 256 rows); two on a CU in place of kRows256Wide, on short key axes only (Narrow / 256 rows,
 // d = 64: 32 x 2048 30.7 / 31.6, 24 x 2500 35.5 / 36.1, then 20 x 3000 39.2 / 37.1, 8 x 6000 65.2 / 60.3, 3 x 20000 235 / 226).

@@ -132,9 +132,20 @@ __device__ __forceinline__ void copy_to_lds_b32(i32x4 rsrc, uint32_t lds, int vo
                  :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 
+// LDS of a workgroup: the tile buffers; Q behind them where two of them do not hold it.
+template <int D, QKType QKT, bool MULT> constexpr int pipelined_buffer_bytes() { return kBC * (D * (QKT == QKType::Fp8 ? 1 : 2) + D * 2 + (MULT ? 4 : 0)); }
+template <int D, int NQ, QKType QKT, bool MULT, int WAVES>
+constexpr bool pipelined_q_behind() { return WAVES * 16 * NQ * D * (QKT == QKType::Fp8 ? 1 : 2) > 2 * pipelined_buffer_bytes<D, QKT, MULT>(); }
+template <int D, int NQ, QKType QKT, bool MULT, int WAVES>
+constexpr int pipelined_lds_bytes()
+{
+    return kNBuf * pipelined_buffer_bytes<D, QKT, MULT>() + (pipelined_q_behind<D, NQ, QKT, MULT, WAVES>() ? WAVES * 16 * NQ * D * (QKT == QKType::Fp8 ? 1 : 2) : 0);
+}
+
+
 // One work item: the query tile (and key slice) number `item` of the launch's n_items, streamed
 // forwards or backwards over its keys.  Called by every thread of the workgroup.
-template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL>
+template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL, int WAVES>
 __device__ __forceinline__
 void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
                         const void* __restrict__ Vv, void* __restrict__ Ov,
@@ -146,7 +157,7 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     constexpr bool FP8 = QKT == QKType::Fp8;
     constexpr bool HALF = QKT == QKType::F16;      // 16-bit type of V, O and P
     constexpr int BC = kBC;
-    constexpr int BR = kWaves * 16 * NQ;
+    constexpr int BR = WAVES * 16 * NQ;
     constexpr int EQ = FP8 ? 1 : 2;                // bytes per Q/K element
     constexpr int KROWB = D * EQ, KCH = KROWB / 16, KTILE = BC * KROWB;   // as stored in HBM
     constexpr int VROWB = D * 2, VCH = VROWB / 16, VTILE = BC * VROWB;
@@ -160,8 +171,10 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     constexpr int KLDS = KTILE;                    // K tile in LDS
     constexpr int MLDS = KTILE + VTILE;            // the tile's 64 multiplicities (MULT only)
     constexpr int BUF_BYTES = KTILE + VTILE + (MULT ? BC * 4 : 0);   // K tile, V tile, multiplicities
-    constexpr int LDK = KBLK;                      // 1 KB copies per wave per K tile (wave w: rows 16w..16w+15)
-    constexpr int LDV = DB / 2;                    // ... per V tile (two V blocks each)
+    constexpr int LDK = (4 * KBLK + WAVES - 1) / WAVES;   // 1 KB copies per wave per K tile, a block each (four waves: rows 16w..16w+15)
+    constexpr int KSHARES = 4 * KBLK / LDK;        // (fewer than waves: the same blocks twice)
+    constexpr int LDV = 2 * DB / WAVES;            // ... per V tile (two V blocks each)
+    static_assert(LDK <= KBLK && LDV <= DB / 2, "a wave's share lies in one row of blocks");
     constexpr int NST = LDK + LDV + (MULT ? 1 : 0);   // and one 256-byte copy (wave 0) of multiplicities
     constexpr int SLOTS = DB;                      // slots per sub-step: one V^T fragment each
     constexpr int KK = D / 32;                     // 16-bit: k-steps of K Q^T
@@ -224,8 +237,10 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // global -> LDS copies: lane l of a copy lands at LDS byte 16 l of the copy's 1 KB
     //   K copy c of wave w: block (w, c): row 16w + l/4, bytes 64c + 16 p, p = the piece of slot l%4
     //   V copy c of wave w: blocks (w, 2c), (w, 2c+1): row 16w + (l%32)/2, bytes 64c + 32 (l/32) + 16 (l%2)
-    const int kld_lane = (16 * wave + (lane >> 2)) * KROWB + block_piece_in_slot(lane) * 16;
-    const int vld_lane = (16 * wave + ((lane & 31) >> 1)) * VROWB + (lane >> 5) * 32 + (lane & 1) * 16;
+    // (eight waves: share w of the blocks in this order)
+    const int kfirst = wave % KSHARES * LDK, vfirst = wave * LDV;
+    const int kld_lane = (16 * (kfirst / KBLK) + (lane >> 2)) * KROWB + kfirst % KBLK * 64 + block_piece_in_slot(lane) * 16;
+    const int vld_lane = (16 * (vfirst / (DB / 2)) + ((lane & 31) >> 1)) * VROWB + vfirst % (DB / 2) * 64 + (lane >> 5) * 32 + (lane & 1) * 16;
 
     // Q is read once and O written once by this workgroup and by no other: both go past the L2's
     // retention (non-temporal), so that what stays in the XCD's L2 between batches of workgroups
@@ -274,9 +289,9 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
         const uint32_t base = (uint32_t)(uintptr_t)buf;
         const int tile = src_tile(t);
         if (c < LDK)
-            copy_to_lds(krw, base + (wave_u * KBLK + c) * 1024, kld_lane, tile * KTILE + c * 64);
+            copy_to_lds(krw, base + (wave_u % KSHARES * LDK + c) * 1024, kld_lane, tile * KTILE + c * 64);
         else if (c < LDK + LDV)
-            copy_to_lds(vrw, base + KLDS + (wave_u * DB + 2 * (c - LDK)) * 512, vld_lane, tile * VTILE + (c - LDK) * 64);
+            copy_to_lds(vrw, base + KLDS + (wave_u * LDV + c - LDK) * 1024, vld_lane, tile * VTILE + (c - LDK) * 64);
         else                                       // the tile's 64 multiplicities, by every wave
             copy_to_lds_b32(mrw, base + MLDS, lane * 4, tile * BC * 4);
     };
@@ -286,9 +301,9 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // instruction's 64 lanes touch 16 rows and Q arrives at 16 bytes per cycle and CU: 1.9 us for the
     // 64 KB of d = 128; copied, at twice that).
     constexpr int QWAVE = 16 * NQ * KROWB;
-    static_assert(kWaves * QWAVE <= 2 * BUF_BYTES, "Q fits buffers 2 and 3");
+    constexpr int QLDS = pipelined_q_behind<D, NQ, QKT, MULT, WAVES>() ? NBUF * BUF_BYTES : 2 * BUF_BYTES;
     const i32x4 qrw = rsrc_words(Qh, (uint32_t)Nq * KROWB);   // rows past the last query arrive as zeros
-    const uint32_t qlds = 2 * BUF_BYTES + wave_u * QWAVE;
+    const uint32_t qlds = QLDS + wave_u * QWAVE;
     const int qld_lane = (lane >> 2) * KROWB + block_piece_in_slot(lane) * 16;
 #pragma unroll
     for (int c = 0; c < NST; ++c) copy_chunk(c, 0, smem);
@@ -331,7 +346,7 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // buffer 3 plays "tile -1" for the first stage C, which multiplies its second sub-step of V with P = 0
     {
         const i32x4 zero4 = {0, 0, 0, 0};
-        for (int i = tid; i < VTILE / 32; i += kThreads)
+        for (int i = tid; i < VTILE / 32; i += 64 * WAVES)
             *reinterpret_cast<SPH_LDS i32x4*>(smem + (NBUF - 1) * BUF_BYTES + KLDS + VTILE / 2 + i * 16) = zero4;
     }
 #pragma unroll
@@ -661,7 +676,7 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // tile), 16 bytes per lane and whole rows per instruction.
     const __amdgpu_buffer_rsrc_t orw = make_rsrc((unsigned short*)Ov + head_off, (uint32_t)Nq * D * 2);
     constexpr int ROWS = 16 * NQ;
-    static_assert(kWaves * ROWS * (D * 2 + 16) <= NBUF * BUF_BYTES, "the output stage fits the tile buffers");
+    static_assert(WAVES * ROWS * (D * 2 + 16) <= pipelined_lds_bytes<D, NQ, QKT, MULT, WAVES>(), "the output stage fits the tile buffers");
     SPH_LDS unsigned char* stage = smem + wave * ROWS * (D * 2 + 16);
     __syncthreads();
 #pragma unroll
@@ -709,13 +724,14 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
 // fp32 rounding).  O goes past the L2's retention (non-temporal stores) only when later batches
 // follow; a one-batch launch gains nothing from that, and its last stores would complete later
 // (measured on 256 workgroups of 32 tiles: 30.9 against 28.9 us).
-// At d = 64 two workgroups share a CU (64 KB of LDS each, 48 KB with fp8 Q/K; two waves per SIMD,
+// At d = 64 two workgroups of four waves share a CU, or one of eight has it (WAVES; rows512_pay in sphattn_choice.hpp).
+// Two share it (64 KB of LDS each, 48 KB with fp8 Q/K; two waves per SIMD,
 // which fill each other's waits): the kernels are held to the 256 registers that this takes.  The
 // spherical one needs 258 otherwise, and one workgroup per CU costs it 5 % on 8 x 32768 x 64; the
 // SoftMax normalizer, whose stage B is the longer, gains 21 % (with 32 bytes of scratch per lane),
 // the fp8 Q/K kernel 4.5 % (20 to 68 bytes).
-template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL = false>
-__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1)
+template <int D, int NQ, QKType QKT, Norm NORM, bool MULT, bool PARTIAL = false, int WAVES = kWaves>
+__global__ __launch_bounds__(64 * WAVES, D == 64 ? 2 : 1)
 void fwd_pipelined_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv,
                           const void* __restrict__ Vv, void* __restrict__ Ov,
                           const float* __restrict__ mult, float* __restrict__ Zv,
@@ -728,7 +744,7 @@ void fwd_pipelined_kernel(const void* __restrict__ Qv, const void* __restrict__ 
     for (int item = item_begin + blockIdx.x; item < item_end; item += gridDim.x, ++batch) {
         // the LDS buffers change hands: every wave must be done with the previous item's tiles
         if (batch > 0) __syncthreads();
-        fwd_pipelined_item<D, NQ, QKT, NORM, MULT, PARTIAL>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
+        fwd_pipelined_item<D, NQ, QKT, NORM, MULT, PARTIAL, WAVES>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
                                                             n_splits, keys_per_split, scale_log2,
                                                             item, batch % 2 == 1, several_batches);
     }
