@@ -211,16 +211,16 @@ long long balanced_grid(long long n_items, long long resident)
 }
 
 // The key-split kernel over a launch's items of 16 NQ RG query rows.
-template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int RG, int KG>
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int RG, int KG, int CS = 1>
 int launch_keysplit(const Problem& p)
 {
-    constexpr int BR = 16 * NQ * RG, threads = 64 * keysplit_waves<RG, KG>(), lds_bytes = keysplit_lds_bytes<D, NQ, RG, KG, QKT, MULT>();
-    auto kern = fwd_keysplit_kernel<D, NQ, QKT, MULT, PARTIAL, RG, KG>;
+    constexpr int BR = 16 * NQ * RG, threads = 64 * keysplit_waves<RG, KG>(), lds_bytes = keysplit_lds_bytes<D, NQ, RG, KG, QKT, MULT, D / CS>();
+    auto kern = fwd_keysplit_kernel<D, NQ, QKT, MULT, PARTIAL, CS, RG, KG>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
     const int n_qtiles = (p.Nq + BR - 1) / BR;
-    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
+    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits * CS;
     if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
     const long long grid = balanced_grid(n_wg, (long long)kXcds * stream_period(kern, lds_bytes, period, threads));
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), lds_bytes, p.stream,
@@ -237,7 +237,7 @@ template <int D, QKType QKT>
 long long launch_halves(const Problem& p, int n_qtiles, int n_items, int item_begin, bool backwards, bool resident_only)
 {
     constexpr int lds_bytes = keysplit_lds_bytes<D, 4, 2, 2, QKT, false>();
-    auto kern = fwd_keysplit_kernel<D, 4, QKT, false, false, 2, 2>;
+    auto kern = fwd_keysplit_kernel<D, 4, QKT, false, false, 1, 2, 2>;
     static std::atomic<uint64_t> done{0};
     static std::atomic<int> period[64];
     if (!raise_lds_limit(kern, lds_bytes, done)) return 0;
@@ -368,8 +368,11 @@ int launch_spherical(const Problem& p)
 {
     constexpr bool FP8 = QKT == QKType::Fp8, BF16 = QKT == QKType::Bf16;
     const long long slices = (long long)p.B * p.H * p.n_splits, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
-    Form form = p.tile_rows == 128 ? kRows128 : p.tile_rows == 256 ? kRows256
-              : choose_form(slices, p.Nq, tiles, D, Storage{BF16 && !PARTIAL, FP8, MULT}, cus).form;
+    const Storage st{BF16 && !PARTIAL, FP8, MULT};
+    const FormChoice choice = p.tile_rows != 0 ? FormChoice{p.tile_rows == 128 ? kRows128 : kRows256, 0.0} : choose_form(slices, p.Nq, tiles, D, st, cus);
+    if constexpr (!FP8)
+        if (!p.one_key_order && half_columns(choice, slices, p.Nq, tiles, D, st, cus)) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 4, 2>(p);
+    Form form = choice.form;
     if (p.one_key_order) form = in_one_key_order(form, tiles, BF16 && !MULT && !PARTIAL);
     if constexpr (BF16 && !MULT && !PARTIAL)
         if (form == kNarrow) return launch_pipelined<D, 2, QKT, Norm::Spherical, MULT, PARTIAL>(p);
@@ -710,7 +713,8 @@ int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
 // The library's choice of slices for a rectangular problem, in the launch's terms (packed_group).
 // A launch is cut only while all its slices still run at once as workgroups of 128 rows or fewer, one
 // per CU (1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  Either side is priced as the launch it would be
-// (choose_form, choose_f32), as without counts, which the plan does not know and which raise both, and without Narrow, which parts have not
+// (choose_form, choose_f32; halves of the columns, which both sides may be launched in, change no more than the two's difference on short
+// axes: priced, 1 x 2048 x 128 13.9 -> 12.5 us, with counts 14.2 -> 14.4, 1 x 4000 x 64 12.2 -> 14.0), as without counts, which the plan does not know and which raise both, and without Narrow, which parts have not
 // and with which no plan over 2535 shapes differs; the second launch costs 4 us, and each part is written and read at 6 TB/s together.
 // Measured with the slices this picks against one: 1 x 8192 x 128 38 against 44 us, 1 x 8192 x 64 24 against 27.5; not cut:
 // 4 x 1999 x 128 (22.7 at best against 15.7), 8 x 1000 x 128 (18.1 against 10.9).

@@ -199,16 +199,18 @@ __device__ __forceinline__ void put_piece(SPH_LDS unsigned char* stage, int row,
     *reinterpret_cast<SPH_LDS i32x2*>(stage + row * (ROWB + 16) + byte) = v;
 }
 
-template <int ROWS, int ROWB>
+// (of STRIDE bytes, from byte `at` of them on)
+template <int ROWS, int ROWB, int STRIDE = ROWB>
 __device__ __forceinline__ void store_tile(const SPH_LDS unsigned char* stage, __amdgpu_buffer_rsrc_t rsrc,
-                                           int row0, int n_rows, int lane, bool non_temporal)
+                                           int row0, int n_rows, int lane, bool non_temporal, int at = 0)
 {
     constexpr int LPR = ROWB / 16;                 // lanes per row
 #pragma unroll
-    for (int i = 0; i < ROWS * LPR / 64; ++i) {
+    for (int i = 0; i < (ROWS * LPR + 63) / 64; ++i) {
         const int r = i * (64 / LPR) + lane / LPR, c = (lane % LPR) * 16;
+        if (ROWS * LPR % 64 != 0 && r >= ROWS) break;   // (fewer rows than lanes for them)
         const i32x4 v = *reinterpret_cast<const SPH_LDS i32x4*>(stage + r * (ROWB + 16) + c);
-        if (row0 + r < n_rows) store_b128(rsrc, (row0 + r) * ROWB + c, v, non_temporal);
+        if (row0 + r < n_rows) store_b128(rsrc, (row0 + r) * STRIDE + at + c, v, non_temporal);
     }
 }
 

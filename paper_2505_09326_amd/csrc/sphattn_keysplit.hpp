@@ -15,6 +15,8 @@
 //   2  2  4   64 rows, two waves per SIMD: 0.28 (0.16).  At d = 128 a tile is 64 KB and the copies (64 bytes per cycle and CU at
 //             most) and the fragment reads, both of the LDS, take 0.64 us of the 0.55 to 0.65 of 128 keys.
 //             1 x 12000 x 64 55.8 -> 41.1, 4 x 1999 x 128 17.0 -> 15.6 us.
+//   2  2  4   with CS = 2, half of the columns of V and O per workgroup, where that leaves no more than one on a CU: 0.255 (0.141), the copies
+//             48 KB of a tile's 64 (half_columns in sphattn_choice.hpp).  4 x 1999 x 128 15.6 -> 14.3, 8 x 1000 x 128 10.8 -> 9.5 us.
 //   4  1  4   64 rows, d = 128: every wave holds all rows, so each byte of K and V is read from LDS once and
 //             by the wave that copied it; no barrier in the loop.  0.28, less where many CUs stream (1 x 8192 x 128 53.5 -> 44.4) and
 //             with counts (61 -> 54); and the 64-row form of fp8 Q/K, whose score instruction wants four query blocks
@@ -50,33 +52,34 @@ template <int KG> constexpr int keysplit_keys() { return 32 * KG; }
 template <int D, int KG> constexpr int keysplit_buffers() { return KG == 4 && D == 128 ? 2 : kNBuf; }
 template <int D, int KG, bool MULT> constexpr int keysplit_v_buffers() { return keysplit_buffers<D, KG>() == 2 && !MULT ? 3 : keysplit_buffers<D, KG>(); }
 
-// LDS: the rings of K, V and the multiplicities; Q behind them where it does not fit V's ring.
-template <int D, int NQ, int RG, int KG, QKType QKT, bool MULT>
+// LDS: the rings of K, V (DV columns of it) and the multiplicities; Q behind them where it does not fit V's ring.
+template <int D, int NQ, int RG, int KG, QKType QKT, bool MULT, int DV = D>
 constexpr int keysplit_ring_bytes()
 {
-    return keysplit_keys<KG>() * D * (keysplit_buffers<D, KG>() * (QKT == QKType::Fp8 ? 1 : 2) + keysplit_v_buffers<D, KG, MULT>() * 2) +
+    return keysplit_keys<KG>() * (keysplit_buffers<D, KG>() * D * (QKT == QKType::Fp8 ? 1 : 2) + keysplit_v_buffers<D, KG, MULT>() * DV * 2) +
            (MULT ? 2 * keysplit_buffers<D, KG>() * (RG == 1 ? KG * 64 : keysplit_keys<KG>()) * 4 : 0);
 }
-template <int D, int NQ, int RG, int KG, QKType QKT>
+template <int D, int NQ, int RG, int KG, QKType QKT, int DV = D>
 constexpr bool keysplit_q_behind()
 {
-    return 16 * NQ * RG * (QKT == QKType::Fp8 ? 1 : 2) > (keysplit_buffers<D, KG>() == 2 ? 1 : 2) * keysplit_keys<KG>() * 2;
+    return 16 * NQ * RG * D * (QKT == QKType::Fp8 ? 1 : 2) > (keysplit_buffers<D, KG>() == 2 ? 1 : 2) * keysplit_keys<KG>() * DV * 2;
 }
 // What a wave receives when the key groups are added up, and the output stage.
-template <int D, int NQ> constexpr int keysplit_exchange_bytes() { return NQ / 2 * (D / 16 * 1024 + 256); }
-template <int D, int NQ, int RG> constexpr int keysplit_stage_bytes() { return 16 * NQ * RG * (D * 2 + 16); }
-template <int D, int NQ, int RG, int KG, QKType QKT, bool MULT>
+template <int DV, int NQ> constexpr int keysplit_exchange_bytes() { return NQ / 2 * (DV / 16 * 1024 + 256); }
+template <int DV, int NQ, int RG> constexpr int keysplit_stage_bytes() { return 16 * NQ * RG * (DV * 2 + 16); }
+template <int D, int NQ, int RG, int KG, QKType QKT, bool MULT, int DV = D>
 constexpr int keysplit_lds_bytes()
 {
-    constexpr int loop = keysplit_ring_bytes<D, NQ, RG, KG, QKT, MULT>() +
-                         (keysplit_q_behind<D, NQ, RG, KG, QKT>() ? 16 * NQ * RG * D * (QKT == QKType::Fp8 ? 1 : 2) : 0);
-    constexpr int exchange = keysplit_waves<RG, KG>() * keysplit_exchange_bytes<D, NQ>(), stage = keysplit_stage_bytes<D, NQ, RG>();
+    constexpr int loop = keysplit_ring_bytes<D, NQ, RG, KG, QKT, MULT, DV>() +
+                         (keysplit_q_behind<D, NQ, RG, KG, QKT, DV>() ? 16 * NQ * RG * D * (QKT == QKType::Fp8 ? 1 : 2) : 0);
+    constexpr int exchange = keysplit_waves<RG, KG>() * keysplit_exchange_bytes<DV, NQ>(), stage = keysplit_stage_bytes<DV, NQ, RG>();
     return loop > exchange ? (loop > stage ? loop : stage) : (exchange > stage ? exchange : stage);
 }
 
 // One work item; arguments as fwd_pipelined_item, and: query tiles are tile_rows apart (the workgroup's rows, or
-// twice as many when the item is one half, starting at row_off, of a wider tile).
-template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int RG, int KG>
+// twice as many when the item is one half, starting at row_off, of a wider tile).  CS = 2: an item is half of V's and O's columns
+// (items alternate between the halves).
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int CS, int RG, int KG>
 __device__ __forceinline__
 void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
                        const void* __restrict__ Vv, void* __restrict__ Ov,
@@ -94,17 +97,20 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     constexpr int MRING = 2 * NBUF;                // multiplicities outlive their K tile: a longer ring
     constexpr int EQ = FP8 ? 1 : 2;
     constexpr int KROWB = D * EQ, KTILE = BC * KROWB;
-    constexpr int VROWB = D * 2, VTILE = BC * VROWB;
-    constexpr int DB = D / 16, KBLK = KROWB / 64, VBLK = VROWB / 64, KK = D / 32;
+    constexpr int DV = D / CS;                     // columns of V and O of an item
+    constexpr int VROWB = D * 2, VTILE = BC * DV * 2;   // row of V in HBM, its tile in LDS
+    constexpr int DB = DV / 16, KBLK = KROWB / 64, VBLK = DV * 2 / 64, KK = D / 32;
     constexpr int VLDS = NBUF * KTILE;             // V ring behind the K ring
     constexpr int MLDS = VLDS + NVB * VTILE;       // multiplicities behind both
     constexpr int LDK = (BC / 16 * KBLK + WAVES - 1) / WAVES, LDV = BC / 16 * VBLK / WAVES;   // 1 KB copies per wave per K and per V tile
     constexpr int NST = LDK + LDV + (MULT ? 1 : 0);
-    constexpr int SLOTS = DB, PD = 3, RING = 4;
+    constexpr int SLOTS = D / 16, PD = 3, RING = 4;
+    constexpr int VSTEP = SLOTS / DB;              // slots per V^T fragment
     constexpr int QKM = FP8 ? 2 * NQ / SLOTS : NQ; // score matrix instructions per slot
     constexpr int PAIRS = 4 * NQ / SLOTS;          // score register pairs of stage B per slot
-    constexpr int VALU_PER_MFMA = (MULT || D == 64) ? 2 : 1;
+    constexpr int VALU_PER_MFMA = (MULT || D == 64 || CS == 2) ? 2 : 1;
     static_assert(NQ == 4 || NQ == 2, "64 or 32 query rows per wave");
+    static_assert(CS == 1 || (CS == 2 && !FP8 && RG == 2 && KG == 4 && NQ == 2), "halves of the columns: the form that has them");
     static_assert(KG == 2 || KG == 4, "two or four key groups");
     constexpr int KSHARES = BC / 16 * KBLK / LDK;  // (fewer than waves: the same blocks twice)
     static_assert(KSHARES * LDK * 16 == BC * KBLK && WAVES % KSHARES == 0 && LDV * WAVES * 16 == BC * VBLK && (LDK % KBLK == 0 || KBLK % LDK == 0) && (LDV % VBLK == 0 || VBLK % LDV == 0),
@@ -129,7 +135,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int rg = wave_u % RG, kg = wave_u / RG;  // row group, key group
 
-    const int lid = xcd_contiguous_id(item, n_items);
+    const int id = xcd_contiguous_id(item, n_items), lid = id / CS, cs = id % CS;
     const int qt = lid % n_qtiles;
     const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
     const int bh = PARTIAL ? lid / (n_qtiles * n_splits) : lid / n_qtiles;
@@ -149,7 +155,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     auto vfrag = [&](int i) { return V32 ? vlane[0] + i * 512 : vlane[i & 1] + (i >> 1) * 1024; };   // V^T fragment i of the wave's keys
     const int kshare = wave % KSHARES;
     const int kld_lane = (kshare * LDK / KBLK * 16 + (lane >> 2)) * KROWB + kshare * LDK % KBLK * 64 + block_piece_in_slot(lane) * 16;
-    const int vld_lane = wave * LDV / VBLK * 16 * VROWB + wave * LDV % VBLK * 64 +
+    const int vld_lane = cs * DV * 2 + wave * LDV / VBLK * 16 * VROWB + wave * LDV % VBLK * 64 +
                          (V32 ? ((lane & 31) >> 1) * VROWB + (lane >> 5) * 32 + (lane & 1) * 16 : (lane >> 2) * VROWB + block_piece_in_slot(lane) * 16);
 
     const int n_tiles = (N + BC - 1) / BC;
@@ -165,7 +171,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     uint32_t rot[3] = {2 * VTILE, 0, VTILE};
     auto v_buffer = [&](int t, int r) -> uint32_t { return NVB == 3 ? rot[(r + 1) % 3] : (uint32_t)((t + r) & (NBUF - 1)) * VTILE; };
     auto copy_v = [&](int c, int t, uint32_t buffer) {
-        copy_to_lds(vrw, lds0 + VLDS + buffer + (wave_u * LDV + c) * 1024, vld_lane, src_tile(t) * VTILE + c / VBLK * 16 * VROWB + c % VBLK * 64);
+        copy_to_lds(vrw, lds0 + VLDS + buffer + (wave_u * LDV + c) * 1024, vld_lane, src_tile(t) * (BC * VROWB) + c / VBLK * 16 * VROWB + c % VBLK * 64);
     };
     constexpr int MSLOT = OWN ? WAVES * 256 : BC * 4;
     auto copy_m = [&](int t) {                     // 64 of the tile's multiplicities, by every other or by every wave
@@ -191,9 +197,9 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     // and both key groups would fetch it (64 KB = 1.8 us at d = 128); as 1 KB block copies, once, it
     // takes a quarter of that.  It waits in the buffers of V_1 and V_2 (V_0 where there are two), or behind the rings, in
     // K's block format.
-    constexpr bool QBEHIND = keysplit_q_behind<D, NQ, RG, KG, QKT>();
+    constexpr bool QBEHIND = keysplit_q_behind<D, NQ, RG, KG, QKT, DV>();
     constexpr int QTILE = 16 * NQ * RG * KROWB;
-    constexpr int QLDS = QBEHIND ? keysplit_ring_bytes<D, NQ, RG, KG, QKT, MULT>() : NVB == 2 ? VLDS : VLDS + VTILE;
+    constexpr int QLDS = QBEHIND ? keysplit_ring_bytes<D, NQ, RG, KG, QKT, MULT, DV>() : NVB == 2 ? VLDS : VLDS + VTILE;
     constexpr int QBLOCKS = QTILE / 1024, QCOPIES = (QBLOCKS + WAVES - 1) / WAVES;
     static_assert(QBLOCKS % WAVES == 0 || WAVES % QBLOCKS == 0, "every wave copies as many blocks (where there are few, the same ones)");
     const int tile_row0 = qt * tile_rows + row_off;
@@ -333,10 +339,12 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
         // (named by the tile read where that schedules the loop better: two key groups with counts 4 to 5 % on short key axes; not with four,
         // 1 x 12000 x 64 39.2 us for 38.2, nor in 256 rows with counts, 1 %)
         constexpr bool BY_TILE = KG == 2 && (RG == 2 || !MULT);
-        const SPH_LDS unsigned char* a = smem + (BY_TILE ? v_buffer(tt, -1) : v_buffer(t, u < SLOTS ? -1 : 0)) + vfrag(i);
-        const i32x2 lo = lds_read_tr64(a);
-        const i32x2 hi = lds_read_tr64(a + DB * 512);
-        vf[i % RING] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+        if (VSTEP == 1 || i % VSTEP == 0) {
+            const SPH_LDS unsigned char* a = smem + (BY_TILE ? v_buffer(tt, -1) : v_buffer(t, u < SLOTS ? -1 : 0)) + vfrag(i / VSTEP);
+            const i32x2 lo = lds_read_tr64(a);
+            const i32x2 hi = lds_read_tr64(a + DB * 512);
+            vf[i % RING] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+        }
         if constexpr (FP8) {
             if (i % (SLOTS / 2) == 0) {
                 const int kb = i / (SLOTS / 2);
@@ -398,10 +406,12 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
                     Sn[kb][qb] = mfma_qk(kf[i % RING], qf[qb][kk], kk == 0 ? zero : Sn[kb][qb]);
                 }
             }
-            // C: V^T fragment i against the previous tile's P
+            // C: V^T fragment i (one in VSTEP slots) against the previous tile's P
+            if (VSTEP == 1 || i % VSTEP == 0) {
 #pragma unroll
-            for (int qb = 0; qb < NQ; ++qb)
-                oacc[i][qb] = mfma16x16<HALF>(vf[i % RING], Pp[qb], oacc[i][qb]);
+                for (int qb = 0; qb < NQ; ++qb)
+                    oacc[i / VSTEP][qb] = mfma16x16<HALF>(vf[i % RING], Pp[qb], oacc[i / VSTEP][qb]);
+            }
             // B: PAIRS register pairs of the current tile's scores
 #pragma unroll
             for (int u = 0; u < PAIRS; ++u) {
@@ -424,7 +434,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
             if (i >= SLOTS - PD) copy_group(i - (SLOTS - PD), t, v_buffer(t, NVB - 1));
             else copy_group(i + PD, t - 1, v_buffer(t, NVB - 2));
             {
-                constexpr int NM = QKM + NQ;
+                const int NM = QKM + (i % VSTEP == 0 ? NQ : 0);
 #pragma unroll
                 for (int m = 0; m < NM; ++m) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
@@ -447,7 +457,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     {
         const SPH_LDS unsigned char* vp = smem + v_buffer(n_run, -1);
 #pragma unroll
-        for (int i = 0; i < SLOTS; ++i) {
+        for (int i = 0; i < DB; ++i) {
             const i32x2 lo = lds_read_tr64(vp + vfrag(i));
             const i32x2 hi = lds_read_tr64(vp + vfrag(i) + DB * 512);
             const i32x4 vfr = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
@@ -461,7 +471,7 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     // is left, its columns.
     constexpr int HQ = NQ / 2;
     constexpr bool FOUR = KG == 4, DSPLIT = FOUR && HQ == 1;
-    constexpr int EXB = keysplit_exchange_bytes<D, NQ>();
+    constexpr int EXB = keysplit_exchange_bytes<DV, NQ>();
     __builtin_amdgcn_s_waitcnt(0x0F70);            // the copies past the end must not land in what follows
     __syncthreads();
     const bool odd = kg & 1, high = FOUR && kg >= 2;
@@ -533,15 +543,15 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     const int row0 = tile_row0 + wrow;
 
     if constexpr (PARTIAL) {
-        const size_t rows0 = ((size_t)split * (n_items / (n_qtiles * n_splits)) + bh) * Nq;
+        const size_t rows0 = ((size_t)split * (n_items / (CS * n_qtiles * n_splits)) + bh) * Nq;
         float* Op = (float*)Ov + rows0 * D;
         float* Zp = Zv + rows0;
 #pragma unroll
         for (int q = 0; q < FQ; ++q) {
             const int row = row0 + q * 16 + n16;
             if (row < Nq) {
-                if (g == 0 && db0 == 0) Zp[row] = zf[q];
-                float* dst = Op + (size_t)row * D + db0 * 16 + 4 * g;
+                if (g == 0 && db0 == 0 && cs == 0) Zp[row] = zf[q];
+                float* dst = Op + (size_t)row * D + cs * DV + db0 * 16 + 4 * g;
 #pragma unroll
                 for (int db = 0; db < FD; ++db) *reinterpret_cast<f32x4*>(dst + db * 16) = fin[db][q];
             }
@@ -559,25 +569,25 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     for (int q = 0; q < FQ; ++q) {
         const float inv = zf[q] > 0.f ? 1.0f / __builtin_sqrtf(zf[q]) : 0.f;
         const int row = row0 + q * 16 + n16;
-        if (Zv != nullptr && g == 0 && db0 == 0 && row < Nq) Zv[(size_t)bh * Nq + row] = zf[q];
+        if (Zv != nullptr && g == 0 && db0 == 0 && cs == 0 && row < Nq) Zv[(size_t)bh * Nq + row] = zf[q];
 #pragma unroll
         for (int db = 0; db < FD; ++db) {
             const i32x2 o4 = {pack2<HALF>(fin[db][q][0] * inv, fin[db][q][1] * inv),
                               pack2<HALF>(fin[db][q][2] * inv, fin[db][q][3] * inv)};
-            put_piece<D * 2>(smem, wrow + q * 16 + n16, (db0 + db) * 32 + 8 * g, o4);
+            put_piece<DV * 2>(smem, wrow + q * 16 + n16, (db0 + db) * 32 + 8 * g, o4);
         }
     }
     if constexpr (FOUR) {
         __syncthreads();
-        store_tile<WROWS, D * 2>(smem + wave_u * WROWS * (D * 2 + 16), orw, tile_row0 + (int)wave_u * WROWS, Nq, lane, stream_out);
+        store_tile<WROWS, DV * 2, D * 2>(smem + wave_u * WROWS * (DV * 2 + 16), orw, tile_row0 + (int)wave_u * WROWS, Nq, lane, stream_out, cs * DV * 2);
     } else {                                       // (whole rows, the wave's own)
-        store_tile<WROWS, D * 2>(smem + wrow * (D * 2 + 16), orw, row0, Nq, lane, stream_out);
+        store_tile<WROWS, DV * 2, D * 2>(smem + wrow * (DV * 2 + 16), orw, row0, Nq, lane, stream_out, cs * DV * 2);
     }
 }
 
 // Persistent workgroups over the items, every other batch streaming the keys backwards, and the
 // remainder launch of half tiles: as fwd_pipelined_kernel.
-template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int RG, int KG>
+template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int CS, int RG, int KG>
 __global__ __launch_bounds__(64 * RG * KG, D == 64 || KG * RG == 8 ? 2 : 1)
 void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ Kv,
                          const void* __restrict__ Vv, void* __restrict__ Ov,
@@ -586,7 +596,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
                          int n_splits, int keys_per_split, int item_begin, int item_end, int halves)
 {
     constexpr int BR = 16 * NQ * RG;
-    constexpr bool HALVES = D == 64 && NQ == 4 && RG == 2 && KG == 2 && !MULT && !PARTIAL && QKT != QKType::Fp8;   // launch_halves
+    constexpr bool HALVES = D == 64 && CS == 1 && NQ == 4 && RG == 2 && KG == 2 && !MULT && !PARTIAL && QKT != QKType::Fp8;   // launch_halves
     if constexpr (HALVES) {
         if (halves) {
             // Remainder launch: the items item_begin .. item_end - 1 of a launch whose tiles are
@@ -599,7 +609,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
             if (item >= item_end) return;
             const int qt = xcd_contiguous_id(item, n_items) % n_qtiles;
             if (qt * 2 * BR + half * BR >= Nq) return;     // the tile's second half lies past the last row
-            fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL, RG, KG>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
+            fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL, CS, RG, KG>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
                                                      n_splits, keys_per_split, item, halves == 2, true, 2 * BR, half * BR);
             return;
         }
@@ -608,7 +618,7 @@ void fwd_keysplit_kernel(const void* __restrict__ Qv, const void* __restrict__ K
     int batch = 0;
     for (int item = item_begin + blockIdx.x; item < item_end; item += gridDim.x, ++batch) {
         if (batch > 0) __syncthreads();            // every wave is done with the previous item's LDS
-        fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL, RG, KG>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
+        fwd_keysplit_item<D, NQ, QKT, MULT, PARTIAL, CS, RG, KG>(Qv, Kv, Vv, Ov, mult, Zv, Nq, Nk, H, kv_group, n_qtiles, n_items,
                                                  n_splits, keys_per_split, item, batch % 2 == 1, several_batches, BR, 0);
     }
 }

@@ -22,6 +22,13 @@ extern "C" int form(long long slices, long long Nq, long long Nk, int d, int bf1
 extern "C" int form_in_one_order(int form, long long Nk) { return in_one_key_order((Form)form, (Nk + kChoiceTile - 1) / kChoiceTile, true); }
 extern "C" int f32_rows(long long heads, long long Nq, long long Nk, int d) { return choose_f32(heads, Nq, Nk, 1, d, %d).rows; }
 extern "C" int two_parts(long long Nk, int d) { return f32_two_parts(Nk, d); }
+extern "C" int halves(long long slices, long long Nq, long long Nk, int d, int bf16, int fp8, int counts)
+{
+    const long long tiles = (Nk + kChoiceTile - 1) / kChoiceTile;
+    const Storage st{bf16 != 0, fp8 != 0, counts != 0};
+    FormChoice c = choose_form(slices, Nq, tiles, d, st, %d);
+    return half_columns(c, slices, Nq, tiles, d, st, %d);
+}
 extern "C" int rows512(long long slices, long long Nq, long long Nk, int bf16, int fp8, int counts, int whole)
 {
     return rows512_pay(slices, Nq, (Nk + kChoiceTile - 1) / kChoiceTile, Storage{bf16 != 0, fp8 != 0, counts != 0}, whole != 0, %d);
@@ -31,7 +38,7 @@ extern "C" int fp8_shape(long long heads, long long N, int d, int counts)
     const Fp8Shape s = choose_fp8(heads, N, d, counts != 0, %d);
     return s.nq * 16 + s.waves;
 }
-""" % (CUS, CUS, CUS, CUS)
+""" % ((CUS,) * 6)
 
 
 @functools.lru_cache(maxsize=None)
@@ -46,6 +53,7 @@ def _library():
     lib.form_in_one_order.argtypes = [ctypes.c_int, ctypes.c_longlong]
     lib.f32_rows.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     lib.two_parts.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    lib.halves.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.rows512.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.fp8_shape.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int] * 2
     return lib
@@ -78,3 +86,8 @@ def fp8_shape(H, N, d, counts):
 def rows512(H, H_kv, Nq, Nk, dtype, counts, whole=True):
     """Whether a launch of d = 64 takes 512 rows in eight waves."""
     return bool(_library().rows512(H_kv, Nq * (H // H_kv), Nk, dtype == "bf16", dtype == "fp8qk_bf16v", counts, whole))
+
+
+def half_columns(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
+    """Whether a launch's workgroups have half of V's columns each."""
+    return bool(_library().halves(H_kv, Nq * (H // H_kv), Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts))
