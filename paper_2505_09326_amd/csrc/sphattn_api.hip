@@ -300,18 +300,19 @@ int launch_pipelined(const Problem& p)
     return hipGetLastError() == hipSuccess ? SPHATTN_OK : SPHATTN_ERR_LAUNCH;
 }
 
-// ROWS query rows per workgroup: 32 (four waves) or 16
-template <int D, int ROWS, bool MULT, bool PARTIAL>
+// ROWS query rows per workgroup: 32 (four waves) or 16, of which CS workgroups share the columns of V
+template <int D, int ROWS, bool MULT, bool PARTIAL, int CS = 1>
 int launch_f32(const Problem& p)
 {
+    static_assert(ROWS == kF32SmallRows || CS == 1, "shares of the columns: 16 rows");
     constexpr bool SMALL = ROWS == kF32SmallRows;
     constexpr int waves = SMALL ? f32_small_waves<D>() : kWaves;
     constexpr int lds_bytes = SMALL ? f32_small_lds_bytes<D>() : waves * 2 * 32 * (D + 4) * 4;
-    constexpr auto kern = SMALL ? fwd_f32_small_kernel<D, MULT, PARTIAL> : fwd_f32_kernel<D, MULT, PARTIAL>;
+    constexpr auto kern = SMALL ? fwd_f32_small_kernel<D, MULT, PARTIAL, CS> : fwd_f32_kernel<D, MULT, PARTIAL>;
     static std::atomic<uint64_t> done{0};
     if (!raise_lds_limit(kern, lds_bytes, done)) return SPHATTN_ERR_LAUNCH;
     const int n_qtiles = (p.Nq + ROWS - 1) / ROWS;
-    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits;
+    const long long n_wg = (long long)p.B * p.H * n_qtiles * p.n_splits * CS;
     if (n_wg > 0x7fffffff) return SPHATTN_ERR_SHAPE;
     hipLaunchKernelGGL(kern, dim3((unsigned)n_wg), dim3(64 * waves), lds_bytes, p.stream,
                        (const float*)p.Q, (const float*)p.K, (const float*)p.V, (float*)p.O, p.mult, p.Z,
@@ -343,7 +344,12 @@ int launch_f32_any(const Problem& p)
     const bool two = f32_two_parts(PARTIAL ? p.keys_per_split : p.Nk, D);
     if (rows == 128) return two ? launch_f32_parts<D, 1, MULT, PARTIAL, true>(p) : launch_f32_parts<D, 1, MULT, PARTIAL, false>(p);
     if (rows == 256) return two ? launch_f32_parts<D, 2, MULT, PARTIAL, true>(p) : launch_f32_parts<D, 2, MULT, PARTIAL, false>(p);
-    return rows == 16 ? launch_f32<D, 16, MULT, PARTIAL>(p) : launch_f32<D, 32, MULT, PARTIAL>(p);
+    if (rows == 32) return launch_f32<D, 32, MULT, PARTIAL>(p);
+    switch (f32_small_column_shares((long long)p.B * p.H * p.n_splits, p.Nq, cu_count())) {
+    case 4: return launch_f32<D, 16, MULT, PARTIAL, 4>(p);
+    case 2: return launch_f32<D, 16, MULT, PARTIAL, 2>(p);
+    default: return launch_f32<D, 16, MULT, PARTIAL>(p);
+    }
 }
 
 template <int D>

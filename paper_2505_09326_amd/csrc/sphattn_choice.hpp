@@ -133,6 +133,15 @@ inline F32Choice choose_f32(long long heads, long long Nq, long long keys_per_sl
     return best;
 }
 
+// Workgroups that share the columns of V of 16 rows on the fp32 instruction, as long as all have a CU of their own: such launches wait for one
+// wave's chain of matrix instructions, half of which are V's.  Four shares, 1 x 256 x 64 6.5 -> 5.3 us, of 128 10.6 -> 8.1; two, 4 x 300 x 64 7.6 -> 6.8, of 128
+// 14.1 -> 11.7.
+inline int f32_small_column_shares(long long slices, long long Nq, long long cus)
+{
+    const long long items = slices * ((Nq + 15) / 16);
+    return 4 * items <= cus ? 4 : 2 * items <= cus ? 2 : 1;
+}
+
 // The all-E4M3 forward's workgroup (sphattn_fp8.hpp): query blocks of 16 rows per wave, and waves.  64 rows while every CU gets at most
 // one such workgroup, else 128 likewise, else 256: over 300 launches of 1 to 64 heads of 190 to 23000 keys, every shape timed on each, that is 0 to
 // 0.5 % slower than the best shape in the mean and 4 % at most, and 0.68 to 0.76 of 256 rows in four waves (geometric mean; nowhere slower).

@@ -392,7 +392,7 @@ void fwd_f32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
 //
 // Half the rows and, at d = 64, where LDS holds eight waves' tiles, half the keys per wave: for one head
 // of 256 x 64 a wave spends 0.85 us on matrix instructions instead of 3.4.  One head of 256 x 64 11.4 us with
-// 32 rows, 6.5 with 16; of 256 x 128 20.6 / 10.6; 4 x 1000 x 64 27.3 / 15.7; 4 x 1000 x 128 52 / 33.  It
+// 32 rows, 6.5 with 16 (5.3 with the columns shared out); of 256 x 128 20.6 / 10.6 (8.1); 4 x 1000 x 64 27.3 / 15.7; 4 x 1000 x 128 52 / 33.  It
 // stages a tile for half the rows, so it loses where both shapes fill the CUs (2 x 4096 x 64 91 / 95,
 // 1 x 8192 x 128 352 / 467).
 // ---------------------------------------------------------------------------
@@ -403,8 +403,9 @@ constexpr int kF32SmallRows = 16;
 template <int D>
 constexpr int f32_small_lds_bytes() { return f32_small_waves<D>() * 2 * 32 * (D + 4) * 4; }
 
+// CS: the columns of V and O are dealt to CS workgroups per 16 rows, each of which forms all scores (f32_small_column_shares).
 // Nq, Nk, Zv, PARTIAL, n_splits and keys_per_split as in fwd_pipelined_kernel.
-template <int D, bool MULT, bool PARTIAL = false>
+template <int D, bool MULT, bool PARTIAL, int CS>
 __global__ __launch_bounds__(64 * f32_small_waves<D>(), 1)
 void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                     const float* __restrict__ V, float* __restrict__ O,
@@ -417,8 +418,9 @@ void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__
     constexpr int ROWF = D + 4;                    // padded row, in floats: conflict-free columns
     constexpr int TILE_F = BC * ROWF;
     constexpr int WAVE_F = 2 * TILE_F;             // K tile then V tile, private to a wave
-    constexpr int DB = D / 16, M = D / 16;
-    constexpr int LD = BC * D / 4 / 64;            // float4 loads per lane per tensor per tile
+    constexpr int DV = D / CS, VROWF = DV + 4;     // this workgroup's columns of V; padded row
+    constexpr int DB = DV / 16, M = D / 16;
+    constexpr int LD = BC * D / 4 / 64, LDV = BC * DV / 4 / 64;   // float4 loads per lane of K, of V per tile
     constexpr int PART = (DB * 4 + 1) * 64;        // a wave's partial: DB float4 per lane, then z
     static_assert(W * PART <= W * WAVE_F, "partials fit the staging space");
 
@@ -428,7 +430,7 @@ void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int n16 = lane & 15, g = lane >> 4;
-    const int lid = xcd_contiguous_id(blockIdx.x, n_wg);
+    const int id = xcd_contiguous_id(blockIdx.x, n_wg), lid = id / CS, cs = id % CS;
     const int qt = lid % n_qtiles;
     const int split = PARTIAL ? (lid / n_qtiles) % n_splits : 0;
     const int bh = PARTIAL ? lid / (n_qtiles * n_splits) : lid / n_qtiles;
@@ -437,34 +439,39 @@ void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__
     const int N = PARTIAL ? min(Nk - k0, keys_per_split) : Nk;      // keys k0 .. k0 + N - 1
     const size_t kv_off = ((size_t)(bidx * (H / kv_group) + (bh % H) / kv_group) * Nk + k0) * D;
     const float* Kh = K + kv_off;
-    const float* Vh = V + kv_off;
+    const float* Vh = V + kv_off + cs * DV;
     const float* mrow = MULT ? mult + (size_t)bidx * Nk + k0 : nullptr;
     const int q0 = qt * kF32SmallRows;
 
     SPH_LDS float* kb_ = smem + wave * WAVE_F;
     SPH_LDS float* vb_ = kb_ + TILE_F;
-    f32x4 kreg[LD], vreg[LD];
+    f32x4 kreg[LD], vreg[LDV];
     auto load_tile = [&](int j0) {
 #pragma unroll
         for (int i = 0; i < LD; ++i) {
-            const int id = lane + i * 64;
-            const int r = id / (D / 4), c = id % (D / 4);
-            if (j0 + r < N) {
-                kreg[i] = *reinterpret_cast<const f32x4*>(Kh + (size_t)(j0 + r) * D + 4 * c);
-                vreg[i] = *reinterpret_cast<const f32x4*>(Vh + (size_t)(j0 + r) * D + 4 * c);
-            } else {                               // zero keys add nothing to o or z
-                kreg[i] = f32x4{0, 0, 0, 0};
-                vreg[i] = f32x4{0, 0, 0, 0};
-            }
+            const int at = lane + i * 64;
+            const int r = at / (D / 4), c = at % (D / 4);
+            kreg[i] = f32x4{0, 0, 0, 0};           // zero keys add nothing to o or z
+            if (j0 + r < N) kreg[i] = *reinterpret_cast<const f32x4*>(Kh + (size_t)(j0 + r) * D + 4 * c);
+        }
+#pragma unroll
+        for (int i = 0; i < LDV; ++i) {
+            const int at = lane + i * 64;
+            const int r = at / (DV / 4), c = at % (DV / 4);
+            vreg[i] = f32x4{0, 0, 0, 0};
+            if (j0 + r < N) vreg[i] = *reinterpret_cast<const f32x4*>(Vh + (size_t)(j0 + r) * D + 4 * c);
         }
     };
     auto store_tile = [&]() {
 #pragma unroll
         for (int i = 0; i < LD; ++i) {
-            const int id = lane + i * 64;
-            const int r = id / (D / 4), c = id % (D / 4);
-            *reinterpret_cast<SPH_LDS f32x4*>(kb_ + r * ROWF + 4 * c) = kreg[i];
-            *reinterpret_cast<SPH_LDS f32x4*>(vb_ + r * ROWF + 4 * c) = vreg[i];
+            const int at = lane + i * 64;
+            *reinterpret_cast<SPH_LDS f32x4*>(kb_ + at / (D / 4) * ROWF + at % (D / 4) * 4) = kreg[i];
+        }
+#pragma unroll
+        for (int i = 0; i < LDV; ++i) {
+            const int at = lane + i * 64;
+            *reinterpret_cast<SPH_LDS f32x4*>(vb_ + at / (DV / 4) * VROWF + at % (DV / 4) * 4) = vreg[i];
         }
     };
 
@@ -520,7 +527,7 @@ void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
-                    oacc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb_[(16 * kb + 4 * g + t) * ROWF + db * 16 + n16], s[kb][t], oacc[db], 0, 0, 0);
+                    oacc[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vb_[(16 * kb + 4 * g + t) * VROWF + db * 16 + n16], s[kb][t], oacc[db], 0, 0, 0);
     }
 
     // ---- add the waves' partial (o, z): block db of wave w at part[w][db][lane], z at part[w][DB][lane]
@@ -541,14 +548,14 @@ void fwd_f32_small_kernel(const float* __restrict__ Q, const float* __restrict__
         const float inv = PARTIAL ? 1.f : zt > 0.f ? 1.0f / __builtin_sqrtf(zt) : 0.f;
         const int row = q0 + n16;
         // partial: the fp32 pair (o, z) of this key slice, slice-major
-        const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (n_qtiles * n_splits)) + bh) * Nq
+        const size_t rows0 = PARTIAL ? ((size_t)split * (n_wg / (CS * n_qtiles * n_splits)) + bh) * Nq
                                      : (size_t)bh * Nq;
-        if (wave == 0 && g == 0 && row < Nq && (PARTIAL || Zv != nullptr)) Zv[rows0 + row] = zt;
+        if (wave == 0 && g == 0 && cs == 0 && row < Nq && (PARTIAL || Zv != nullptr)) Zv[rows0 + row] = zt;
         for (int db = wave; db < DB; db += W) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < W; ++w) acc += *reinterpret_cast<const SPH_LDS f32x4*>(part + w * PART + db * 256 + lane * 4);
-            if (row < Nq) *reinterpret_cast<f32x4*>(O + (rows0 + row) * D + db * 16 + 4 * g) = acc * inv;
+            if (row < Nq) *reinterpret_cast<f32x4*>(O + (rows0 + row) * D + cs * DV + db * 16 + 4 * g) = acc * inv;
         }
     }
 }

@@ -22,6 +22,7 @@ extern "C" int form(long long slices, long long Nq, long long Nk, int d, int bf1
 extern "C" int form_in_one_order(int form, long long Nk) { return in_one_key_order((Form)form, (Nk + kChoiceTile - 1) / kChoiceTile, true); }
 extern "C" int f32_rows(long long heads, long long Nq, long long Nk, int d) { return choose_f32(heads, Nq, Nk, 1, d, %d).rows; }
 extern "C" int two_parts(long long Nk, int d) { return f32_two_parts(Nk, d); }
+extern "C" int f32_shares(long long slices, long long Nq) { return f32_small_column_shares(slices, Nq, %d); }
 extern "C" int halves(long long slices, long long Nq, long long Nk, int d, int bf16, int fp8, int counts)
 {
     const long long tiles = (Nk + kChoiceTile - 1) / kChoiceTile;
@@ -38,7 +39,7 @@ extern "C" int fp8_shape(long long heads, long long N, int d, int counts)
     const Fp8Shape s = choose_fp8(heads, N, d, counts != 0, %d);
     return s.nq * 16 + s.waves;
 }
-""" % ((CUS,) * 6)
+""" % ((CUS,) * 7)
 
 
 @functools.lru_cache(maxsize=None)
@@ -53,6 +54,7 @@ def _library():
     lib.form_in_one_order.argtypes = [ctypes.c_int, ctypes.c_longlong]
     lib.f32_rows.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     lib.two_parts.argtypes = [ctypes.c_longlong, ctypes.c_int]
+    lib.f32_shares.argtypes = [ctypes.c_longlong] * 2
     lib.halves.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.rows512.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.fp8_shape.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int] * 2
@@ -91,3 +93,8 @@ def rows512(H, H_kv, Nq, Nk, dtype, counts, whole=True):
 def half_columns(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
     """Whether a launch's workgroups have half of V's columns each."""
     return bool(_library().halves(H_kv, Nq * (H // H_kv), Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts))
+
+
+def f32_shares(H, Nq):
+    """Workgroups that share the columns of 16 rows of an fp32 launch."""
+    return _library().f32_shares(H, Nq)
