@@ -376,8 +376,12 @@ int launch_spherical(const Problem& p)
     const long long slices = (long long)p.B * p.H * p.n_splits, tiles = ((PARTIAL ? p.keys_per_split : p.Nk) + kBC - 1) / kBC, cus = cu_count();
     const Storage st{BF16 && !PARTIAL, FP8, MULT};
     const FormChoice choice = p.tile_rows != 0 ? FormChoice{p.tile_rows == 128 ? kRows128 : kRows256, 0.0} : choose_form(slices, p.Nq, tiles, D, st, cus);
-    if constexpr (!FP8)
-        if (!p.one_key_order && half_columns(choice, slices, p.Nq, tiles, D, st, cus)) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 4, 2>(p);
+    if constexpr (!FP8) {
+        const int shares = p.one_key_order ? 1 : column_shares(choice, slices, p.Nq, tiles, D, st, cus);
+        if constexpr (D == 128)
+            if (shares == 4) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 4, 4>(p);
+        if (shares == 2) return launch_keysplit<D, 2, QKT, MULT, PARTIAL, 2, 4, 2>(p);
+    }
     Form form = choice.form;
     if (p.one_key_order) form = in_one_key_order(form, tiles, BF16 && !MULT && !PARTIAL);
     if constexpr (BF16 && !MULT && !PARTIAL)
@@ -719,7 +723,7 @@ int choose_splits(long long heads, long long Nq, long long Nk, int d, int dtype)
 // The library's choice of slices for a rectangular problem, in the launch's terms (packed_group).
 // A launch is cut only while all its slices still run at once as workgroups of 128 rows or fewer, one
 // per CU (1 x 8192 x 64 in 4 slices, 256 workgroups, 23.8 us; 6: 26.6; 12: 34.8).  Either side is priced as the launch it would be
-// (choose_form, choose_f32; halves of the columns, which both sides may be launched in, change no more than the two's difference on short
+// (choose_form, choose_f32; shares of the columns, which both sides may be launched in, change no more than the two's difference on short
 // axes: priced, 1 x 2048 x 128 13.9 -> 12.5 us, with counts 14.2 -> 14.4, 1 x 4000 x 64 12.2 -> 14.0), as without counts, which the plan does not know and which raise both, and without Narrow, which parts have not
 // and with which no plan over 2535 shapes differs; the second launch costs 4 us, and each part is written and read at 6 TB/s together.
 // Measured with the slices this picks against one: 1 x 8192 x 128 38 against 44 us, 1 x 8192 x 64 24 against 27.5; not cut:

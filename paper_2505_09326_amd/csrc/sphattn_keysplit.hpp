@@ -15,8 +15,8 @@
 //   2  2  4   64 rows, two waves per SIMD: 0.28 (0.16).  At d = 128 a tile is 64 KB and the copies (64 bytes per cycle and CU at
 //             most) and the fragment reads, both of the LDS, take 0.64 us of the 0.55 to 0.65 of 128 keys.
 //             1 x 12000 x 64 55.8 -> 41.1, 4 x 1999 x 128 17.0 -> 15.6 us.
-//   2  2  4   with CS = 2, half of the columns of V and O per workgroup, where that leaves no more than one on a CU: 0.255 (0.141), the copies
-//             48 KB of a tile's 64 (half_columns in sphattn_choice.hpp).  4 x 1999 x 128 15.6 -> 14.3, 8 x 1000 x 128 10.8 -> 9.5 us.
+//   2  2  4   with CS = 2 or 4, that part of the columns of V and O per workgroup, where it leaves no more than one on a CU: 0.255 (0.141) with two, the
+//             copies 48 KB of a tile's 64, 40 with four (column_shares in sphattn_choice.hpp).  4 x 1999 x 128 15.6 -> 14.3, 8 x 1000 x 128 10.8 -> 9.5 us.
 //   4  1  4   64 rows, d = 128: every wave holds all rows, so each byte of K and V is read from LDS once and
 //             by the wave that copied it; no barrier in the loop.  0.28, less where many CUs stream (1 x 8192 x 128 53.5 -> 44.4) and
 //             with counts (61 -> 54); and the 64-row form of fp8 Q/K, whose score instruction wants four query blocks
@@ -77,8 +77,8 @@ constexpr int keysplit_lds_bytes()
 }
 
 // One work item; arguments as fwd_pipelined_item, and: query tiles are tile_rows apart (the workgroup's rows, or
-// twice as many when the item is one half, starting at row_off, of a wider tile).  CS = 2: an item is half of V's and O's columns
-// (items alternate between the halves).
+// twice as many when the item is one half, starting at row_off, of a wider tile).  CS > 1: an item is a share of V's and O's columns
+// (items go through the shares).
 template <int D, int NQ, QKType QKT, bool MULT, bool PARTIAL, int CS, int RG, int KG>
 __device__ __forceinline__
 void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
@@ -108,9 +108,9 @@ void fwd_keysplit_item(const void* __restrict__ Qv, const void* __restrict__ Kv,
     constexpr int VSTEP = SLOTS / DB;              // slots per V^T fragment
     constexpr int QKM = FP8 ? 2 * NQ / SLOTS : NQ; // score matrix instructions per slot
     constexpr int PAIRS = 4 * NQ / SLOTS;          // score register pairs of stage B per slot
-    constexpr int VALU_PER_MFMA = (MULT || D == 64 || CS == 2) ? 2 : 1;
+    constexpr int VALU_PER_MFMA = (MULT || D == 64 || CS > 1) ? 2 : 1;
     static_assert(NQ == 4 || NQ == 2, "64 or 32 query rows per wave");
-    static_assert(CS == 1 || (CS == 2 && !FP8 && RG == 2 && KG == 4 && NQ == 2), "halves of the columns: the form that has them");
+    static_assert(CS == 1 || ((CS == 2 || (CS == 4 && D == 128)) && !FP8 && RG == 2 && KG == 4 && NQ == 2), "shares of the columns: the form that has them");
     static_assert(KG == 2 || KG == 4, "two or four key groups");
     constexpr int KSHARES = BC / 16 * KBLK / LDK;  // (fewer than waves: the same blocks twice)
     static_assert(KSHARES * LDK * 16 == BC * KBLK && WAVES % KSHARES == 0 && LDV * WAVES * 16 == BC * VBLK && (LDK % KBLK == 0 || KBLK % LDK == 0) && (LDV % VBLK == 0 || VBLK % LDV == 0),

@@ -23,12 +23,12 @@ extern "C" int form_in_one_order(int form, long long Nk) { return in_one_key_ord
 extern "C" int f32_rows(long long heads, long long Nq, long long Nk, int d) { return choose_f32(heads, Nq, Nk, 1, d, %d).rows; }
 extern "C" int two_parts(long long Nk, int d) { return f32_two_parts(Nk, d); }
 extern "C" int f32_shares(long long slices, long long Nq) { return f32_small_column_shares(slices, Nq, %d); }
-extern "C" int halves(long long slices, long long Nq, long long Nk, int d, int bf16, int fp8, int counts)
+extern "C" int column_share(long long slices, long long Nq, long long Nk, int d, int bf16, int fp8, int counts)
 {
     const long long tiles = (Nk + kChoiceTile - 1) / kChoiceTile;
     const Storage st{bf16 != 0, fp8 != 0, counts != 0};
     FormChoice c = choose_form(slices, Nq, tiles, d, st, %d);
-    return half_columns(c, slices, Nq, tiles, d, st, %d);
+    return column_shares(c, slices, Nq, tiles, d, st, %d);
 }
 extern "C" int rows512(long long slices, long long Nq, long long Nk, int bf16, int fp8, int counts, int whole)
 {
@@ -55,7 +55,7 @@ def _library():
     lib.f32_rows.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int]
     lib.two_parts.argtypes = [ctypes.c_longlong, ctypes.c_int]
     lib.f32_shares.argtypes = [ctypes.c_longlong] * 2
-    lib.halves.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
+    lib.column_share.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.rows512.argtypes = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 4
     lib.fp8_shape.argtypes = [ctypes.c_longlong] * 2 + [ctypes.c_int] * 2
     return lib
@@ -90,9 +90,9 @@ def rows512(H, H_kv, Nq, Nk, dtype, counts, whole=True):
     return bool(_library().rows512(H_kv, Nq * (H // H_kv), Nk, dtype == "bf16", dtype == "fp8qk_bf16v", counts, whole))
 
 
-def half_columns(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
-    """Whether a launch's workgroups have half of V's columns each."""
-    return bool(_library().halves(H_kv, Nq * (H // H_kv), Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts))
+def column_shares(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
+    """Workgroups that share the columns of V of a launch's row tile."""
+    return _library().column_share(H_kv, Nq * (H // H_kv), Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts)
 
 
 def f32_shares(H, Nq):

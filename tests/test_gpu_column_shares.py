@@ -1,4 +1,4 @@
-"""Launches whose workgroups have 64 rows and half of the columns of V and O each (half_columns in sphattn_choice.hpp): ragged rows and
+"""Launches whose workgroups have 64 rows and a half or a quarter of the columns of V and O each (column_shares in sphattn_choice.hpp): ragged rows and
 keys, odd numbers of tiles, shared K/V heads, as many workgroups as CUs, whole results and partial accumulators, cut key axes.
 Compared with 64 bits within what the storage type allows, as in test_gpu_forward_forms.py."""
 import pytest
@@ -12,8 +12,10 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 U = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}
 
-# H, H_kv, N_q, N_k, d
-SHAPES = [(1, 1, 1, 1100, 128), (2, 2, 64, 129, 128), (5, 5, 300, 300, 128), (2, 2, 100, 385, 64), (4, 2, 63, 1025, 128), (4, 4, 1999, 1999, 128), (2, 1, 65, 1281, 64), (128, 128, 64, 1400, 64), (3, 3, 700, 2049, 64), (128, 128, 33, 1088, 128)]
+# H, H_kv, N_q, N_k, d, shares
+SHAPES = [(1, 1, 1, 1100, 128, 4), (2, 2, 64, 129, 128, 4), (5, 5, 300, 300, 128, 4), (4, 2, 63, 1025, 128, 4), (64, 64, 64, 1281, 128, 4),
+          (4, 4, 1999, 1999, 128, 2), (128, 128, 33, 1088, 128, 2), (1, 1, 70, 4161, 128, 2),
+          (2, 2, 100, 385, 64, 2), (2, 1, 65, 1281, 64, 2), (128, 128, 64, 1400, 64, 2), (3, 3, 700, 2049, 64, 2)]
 
 
 @pytest.fixture(scope="module")
@@ -25,10 +27,10 @@ def pkg():
 
 @pytest.mark.parametrize("counts", [False, True])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("H,H_kv,Nq,Nk,d", SHAPES)
-def test_against_64_bits(pkg, H, H_kv, Nq, Nk, d, dtype, counts):
-    print(f"case half columns {H} on {H_kv}, {Nq} of {Nk} x {d} {dtype} counts={counts}", flush=True)
-    assert all(launch_choice.half_columns(H, H_kv, Nq, Nk, d, dtype, counts, partial) for partial in (False, True))
+@pytest.mark.parametrize("H,H_kv,Nq,Nk,d,shares", SHAPES)
+def test_against_64_bits(pkg, H, H_kv, Nq, Nk, d, shares, dtype, counts):
+    print(f"case column shares {H} on {H_kv}, {Nq} of {Nk} x {d} {dtype} counts={counts}", flush=True)
+    assert {launch_choice.column_shares(H, H_kv, Nq, Nk, d, dtype, counts, partial) for partial in (False, True)} == {shares}
     q, _, _ = si.make_qkv(1, H, Nq, d, dtype, seed=8100 + Nq)
     _, k, v = si.make_qkv(1, H_kv, Nk, d, dtype, seed=8200 + Nk)
     m = torch.poisson(torch.full((1, Nk), 1.5), generator=torch.Generator(device="cpu").manual_seed(8300 + Nk)) if counts else None
