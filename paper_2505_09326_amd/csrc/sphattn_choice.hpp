@@ -61,8 +61,9 @@ inline FormChoice choose_form(long long slices, long long Nq, long long tiles, i
 // 4 x 1999 x 128 15.6 -> 14.3 us, 8 x 1000 x 128 10.8 -> 9.4, with counts 2 x 3000 22.9 -> 20.5, 4 x 1999 x 64 9.9 -> 9.5.  On long key axes with most
 // CUs busy K, then read twice, costs more than it gives (1 x 8000 x 128 43.8 us, 47.8 with halves; d = 64, 4 x 1999 of 4000, with counts 19.0 and 19.3).
 // In place of Rows64 with two key groups from 3 tiles (d = 64: 7) on, 0.85 to 0.99 of the time there; below, halves take up to 8 % longer.
-// At d = 128 four have quarters while that leaves no more than one workgroup on a CU and the key axis is no longer than 64 tiles: 0.92 to 0.97 of the
-// halves' time over 90 launches (64 x 1000 8.8 -> 8.0 us, 2 x 500 7.2 -> 6.7, 2 x 2048 15.0 -> 14.3); on longer axes 0.91 to 1.27, K's copies again.
+// At d = 128 four have quarters on axes of up to 64 tiles (on longer ones 0.91 to 1.27 of the halves' time): 64 x 1000 8.45 -> 7.93 us, 2 x 500
+// 6.92 -> 6.60, with counts 9.43 -> 8.63 and 7.45 -> 7.00.  With nearly every CU busy K's copies, four times over, cost it again from 13 tiles on: 52 row
+// tiles x 3000 16.7 -> 16.6 us, 60 17.3 -> 17.7, 64 17.8 -> 18.4; with counts, more work to hide them, 19.1 -> 18.0, 19.8 -> 19.2, 19.6 -> 19.6.
 constexpr FormCost kHalfColumnsCost[2][2] = {{{4.28f, .141f, .045f}, {4.27f, .209f, .035f}}, {{4.32f, .255f, .115f}, {4.68f, .296f, .115f}}};
 inline int column_shares(FormChoice c, long long slices, long long Nq, long long tiles, int d, Storage st, long long cus)
 {
@@ -71,7 +72,8 @@ inline int column_shares(FormChoice c, long long slices, long long Nq, long long
     const FormCost h = kHalfColumnsCost[d == 128][st.counts];
     const double us = h.start + (double)((tiles + 3) & -4) * (h.tile + h.share * (double)items / (double)cus);
     if (items > cus || (d == 64 && tiles > 48) || (c.form == kRows64 ? tiles < (d == 128 ? 3 : 7) : us >= c.us)) return 1;
-    return d == 128 && 2 * items <= cus && tiles <= 64 ? 4 : 2;
+    const long long sixteenths = tiles <= 12 ? 16 : st.counts ? 15 : 13;
+    return d == 128 && 32 * items <= sixteenths * cus && tiles <= 64 ? 4 : 2;
 }
 
 // d = 64, launches of more 256-row workgroups than CUs: 512 rows in eight waves, one workgroup per CU, in place of two of 256 rows in four

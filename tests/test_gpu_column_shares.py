@@ -13,8 +13,8 @@ DEV = "cuda:0"
 U = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11}
 
 # H, H_kv, N_q, N_k, d, shares
-SHAPES = [(1, 1, 1, 1100, 128, 4), (2, 2, 64, 129, 128, 4), (5, 5, 300, 300, 128, 4), (4, 2, 63, 1025, 128, 4), (64, 64, 64, 1281, 128, 4),
-          (4, 4, 1999, 1999, 128, 2), (128, 128, 33, 1088, 128, 2), (1, 1, 70, 4161, 128, 2),
+SHAPES = [(1, 1, 1, 1100, 128, 4), (2, 2, 64, 129, 128, 4), (5, 5, 300, 300, 128, 4), (4, 2, 63, 1025, 128, 4), (52, 52, 64, 1281, 128, 4),
+          (4, 4, 1999, 1999, 128, 2), (64, 64, 64, 1281, 128, 2), (64, 64, 64, 700, 128, 4), (128, 128, 33, 1088, 128, 2), (1, 1, 70, 4161, 128, 2),
           (2, 2, 100, 385, 64, 2), (2, 1, 65, 1281, 64, 2), (128, 128, 64, 1400, 64, 2), (3, 3, 700, 2049, 64, 2)]
 
 
