@@ -79,14 +79,15 @@ inline int column_shares(FormChoice c, long long slices, long long Nq, long long
 // d = 64, launches of more 256-row workgroups than CUs: 512 rows in eight waves, one workgroup per CU, in place of two of 256 rows in four
 // waves, which share nothing: each byte of K and V is copied to LDS once per CU and not twice, and the waves of a SIMD stay at one tile by themselves.  8 x
 // 32768 1354.5 -> 1326.7 us, 32 x 8192 370 -> 350, 9 x 8192 (one round, half filled) 152 -> 135, with counts 20 x 8192 358 -> 332, fp8 Q/K 289 -> 266;
-// fp8 Q/K with counts, which spills, 2 to 5 % slower.  Above one round it is the thinner last round that decides (a round filled to f
+// fp8 Q/K with counts, which spills, 2 to 5 % slower.  With counts or fp8 Q/K not above 192 key tiles (3 MB of K and V per head): there it gains 0 to 1 % where
+// clocks hold (8 x 32768 with counts 1645 -> 1639 us, fp8 Q/K 1300 -> 1291), and loses 1 to 4 on cards that step them down (1562 -> 1604, 1230 -> 1249).  Above one round it is the thinner last round that decides (a round filled to f
 // costs 0.5 + 0.5 f; 256-row launches of 16-bit storage without counts may run theirs as halves, launch_pipelined): 8 x 17000 481 us, 547 with this,
 // 8 x 24576 856 and 879.  Not on short key axes there (260 x 512 with counts 26.2, 33.8; 200 x 700 41.4, 40.3).  Rows are added up in the
 // same order either way.
 inline bool rows512_pay(long long slices, long long Nq, long long tiles, Storage st, bool whole, long long cus)
 {
     const long long n256 = slices * ((Nq + 255) / 256), n512 = slices * ((Nq + 511) / 512);
-    if (n256 <= cus || (st.fp8 && st.counts)) return false;
+    if (n256 <= cus || (st.fp8 && st.counts) || ((st.fp8 || st.counts) && tiles > 192)) return false;
     if (n512 <= cus) return true;
     const long long full = n256 / (2 * cus), rest = n256 % (2 * cus);
     double cost256 = 0.5 * (double)(full + (rest != 0)) + 0.25 * (double)n256 / (double)cus;
