@@ -14,7 +14,7 @@ DEV = "cuda:0"
 U = {"bf16": 2.0 ** -8, "f16": 2.0 ** -11, "fp8qk_bf16v": 2.0 ** -8}
 
 # H, H_kv, N_q, N_k
-SHAPES = [(100, 100, 700, 700), (120, 120, 513, 60), (70, 35, 1537, 641), (250, 250, 300, 129), (60, 60, 1500, 65), (256, 256, 1000, 705), (64, 32, 4000, 1281)]
+SHAPES = [(100, 100, 700, 700), (120, 120, 513, 60), (70, 35, 1537, 641), (250, 250, 300, 129), (60, 60, 1500, 65), (256, 256, 1000, 705), (64, 32, 4000, 1281), (100, 20, 700, 8257)]
 
 
 @pytest.fixture(scope="module")
