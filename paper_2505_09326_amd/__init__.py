@@ -16,7 +16,8 @@ differ from sphattn_fwd in the last place.
 
 Calls that allocate their outputs and give no stream go through _marshal (csrc/marshal.cpp), which does in C++ what the
 functions here do in Python and does nothing where anything about a call is not as it has to be; the Python below it then
-finds out what, and takes the calls that bring an output or a stream.
+finds out what, and takes the calls that bring an output or a stream.  It takes all calls, at more host time each, where
+_marshal is not built or was built for another torch.
 
 The C ABI cannot see how large a buffer behind a pointer is, so the binding checks what it
 can see before any launch: every tensor's shape against the shapes the entry point's header
@@ -51,7 +52,15 @@ EXPORTED_SYMBOLS = ("sphattn_fwd", "sphattn_fwd_z", "sphattn_fwd_tile_rows", "sp
 NORMALIZERS = {"l2": 0, "softmax": 1, "l1": 2, "sqrelu": 3}
 
 _lib = None
-_fast = None                                       # _marshal, bound to _lib's entry points
+_fast = None                                       # _marshal, bound to _lib's entry points, or _PythonOnly
+
+
+class _PythonOnly:
+    """In _marshal's place: every call takes the Python path."""
+    @staticmethod
+    def forward(*args):
+        return None
+    backward = fp8_forward = forward
 
 
 class SphattnError(RuntimeError):
@@ -120,16 +129,26 @@ def load_library() -> ctypes.CDLL:
         lib.sphattn_strerror.argtypes = [ip]
         lib.sphattn_version.restype = ip
         lib.sphattn_version.argtypes = []
-        if not os.path.exists(MARSHAL_PATH):
-            raise ImportError(
-                f"{MARSHAL_PATH} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
-        import torch  # noqa: F401  (whose libraries _marshal links against)
-        from . import _marshal
-        names = ("sphattn_cross_fwd", "sphattn_cross_splitkv_fwd", "sphattn_cross_splitkv_workspace_bytes", "sphattn_grn_bwd",
-                 "sphattn_grn_bwd_split", "sphattn_bwd_workspace_bytes", "sphattn_fp8_grn_fwd")
-        _marshal.bind(_raise_on, *(ctypes.cast(getattr(lib, name), vp).value for name in names))
-        _lib, _fast = lib, _marshal
+        _fast = _bound_marshal(lib)                # (first: whoever sees _lib uses _fast)
+        _lib = lib
     return _lib
+
+
+def _bound_marshal(lib):
+    """_marshal on the library's entry points, or _PythonOnly where it is not there for this torch."""
+    if not os.path.exists(MARSHAL_PATH):
+        return _PythonOnly
+    try:
+        import torch                               # (whose libraries it links against)
+        from . import _marshal
+    except ImportError:                            # no torch, or one with other symbols
+        return _PythonOnly
+    if _marshal.built_for != torch.__version__:
+        return _PythonOnly
+    names = ("sphattn_cross_fwd", "sphattn_cross_splitkv_fwd", "sphattn_cross_splitkv_workspace_bytes", "sphattn_grn_bwd",
+             "sphattn_grn_bwd_split", "sphattn_bwd_workspace_bytes", "sphattn_fp8_grn_fwd")
+    _marshal.bind(_raise_on, *(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in names))
+    return _marshal
 
 
 def sphattn_strerror(code: int) -> str:

@@ -47,7 +47,7 @@ def build_marshal(verbose: bool = False) -> str:
     import torch
     base = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DMARSHAL_TORCH="{torch.__version__}"',
            f"-I{base}/include", f"-I{base}/include/torch/csrc/api/include", "-I/opt/rocm/include", f"-I{sysconfig.get_paths()['include']}",
            "-o", MARSHAL_PATH, os.path.join(CSRC, "marshal.cpp"), f"-L{base}/lib", "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -296,4 +296,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", "Checks, outputs, works
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject* m = PyModule_Create(&module);
+    // the torch whose headers this was compiled with (its tensors' layout), for the binding to compare
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", MARSHAL_TORCH) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -1,9 +1,14 @@
 """_marshal, the binding's fast way into the library: it does exactly the calls that the Python path accepts, with the same results, and
 leaves everything else to it."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 import paper_2505_09326_amd as pkg
+from paper_2505_09326_amd._build import MARSHAL_PATH, build_marshal
 from paper_2505_09326_amd.autograd import spherical_attention
 
 DEV = "cuda:0"
@@ -21,18 +26,57 @@ class Subclass(torch.Tensor):
     pass
 
 
+@pytest.mark.parametrize("marshal", ["missing", "another torch's", "for another torch"])
+def test_the_package_works_without_it(tmp_path, marshal):
+    """build_library() is all that the binding needs: without _marshal, or with one that cannot be used, every call takes the Python path."""
+    if not os.path.exists(pkg.LIB_PATH):
+        pkg.build_library()
+    copy, here = tmp_path / "paper_2505_09326_amd", os.path.dirname(pkg.__file__)
+    copy.mkdir()
+    for name in ("__init__.py", "_build.py", "autograd.py", "libsphattn.so"):
+        os.symlink(os.path.join(here, name), copy / name)
+    if marshal == "another torch's":               # (which the loader refuses)
+        (copy / "_marshal.so").write_bytes(b"")
+    if marshal == "for another torch":
+        (copy / "_marshal.so").write_bytes(open(_built_marshal(), "rb").read())
+    code = f"""
+import torch
+if {marshal == "for another torch"}:
+    torch.__version__ = "0.0"
+import paper_2505_09326_amd as pkg
+assert pkg.__file__.startswith({str(tmp_path)!r}) and pkg.sphattn_version() > 0 and pkg._fast is pkg._PythonOnly
+t = torch.zeros((1, 1, 8, 64), dtype=torch.bfloat16)
+for call in (lambda: pkg.sphattn_fwd(t, t, t), lambda: pkg.sphattn_bwd(t, t, t, t, t, torch.zeros((1, 1, 8)))):
+    try:
+        call()
+    except ValueError as e:
+        assert "device tensor" in str(e), e
+    else:
+        raise AssertionError("accepted tensors of the CPU")
+"""
+    run = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, env={**os.environ, "PYTHONPATH": str(tmp_path)})
+    assert run.returncode == 0, run.stderr[-2000:]
+
+
+def _built_marshal():
+    if not os.path.exists(MARSHAL_PATH):
+        build_marshal()
+    return MARSHAL_PATH
+
+
 def test_what_is_not_right_is_left_to_python():
-    pkg.load_library()
+    _built_marshal()
+    fast = pkg._bound_marshal(pkg.load_library())
     t = torch.zeros((1, 1, 8, 64), dtype=torch.bfloat16)
-    fwd = lambda q, k, v, m=None, z=None, code=1: pkg._fast.forward(q, k, v, m, z, code, True, True, False)
+    fwd = lambda q, k, v, m=None, z=None, code=1: fast.forward(q, k, v, m, z, code, True, True, False)
     assert fwd(t, t, t) is None                    # not on a device
     assert fwd(t, t, None) is None and fwd(t.numpy, t, t) is None and fwd(t, t, t, 3) is None and fwd(t, t, t, code=9) is None
     assert fwd(t.as_subclass(Subclass), t, t) is None
-    assert pkg._fast.backward(t, t, t, None, t, t, t, 1, True) is None and pkg._fast.fp8_forward(t, t, t, None, t) is None
+    assert fast.backward(t, t, t, None, t, t, t, 1, True) is None and fast.fp8_forward(t, t, t, None, t) is None
     with pytest.raises(TypeError):
-        pkg._fast.forward(t)
+        fast.forward(t)
     with pytest.raises(TypeError):
-        pkg._fast.forward(t, t, t, None, None, "bf16", True, True, False)
+        fast.forward(t, t, t, None, None, "bf16", True, True, False)
 
 
 def _qkv(dtype, H, H_kv, Nq, Nk, d, seed):
