@@ -189,6 +189,19 @@ def test_forward_tile_loops_do_not_drain_their_reads(compiled):
             assert wait and int(wait.group(1)) >= 4, (name, wait and wait.group(0))
 
 
+def test_small_fp32_kernel_checks_a_key_once(compiled):
+    """Undivided rows of K and V are loaded under one check of the key (with one each the loads came in two chains of branches:
+    12 x 204 x 128 11.19 us for 10.67)."""
+    text = compiled[1]
+    for d in (64, 128):
+        for counts in (0, 1):
+            for partial in (0, 1):
+                start = text.index(f"\n_ZN7sphattn20fwd_f32_small_kernelILi{d}ELb{counts}ELb{partial}ELi1E") + 1
+                body = text[start:text.index(".end_amdhsa_kernel", start)]
+                loads, checks = body.count("global_load"), body.count("s_and_saveexec")
+                assert loads >= 2 * d // 4 and checks <= 0.75 * loads, (d, counts, partial, loads, checks)
+
+
 def test_fp8_preparation_takes_a_keys_loads_together(compiled):
     """All of a key's loads for its norm stand in one block, without a wait between them (a branch each made two trips)."""
     text = compiled[1]
