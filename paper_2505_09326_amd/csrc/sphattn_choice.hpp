@@ -77,25 +77,37 @@ inline int column_shares(FormChoice c, long long slices, long long Nq, long long
 }
 
 // d = 64, launches of more 256-row workgroups than CUs: 512 rows in eight waves, one workgroup per CU, in place of two of 256 rows in four
-// waves, which share nothing: each byte of K and V is copied to LDS once per CU and not twice, and the waves of a SIMD stay at one tile by themselves.  8 x
-// 32768 1354.5 -> 1326.7 us, 32 x 8192 370 -> 350, 9 x 8192 (one round, half filled) 152 -> 135, with counts 20 x 8192 358 -> 332, fp8 Q/K 289 -> 266;
-// fp8 Q/K with counts, which spills, 2 to 5 % slower.  With counts or fp8 Q/K not above 192 key tiles (3 MB of K and V per head): there it gains 0 to 1 % where
-// clocks hold (8 x 32768 with counts 1645 -> 1639 us, fp8 Q/K 1300 -> 1291), and loses 1 to 4 on cards that step them down (1562 -> 1604, 1230 -> 1249).  Above one round it is the thinner last round that decides (a round filled to f
-// costs 0.5 + 0.5 f; 256-row launches of 16-bit storage without counts may run theirs as halves, launch_pipelined): 8 x 17000 481 us, 547 with this,
-// 8 x 24576 856 and 879.  Not on short key axes there (260 x 512 with counts 26.2, 33.8; 200 x 700 41.4, 40.3).  Rows are added up in the
-// same order either way.
+// waves, which share nothing: each byte of K and V is copied to LDS once per CU and not twice, and the waves of a SIMD stay at one tile by
+// themselves.  8 x 32768 1415 -> 1384 us, 32 x 8192 370 -> 350, 9 x 8192 (one round, half filled) 152 -> 135, with counts 20 x 8192 358 -> 332,
+// fp8 Q/K 289 -> 266.  Lines from 2200 launches of 257 to 5000 workgroups of 256 rows and 20 to 33000 keys, both forms timed on each (512 over
+// 256 rows; taken: 0.96 in one round, 0.97 in several, 1.015 at most):
+//   fp8 Q/K with counts    spills, 1.02 to 1.05
+//   K and V past 256 MB    the last-level cache; eight waves wait for HBM together: 48 x 1333 of 29898 1.07, fp8 Q/K 286 x 420 of 7777 1.03
+//   from 129 key tiles on  256 rows have wave priorities by tile there.  In one round 0.97 to 1.05, counts and fp8 Q/K 1.00 to 1.10 in any (fp8 Q/K
+//                          16 x 11180 374 and 394 us, with counts 20 x 10795 481 and 492); 16-bit storage in full rounds 0.98 to 1.01
+//   short key axes         one round: 1 and 2 tiles 0.95 to 1.04, with counts up to 9 tiles 1.03; several: up to 16 tiles 0.93 to 1.05
+//                          (216 x 3519 of 581 124 and 127), with counts 1.04
+// Several rounds otherwise as they are filled: a round filled to f costs 0.5 + 0.5 f, and 256-row launches of 16-bit storage without counts may run
+// their last one as halves (launch_pipelined): 8 x 17000 481 us, 547 with this, 8 x 24576 856 and 879.  Up to eight workgroups behind one round of
+// 256 rows take one more item each on eight CUs, not a round (14 x 9470 with counts 327 and 366, 260 x 341 of 3124 99 and 129).
+// In a launch of one round rows are added up in the same order either way; in several, every other one of which streams the keys
+// backwards, a row may be in another kind of round.
 inline bool rows512_pay(long long slices, long long Nq, long long tiles, Storage st, bool whole, long long cus)
 {
     const long long n256 = slices * ((Nq + 255) / 256), n512 = slices * ((Nq + 511) / 512);
-    if (n256 <= cus || (st.fp8 && st.counts) || ((st.fp8 || st.counts) && tiles > 192)) return false;
-    if (n512 <= cus) return true;
+    const bool one_round = n512 <= cus;
+    if (n256 <= cus || (st.fp8 && st.counts) || slices * tiles * (kChoiceTile * 64 * (st.fp8 ? 3 : 4)) > (256ll << 20)) return false;
+    if (tiles > 128 && (one_round || st.fp8 || st.counts)) return false;
+    if (one_round) return tiles >= (st.counts ? 10 : 3);
     const long long full = n256 / (2 * cus), rest = n256 % (2 * cus);
+    if (tiles < 17 || (full == 1 && rest > 0 && rest <= 8)) return false;
     double cost256 = 0.5 * (double)(full + (rest != 0)) + 0.25 * (double)n256 / (double)cus;
     if (whole && !st.fp8 && !st.counts && full >= 1 && rest > 0 && rest <= cus) {
         const double halves = (double)full + 0.3 + 0.3 * (double)rest / (double)cus;
         cost256 = halves < cost256 ? halves : cost256;
     }
-    return tiles >= 10 && 0.5 * (double)((n512 + cus - 1) / cus) + 0.5 * (double)n512 / (double)cus <= 1.02 * cost256;
+    const double cost512 = 0.5 * (double)((n512 + cus - 1) / cus) + 0.5 * (double)n512 / (double)cus;
+    return cost512 <= (tiles > 128 ? 1.0 : 1.02) * cost256;
 }
 
 // The same for a launch that has to add a row's terms in the order of kRows256, as Narrow does too (where the launch has it).  Narrow where it is one

@@ -623,8 +623,8 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
         // (priority_by_tile) outside the loop over tiles, which stays free of branches.  Up to
         // 128 tiles a head's K and V (2 MB) stay in the 4 MB L2 however far the workgroups
         // drift apart, and the tiles run as one group (a group boundary costs about 40 ns).  So do those of eight waves, which
-        // the barriers keep at one tile: 8 x 32768 1426 -> 1420 us, 16 x 16384 730 -> 726 (fp8 Q/K 1255 -> 1272: as it was).
-        const int group = n_tiles > 128 && (WAVES == 4 || FP8) ? 8 : n_tiles;
+        // the barriers keep at one tile: 8 x 32768 1426 -> 1420 us, 16 x 16384 730 -> 726.
+        const int group = n_tiles > 128 && WAVES == 4 ? 8 : n_tiles;
         for (int j0 = 0; j0 < n_tiles; j0 += group) {
             priority_by_tile(j0);
             run_tiles(j0, j0 + group < n_tiles ? j0 + group : n_tiles);
