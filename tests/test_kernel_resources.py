@@ -189,6 +189,21 @@ def test_forward_tile_loops_do_not_drain_their_reads(compiled):
             assert wait and int(wait.group(1)) >= 4, (name, wait and wait.group(0))
 
 
+def test_four_waves_take_no_remainder_of_the_wave(compiled):
+    """Which blocks of a K tile a wave copies: in four waves of 16-bit storage its number says it, and the copies' addresses are folded (a
+    remainder that is the number itself cost an addition per copy, 3 to 4 % on one or two key tiles with counts)."""
+    text = compiled[1]
+    for d in (64, 128):
+        for qk in (0, 2):
+            for counts in (0, 1):
+                start = text.index(f"\n_ZN7sphattn20fwd_pipelined_kernelILi{d}ELi4ELNS_6QKTypeE{qk}ELNS_4NormE0ELb{counts}ELb0ELi4E") + 1
+                body = text[start:text.index(".end_amdhsa_kernel", start)]
+                wave = set(re.findall(r"v_readfirstlane_b32 (s\d+), v\d+", body))
+                shifted = set(re.findall(r"s_lshl_b32 (s\d+), s\d+, 1[012]\b", body)) | wave
+                masked = [x for x in re.findall(r"s_and_b32 (s\d+), (s\d+), (0x\w+|3)\b", body) if x[1] in shifted and x[2] in ("3", "0xc00", "0x1800", "0x3000")]
+                assert not masked, (d, qk, counts, masked)
+
+
 def test_small_fp32_kernel_checks_a_key_once(compiled):
     """Undivided rows of K and V are loaded under one check of the key (with one each the loads came in two chains of branches:
     12 x 204 x 128 11.19 us for 10.67)."""
