@@ -7,14 +7,15 @@
 // heads on 2 of 1500 x 64 with counts 137 -> 89).
 //
 // A function here does a call only if everything about it is as it has to be: exactly torch's tensor type, with storage, the
-// shapes, element types and device that the entry point's header states, contiguous.  For anything else, and for whatever throws on
-// the way (no memory for an output), it returns None, having launched nothing, and the binding's Python does the call and finds out what is wrong.
+// shapes, element types and device that the entry point's header states, contiguous, no function or dispatch mode in force.  For anything
+// else, and for whatever throws on the way (no memory for an output), it returns None, having launched nothing, and the binding's Python does the call and finds out what is wrong.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -138,7 +139,8 @@ bool arguments(Py_ssize_t n, Py_ssize_t want)
     return false;
 }
 
-bool ready() { return entry.cross != nullptr && !at::impl::torch_function_mode_enabled(); }
+// (A dispatch mode makes its own tensors for what is allocated here: Python checks those as it does a caller's.)
+bool ready() { return entry.cross != nullptr && !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
 // forward(Q, K, V, mult, Z, code, same_n, same_h, want_z) -> O, with want_z (O, Z)
 PyObject* forward(PyObject*, PyObject* const* args, Py_ssize_t n)

@@ -176,3 +176,29 @@ def test_the_current_stream_is_used():
         got = pkg.sphattn_fwd(*copies)
     side.synchronize()
     assert torch.equal(got, want)
+
+
+@pytest.mark.gpu
+def test_modes_are_left_to_python():
+    """Under a dispatch or a function mode nothing is allocated or launched in C++: the mode's own tensors go through Python's checks."""
+    from torch.overrides import TorchFunctionMode
+    from torch.utils._python_dispatch import TorchDispatchMode
+    q, k, v = _qkv("bf16", 2, 2, 64, 64, 64, 37)
+    e4m3 = _qkv("e4m3", 2, 2, 64, 64, 64, 38)
+    ws = torch.empty(pkg.sphattn_fp8_workspace_bytes(2, 2, 64, 64), dtype=torch.uint8, device=DEV)
+    o, z = pkg.sphattn_fwd_z(q, k, v)
+
+    class Dispatch(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    class Function(TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+    calls = [lambda: pkg._fast.forward(q, k, v, None, None, 1, True, True, False), lambda: pkg._fast.backward(q, k, v, None, o, q, z, 1, True),
+             lambda: pkg._fast.fp8_forward(*e4m3, None, ws)]
+    for mode in (Dispatch, Function):
+        with mode():
+            assert [c() for c in calls] == [None] * 3
+            assert torch.equal(pkg.sphattn_fwd(q, k, v), o)
+    assert all(c() is not None for c in calls)
