@@ -150,6 +150,115 @@ def test_e4m3_calls_equal_the_python_path(monkeypatch, counts):
     _same(fast, call())
 
 
+def _defects(t, of_shape=True):
+    """What a tensor must not be, by name: a wrong size in each dimension, element type, layout, device, Python type."""
+    out = {}
+    if of_shape:
+        for dim in range(t.dim()):
+            out[f"size {dim}"] = t.narrow(dim, 0, t.size(dim) - 1).contiguous()
+        out["dimensions"] = t[0]
+    out["type"] = t.view(torch.int16) if t.element_size() == 2 else t.view(torch.int32) if t.element_size() == 4 else t.view(torch.int8)
+    out["strides"] = torch.stack([t.view(out["type"].dtype)] * 2, -1)[..., 0].view(t.dtype)
+    out["device"] = t.cpu()
+    out["Python type"] = t.as_subclass(Subclass)
+    out["no tensor"] = 3
+    return out
+
+
+def _refused(call, args, tensors):
+    """call(*args) is done, and left to Python with any one defect in any one tensor."""
+    assert call(*args) is not None
+    for i, whole in tensors.items():
+        for what, bad in _defects(args[i], whole).items():
+            assert call(*args[:i], bad, *args[i + 1:]) is None, (i, what)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_forward_takes_nothing_with_a_defect():
+    q, k, v = _qkv("bf16", 4, 2, 64, 64, 64, 41)
+    m, z = torch.rand((2, 64), device=DEV), torch.empty((2, 4, 64), device=DEV)
+    fwd = pkg._fast.forward
+    _refused(fwd, (q, k, v, m, z, 1, True, False, False), dict.fromkeys(range(5), True))
+    _refused(fwd, (q, k, v, None, None, 1, False, False, True), {0: False, 1: False, 2: True})   # (rectangular: K's own size is N_k)
+    assert fwd(q, k, v, m, z, 1, True, True, False) is None                        # shared heads where there are none
+    k3, v3 = (torch.cat([x, x[:, :1]], 1) for x in (k, v))
+    assert fwd(q, k3, v3, m, z, 1, True, False, False) is None                     # 3 does not divide 4
+    k0, v0 = (x[:, :0].contiguous() for x in (k, v))
+    assert fwd(q, k0, v0, m, z, 1, True, False, False) is None
+    k63, v63 = (x[:, :, :63].contiguous() for x in (k, v))
+    assert fwd(q, k63, v63, None, z, 1, True, False, False) is None and fwd(q, k63, v63, None, z, 1, False, False, False) is not None
+    for code in (0, 2, 3, 4, -2, 9):
+        assert fwd(q, k, v, m, z, code, True, False, False) is None, code
+    for x in ("f32", "f16", "fp8qk_bf16v"):
+        qx, kx, vx = _qkv(x, 4, 2, 64, 64, 64, 42)
+        code = pkg._dtype_code(x)
+        _refused(fwd, (qx, kx, vx, m, z, code, True, False, False), {0: True, 1: True, 2: True})
+        assert fwd(qx, kx, v.to(torch.int16), m, z, code, True, False, False) is None and fwd(q, kx, vx, m, z, code, True, False, False) is None
+
+
+@pytest.mark.gpu
+def test_backward_takes_nothing_with_a_defect():
+    q, k, v = _qkv("f16", 4, 2, 64, 64, 64, 43)
+    m = torch.rand((2, 64), device=DEV)
+    o, z = pkg._cross_fwd_z(q, k, v, m, "f16")
+    do = torch.randn(q.shape, device=DEV).half()
+    bwd, args = pkg._fast.backward, (q, k, v, m, o, do, z, 3, False)
+    _refused(bwd, args, dict.fromkeys(range(7), True))
+    assert bwd(q, k, v, m, o, do, z, 3, True) is None
+    k3, v3 = (torch.cat([x, x[:, :1]], 1) for x in (k, v))
+    assert bwd(q, k3, v3, m, o, do, z, 3, False) is None
+    for code in (0, 1, 2, 4, -2):
+        assert bwd(q, k, v, m, o, do, z, code, False) is None, code
+    for i in (4, 5, 6):
+        assert bwd(*args[:i], None, *args[i + 1:]) is None, i
+
+
+@pytest.mark.gpu
+def test_e4m3_takes_nothing_with_a_defect():
+    q, k, v = _qkv("e4m3", 4, 2, 64, 64, 64, 44)
+    m = torch.rand((2, 64), device=DEV)
+    ws = torch.empty(pkg.sphattn_fp8_workspace_bytes(2, 2, 64, 64), dtype=torch.uint8, device=DEV)
+    fp8 = pkg._fast.fp8_forward
+    _refused(fp8, (q, k, v, m, ws), dict.fromkeys(range(4), True))
+    for bad in (ws.cpu(), ws[None], torch.stack([ws, ws], -1)[:, 0], ws.as_subclass(Subclass), None):
+        assert fp8(q, k, v, m, bad) is None
+    k3, v3 = (torch.cat([x.view(torch.uint8), x.view(torch.uint8)[:, :1]], 1).view(torch.float8_e4m3fn) for x in (k, v))
+    assert fp8(q, k3, v3, m, ws) is None
+    with pytest.raises(pkg.SphattnError):          # (its size is the library's to check)
+        fp8(q, k, v, m, ws[:-1])
+
+
+@pytest.mark.gpu
+def test_without_memory_for_the_workspace_a_call_runs_uncut(monkeypatch):
+    """The allocator is held to 24 MB more than it has: enough for the outputs, not for the workspace (more than 30)."""
+    q, k, v = _qkv("f32", 8, 2, 256, 16384, 128, 45)
+    tq, tk, tv = _qkv("f16", 2, 2, 2048, 2048, 128, 46)
+    to, tz = pkg.sphattn_fwd_z(tq, tk, tv, dtype="f16")
+    lib = pkg.load_library()
+    assert lib.sphattn_cross_splitkv_workspace_bytes(2, 8, 2, 256, 16384, 128, 0) >= 30 << 20
+    assert lib.sphattn_bwd_workspace_bytes(2, 2, 2, 2048, 128, 3) >= 30 << 20
+    forward, backward = lambda **kw: pkg.sphattn_cross_fwd(q, k, v, dtype="f32", **kw), lambda **kw: pkg.sphattn_bwd(tq, tk, tv, to, to, tz, dtype="f16", **kw)
+    current = torch.cuda.current_stream().cuda_stream
+    want = (forward(stream=current), backward(stream=current))   # uncut, as a call with a stream of its own is
+    monkeypatch.setattr(pkg, "_check_forward", None)
+    monkeypatch.setattr(pkg, "_check_backward", None)
+    cut = (forward(), backward())
+    torch.cuda.synchronize()
+    assert not all(torch.equal(a, b) for a, b in zip((cut[0], *cut[1]), (want[0], *want[1])))
+    del cut
+    for call, ref in ((forward, want[0]), (backward, want[1])):
+        torch.cuda.empty_cache()                   # room for the outputs, in one segment of 20 MB and a small one
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (24 << 20)) / torch.cuda.get_device_properties(0).total_memory)
+        try:
+            with pytest.raises(torch.OutOfMemoryError):
+                torch.empty(30 << 20, dtype=torch.uint8, device=DEV)
+            got = call()
+        finally:
+            torch.cuda.set_per_process_memory_fraction(1.0)
+        _same(got, ref)
+
+
 @pytest.mark.gpu
 def test_errors_are_the_python_paths():
     q, k, v = _qkv("bf16", 2, 2, 64, 64, 64, 34)
