@@ -95,6 +95,18 @@ def column_shares(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
     return _library().column_share(H_kv, Nq * (H // H_kv), Nk, d, dtype == "bf16" and not partial, dtype == "fp8qk_bf16v", counts)
 
 
+def launched(H, H_kv, Nq, Nk, d, dtype, counts, partial=False):
+    """What runs: the form's name with the workgroups that share its columns ("Shared2", whichever 64-row form had the launch),
+    or "Rows512"; and whether two of its workgroups share a CU."""
+    name, two = form(H, H_kv, Nq, Nk, d, dtype, counts, partial)
+    shares = column_shares(H, H_kv, Nq, Nk, d, dtype, counts, partial)
+    if shares > 1:
+        return f"Shared{shares}", False
+    if name == "Rows256" and d == 64 and rows512(H, H_kv, Nq, Nk, dtype, counts, not partial):
+        return "Rows512", False
+    return name, two
+
+
 def f32_shares(H, Nq):
     """Workgroups that share the columns of 16 rows of an fp32 launch."""
     return _library().f32_shares(H, Nq)

@@ -22,7 +22,8 @@ SHAPES = [(2, 2, 64, 641, 64), (3, 3, 130, 575, 64), (4, 2, 200, 1025, 64), (256
           (20, 20, 999, 1300, 64), (6, 3, 3000, 1281, 64),                                             # 128 rows, four key groups with counts
           (64, 64, 290, 1985, 64), (64, 64, 289, 310, 64), (16, 8, 2000, 1990, 128), (64, 64, 290, 61, 128),   # four without, and two
           (64, 64, 290, 61, 64), (1, 1, 33, 60, 64), (1, 1, 33, 61, 128),                              # two workgroups on a CU; a single tile
-          (100, 100, 400, 1000, 64), (64, 64, 1024, 449, 64), (12, 3, 5003, 129, 64)]                  # 256 rows, two key groups
+          (100, 100, 400, 1000, 64), (64, 64, 1024, 449, 64), (12, 3, 5003, 129, 64),                  # 256 rows, two key groups
+          (1, 1, 33, 150, 64), (6, 6, 1900, 1217, 128), (8, 4, 1985, 961, 128), (4, 4, 2000, 4600, 128)]   # 64 rows that do not share their columns
 
 
 @pytest.fixture(scope="module")

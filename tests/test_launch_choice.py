@@ -4,8 +4,10 @@ import itertools
 import pytest
 
 import launch_choice
+import test_gpu_column_shares as columns
 import test_gpu_f32_two_parts as two_parts
 import test_gpu_forward_forms as forms
+import test_gpu_rows512 as rows512
 
 
 @pytest.mark.parametrize("partial", [False, True])
@@ -14,12 +16,14 @@ import test_gpu_forward_forms as forms
 @pytest.mark.parametrize("d", [64, 128])
 def test_every_form_has_a_shape(d, dtype, counts, partial):
     """Whatever a launch may take, over a grid of sizes, one of the tested shapes takes too."""
-    reached = {launch_choice.form(h, h, nq, nk, d, dtype, counts, partial)
+    reached = {launch_choice.launched(h, h, nq, nk, d, dtype, counts, partial)
                for h, nq, nk in itertools.product((1, 2, 4, 8, 12, 20, 40, 64, 100, 200), (33, 64, 100, 300, 500, 999, 2000, 4000),
                                                   (60, 150, 300, 500, 700, 1000, 1300, 2000, 3000, 4600, 7000))}
-    tested = {launch_choice.form(H, H_kv, Nq, Nk, d, dtype, counts, partial) for H, H_kv, Nq, Nk, dd in forms.SHAPES if dd == d}
+    shapes = forms.SHAPES + [s[:5] for s in columns.SHAPES if dtype != "fp8qk_bf16v"]
+    shapes += [(*s, 64) for s, t, c in rows512.CASES if (t, c) == (dtype, counts)]
+    tested = {launch_choice.launched(H, H_kv, Nq, Nk, d, dtype, counts, partial) for H, H_kv, Nq, Nk, dd in shapes if dd == d}
     reached.discard(("Rows256", False))            # (fwd_pipelined_kernel has tests of its own)
-    assert len(reached) >= (2 if dtype == "fp8qk_bf16v" and d == 128 else 3)
+    assert len(reached) >= (2 if dtype == "fp8qk_bf16v" and d == 128 else 4)
     assert reached <= tested, reached - tested
 
 
