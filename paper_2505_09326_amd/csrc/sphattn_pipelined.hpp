@@ -175,7 +175,7 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     constexpr int KSHARES = 4 * KBLK / LDK;        // (fewer than waves: the same blocks twice)
     constexpr int LDV = 2 * DB / WAVES;            // ... per V tile (two V blocks each)
     static_assert(LDK <= KBLK && LDV <= DB / 2, "a wave's share lies in one row of blocks");
-    constexpr int NST = LDK + LDV + (MULT ? 1 : 0);   // and one 256-byte copy (wave 0) of multiplicities
+    constexpr int NST = LDK + LDV + (MULT ? 1 : 0);   // and one 256-byte copy of multiplicities, all of them by every wave
     constexpr int SLOTS = DB;                      // slots per sub-step: one V^T fragment each
     constexpr int KK = D / 32;                     // 16-bit: k-steps of K Q^T
     constexpr int QKM = FP8 ? 2 * NQ / SLOTS : NQ; // score matrix instructions per slot
@@ -626,8 +626,9 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
         // (priority_by_tile) outside the loop over tiles, which stays free of branches.  Up to
         // 128 tiles a head's K and V (2 MB) stay in the 4 MB L2 however far the workgroups
         // drift apart, and the tiles run as one group (a group boundary costs about 40 ns).  So do those of eight waves, which
-        // the barriers keep at one tile: 8 x 32768 1426 -> 1420 us, 16 x 16384 730 -> 726.
-        const int group = n_tiles > 128 && WAVES == 4 ? 8 : n_tiles;
+        // the barriers keep at one tile: 8 x 32768 1426 -> 1420 us, 16 x 16384 730 -> 726.  (With fp8 Q/K, which has 128 tiles at most
+        // there, the loop over groups is kept for what the compiler makes of the one inside it: without, 20 x 8192 270 us for 261.5.)
+        const int group = n_tiles > 128 && (WAVES == 4 || FP8) ? 8 : n_tiles;
         for (int j0 = 0; j0 < n_tiles; j0 += group) {
             priority_by_tile(j0);
             run_tiles(j0, j0 + group < n_tiles ? j0 + group : n_tiles);
