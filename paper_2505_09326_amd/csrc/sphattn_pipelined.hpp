@@ -285,14 +285,13 @@ void fwd_pipelined_item(const void* __restrict__ Qv, const void* __restrict__ Kv
     // multiplicities of this cell's keys; those past the last key arrive as 0 (their keys are zero anyway)
     const i32x4 mrw = rsrc_words(MULT ? mult + (size_t)bidx * Nk + k0 : nullptr, MULT ? (uint32_t)N * 4 : 0);
     const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
-    // (16-bit storage in four waves takes no remainder here and above, which is the wave number but costs every copy an addition: with counts
+    // (16-bit storage in four waves takes no remainder below and above, which is the wave number but costs every copy an addition: with counts
     // 197 x 1267 of 105 x 64 22.1 -> 21.3 us, 452 x 458 of 98 20.4 -> 20.0.  fp8 Q/K keeps it: without, 1350 x 230 of 30 x 64 with counts took 21.0 us for 18.9.)
-    const uint32_t share = KSHARES < WAVES || FP8 ? wave_u % KSHARES : wave_u;
     auto copy_chunk = [&](int c, int t, SPH_LDS unsigned char* buf) {
         const uint32_t base = (uint32_t)(uintptr_t)buf;
         const int tile = src_tile(t);
         if (c < LDK)
-            copy_to_lds(krw, base + (share * LDK + c) * 1024, kld_lane, tile * KTILE + c * 64);
+            copy_to_lds(krw, base + ((KSHARES < WAVES || FP8 ? wave_u % KSHARES : wave_u) * LDK + c) * 1024, kld_lane, tile * KTILE + c * 64);
         else if (c < LDK + LDV)
             copy_to_lds(vrw, base + KLDS + (wave_u * LDV + c - LDK) * 1024, vld_lane, tile * VTILE + (c - LDK) * 64);
         else                                       // the tile's 64 multiplicities, by every wave
