@@ -43,8 +43,8 @@
 //
 // d = 64 uses the same instruction with the upper half of the first contraction's k-slots
 // zero on both sides (the key and query rows are 64 bytes; there is no fp8 matrix instruction
-// with k = 64 in this shape), and has four V^T fragments per tile instead of eight: 52 matrix
-// instructions per tile and wave for the work of 32 + 4.
+// with k = 64 in this shape), and has four V^T fragments per tile instead of eight: 13 matrix
+// instructions per tile and query block for the work of 8 + 1.
 //
 // Gene multiplicities (paper, Section 3.1): MULT multiplies the fp32 score of key j by mult[b, j]
 // before it is scaled and rounded; the row bound then uses max_j mult_j |k_j| (the preparation
@@ -54,8 +54,8 @@
 //
 // Pipeline.  A slot = one score block row kb of the current tile (NQ matrix instructions, one
 // per query block) + one V^T fragment db of the previous tile (NQ more) + the conversion of the
-// block row finished in the slot before (one convert instruction and one LDS read, two at NQ = 1,
-// behind every matrix instruction, in a fixed order).  P is complete one slot into the next tile,
+// block row finished in the slot before (a convert instruction per group of one matrix instruction, and
+// the slot's four LDS reads, one to a group or two at NQ = 1, in a fixed order).  P is complete one slot into the next tile,
 // so the second contraction of tile T runs in slots 1..7 of tile T+1 and slot 0 of tile T+2.
 // Tiles of 128 keys rotate through four 32 KB LDS buffers, filled straight from HBM/L2
 // (buffer_load ... lds), with one workgroup barrier per tile.
@@ -217,8 +217,8 @@ __global__ void fp8_clear_kernel(float* __restrict__ p, int n)
 // Shapes (choose_fp8 picks; whole calls in us, with counts / without).  A wave alone on its SIMD stops the matrix pipe for
 // its own conversions, multiplications, register moves and LDS reads (busy 0.61 / 0.72 of the time); two fill each other's gaps, though
 // every fragment read from LDS then feeds two matrix instructions instead of four:
-//   256 rows  NQ 2, 8 waves  8 on 4 x 8000 x 128 108.5 / 100.5 (4 waves of 64 rows, which was the only shape: 114.9 / 103.2), 24 heads on 6
-//             of 3001 76.3 (89.4), 8 x 8000 x 64 81.4 / 72.1 (85.4 / 75.8); 64 x 16384 x 128 as before, 2970, at the power limit
+//   256 rows  NQ 2, 8 waves  8 on 4 x 8000 x 128 111.2 / 102.4 (4 waves of 64 rows, which was the only shape: 117.9 / 105.0), 24 heads on 6
+//             of 3001 76.3 (89.4), 8 x 8000 x 64 81.4 / 72.1 (85.4 / 75.8); 64 x 16384 x 128 3160 / 2890 (3320 / 2925)
 //   256 rows  NQ 4, 4 waves  d = 64 without counts above one round, where two such workgroups share a CU: 8 x 32768 947 (8 waves 1037)
 //   128 rows  NQ 1, 8 waves  half of the CUs: 8 x 3000 x 128 28.1 / 25.6 (256 rows 38.0 / 35.4; NQ 2, 4 waves 30.1 / 27.9)
 //   128 rows  NQ 2, 4 waves  d = 64, two on a CU, where 256 rows leave their last round thin: 8 x 9000 138 / 126 (165 / 132)
@@ -354,8 +354,8 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
     // every other batch of workgroups of an XCD streams the keys backwards (see fwd_pipelined_kernel)
     const bool backwards = stream_period > 0 && (((int)blockIdx.x / kXcds) / stream_period) % 2 == 1;
     auto src_tile = [&](int t) { return t >= n_tiles ? n_tiles : backwards ? n_tiles - 1 - t : t; };
-    // copy c of this wave's share of tile t into buffer `buf`: c < KCOPY K, then V^T, then (wave 0)
-    // the multiplicities.  K rows past the end of the head are out of the descriptor's range and
+    // copy c of this wave's share of tile t into buffer `buf`: c < KCOPY K, then V^T, then half of
+    // the multiplicities (even waves the first 64, odd ones the last).  K rows past the end of the head are out of the descriptor's range and
     // arrive as zeros.
     auto copy_chunk = [&](int c, int t, SPH_LDS unsigned char* buf) {
         const uint32_t base = (uint32_t)(uintptr_t)buf;
@@ -505,14 +505,15 @@ void fwd_fp8_kernel(const unsigned char* __restrict__ Q, const unsigned char* __
             // the multiplicities of block row i of this tile, for the next slot's conversion
             if constexpr (MULT)
                 mreg[(s + 1) % 2] = __builtin_bit_cast(f32x4, lds_read_b128(bcur + MLDS + (64 * (i >> 2) + 16 * g + 4 * (i & 3)) * 4));
-            // Eight groups, one matrix instruction each, in exactly this order (the scheduler
-            // may not move anything across a group boundary): the matrix pipe never waits for
-            // the VALU instructions and the one LDS read that follow it.
-            //   groups 0..3  A: block row i of this tile's scores, query block m
-            //   groups 4..7  C: V^T fragment (i+7)%8 of the previous tile (slot 0: of the one
-            //                   before), query block m - 4; d = 64 has fragments 0..3 only
-            //   every group  B: half a register of P from the block row finished in the
-            //                   previous slot (query block m / 2, values 2 (m % 2), + 1)
+            // 2 NQ groups, one matrix instruction each, in exactly this order (the scheduler
+            // may not move anything across a group boundary): the matrix pipe does not wait for
+            // the VALU instructions and the LDS reads of its group.  The four parts of a slot's
+            // reads go RPG to a group, from the first on (NQ = 4: the first four groups; NQ = 1: two each).
+            //   groups 0 .. NQ-1      A: block row i of this tile's scores, query block m
+            //   groups NQ .. 2 NQ-1   C: V^T fragment (i+7)%8 of the previous tile (slot 0: of the one
+            //                            before), query block m - NQ; d = 64 has fragments 0..3 only
+            //   every group           B: half a register of P from the block row finished in the
+            //                            previous slot (query block m / 2, values 2 (m % 2), + 1)
             const frag_t kfr = whole(kfl[s % RING], kfh[s % RING]);
             const frag_t vfr = whole(vfl[s % RING], vfh[s % RING]);
             s16x2 wlo;
