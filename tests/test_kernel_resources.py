@@ -147,11 +147,16 @@ def test_backward_kernels(usage):
 
 
 def test_all_e4m3_kernels(usage):
-    for name, v in _find(usage, "fwd_fp8_kernelILi128E").items():
+    # Li<D>E Lb<SOFTMAX>E Lb<MULT>E Li<NQ>E Li<WAVES>E: every shape runs two waves per SIMD, as eight waves or as two workgroups of four
+    shapes = {(128, 0): ((1, 4), (1, 8), (2, 8)), (128, 1): ((1, 4), (1, 8), (2, 8)),
+              (64, 0): ((1, 4), (1, 8), (2, 4), (2, 8), (4, 4)), (64, 1): ((1, 4), (1, 8), (2, 4), (2, 8))}
+    for (d, counts), kinds in shapes.items():
+        assert len(_find(usage, f"fwd_fp8_kernelILi{d}ELb0ELb{counts}E")) == len(kinds)
+        for nq, waves in kinds:
+            for name, v in _find(usage, f"fwd_fp8_kernelILi{d}ELb0ELb{counts}ELi{nq}ELi{waves}E").items():
+                assert _num(v, "Occupancy [waves/SIMD]") >= 2 and _num(v, "ScratchSize [bytes/lane]") == 0, name
+    for name, v in _find(usage, "fwd_fp8_kernelILi128ELb1E").items():   # the SoftMax twin
         assert _num(v, "ScratchSize [bytes/lane]") == 0, name
-    # d = 64 without multiplicities: two workgroups per CU
-    for name, v in _find(usage, "fwd_fp8_kernelILi64ELb0ELb0E").items():
-        assert _num(v, "Occupancy [waves/SIMD]") >= 2 and _num(v, "ScratchSize [bytes/lane]") == 0, name
 
 
 def test_loops_begin_on_an_instruction_cache_line(compiled):
