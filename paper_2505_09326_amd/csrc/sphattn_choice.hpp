@@ -80,13 +80,14 @@ inline int column_shares(FormChoice c, long long slices, long long Nq, long long
 // waves, which share nothing: each byte of K and V is copied to LDS once per CU and not twice, and the waves of a SIMD stay at one tile by
 // themselves.  8 x 32768 1415 -> 1384 us, 32 x 8192 370 -> 350, 9 x 8192 (one round, half filled) 152 -> 135, with counts 20 x 8192 358 -> 332,
 // fp8 Q/K 289 -> 266.  Lines from 2200 launches of 257 to 5000 workgroups of 256 rows and 20 to 33000 keys, both forms timed on each (512 over
-// 256 rows; taken: 0.96 in one round, 0.97 in several, 1.015 at most):
+// 256 rows; taken: 0.96 in one round, 0.97 in several, 1.026 at most, 9 past 1.01):
 //   fp8 Q/K with counts    spills, 1.02 to 1.05
-//   K and V past 256 MB    the last-level cache; eight waves wait for HBM together: 48 x 1333 of 29898 1.07, fp8 Q/K 286 x 420 of 7777 1.03
-//   from 129 key tiles on  256 rows have wave priorities by tile there.  In one round 0.97 to 1.05, counts and fp8 Q/K 1.00 to 1.10 in any (fp8 Q/K
-//                          16 x 11180 374 and 394 us, with counts 20 x 10795 481 and 492); 16-bit storage in full rounds 0.98 to 1.01
-//   short key axes         one round: 1 and 2 tiles 0.95 to 1.04, with counts up to 9 tiles 1.03; several: up to 16 tiles 0.93 to 1.05
-//                          (216 x 3519 of 581 124 and 127), with counts 1.04
+//   from 129 key tiles on  256 rows have wave priorities by tile there.  Counts and fp8 Q/K 0.99 to 1.10 (fp8 Q/K 16 x 11180 374 and 394 us, with
+//                          counts 20 x 10795 481 and 492); 16-bit storage 0.95 to 1.02, but in one round of heads of up to 3072 rows 0.96 to 1.07, as
+//                          where K and V are past the 256 MB of the last-level cache (48 x 1333 of 29898 480 and 514)
+//   fp8 Q/K past 256 MB    from 65 tiles on 0.97 to 1.03 (286 x 420 of 7777 273 and 281 us), below 0.98
+//   short key axes         one round: 1 and 2 tiles 0.94 to 1.02 on heads of up to 1024 rows, else 0.95 to 1.04; several: up to 16 tiles 0.93 to 1.05
+//                          (216 x 3519 of 581 124 and 127)
 // Several rounds otherwise as they are filled: a round filled to f costs 0.5 + 0.5 f, and 256-row launches of 16-bit storage without counts may run
 // their last one as halves (launch_pipelined): 8 x 17000 481 us, 547 with this, 8 x 24576 856 and 879.  Up to eight workgroups behind one round of
 // 256 rows take one more item each on eight CUs, not a round (14 x 9470 with counts 327 and 366, 260 x 341 of 3124 99 and 129).
@@ -96,9 +97,10 @@ inline bool rows512_pay(long long slices, long long Nq, long long tiles, Storage
 {
     const long long n256 = slices * ((Nq + 255) / 256), n512 = slices * ((Nq + 511) / 512);
     const bool one_round = n512 <= cus;
-    if (n256 <= cus || (st.fp8 && st.counts) || slices * tiles * (kChoiceTile * 64 * (st.fp8 ? 3 : 4)) > (256ll << 20)) return false;
-    if (tiles > 128 && (one_round || st.fp8 || st.counts)) return false;
-    if (one_round) return tiles >= (st.counts ? 10 : 3);
+    if (n256 <= cus || (st.fp8 && st.counts)) return false;
+    if (tiles > 128 && (st.fp8 || st.counts || (one_round && Nq <= 3072))) return false;
+    if (tiles > (st.fp8 ? 64 : 128) && slices * tiles * (kChoiceTile * 64 * (st.fp8 ? 3 : 4)) > (256ll << 20)) return false;
+    if (one_round) return tiles >= 3 || Nq <= 1024;
     const long long full = n256 / (2 * cus), rest = n256 % (2 * cus);
     if (tiles < 17 || (full == 1 && rest > 0 && rest <= 8)) return false;
     double cost256 = 0.5 * (double)(full + (rest != 0)) + 0.25 * (double)n256 / (double)cus;
