@@ -90,8 +90,8 @@ typedef enum {
  * the fp32 maximum (3.4e38); beyond that a row comes out as zeros or NaN.  Inputs are expected
  * to be finite.
  *
- * 16-bit and fp8-Q/K launches use workgroups of 256 query rows, or of 128 or 64 when larger tiles
- * would leave compute units without work (sphattn_fwd_tile_rows forces 256 or 128).
+ * 16-bit and fp8-Q/K launches use workgroups of 256 query rows (at d = 64 also of 512), or of 128 or 64 when
+ * larger tiles would leave compute units without work (sphattn_fwd_tile_rows forces 256 or 128).
  */
 int sphattn_fwd(const void* Q, const void* K, const void* V, void* O,
                 int B, int H, int N, int d, int dtype, void* stream);
