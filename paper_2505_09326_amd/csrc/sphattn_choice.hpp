@@ -164,7 +164,8 @@ inline int f32_small_column_shares(long long slices, long long Nq, long long cus
 
 // The all-E4M3 forward's workgroup (sphattn_fp8.hpp): query blocks of 16 rows per wave, and waves.  64 rows while every CU gets at most
 // one such workgroup, else 128 likewise, else 256: over 300 launches of 1 to 64 heads of 190 to 23000 keys, every shape timed on each, that is 0 to
-// 0.5 % slower than the best shape in the mean and 4 % at most, and 0.68 to 0.76 of 256 rows in four waves (geometric mean; nowhere slower).
+// 0.5 % slower than the best shape in the mean and 4 % at most, and 0.68 to 0.76 of 256 rows in four waves (geometric mean; nowhere slower).  On 243
+// launches of 65 to 800 heads of 60 to 16000 keys 0.81 of 256 rows in four waves (d = 128 0.92 at most, 64 1.01); other shapes were not timed there.
 // At d = 64 above one round of 256 rows two workgroups share a CU, but not two of eight waves: the shape follows from rounds of two and a last
 // round of one or two, in the units of a tile's time measured for them.  Without counts 256 rows in four waves, two on a CU 1.84, one 1.08,
 // or 128 rows, 0.985 and 0.66 (8 x 9000 131.8 and 126.4 us, 12 x 5725 101.5 and 109.6; for a gain of 4 %); with counts 256 rows in eight waves, 1.11
