@@ -143,7 +143,7 @@ def _bound_marshal(lib):
         from . import _marshal
     except ImportError:                            # no torch, or one with other symbols
         return _PythonOnly
-    if _marshal.built_for != torch.__version__:
+    if getattr(_marshal, "built_for", None) != torch.__version__:
         return _PythonOnly
     names = ("sphattn_cross_fwd", "sphattn_cross_splitkv_fwd", "sphattn_cross_splitkv_workspace_bytes", "sphattn_grn_bwd",
              "sphattn_grn_bwd_split", "sphattn_bwd_workspace_bytes", "sphattn_fp8_grn_fwd")
